@@ -1,176 +1,452 @@
-// fp32 causal attention for the full-precision configuration: one wavefront per query row
-// (forward, dQ) or per key row (dK / dV), scores kept in LDS, every sum in fp32 and in a fixed
-// order.  Small and exact rather than fast: that configuration is launch-bound.
+// fp32 causal attention on v_mfma_f32_32x32x2_f32: every product and sum is a full fp32 one, in a
+// fixed order.
+//
+// A workgroup owns 32 query rows (forward, dQ) or 32 key rows (dK / dV) of one (sample, head); its
+// 4 wavefronts take every 4th 32-row tile of the other side and their partial results are merged
+// through LDS in wavefront order.  Scores are taken transposed to the owner (a lane owns one query,
+// or one key, of every accumulator), so that an accumulator register is, as it stands, an operand
+// of the next product: register v of a lane in half g holds tile row 8 (v / 4) + 4 g + v % 4, and a
+// 32x32x2 product takes one row from each half.  Operands therefore come straight from global
+// memory (16 B per lane along the head dimension, or 128 B runs of one row per half wavefront) with
+// no staging and no barrier inside the loop; a tile costs a wavefront 4096 to 16384 cycles of the
+// matrix pipe against 0.5 to 1 kB per row pair of cache reads, so the matrix pipe is the bound once
+// a few wavefronts share a SIMD.
+// Head dimensions up to 128 are padded with zeros to 32, 64 or 128.  With 16 heads of 64, S 512, batch 2:
+// forward 1031 -> 25 us, dQ 2222 -> 41 us, dK / dV 2426 -> 47 us against one wavefront per row with
+// scalar multiply-adds.
 #include "gx_kernels.h"
 
 namespace gx {
 namespace {
 
-// qkv row stride is 3*Hl; head h's Q, K, V start at columns h*dh, Hl + h*dh, 2*Hl + h*dh.
-struct HeadView {
-  const float* q; const float* k; const float* v;
-  int ld;
-};
-GX_DEVINL HeadView head_view(const float* qkv, int b, int h, int S, int nl, int dh) {
-  const int Hl = nl * dh;
-  const float* base = qkv + (size_t)b * S * 3 * Hl + h * dh;
-  return HeadView{base, base + Hl, base + 2 * Hl, 3 * Hl};
-}
+constexpr int PARTS = 4;          // wavefronts of a workgroup
 
-// Dropout of the probabilities: keep bits of (sample, head) pair bh, row-major (bit j % 32 of word
-// j / 32 of query row i); a null array keeps everything.
-struct KeepBits {
-  const unsigned* row;   // this pair's [S][wpr] words, or null
-  int wpr;
-  float scale;           // multiplier of a kept probability
-  GX_DEVINL float factor(int i, int j) const {
-    if (!row) return 1.0f;
-    return ((row[(size_t)i * wpr + (j >> 5)] >> (j & 31)) & 1u) ? scale : 0.0f;
-  }
-};
-GX_DEVINL KeepBits keep_view(const unsigned* rowbits, int wpr, float scale, int b, int h, int S, int nl) {
-  return KeepBits{rowbits ? rowbits + ((size_t)b * nl + h) * S * wpr : nullptr, wpr, scale};
+GX_DEVINL f32x16 zero16() {
+  f32x16 z;
+#pragma unroll
+  for (int v = 0; v < 16; v++) z[v] = 0.f;
+  return z;
 }
+GX_DEVINL int acc_row(int v, int g) { return 8 * (v >> 2) + 4 * g + (v & 3); }
+GX_DEVINL f32x16 mfma(float a, float b, const f32x16& c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 
-__global__ void __launch_bounds__(64) attn_fwd_f32_kernel(const float* __restrict__ qkv, float* __restrict__ ctx,
-                                                          float* __restrict__ lse, int S, int nl, int dh,
-                                                          const unsigned* __restrict__ rowbits, int wpr,
-                                                          float keep_scale) {
-  extern __shared__ float sc[];          // [S] scores of this row, then probabilities
-  const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
-  const HeadView hv = head_view(qkv, b, h, S, nl, dh);
-  const KeepBits kb = keep_view(rowbits, wpr, keep_scale, b, h, S, nl);
-  const float scale = rsqrtf((float)dh);
-  const float* qi = hv.q + (size_t)i * hv.ld;
-  float mx = -INFINITY;
-  for (int j = lane; j <= i; j += 64) {
-    const float* kj = hv.k + (size_t)j * hv.ld;
-    float s = 0.f;
-    for (int d = 0; d < dh; d++) s = fmaf(qi[d], kj[d], s);
-    s *= scale;
-    sc[j] = s;
-    mx = fmaxf(mx, s);
-  }
-  mx = wave_max(mx);
-  float sum = 0.f;
-  for (int j = lane; j <= i; j += 64) {
-    const float p = expf(sc[j] - mx);
-    sc[j] = p * kb.factor(i, j);         // the normaliser below is the sum of the undropped values
-    sum += p;
-  }
-  sum = wave_sum(sum);
-  __syncthreads();
-  const float inv = 1.0f / sum;
-  for (int d = lane; d < dh; d += 64) {
-    float o = 0.f;
-    for (int j = 0; j <= i; j++) o = fmaf(sc[j], hv.v[(size_t)j * hv.ld + d], o);
-    ctx[((size_t)b * S + i) * (nl * dh) + h * dh + d] = o * inv;
-  }
-  if (lane == 0) lse[((size_t)b * nl + h) * S + i] = mx + logf(sum);
-}
-
-// per query row: D_i = dO_i . O_i, dS_ij = P_ij (dO_i . V_j - D_i), dQ_i = scale * sum_j dS_ij K_j
-__global__ void __launch_bounds__(64) attn_bwd_dq_f32_kernel(const float* __restrict__ qkv,
-                                                             const float* __restrict__ ctx,
-                                                             const float* __restrict__ dctx,
-                                                             const float* __restrict__ lse, float* __restrict__ dsum,
-                                                             float* __restrict__ dqkv, int S, int nl, int dh,
-                                                             const unsigned* __restrict__ rowbits, int wpr,
-                                                             float keep_scale) {
-  extern __shared__ float ds[];          // [S]
-  const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
-  const HeadView hv = head_view(qkv, b, h, S, nl, dh);
-  const KeepBits kb = keep_view(rowbits, wpr, keep_scale, b, h, S, nl);
-  const int Hl = nl * dh;
-  const float scale = rsqrtf((float)dh);
-  const float* qi = hv.q + (size_t)i * hv.ld;
-  const float* doi = dctx + ((size_t)b * S + i) * Hl + h * dh;
-  const float* oi = ctx + ((size_t)b * S + i) * Hl + h * dh;
-  float dd = 0.f;
-  for (int d = lane; d < dh; d += 64) dd = fmaf(doi[d], oi[d], dd);
-  dd = wave_sum(dd);
-  const float l = lse[((size_t)b * nl + h) * S + i];
-  if (lane == 0) dsum[((size_t)b * nl + h) * S + i] = dd;
-  for (int j = lane; j <= i; j += 64) {
-    const float* kj = hv.k + (size_t)j * hv.ld;
-    const float* vj = hv.v + (size_t)j * hv.ld;
-    float s = 0.f, dp = 0.f;
-    for (int d = 0; d < dh; d++) { s = fmaf(qi[d], kj[d], s); dp = fmaf(doi[d], vj[d], dp); }
-    ds[j] = expf(s * scale - l) * (dp * kb.factor(i, j) - dd);
-  }
-  __syncthreads();
-  float* dq = dqkv + ((size_t)b * S + i) * 3 * Hl + h * dh;
-  for (int d = lane; d < dh; d += 64) {
-    float a = 0.f;
-    for (int j = 0; j <= i; j++) a = fmaf(ds[j], hv.k[(size_t)j * hv.ld + d], a);
-    dq[d] = a * scale;
-  }
-}
-
-// per key row j: dV_j = sum_{i>=j} P_ij dO_i, dK_j = scale * sum_{i>=j} dS_ij Q_i
-__global__ void __launch_bounds__(64) attn_bwd_dkv_f32_kernel(const float* __restrict__ qkv,
-                                                              const float* __restrict__ dctx,
-                                                              const float* __restrict__ lse,
-                                                              const float* __restrict__ dsum,
-                                                              float* __restrict__ dqkv, int S, int nl, int dh,
-                                                              const unsigned* __restrict__ rowbits, int wpr,
-                                                              float keep_scale) {
-  extern __shared__ float sm[];          // p[S] (as it multiplies V: dropped and rescaled) | ds[S]
-  float* pp = sm;
-  float* ds = sm + S;
-  const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
-  const HeadView hv = head_view(qkv, b, h, S, nl, dh);
-  const int Hl = nl * dh;
-  const float scale = rsqrtf((float)dh);
-  const float* kj = hv.k + (size_t)j * hv.ld;
-  const float* vj = hv.v + (size_t)j * hv.ld;
-  const float* lrow = lse + ((size_t)b * nl + h) * S;
-  const float* drow = dsum + ((size_t)b * nl + h) * S;
-  const KeepBits kb = keep_view(rowbits, wpr, keep_scale, b, h, S, nl);
-  for (int i = j + lane; i < S; i += 64) {
-    const float* qi = hv.q + (size_t)i * hv.ld;
-    const float* doi = dctx + ((size_t)b * S + i) * Hl + h * dh;
-    float s = 0.f, dp = 0.f;
-    for (int d = 0; d < dh; d++) { s = fmaf(qi[d], kj[d], s); dp = fmaf(doi[d], vj[d], dp); }
-    const float p = expf(s * scale - lrow[i]);
-    const float keep = kb.factor(i, j);
-    pp[i] = p * keep;
-    ds[i] = p * (dp * keep - drow[i]);
-  }
-  __syncthreads();
-  float* dk = dqkv + ((size_t)b * S + j) * 3 * Hl + Hl + h * dh;
-  float* dv = dk + Hl;
-  for (int d = lane; d < dh; d += 64) {
-    float ak = 0.f, av = 0.f;
-    for (int i = j; i < S; i++) {
-      ak = fmaf(ds[i], hv.q[(size_t)i * hv.ld + d], ak);
-      av = fmaf(pp[i], dctx[((size_t)b * S + i) * Hl + h * dh + d], av);
+// One lane's share of 32 rows by DHP columns whose reduction index is the column: chunk c holds columns
+// 8 c + 4 g .. + 3 of the lane's row.  EXACT: the head dimension is DHP, so that rows start at 16-byte
+// boundaries and none is padded; otherwise columns beyond dh read as zero, one at a time.
+template <int DHP, bool EXACT>
+GX_DEVINL void load_rows(const float* row, int dh, int g, f32x4 (&out)[DHP / 8]) {
+#pragma unroll
+  for (int c = 0; c < DHP / 8; c++) {
+    const int d = 8 * c + 4 * g;
+    if (EXACT) {
+      out[c] = *reinterpret_cast<const f32x4*>(row + d);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; e++) out[c][e] = (d + e < dh) ? row[d + e] : 0.f;
     }
-    dk[d] = ak * scale;
-    dv[d] = av;
   }
 }
+// a per-row vector's values for the 16 tile rows of this lane's accumulator registers
+GX_DEVINL void load_row_stats(const float* tile, int rows, int g, float (&out)[16]) {
+  typedef f32x4 __attribute__((aligned(4))) f32x4_u;
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    if (rows >= 32) {
+      const f32x4 t = *reinterpret_cast<const f32x4_u*>(tile + 8 * q + 4 * g);
+#pragma unroll
+      for (int e = 0; e < 4; e++) out[4 * q + e] = t[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; e++) out[4 * q + e] = tile[min(8 * q + 4 * g + e, rows - 1)];
+    }
+  }
+}
+// 32 x 32 scores: sum over columns of a[row] * b[col]
+template <int DHP>
+GX_DEVINL f32x16 row_product(const f32x4 (&a)[DHP / 8], const f32x4 (&b)[DHP / 8]) {
+  f32x16 s = zero16();
+#pragma unroll
+  for (int c = 0; c < DHP / 8; c++)
+#pragma unroll
+    for (int e = 0; e < 4; e++) s = mfma(a[c][e], b[c][e], s);
+  return s;
+}
+
+// acc[dt][d][col] += sum over the 32 rows r of the tile of src[r][d] * w[r][col], w being an
+// accumulator.  On the tile that touches the diagonal some weights stand for masked pairs and are
+// 0; a value of src that is not finite must not reach the columns it is masked for (0 * inf), so
+// such a tile takes the second form: weights through LDS and one multiply-add per unmasked pair.
+// LATER: a row is masked for the columns below it (keys for queries); else for those above it.
+template <int DHP, bool EXACT, bool LATER>
+GX_DEVINL void col_product(f32x16 (&acc)[DHP / 32], const f32x16& w, const float* src, int ld, int rows, int dh,
+                           bool diagonal, float* spill, int lane) {
+  const int g = lane >> 5, l32 = lane & 31;
+  constexpr int CH = DHP >= 64 ? 2 : 1;                      // column blocks in registers at a time
+#pragma unroll
+  for (int d0 = 0; d0 < DHP / 32; d0 += CH) {
+    float x[CH][16];
+#pragma unroll
+    for (int c = 0; c < CH; c++) {
+      const int dd = 32 * (d0 + c) + l32;
+      const int d = EXACT ? dd : min(dd, dh - 1);            // columns beyond dh are never stored
+      if (rows >= 32) {
+        const unsigned off = (unsigned)(4 * g * ld + d);
+#pragma unroll
+        for (int v = 0; v < 16; v++) x[c][v] = (src + (size_t)acc_row(v, 0) * ld)[off];
+      } else {
+        // rows beyond the tensor have weight 0 and take the last row's values: where that row is
+        // not finite, so is the result of every column that sees it, and the diagonal form below
+        // keeps it from the others
+#pragma unroll
+        for (int v = 0; v < 16; v++) x[c][v] = src[(unsigned)(min(acc_row(v, g), rows - 1) * ld + d)];
+      }
+    }
+    bool bad = false;
+    if (diagonal) {
+#pragma unroll
+      for (int c = 0; c < CH; c++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) bad |= !(fabsf(x[c][v]) < INFINITY);
+    }
+    if (__builtin_amdgcn_ballot_w64(bad)) {
+#pragma unroll
+      for (int v = 0; v < 16; v++) spill[acc_row(v, g) * 33 + l32] = w[v];
+      for (int r = 0; r < min(rows, 32); r++) {
+        const float wr = spill[r * 33 + l32];
+        if (LATER ? r > l32 : r < l32) continue;
+#pragma unroll
+        for (int c = 0; c < CH; c++)
+#pragma unroll
+          for (int v = 0; v < 16; v++) {
+            const int d = 32 * (d0 + c) + acc_row(v, g);
+            if (d < dh) acc[d0 + c][v] = fmaf(wr, src[(size_t)r * ld + d], acc[d0 + c][v]);
+            if ((v & 3) == 3) asm volatile("" ::: "memory");     // a rare path: few loads in flight, few registers
+          }
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < 16; v++)
+#pragma unroll
+        for (int c = 0; c < CH; c++) acc[d0 + c] = mfma(x[c][v], w[v], acc[d0 + c]);
+    }
+  }
+}
+
+// Adds the parts' accumulators in the order of the wavefronts; the sum is complete in wavefront 0.
+template <int DT>
+GX_DEVINL void merge_parts(f32x16 (&acc)[DT], float* park, int part, int lane) {
+  __syncthreads();
+  if (part > 0)
+#pragma unroll
+    for (int dt = 0; dt < DT; dt++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) park[((part - 1) * DT * 16 + 16 * dt + v) * 64 + lane] = acc[dt][v];
+  __syncthreads();
+  if (part == 0)
+    for (int p = 0; p < PARTS - 1; p++)
+#pragma unroll
+      for (int dt = 0; dt < DT; dt++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc[dt][v] += park[(p * DT * 16 + 16 * dt + v) * 64 + lane];
+}
+// one column (= one row of the tensor) of a transposed result: dst[d] = acc * scale
+template <int DHP, bool EXACT>
+GX_DEVINL void store_column(const f32x16 (&acc)[DHP / 32], float* dst, float scale, int dh, int g) {
+#pragma unroll
+  for (int dt = 0; dt < DHP / 32; dt++)
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const int d = 32 * dt + 8 * q + 4 * g;
+      const f32x4 v = {acc[dt][4 * q] * scale, acc[dt][4 * q + 1] * scale, acc[dt][4 * q + 2] * scale,
+                       acc[dt][4 * q + 3] * scale};
+      if (EXACT) {
+        *reinterpret_cast<f32x4*>(dst + d) = v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+          if (d + e < dh) dst[d + e] = v[e];
+      }
+    }
+}
+
+// LDS: the parts' (O, m, l) or the spilled weights of a diagonal tile (one area per wavefront)
+template <int DHP>
+constexpr int lds_floats() {
+  const int merge = (PARTS - 1) * (DHP / 2 + 2) * 64, spill = PARTS * 32 * 33;
+  return merge > spill ? merge : spill;
+}
+
+struct Args {
+  const float *qkv, *ctx, *dctx;
+  float *out, *lse, *dsum;      // out: ctx (forward) or dqkv (backward)
+  int S, nl, dh, npair;
+  const unsigned* rowbits;      // dropout: keep bits, [pair][S][wpr] words, bit j % 32 of word j / 32; or null
+  int wpr;
+  float keep_scale;
+};
+// this workgroup's (sample, head) pair and tile; the tiles with most work come first in the launch
+struct Where {
+  int b, h, tile, ld;
+  const float *q, *k, *v;
+  GX_DEVINL Where(const Args& a, bool last_first) {
+    const int pair = blockIdx.x % a.npair, n = gridDim.x / a.npair, i = blockIdx.x / a.npair;
+    tile = last_first ? n - 1 - i : i;
+    h = pair % a.nl;
+    b = pair / a.nl;
+    ld = 3 * a.nl * a.dh;
+    q = a.qkv + (size_t)b * a.S * ld + h * a.dh;
+    k = q + a.nl * a.dh;
+    v = k + a.nl * a.dh;
+  }
+};
+
+template <int DHP, bool EXACT>
+__global__ void __launch_bounds__(64 * PARTS, DHP <= 64 ? 2 : 1) attn_fwd_f32_kernel(Args a) {
+  __shared__ float lds[lds_floats<DHP>()];
+  const int lane = threadIdx.x & 63, part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 5, l32 = lane & 31;
+  const Where w(a, true);
+  const int i0 = 32 * w.tile, i = i0 + l32;
+  const float scale = rsqrtf((float)a.dh);
+  const size_t row = ((size_t)w.b * a.nl + w.h) * a.S + min(i, a.S - 1);
+  f32x4 qf[DHP / 8];
+  load_rows<DHP, EXACT>(w.q + (size_t)min(i, a.S - 1) * w.ld, a.dh, g, qf);
+  f32x16 o[DHP / 32];
+#pragma unroll
+  for (int dt = 0; dt < DHP / 32; dt++) o[dt] = zero16();
+  float m = -INFINITY, l = 0.f;
+  for (int t = part; t <= w.tile; t += PARTS) {
+    const int j0 = 32 * t;
+    f32x4 kf[DHP / 8];
+    load_rows<DHP, EXACT>(w.k + (size_t)min(j0 + l32, a.S - 1) * w.ld, a.dh, g, kf);
+    f32x16 s = row_product<DHP>(kf, qf);                         // S^T[j][i]
+    float mx = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      s[v] = (j0 + acc_row(v, g) <= i) ? s[v] * scale : -INFINITY;
+      mx = fmaxf(mx, s[v]);
+    }
+    const float mnew = fmaxf(m, max_across_halves(mx));          // finite: every query sees key j0
+    const float alpha = expf(m - mnew);
+    m = mnew;
+    float sum = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      s[v] = (j0 + acc_row(v, g) <= i) ? expf(s[v] - m) : 0.f;
+      sum += s[v];
+    }
+    l = l * alpha + sum;                                         // of the undropped probabilities
+    if (a.rowbits) {
+      const unsigned bits = a.rowbits[row * a.wpr + t];
+#pragma unroll
+      for (int v = 0; v < 16; v++) s[v] = ((bits >> acc_row(v, g)) & 1u) ? s[v] * a.keep_scale : 0.f;
+    }
+#pragma unroll
+    for (int dt = 0; dt < DHP / 32; dt++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) o[dt][v] *= alpha;
+    col_product<DHP, EXACT, true>(o, s, w.v + (size_t)j0 * w.ld, w.ld, a.S - j0, a.dh, t == w.tile, lds + part * 32 * 33,
+                           lane);
+  }
+  // merge the parts' (m, l, O); a part without a tile has m = -inf, l = 0, O = 0 and adds nothing
+  constexpr int VALS = DHP / 2 + 2;
+  __syncthreads();
+  if (part > 0) {
+    float* p = lds + (part - 1) * VALS * 64 + lane;
+    p[0] = m;
+    p[64] = l;
+#pragma unroll
+    for (int dt = 0; dt < DHP / 32; dt++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) p[(2 + 16 * dt + v) * 64] = o[dt][v];
+  }
+  __syncthreads();
+  if (part > 0) return;
+  for (int pp = 0; pp < min(PARTS - 1, w.tile); pp++) {          // part 0 always has a tile; part p when tile >= p
+    const float* p = lds + pp * VALS * 64 + lane;
+    const float mm = fmaxf(m, p[0]), a0 = expf(m - mm), a1 = expf(p[0] - mm);
+    l = l * a0 + p[64] * a1;
+    m = mm;
+#pragma unroll
+    for (int dt = 0; dt < DHP / 32; dt++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) o[dt][v] = o[dt][v] * a0 + p[(2 + 16 * dt + v) * 64] * a1;
+  }
+  l += __shfl_xor(l, 32, 64);
+  if (i >= a.S) return;
+  store_column<DHP, EXACT>(o, a.out + ((size_t)w.b * a.S + i) * (a.nl * a.dh) + w.h * a.dh, 1.0f / l, a.dh, g);
+  if (g == 0) a.lse[row] = m + logf(l);
+}
+
+// D_i = dO_i . O_i, dS_ij = P_ij (dO_i . V_j - D_i), dQ_i = scale sum_j dS_ij K_j
+template <int DHP, bool EXACT>
+__global__ void __launch_bounds__(64 * PARTS, DHP <= 64 ? 2 : 1) attn_bwd_dq_f32_kernel(Args a) {
+  __shared__ float lds[lds_floats<DHP>()];
+  const int lane = threadIdx.x & 63, part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 5, l32 = lane & 31;
+  const Where w(a, true);
+  const int i0 = 32 * w.tile, i = i0 + l32, ic = min(i, a.S - 1);
+  const float scale = rsqrtf((float)a.dh);
+  const size_t row = ((size_t)w.b * a.nl + w.h) * a.S + ic;
+  const size_t head_row = ((size_t)w.b * a.S + ic) * (a.nl * a.dh) + w.h * a.dh;
+  f32x4 qf[DHP / 8], dof[DHP / 8];
+  load_rows<DHP, EXACT>(w.q + (size_t)ic * w.ld, a.dh, g, qf);
+  load_rows<DHP, EXACT>(a.dctx + head_row, a.dh, g, dof);
+  float dd = 0.f;
+  {
+    f32x4 of[DHP / 8];
+    load_rows<DHP, EXACT>(a.ctx + head_row, a.dh, g, of);
+#pragma unroll
+    for (int c = 0; c < DHP / 8; c++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) dd = fmaf(dof[c][e], of[c][e], dd);
+  }
+  dd += __shfl_xor(dd, 32, 64);
+  const float lse = a.lse[row];
+  if (part == 0 && g == 0 && i < a.S) a.dsum[row] = dd;
+  f32x16 dq[DHP / 32];
+#pragma unroll
+  for (int dt = 0; dt < DHP / 32; dt++) dq[dt] = zero16();
+  for (int t = part; t <= w.tile; t += PARTS) {
+    const int j0 = 32 * t;
+    f32x16 s, dp;
+    {
+      f32x4 kf[DHP / 8];
+      load_rows<DHP, EXACT>(w.k + (size_t)min(j0 + l32, a.S - 1) * w.ld, a.dh, g, kf);
+      s = row_product<DHP>(kf, qf);                              // S^T[j][i]
+      if (DHP > 64) __builtin_amdgcn_sched_barrier(0);           // one operand in registers at a time
+      load_rows<DHP, EXACT>(w.v + (size_t)min(j0 + l32, a.S - 1) * w.ld, a.dh, g, kf);
+      dp = row_product<DHP>(kf, dof);                            // dP^T[j][i]
+    }
+    if (a.rowbits) {
+      const unsigned bits = a.rowbits[row * a.wpr + t];
+#pragma unroll
+      for (int v = 0; v < 16; v++) dp[v] *= ((bits >> acc_row(v, g)) & 1u) ? a.keep_scale : 0.f;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; v++) s[v] = (j0 + acc_row(v, g) <= i) ? expf(s[v] * scale - lse) * (dp[v] - dd) : 0.f;
+    if (DHP > 64) __builtin_amdgcn_sched_barrier(0);
+    col_product<DHP, EXACT, true>(dq, s, w.k + (size_t)j0 * w.ld, w.ld, a.S - j0, a.dh, t == w.tile, lds + part * 32 * 33,
+                           lane);
+  }
+  merge_parts(dq, lds, part, lane);
+  if (part == 0 && i < a.S)
+    store_column<DHP, EXACT>(dq, a.out + ((size_t)w.b * a.S + i) * w.ld + w.h * a.dh, scale, a.dh, g);
+}
+
+// dV_j = sum_{i >= j} P_ij dO_i, dK_j = scale sum_{i >= j} dS_ij Q_i
+template <int DHP, bool EXACT>
+__global__ void __launch_bounds__(64 * PARTS, 1) attn_bwd_dkv_f32_kernel(Args a) {
+  __shared__ float lds[lds_floats<DHP>()];
+  const int lane = threadIdx.x & 63, part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 5, l32 = lane & 31;
+  const Where w(a, false);
+  const int j0 = 32 * w.tile, j = j0 + l32, jc = min(j, a.S - 1);
+  const float scale = rsqrtf((float)a.dh);
+  const size_t pair_row = ((size_t)w.b * a.nl + w.h) * a.S;
+  const int Hl = a.nl * a.dh;
+  const float* dob = a.dctx + (size_t)w.b * a.S * Hl + w.h * a.dh;
+  f32x4 kf[DHP / 8], vf[DHP / 8];
+  load_rows<DHP, EXACT>(w.k + (size_t)jc * w.ld, a.dh, g, kf);
+  load_rows<DHP, EXACT>(w.v + (size_t)jc * w.ld, a.dh, g, vf);
+  f32x16 dk[DHP / 32], dv[DHP / 32];
+#pragma unroll
+  for (int dt = 0; dt < DHP / 32; dt++) dk[dt] = dv[dt] = zero16();
+  const int nt = (a.S + 31) / 32;
+  for (int t = w.tile + part; t < nt; t += PARTS) {
+    const int i0 = 32 * t, ir = min(i0 + l32, a.S - 1);
+    f32x16 p, ds;
+    {
+      f32x4 xf[DHP / 8];
+      load_rows<DHP, EXACT>(w.q + (size_t)ir * w.ld, a.dh, g, xf);
+      p = row_product<DHP>(xf, kf);                              // S[i][j]
+      if (DHP > 64) __builtin_amdgcn_sched_barrier(0);           // one operand in registers at a time
+      load_rows<DHP, EXACT>(dob + (size_t)ir * Hl, a.dh, g, xf);
+      ds = row_product<DHP>(xf, vf);                             // dP[i][j]
+    }
+    float st[16];
+    load_row_stats(a.lse + pair_row + i0, a.S - i0, g, st);
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const int i = i0 + acc_row(v, g);
+      p[v] = (i >= j && i < a.S) ? expf(p[v] * scale - st[v]) : 0.f;
+    }
+    unsigned kept = 0xffffu;
+    if (a.rowbits) {
+      kept = 0;
+#pragma unroll
+      for (int v = 0; v < 16; v++) {
+        const size_t r = pair_row + min(i0 + acc_row(v, g), a.S - 1);
+        kept |= ((a.rowbits[r * a.wpr + w.tile] >> l32) & 1u) << v;
+        ds[v] = ((kept >> v) & 1u) ? ds[v] * a.keep_scale : 0.f;
+      }
+    }
+    load_row_stats(a.dsum + pair_row + i0, a.S - i0, g, st);
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const int i = i0 + acc_row(v, g);
+      ds[v] = (i >= j && i < a.S) ? p[v] * (ds[v] - st[v]) : 0.f;
+    }
+    if (a.rowbits)
+#pragma unroll
+      for (int v = 0; v < 16; v++) p[v] = ((kept >> v) & 1u) ? p[v] * a.keep_scale : 0.f;
+    const bool diagonal = t == w.tile;
+    if (DHP >= 64) __builtin_amdgcn_sched_barrier(0);
+    col_product<DHP, EXACT, false>(dv, p, dob + (size_t)i0 * Hl, Hl, a.S - i0, a.dh, diagonal, lds + part * 32 * 33, lane);
+    if (DHP > 64) __builtin_amdgcn_sched_barrier(0);
+    col_product<DHP, EXACT, false>(dk, ds, w.q + (size_t)i0 * w.ld, w.ld, a.S - i0, a.dh, diagonal, lds + part * 32 * 33,
+                            lane);
+  }
+  merge_parts(dk, lds, part, lane);
+  merge_parts(dv, lds, part, lane);
+  if (part != 0 || j >= a.S) return;
+  float* dst = a.out + ((size_t)w.b * a.S + j) * w.ld + Hl + w.h * a.dh;
+  store_column<DHP, EXACT>(dk, dst, scale, a.dh, g);
+  store_column<DHP, EXACT>(dv, dst + Hl, 1.0f, a.dh, g);
+}
+
+bool shape_ok(const AttnArgs& a) {
+  return a.S > 0 && a.S <= 8192 && a.dh > 0 && a.dh <= 128 && a.nl > 0 && a.B > 0 &&
+         (long)a.B * a.nl * cdiv(a.S, 32) < (1L << 31) && (!a.rowbits || a.wpr >= cdiv(a.S, 32));
+}
+
+Args make_args(const AttnArgs& a, float* out) {
+  return Args{(const float*)a.qkv, (const float*)a.ctx, (const float*)a.dctx, out, a.lse, a.dsum, a.S, a.nl, a.dh,
+              a.nl * a.B, a.rowbits, a.wpr, a.keep_scale};
+}
+
+// Head dimensions of exactly 32, 64 or 128 read rows 16 B at a time; every other one takes the next
+// larger of the three, padded.
+#define GX_F32_ATTN(KERNEL, ARGS)                                                                  \
+  do {                                                                                             \
+    const dim3 grid((unsigned)((ARGS).npair * cdiv((ARGS).S, 32))), block(64 * PARTS);              \
+    switch ((ARGS).dh) {                                                                           \
+      case 32: hipLaunchKernelGGL((KERNEL<32, true>), grid, block, 0, s, (ARGS)); break;            \
+      case 64: hipLaunchKernelGGL((KERNEL<64, true>), grid, block, 0, s, (ARGS)); break;            \
+      case 128: hipLaunchKernelGGL((KERNEL<128, true>), grid, block, 0, s, (ARGS)); break;          \
+      default:                                                                                     \
+        if ((ARGS).dh < 32) hipLaunchKernelGGL((KERNEL<32, false>), grid, block, 0, s, (ARGS));     \
+        else if ((ARGS).dh < 64) hipLaunchKernelGGL((KERNEL<64, false>), grid, block, 0, s, (ARGS)); \
+        else hipLaunchKernelGGL((KERNEL<128, false>), grid, block, 0, s, (ARGS));                   \
+    }                                                                                              \
+  } while (0)
 
 }  // namespace
 
 hipError_t attn_fwd_f32(const AttnArgs& a, hipStream_t s) {
-  if (a.S > 8192) return hipErrorInvalidValue;
-  dim3 grid(a.S, a.nl, a.B);
-  hipLaunchKernelGGL(attn_fwd_f32_kernel, grid, dim3(64), a.S * sizeof(float), s, (const float*)a.qkv,
-                     (float*)a.ctx, a.lse, a.S, a.nl, a.dh, a.rowbits, a.wpr, a.keep_scale);
+  if (!shape_ok(a)) return hipErrorInvalidValue;
+  const Args f = make_args(a, (float*)a.ctx);
+  GX_F32_ATTN(attn_fwd_f32_kernel, f);
   return hipGetLastError();
 }
 
 hipError_t attn_bwd_f32(const AttnArgs& a, hipStream_t s) {
-  if (a.S > 8192) return hipErrorInvalidValue;
-  dim3 grid(a.S, a.nl, a.B);
-  hipLaunchKernelGGL(attn_bwd_dq_f32_kernel, grid, dim3(64), a.S * sizeof(float), s, (const float*)a.qkv,
-                     (const float*)a.ctx, (const float*)a.dctx, a.lse, a.dsum, (float*)a.dqkv, a.S, a.nl, a.dh, a.rowbits,
-                     a.wpr, a.keep_scale);
+  if (!shape_ok(a)) return hipErrorInvalidValue;
+  const Args f = make_args(a, (float*)a.dqkv);
+  GX_F32_ATTN(attn_bwd_dq_f32_kernel, f);      // also leaves D for the next kernel
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_bwd_dkv_f32_kernel, grid, dim3(64), 2 * a.S * sizeof(float), s, (const float*)a.qkv,
-                     (const float*)a.dctx, a.lse, a.dsum, (float*)a.dqkv, a.S, a.nl, a.dh, a.rowbits, a.wpr, a.keep_scale);
+  GX_F32_ATTN(attn_bwd_dkv_f32_kernel, f);
   return hipGetLastError();
 }
 

@@ -1,0 +1,73 @@
+"""fp32 products and attention at the edges of their tiles: remainders of the 32 / 64 row tiles and of
+the reduction stages, head dimensions that are padded, every tile size of the dispatch, and values
+that are not finite in positions that the causal mask hides."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import layer as O
+from paper_2504_03662_amd import inputs as I
+from paper_2504_03662_amd.runtime import DeviceLayer, to_device, to_host
+from parity import TOL, compare, run_both
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hidden,heads,ffn,seq,batch", [
+    (4, 1, 4, 1, 1),            # one token, one chunk
+    (36, 3, 20, 31, 1),         # head dim 12, one tile short of a row
+    (120, 6, 132, 33, 3),       # head dim 20, one row past a tile
+    (100, 2, 200, 65, 2),       # head dim 50: rows that are not multiples of 16 bytes
+    (96, 1, 324, 129, 2),       # head dim 96, five key tiles: one wavefront takes two
+    (256, 2, 516, 160, 2),      # head dim 128
+    (768, 12, 772, 700, 1),     # 64-row tiles, one and two wavefronts per block
+    (512, 8, 2052, 1030, 2),    # more 64-row tiles than compute units, 33 key tiles
+])
+def test_fp32_tile_edges(hidden, heads, ffn, seq, batch):
+    shape = I.LayerShape(hidden, heads, ffn, 1, 1, 0, seq, batch, "f32")
+    params = I.full_params(shape, case=400 + seq, random_affine=True)
+    x, dy = I.activations(shape, case=400 + seq)
+    gpu, ref, _ = run_both(shape, params, x, dy, want_partials=True)
+    compare(gpu, ref, TOL["f32"], want_partials=True)
+
+
+def test_fp32_accumulation_and_dropout_with_padded_heads():
+    shape = I.LayerShape(144, 3, 164, 1, 1, 0, 77, 2, "f32", drop_attn=40, drop_hidden=30, drop_seed=0xABCDEF0123)
+    params = I.full_params(shape, case=431, random_affine=True)
+    x, dy = I.activations(shape, case=431)
+    gpu, ref, layer = run_both(shape, params, x, dy, want_partials=True)
+    compare(gpu, ref, TOL["f32"], want_partials=True)
+    xd, dyd = to_device(x, "f32"), to_device(dy, "f32")
+    layer.backward(xd, dyd, accumulate=True)
+    torch.cuda.synchronize()
+    for n in I.PARAM_NAMES:
+        # twice one backward pass: each element is one fp32 addition of equal values, exact
+        np.testing.assert_array_equal(to_host(layer.grads[n]), 2 * gpu["grads"][n])
+
+
+@pytest.mark.parametrize("heads", [1, 2, 4, 8])
+@pytest.mark.parametrize("at", [40, 99])
+def test_fp32_values_that_are_not_finite_stay_behind_the_mask(heads, at):
+    # one token of one sample is not finite: rows before it (and the other sample) are untouched bit
+    # for bit, its own row is not finite
+    shape = I.LayerShape(256, heads, 256, 1, 1, 0, 100, 2, "f32") if heads > 1 else \
+        I.LayerShape(128, heads, 256, 1, 1, 0, 100, 2, "f32")
+    params = I.full_params(shape, case=440, random_affine=True)
+    x, dy = I.activations(shape, case=440)
+    layer = DeviceLayer(shape, params)
+    dyd = to_device(dy, "f32")
+    xd = to_device(x, "f32")
+    y0 = to_host(layer.forward(xd)["y"])
+    xbad = x.copy()
+    xbad[at] = np.inf
+    xb = to_device(xbad, "f32")
+    y1 = to_host(layer.forward(xb)["y"])
+    dx1 = to_host(layer.backward(xb, dyd))
+    layer.forward(xd)
+    dx0 = to_host(layer.backward(xd, dyd))
+    # the tile that holds the token adds its finite rows in another order, so equal up to rounding there
+    tol = dict(rtol=0, atol=1e-5 * np.abs(y0).max())
+    np.testing.assert_allclose(y1[:at], y0[:at], **tol)
+    np.testing.assert_array_equal(y1[100:], y0[100:])
+    np.testing.assert_array_equal(dx1[100:], dx0[100:])
+    assert not np.isfinite(y1[at]).any()
