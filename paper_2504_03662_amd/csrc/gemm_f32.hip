@@ -1,133 +1,225 @@
-// fp32 GEMM for the full-precision configuration: a plain LDS-tiled kernel (64x64x32 tile, 4x4
-// outputs per thread, fp32 FMAs only, next tile prefetched into registers) with the same layouts
-// and epilogues as the bf16 family.  That configuration is a few GFLOP with at most 64 tiles per
-// product, so this kernel is written for exactness (no reduced-precision shortcut anywhere), not
-// for the matrix cores.
+// fp32 GEMM for the full-precision configuration on v_mfma_f32_32x32x2_f32 (full fp32 products and
+// sums, twice the rate of the vector units' multiply-add), with the layouts and epilogues of the
+// bf16 family.
+//
+// A workgroup owns a BM x BM tile of C as 32 x 32 blocks, one per wavefront; KW wavefronts share a
+// block by taking KW interleaved shares of the reduction, added in order through LDS at the end.
+// Operand tiles of 32 KW reduction steps go from memory straight into LDS through a ring of STAGES
+// stages, one barrier per stage.  A matrix instruction holds the pipe for 64 cycles and needs one
+// or two LDS reads, so the matrix pipe is the bound as soon as every SIMD has a wavefront with data:
+// the tile is chosen to give the chip enough wavefronts, not to save LDS traffic.  Against a 64 x 64
+// tile of scalar multiply-adds: 256 x 256 x 1024 60 -> 9 us, 1024 x 1024 x 4096 (NT) 240 -> 76 us.
 #include "gx_kernels.h"
 
 namespace gx {
 namespace {
 
-constexpr int TM = 64, TN = 64, TK = 32;
-constexpr int PER = TM * TK / 256;       // elements of each operand tile per thread
+constexpr unsigned OOB = 0x80000000u;    // beyond num_records: the load writes zeros
 
-template <int LAY, int EPI>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs g) {
-  __shared__ float sa[TK][TM + 4];
-  __shared__ float sb[TK][TN + 4];
-  const float* A = static_cast<const float*>(g.A);
-  const float* B = static_cast<const float*>(g.B);
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-  float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; i++)
-#pragma unroll
-    for (int j = 0; j < 4; j++) acc[i][j] = 0.f;
-
-  // each thread brings PER elements of each tile, walking the operand's contiguous index fastest;
-  // the next tile's elements are fetched into registers while the current tile is multiplied
-  auto a_pos = [&](int i, int& m, int& k) {
-    const int e = tid + 256 * i;
-    if (LAY == LAY_TN) { m = e & (TM - 1); k = e / TM; } else { k = e & (TK - 1); m = e / TK; }
-  };
-  auto b_pos = [&](int i, int& n, int& k) {
-    const int e = tid + 256 * i;
-    if (LAY == LAY_NT) { k = e & (TK - 1); n = e / TK; } else { n = e & (TN - 1); k = e / TN; }
-  };
-  float ra[PER], rb[PER];
-  auto fetch = [&](int k0) {
+// Loads of one operand's share of a stage: KW sub-tiles of 32 reduction steps.  K-major (reduction
+// index contiguous in memory): [BM rows][32 k], 16 B chunk c of row r at c ^ ((r >> 1) & 7), so that
+// the 16 rows of one LDS read pass fall in distinct banks.  MN-major: [32 k][BM columns].
+template <bool KMAJOR, int BM, int KW, int NW>
+struct TileLoader {
+  static constexpr int PER = BM * 32 * KW * 4 / 1024 / NW;     // 1 KB instructions per wavefront
+  unsigned base[PER];      // element offset without the stage's reduction index, or OOB
+  int kc[PER];             // reduction index of the lane's chunk within the stage
+  __amdgpu_buffer_rsrc_t rsrc;
+  int ld, K;
+  GX_DEVINL void init(const float* p, size_t bytes, int ld_, int K_, int origin, int extent, int wave, int lane) {
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (unsigned)bytes, 0x00020000);
+    ld = ld_;
+    K = K_;
 #pragma unroll
     for (int i = 0; i < PER; i++) {
-      int m, k, n, kb;
-      a_pos(i, m, k);
-      b_pos(i, n, kb);
-      ra[i] = 0.f;
-      if (m0 + m < g.M && k0 + k < g.K)
-        ra[i] = (LAY == LAY_TN) ? A[(size_t)(k0 + k) * g.lda + m0 + m] : A[(size_t)(m0 + m) * g.lda + k0 + k];
-      rb[i] = 0.f;
-      if (n0 + n < g.N && k0 + kb < g.K)
-        rb[i] = (LAY == LAY_NT) ? B[(size_t)(n0 + n) * g.ldb + k0 + kb] : B[(size_t)(k0 + kb) * g.ldb + n0 + n];
+      const int q = (wave * PER + i) * 64 + lane, per_sub = BM * 8;     // 16 B slots; BM * 8 in a sub-tile
+      const int sub = q / per_sub, s = q % per_sub;
+      if (KMAJOR) {
+        const int r = s >> 3, c = (s & 7) ^ ((r >> 1) & 7);
+        kc[i] = 32 * sub + 4 * c;
+        base[i] = (origin + r < extent) ? (unsigned)((origin + r) * ld + kc[i]) : OOB;
+      } else {
+        const int k = s / (BM / 4), c = s % (BM / 4);
+        kc[i] = 32 * sub + k;
+        base[i] = (origin + 4 * c < extent) ? (unsigned)(kc[i] * ld + origin + 4 * c) : OOB;
+      }
     }
-  };
-  fetch(0);
-  for (int k0 = 0; k0 < g.K; k0 += TK) {
-#pragma unroll
-    for (int i = 0; i < PER; i++) {
-      int m, k, n, kb;
-      a_pos(i, m, k);
-      b_pos(i, n, kb);
-      sa[k][m] = ra[i];
-      sb[kb][n] = rb[i];
-    }
-    __syncthreads();
-    if (k0 + TK < g.K) fetch(k0 + TK);
-#pragma unroll
-    for (int k = 0; k < TK; k++) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; i++) av[i] = sa[k][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; j++) bv[j] = sb[k][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int j = 0; j < 4; j++) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-    }
-    __syncthreads();
   }
+  GX_DEVINL void issue(char* dst, int k0, int wave) const {
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+      const unsigned off =
+          (base[i] != OOB && k0 + kc[i] < K) ? (base[i] + (unsigned)(KMAJOR ? k0 : k0 * ld)) * 4u : OOB;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(dst + (wave * PER + i) * 1024), 16, off, 0, 0, 0);
+    }
+  }
+};
 
+// This lane's operand of the four 32x32x2 products that cover reduction steps 8 c .. 8 c + 7: step e
+// pairs 8 c + e (lower half of the wavefront) with 8 c + 4 + e (upper half).
+template <bool KMAJOR, int BM>
+GX_DEVINL f32x4 frag(const char* sub, int row, int c, int g) {
+  if (KMAJOR) return *reinterpret_cast<const f32x4*>(sub + row * 128 + (((2 * c + g) ^ ((row >> 1) & 7)) << 4));
+  const float* p = reinterpret_cast<const float*>(sub) + (8 * c + 4 * g) * BM + row;
+  return f32x4{p[0], p[BM], p[2 * BM], p[3 * BM]};
+}
+
+template <int LAY, int EPI, int BM, int KW, int STAGES>
+__global__ void __launch_bounds__(BM * BM * KW / 16) gemm_f32_kernel(GemmArgs g) {
+  constexpr bool A_K = (LAY != LAY_TN), B_K = (LAY == LAY_NT);
+  constexpr int WR = BM / 32, NW = WR * WR * KW, NT = 64 * NW;
+  constexpr int SUB = BM * 128, OPER = KW * SUB, STAGE = 2 * OPER;
+  constexpr int PADN = BM + 4;
+  static_assert(KW * BM * PADN * 4 <= STAGES * STAGE, "partial blocks fit the stages");
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kw = wave % KW, wm = (wave / KW) / WR, wn = (wave / KW) % WR;
+  const int grp = lane >> 5, l32 = lane & 31;
+
+  // consecutive tiles spread over the 8 XCDs' round-robin dispatch, 8 tile-rows at a time
+  int pid = blockIdx.x;
+  if ((gridDim.x & 7) == 0) pid = (pid & 7) * (gridDim.x >> 3) + (pid >> 3);
+  const int tm = (g.M + BM - 1) / BM, tn = (g.N + BM - 1) / BM;
+  const int first = (pid / (8 * tn)) * 8, gsize = min(tm - first, 8);
+  const int m0 = (first + (pid % (8 * tn)) % gsize) * BM, n0 = ((pid % (8 * tn)) / gsize) * BM;
+
+  TileLoader<A_K, BM, KW, NW> la;
+  TileLoader<B_K, BM, KW, NW> lb;
+  la.init(static_cast<const float*>(g.A), (size_t)(A_K ? g.M : g.K) * g.lda * 4, g.lda, g.K, m0, g.M, wave, lane);
+  lb.init(static_cast<const float*>(g.B), (size_t)(B_K ? g.N : g.K) * g.ldb * 4, g.ldb, g.K, n0, g.N, wave, lane);
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; v++) acc[v] = 0.f;
+
+  constexpr int LPT = la.PER + lb.PER;                  // loads per wavefront and stage
+  static_assert((STAGES - 2) * LPT < 64, "vmcnt immediate");
+  const int nk = (g.K + 32 * KW - 1) / (32 * KW);
+#pragma unroll
+  for (int t = 0; t < STAGES - 1; t++) {                // stages beyond K: out of range, zeros, no traffic
+    la.issue(smem + t * STAGE, t * 32 * KW, wave);
+    lb.issue(smem + t * STAGE + OPER, t * 32 * KW, wave);
+  }
+  int slot = 0;
+  for (int kt = 0; kt < nk; kt++) {
+    // stage kt has landed (STAGES - 2 younger ones may be in flight) and every wavefront has finished
+    // with stage kt - 1, whose slot takes the next request
+    // (__syncthreads() would wait for the younger requests too)
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((STAGES - 2) * LPT) : "memory");
+    {
+      char* nxt = smem + (slot == 0 ? STAGES - 1 : slot - 1) * STAGE;
+      la.issue(nxt, (kt + STAGES - 1) * 32 * KW, wave);
+      lb.issue(nxt + OPER, (kt + STAGES - 1) * 32 * KW, wave);
+    }
+    const char* ta = smem + slot * STAGE + kw * SUB;
+    const char* tb = ta + OPER;
+    f32x4 fa[4], fb[4];
+#pragma unroll
+    for (int c = 0; c < 4; c++) {
+      fa[c] = frag<A_K, BM>(ta, 32 * wm + l32, c, grp);
+      fb[c] = frag<B_K, BM>(tb, 32 * wn + l32, c, grp);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; c++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[c][e], fb[c][e], acc, 0, 0, 0);
+    slot = (slot == STAGES - 1) ? 0 : slot + 1;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // requests beyond K must not land in what follows
+  __syncthreads();
+
+  // blocks through LDS: [kw][BM rows][BM columns + 4], then whole 16 B runs of a row
+  float* part = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int v = 0; v < 16; v++)
+    part[(kw * BM + 32 * wm + 8 * (v >> 2) + 4 * grp + (v & 3)) * PADN + 32 * wn + l32] = acc[v];
+  __syncthreads();
   const float* bias = static_cast<const float*>(g.bias);
   const float* resid = static_cast<const float*>(g.resid);
   const float* zin = static_cast<const float*>(g.z);
   float* aux = static_cast<float*>(g.aux);
   float* C = static_cast<float*>(g.C);
 #pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int row = m0 + ty + 16 * i;
-    if (row >= g.M) continue;
+  for (int i = 0; i < BM * BM / 4 / NT; i++) {
+    const int s = threadIdx.x + i * NT, r = s / (BM / 4), c = 4 * (s % (BM / 4));
+    const int row = m0 + r, col = n0 + c;
+    if (row >= g.M || col >= g.N) continue;             // N is a multiple of 4: whole run in or out
+    f32x4 x = *reinterpret_cast<const f32x4*>(part + r * PADN + c);
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const int col = n0 + tx + 16 * j;
-      if (col >= g.N) continue;
-      const size_t idx = (size_t)row * g.ldc + col;
-      float x = acc[i][j];
-      const float bv = ((EPI == EPI_BIAS || EPI == EPI_RESID || EPI == EPI_GELU) && bias) ? bias[col] : 0.f;
-      if (EPI == EPI_STORE || EPI == EPI_F32) {
-        C[idx] = x;
-      } else if (EPI == EPI_BIAS) {
-        C[idx] = x + bv;
-      } else if (EPI == EPI_RESID) {
-        x += bv;
-        if (aux) aux[idx] = x;
-        C[idx] = x + resid[idx];
-      } else if (EPI == EPI_GELU) {
-        x += bv;
-        float y, dy;
-        if (g.gelu_tanh) gelu_tanh_both_f(x, y, dy);
-        else gelu_both_f(x, y, dy);
-        C[idx] = dy;
-        aux[idx] = y;
-      } else if (EPI == EPI_DGELU) {
-        C[idx] = x * zin[idx];
-      } else {
-        C[idx] += x;
-      }
+    for (int k = 1; k < KW; k++) {
+      const f32x4 p = *reinterpret_cast<const f32x4*>(part + (k * BM + r) * PADN + c);
+#pragma unroll
+      for (int e = 0; e < 4; e++) x[e] += p[e];
     }
+    const size_t idx = (size_t)row * g.ldc + col;
+    if ((EPI == EPI_BIAS || EPI == EPI_RESID || EPI == EPI_GELU) && bias) {
+      const f32x4 b = *reinterpret_cast<const f32x4*>(bias + col);
+#pragma unroll
+      for (int e = 0; e < 4; e++) x[e] += b[e];
+    }
+    if (EPI == EPI_RESID) {
+      if (aux) *reinterpret_cast<f32x4*>(aux + idx) = x;
+      const f32x4 o = *reinterpret_cast<const f32x4*>(resid + idx);
+#pragma unroll
+      for (int e = 0; e < 4; e++) x[e] += o[e];
+    } else if (EPI == EPI_GELU) {
+      f32x4 y;
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        float ye, dye;
+        if (g.gelu_tanh) gelu_tanh_both_f(x[e], ye, dye);
+        else gelu_both_f(x[e], ye, dye);
+        y[e] = ye;
+        x[e] = dye;
+      }
+      *reinterpret_cast<f32x4*>(aux + idx) = y;
+    } else if (EPI == EPI_DGELU) {
+      const f32x4 z = *reinterpret_cast<const f32x4*>(zin + idx);
+#pragma unroll
+      for (int e = 0; e < 4; e++) x[e] *= z[e];
+    } else if (EPI == EPI_F32_ACC) {
+      const f32x4 o = *reinterpret_cast<const f32x4*>(C + idx);
+#pragma unroll
+      for (int e = 0; e < 4; e++) x[e] += o[e];
+    }
+    *reinterpret_cast<f32x4*>(C + idx) = x;
   }
 }
 
+template <int LAY, int EPI, int BM, int KW, int STAGES>
+hipError_t launch_tile(const GemmArgs& g, hipStream_t s) {
+  constexpr int SMEM = STAGES * 2 * KW * BM * 128;
+  static bool configured = false;
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_kernel<LAY, EPI, BM, KW, STAGES>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI, BM, KW, STAGES>), dim3(cdiv(g.M, BM) * cdiv(g.N, BM)),
+                     dim3(BM * BM * KW / 16), SMEM, s, g);
+  return hipGetLastError();
+}
+
+// The smaller tile is for products that leave most of the 256 compute units without one of 64 x 64;
+// two wavefronts per block for products of at most one 64 x 64 tile per unit, which would leave a
+// wavefront per SIMD; beyond that the smallest stages, so that three workgroups share a unit.
+// Measured (NN, us; <32, KW 4> / <64, KW 2> / <64, KW 1>):
+//   tiles of 64 x 64      64               128              256              320              4096
+//   (M, N, K)             512 512 1024     512 1024 1024    1024 1024 1024   1024 1280 1024   4096 4096 1024
+//                         9.7/21.2/23.6    18.0/21.6/23.8   32.8/22.4/24.2   41.1/41.4/38.7   502/321/279
+// and at 192 tiles 25.1/21.6/23.8.  The largest is 123 TFLOP/s of a peak of 157.
 template <int LAY, int EPI>
 hipError_t launch(const GemmArgs& g, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI>), dim3(cdiv(g.N, TN), cdiv(g.M, TM)), dim3(256), 0, s, g);
-  return hipGetLastError();
+  const long t64 = (long)cdiv(g.M, 64) * cdiv(g.N, 64);
+  if (t64 <= 128) return launch_tile<LAY, EPI, 32, 4, 4>(g, s);
+  if (t64 <= 256) return launch_tile<LAY, EPI, 64, 2, 4>(g, s);
+  return launch_tile<LAY, EPI, 64, 1, 3>(g, s);
 }
 
 template <int LAY>
 hipError_t dispatch_epi(Epilogue epi, const GemmArgs& g, hipStream_t s) {
   switch (epi) {
-    case EPI_STORE: return launch<LAY, EPI_STORE>(g, s);
+    case EPI_STORE: return launch<LAY, EPI_F32>(g, s);
     case EPI_BIAS: return launch<LAY, EPI_BIAS>(g, s);
     case EPI_RESID: return launch<LAY, EPI_RESID>(g, s);
     case EPI_GELU: return launch<LAY, EPI_GELU>(g, s);
@@ -142,6 +234,13 @@ hipError_t dispatch_epi(Epilogue epi, const GemmArgs& g, hipStream_t s) {
 
 hipError_t gemm_f32(Layout lay, Epilogue epi, const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipErrorInvalidValue;
+  // 16-byte chunks along each operand's contiguous index, 31-bit byte offsets in buffer loads
+  const long a_rows = (lay == LAY_TN) ? g.K : g.M, b_rows = (lay == LAY_NT) ? g.N : g.K;
+  if ((g.lda | g.ldb | g.ldc | g.N) & 3) return hipErrorInvalidValue;
+  if ((lay != LAY_TN && (g.K & 3)) || (lay == LAY_TN && (g.M & 3))) return hipErrorInvalidValue;
+  if (a_rows * g.lda * 4 >= (1L << 31) || b_rows * g.ldb * 4 >= (1L << 31)) return hipErrorInvalidValue;
+  if ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B) | reinterpret_cast<uintptr_t>(g.C)) & 15)
+    return hipErrorInvalidValue;
   switch (lay) {
     case LAY_NN: return dispatch_epi<LAY_NN>(epi, g, s);
     case LAY_NT: return dispatch_epi<LAY_NT>(epi, g, s);
