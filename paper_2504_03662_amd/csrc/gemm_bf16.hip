@@ -1,40 +1,71 @@
 // bf16 MFMA GEMM family for gfx950: the dense contractions of one rank's transformer-block share
 // (column-parallel QKV / FC1, row-parallel out-proj / FC2, their input and weight gradients).
 //
-// One workgroup of 8 wavefronts computes a 256x256 tile of C with a K step of 64 through a double
-// buffer, or a 128x128 tile with a K step of 32 through a ring of four stages (products with few
-// tiles keep only one small workgroup per compute unit, which needs the deeper prefetch).  Operand
-// tiles go from HBM straight into LDS (buffer_load ... lds, 16 B per lane, no register staging); fragments for v_mfma_f32_32x32x16_bf16 are read with ds_read_b128 when the
-// reduction index is contiguous in memory ("K-major" tiles) and with the transposing
-// ds_read_b64_tr_b16 when it is strided ("MN-major" tiles), so no operand is ever transposed in
-// HBM.  LDS positions are XOR-swizzled on the global-address side because a direct-to-LDS load
-// fixes each lane's LDS slot.
+// One workgroup computes a tile of C through LDS stages that loads fill straight from HBM
+// (buffer_load ... lds, 16 B per lane, no register staging): 256 x 256 by 8 wavefronts of 128 x 64 and a
+// double buffer of 64 reduction steps, or, for products with few tiles, 128 x 128 by two sets of 4
+// wavefronts of 64 x 64 that share every stage's reduction steps, and a ring of four stages.
+// Products are v_mfma_f32_16x16x32_bf16: on this chip the large products run at the board's power
+// limit, and a register-only loop on normal data holds 1977 TFLOP/s with that instruction against
+// 1816 with 32x32x16 (on zeros 2420 and 2481): it reads and writes an accumulator half as often.
+// Fragments come from ds_read_b128 when the reduction index is contiguous in memory ("K-major" tiles)
+// and from the transposing ds_read_b64_tr_b16 when it is strided ("MN-major" tiles), so no operand is
+// ever transposed in HBM.  LDS positions are XOR-swizzled on the global-address side because a
+// direct-to-LDS load fixes each lane's LDS slot.
+// Measured, TFLOP/s at 4096^3 / 8192^3 (warm, normal data) against the 32x32x16 form of the same loop:
+// NN 1262 / 1360 -> 1383 / 1443, NT 1275 / 1368 -> 1407 / 1448, TN 1224 / 1337 -> 1285 / 1355; the 128 x 128
+// tile against one with 8 wavefronts of 64 x 32: 4096 x 1024 x 4096 NT 40.1 -> 31.7 us, NN 42.5 -> 33.0,
+// 1024 x 4096 x 4096 TN 44.0 -> 35.0.
 #include "gx_kernels.h"
+#include <type_traits>
 
 namespace gx {
 namespace {
 
-constexpr int NTHREADS = 512;
-constexpr int NWAVES = NTHREADS / 64;
 constexpr unsigned OOB = 0x80000000u;           // beyond num_records: the load writes zeros
+
+// A workgroup's tile: BM x BN of C by WGM x WGN wavefronts, times KW wavefronts that share each of
+// those places and take interleaved shares of every stage of KE reduction steps; STAGES stages in LDS.
+template <int BM_, int BN_, int WGM_, int WGN_, int KW_, int KE_, int STAGES_>
+struct Tile {
+  static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, KW = KW_, KE = KE_, STAGES = STAGES_;
+  static constexpr int NW = WGM * WGN * KW, THREADS = 64 * NW;
+  static constexpr int WM = BM / WGM, WN = BN / WGN;           // a wavefront's part of C
+  static constexpr int TM = WM / 16, TN = WN / 16;             // in 16 x 16 accumulators
+  static constexpr int KS = KE / KW / 32;                      // sub-steps of a wavefront's share of a stage
+  static constexpr int A_BYTES = BM * KE * 2, B_BYTES = BN * KE * 2;
+  static constexpr int RING = STAGES * (A_BYTES + B_BYTES);
+  static constexpr int PADN = BN + 4;                          // row of a parked tile, in floats (KW > 1)
+  static constexpr int PARK = KW > 1 ? KW * BM * PADN * 4 + NW * BN * 4 : 0;
+  static constexpr int SMEM = RING > PARK ? RING : PARK;
+  static_assert(KE <= 128 || KE == 256, "swizzle");
+  static_assert(KS == 1 || KS == 2, "the loop over tiles alternates fragment buffers");
+};
 
 // K-major tile: [R rows][BK k], 2 BK bytes per row, 16 B chunk c of row r stored at c ^ swz_k(r):
 // the 16 rows that one ds_read_b128 pass covers at a fixed chunk then fall in distinct banks.
 template <int BK>
-GX_DEVINL int swz_k(int r) { return BK == 64 ? ((r >> 1) & 7) : ((r >> 2) & 3); }
+GX_DEVINL int swz_k(int r) { return BK >= 128 ? (r & 15) : ((r >> 1) & 7); }
 // MN-major tile: [BK k-rows][R cols], 2R B per k-row, 16 B chunk c of k-row kr stored at
-// c ^ swz_mn(kr) (moves whole 64 B groups so that 4 consecutive k-rows fall in distinct banks).
-GX_DEVINL int swz_mn(int kr) { return (kr & 3) << 2; }
+// c ^ swz_mn(kr): whole 64 B groups move so that 4 consecutive k-rows fall in distinct banks (where
+// rows are an odd multiple of 128 B, consecutive rows already alternate between bank halves), and the
+// 32 B halves of a group swap every 8 k-rows, because one pass of the transposing read takes 32 B
+// of 4 consecutive k-rows and of the 4 that lie 8 further on.
+template <int R>
+GX_DEVINL int swz_mn(int kr) {
+  return (R % 128 == 0 ? (kr & 3) << 2 : ((kr >> 1) & 1) << 2) | (((kr >> 3) & 1) << 1);
+}
 
 GX_DEVINL __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsigned bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
 
-// This wave's share of the direct-to-LDS loads of one operand tile (R = 256 or 128 rows/columns
-// by BK reduction steps): R * BK / 4096 instructions of 64 lanes x 16 B each.
-template <bool KMAJOR, int R, int BK>
+// This wave's share of the direct-to-LDS loads of one operand tile (R rows/columns by BK reduction
+// steps): R * BK / (512 NW) instructions of 64 lanes x 16 B each.
+template <bool KMAJOR, int R, int BK, int NW>
 struct TileLoader {
-  static constexpr int PER = R * BK / (512 * NWAVES);
+  static constexpr int PER = R * BK / (512 * NW);
+  static_assert(PER * 512 * NW == R * BK, "whole instructions per wavefront");
   unsigned base[PER];   // k-invariant part of the lane's element offset, or OOB
   int kc[PER];          // K-major: k offset of the chunk; MN-major: k-row of the chunk
   unsigned voff[PER];   // the same as a byte offset (or OOB): the vector offset of the cheap form
@@ -56,16 +87,14 @@ struct TileLoader {
         const int c = (lane % CPR) ^ swz_k<BK>(r);
         kc[i] = c * 8;
         base[i] = (origin + r < extent) ? (unsigned)((origin + r) * ld + c * 8) : OOB;
-        voff[i] = (base[i] != OOB) ? base[i] * 2u : OOB;
       } else {
         constexpr int CPR = R / 8;                 // 16 B chunks per k-row
-        constexpr int KPI = 64 / CPR;              // k-rows per instruction
-        const int kr = KPI * q + lane / CPR;
-        const int c = (lane % CPR) ^ swz_mn(kr);
+        const int kr = (64 * q + lane) / CPR;
+        const int c = ((64 * q + lane) % CPR) ^ swz_mn<R>(kr);
         kc[i] = kr;
         base[i] = (origin + c * 8 < extent) ? (unsigned)(kr * ld + origin + c * 8) : OOB;
-        voff[i] = (base[i] != OOB) ? base[i] * 2u : OOB;
       }
+      voff[i] = (base[i] != OOB) ? base[i] * 2u : OOB;
     }
   }
   // instruction i of this wave's share of the tile that starts at reduction index k0, into LDS at
@@ -92,25 +121,25 @@ struct TileLoader {
   }
 };
 
-// fragment of a 32-row block for k sub-step ks (16 k), K-major tile
-template <int BK>
-GX_DEVINL bf16x8 frag_k(const char* tile, int row, int ks, int g) {
-  const int c = (2 * ks + g) ^ swz_k<BK>(row);
-  return *reinterpret_cast<const bf16x8*>(tile + row * (2 * BK) + (c << 4));
-}
-// A fragment being fetched: either complete (K-major tile, one ds_read_b128 the compiler tracks)
-// or two untracked transposing reads of an MN-major tile that lds_wait_all() must cover.
+// Operands of v_mfma_f32_16x16x32_bf16: lane l holds row (or column) l % 16 and reduction steps
+// 8 (l / 16) .. + 7 of the sub-step.  A fragment being fetched is either complete (K-major tile, one
+// ds_read_b128 the compiler tracks) or two untracked transposing reads of an MN-major tile, which
+// the loop waits for by count.
 struct Frag {
   bf16x8 full;
   bf16x4 lo, hi;
 };
-// fragment of a 32-column block for k sub-step ks, MN-major tile of R columns: issue only
+template <int BK>
+GX_DEVINL bf16x8 frag_k(const char* tile, int row, int k32, int q) {
+  const int c = (4 * k32 + q) ^ swz_k<BK>(row);
+  return *reinterpret_cast<const bf16x8*>(tile + row * (2 * BK) + (c << 4));
+}
 template <int R>
-GX_DEVINL void frag_mn_issue(const char* tile, int col0, int ks, int lane, Frag& f) {
-  const int g = lane >> 5, s = lane & 15;
-  const int kr = 16 * ks + 8 * g + (s >> 2);
-  const int ne = col0 + 16 * ((lane >> 4) & 1) + 4 * (s & 3);
-  const int c = (ne >> 3) ^ swz_mn(kr);
+GX_DEVINL void frag_mn_issue(const char* tile, int col0, int k32, int lane, Frag& f) {
+  const int q = lane >> 4, s = lane & 15;
+  const int kr = 32 * k32 + 8 * q + (s >> 2);
+  const int ne = col0 + 4 * (s & 3);
+  const int c = (ne >> 3) ^ swz_mn<R>(kr);
   const unsigned addr = lds_addr(tile + kr * (2 * R) + (c << 4) + (ne & 7) * 2);
   f.lo = lds_read_tr_issue<0>(addr);
   f.hi = lds_read_tr_issue<4 * (2 * R)>(addr);
@@ -120,27 +149,107 @@ GX_DEVINL bf16x8 frag_mn_finish(Frag& f) {
   lds_pin(f.hi);
   return __builtin_shufflevector(f.lo, f.hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
+// wait until at most n LDS operations of this wavefront are outstanding; n is a constant once the
+// caller's loops are unrolled (one short of the counter's maximum at most)
+GX_DEVINL void lds_wait_most(int n) {
+#define GX_W(N) case N: lds_wait_le<N>(); break;
+  switch (n) {
+    GX_W(0) GX_W(1) GX_W(2) GX_W(3) GX_W(4) GX_W(5) GX_W(6) GX_W(7) GX_W(8) GX_W(9) GX_W(10) GX_W(11) GX_W(12)
+    GX_W(13)
+    default: lds_wait_le<14>();
+  }
+#undef GX_W
+}
 
-// BM x BN output tile (256 x 256, or 128 x 128 for products with too few large tiles to fill the
-// chip); 8 wavefronts as 2 x 4, each owning (BM/2) x (BN/4).  K step BK through STAGES LDS stages.
-template <int LAY, int EPI, int BM, int BN, int BK>
-__global__ void __launch_bounds__(NTHREADS) gemm_kernel(GemmArgs g) {
-  constexpr int STAGES = (BK == 64) ? 2 : 4;
+// Side inputs of an epilogue: what it reads besides the accumulators (the residual, gelu'(z), the
+// weight gradient being added to), one run of 4 columns.
+template <int EPI>
+struct Side {
+  static constexpr bool B16 = (EPI == EPI_RESID || EPI == EPI_DGELU), F32 = (EPI == EPI_F32_ACC), ANY = B16 || F32;
+  bf16x4 h;
+  f32x4 f;
+  GX_DEVINL void fetch(const GemmArgs& g, size_t idx) {
+    if (B16) h = *reinterpret_cast<const bf16x4*>(static_cast<const bf16*>(EPI == EPI_RESID ? g.resid : g.z) + idx);
+    if (F32) f = *reinterpret_cast<const f32x4*>(static_cast<const float*>(g.C) + idx);
+  }
+};
+template <int EPI>
+GX_DEVINL void load_bias(const GemmArgs& g, int col, float (&bv)[4]) {
+#pragma unroll
+  for (int e = 0; e < 4; e++) bv[e] = 0.f;
+  if ((EPI == EPI_BIAS || EPI == EPI_RESID || EPI == EPI_GELU) && g.bias && col < g.N) {
+    const bf16x4 b4 = *reinterpret_cast<const bf16x4*>(static_cast<const bf16*>(g.bias) + col);
+#pragma unroll
+    for (int e = 0; e < 4; e++) bv[e] = (float)b4[e];
+  }
+}
+// One run of 4 columns of C from its sums: bias, the epilogue's arithmetic, the stores.  cs (EPI_DGELU):
+// the stored values are added to it.
+template <int EPI>
+GX_DEVINL void finish_run(const GemmArgs& g, size_t idx, const f32x4& xv, const float (&bv)[4], const Side<EPI>& side,
+                          float (&cs)[4]) {
+  float x[4] = {xv[0] + bv[0], xv[1] + bv[1], xv[2] + bv[2], xv[3] + bv[3]};
+  bf16* aux = static_cast<bf16*>(g.aux);
+  if (EPI == EPI_F32) {
+    *reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + idx) = f32x4{x[0], x[1], x[2], x[3]};
+    return;
+  }
+  if (EPI == EPI_F32_ACC) {
+    *reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + idx) =
+        f32x4{side.f[0] + x[0], side.f[1] + x[1], side.f[2] + x[2], side.f[3] + x[3]};
+    return;
+  }
+  bf16x4 o;
+  if (EPI == EPI_RESID) {
+    if (aux) {
+#pragma unroll
+      for (int e = 0; e < 4; e++) o[e] = (bf16)x[e];
+      *reinterpret_cast<bf16x4*>(aux + idx) = o;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; e++) x[e] += (float)side.h[e];
+  } else if (EPI == EPI_GELU) {
+    bf16x4 ga;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      float y, dy;
+      if (g.gelu_tanh) gelu_tanh_both_fast(x[e], y, dy);
+      else gelu_both_fast(x[e], y, dy);
+      ga[e] = (bf16)y;
+      x[e] = dy;                                     // C receives gelu'(z)
+    }
+    *reinterpret_cast<bf16x4*>(aux + idx) = ga;
+  } else if (EPI == EPI_DGELU) {
+#pragma unroll
+    for (int e = 0; e < 4; e++) x[e] *= (float)side.h[e];
+  }
+#pragma unroll
+  for (int e = 0; e < 4; e++) o[e] = (bf16)x[e];
+  *reinterpret_cast<bf16x4*>(static_cast<bf16*>(g.C) + idx) = o;
+  if (EPI == EPI_DGELU) {
+#pragma unroll
+    for (int e = 0; e < 4; e++) cs[e] += (float)o[e];
+  }
+}
+
+template <int LAY, int EPI, class T>
+__global__ void __launch_bounds__(T::THREADS, 2) gemm_kernel(GemmArgs g) {
+  constexpr int BM = T::BM, BN = T::BN, KE = T::KE, KS = T::KS, STAGES = T::STAGES, TM = T::TM, TN = T::TN;
+  constexpr int WM = T::WM, WN = T::WN, NW = T::NW, KW = T::KW;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr bool A_K = (LAY != LAY_TN);
   constexpr bool B_K = (LAY == LAY_NT);
-  constexpr int TM = BM / 64, TN = BN / 128;          // 32x32 accumulators per wave
-  constexpr int WM = BM / 2, WN = BN / 4;             // wave tile
-  constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
-  constexpr int KS = BK / 16;
-  static_assert(KS % 2 == 0, "fragment double buffer assumes an even number of sub-steps");
+  constexpr int A_BYTES = T::A_BYTES, B_BYTES = T::B_BYTES;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wave >> 2, wn = wave & 3;
-  const int grp = lane >> 5, l32 = lane & 31;
+  const int kw = wave / (T::WGM * T::WGN), place = wave % (T::WGM * T::WGN);
+  const int wm = place / T::WGN, wn = place % T::WGN;
+  const int q4 = lane >> 4, l16 = lane & 15;
 
   // tile index: spread consecutive tiles over the 8 XCDs' round-robin dispatch so that each XCD
-  // (own L2) works on a compact block of tiles, then walk tiles in groups of 8 tile-rows.
+  // (own L2) works on a compact block of tiles, then walk tiles in groups of 8 tile-rows, or of 4
+  // where a launch takes several rounds (8192^3 NT 779 -> 748 us, NN 807 -> 791; 28672 x 8192 x 4096 TN
+  // 1606 -> 1554; within one round the two are equal).
   int pid = blockIdx.x;
   const int nwg = gridDim.x;
   if ((nwg & 7) == 0) pid = (pid & 7) * (nwg >> 3) + (pid >> 3);
@@ -150,10 +259,10 @@ __global__ void __launch_bounds__(NTHREADS) gemm_kernel(GemmArgs g) {
   const int SB = g.tail ? 2 : 1;
   if (g.tail) pid = g.tile_first + (pid >> 2);
   const int tm = (g.M + SB * BM - 1) / (SB * BM), tn = (g.N + SB * BN - 1) / (SB * BN);
-  constexpr int GROUP = 8;
-  const int in_group = GROUP * tn;
-  const int first_m = (pid / in_group) * GROUP;
-  const int gsize = min(tm - first_m, GROUP);
+  const int group = g.group;
+  const int in_group = group * tn;
+  const int first_m = (pid / in_group) * group;
+  const int gsize = min(tm - first_m, group);
   const int pm = first_m + (pid % in_group) % gsize;
   const int pn = (pid % in_group) / gsize;
   const int m0 = (SB * pm + (sub >> 1)) * BM, n0 = (SB * pn + (sub & 1)) * BN;
@@ -161,364 +270,396 @@ __global__ void __launch_bounds__(NTHREADS) gemm_kernel(GemmArgs g) {
 
   const bf16* A = static_cast<const bf16*>(g.A);
   const bf16* B = static_cast<const bf16*>(g.B);
-  TileLoader<A_K, BM, BK> la;
-  TileLoader<B_K, BN, BK> lb;
+  TileLoader<A_K, BM, KE, NW> la;
+  TileLoader<B_K, BN, KE, NW> lb;
   la.init(A, (unsigned)((size_t)(A_K ? g.M : g.K) * g.lda * 2), g.lda, g.K, m0, g.M, wave, lane);
   lb.init(B, (unsigned)((size_t)(B_K ? g.N : g.K) * g.ldb * 2), g.ldb, g.K, n0, g.N, wave, lane);
 
-  f32x16 acc[TM][TN];
+  f32x4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; i++)
 #pragma unroll
-    for (int j = 0; j < TN; j++)
-#pragma unroll
-      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
+    for (int j = 0; j < TN; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // Epilogue set-up; it sits ahead of the K loop because the first block of what the epilogue
-  // reads is requested two tiles before the loop ends.
-  const bf16* bias = static_cast<const bf16*>(g.bias);
-  const bf16* resid = static_cast<const bf16*>(g.resid);
-  const bf16* zin = static_cast<const bf16*>(g.z);
-  bf16* aux = static_cast<bf16*>(g.aux);
-  constexpr int EPAD = WN + 4;
-  constexpr int LPR = WN / 4;                          // lanes per row when reading back
-  constexpr int RPI = 64 / LPR;                        // rows per read instruction
-  float* stage = reinterpret_cast<float*>(smem + wave * (32 * EPAD * 4));
-  const int ecol = n0 + wn * WN + 4 * (lane % LPR);
-  float bv[4] = {0.f, 0.f, 0.f, 0.f};
-  if ((EPI == EPI_BIAS || EPI == EPI_RESID || EPI == EPI_GELU) && bias && ecol < g.N) {
-    const bf16x4 b4 = *reinterpret_cast<const bf16x4*>(bias + ecol);
-#pragma unroll
-    for (int e = 0; e < 4; e++) bv[e] = (float)b4[e];
-  }
-  // EPI_DGELU may also leave partial column sums of what it stores (stage 1 of the bias gradient of
-  // the product that made z): a wavefront's rows split into blocks of 64 (two 32-row passes), each
-  // lane adds its rows of a block, lanes that share columns combine by shuffles, and the block's
-  // sums go to colpart[(m0 + wave row) / 64 + block][column].  Every (block, column) has exactly
-  // one writer.
-  static_assert(WM % 64 == 0, "column-sum blocks of 64 rows");
-  float cs[4] = {0.f, 0.f, 0.f, 0.f};
-  // What an epilogue reads besides the accumulators (the residual, gelu'(z), the weight gradient
-  // being added to) is fetched one 32-row block ahead, all of a block's loads together.  Written
-  // as load - use - store per row, every load sits behind the previous row's store (the compiler
+  // reads is requested before the loop ends.
+  //   KW == 1: a wavefront finishes its own WM x WN part, 32 rows at a time through a private LDS
+  //     region; a row is WN / 4 runs of 4 columns, NJ runs per lane and 32 rows.  Where WN / 4 does not
+  //     divide 64 a lane meets NC different column places in turn.
+  //   KW > 1: all partial tiles go to LDS and wavefront w finishes rows w BM / NW onwards.
+  constexpr int LPR = (KW == 1 ? WN : BN) / 4;         // runs per row
+  constexpr int EROWS = KW == 1 ? 32 : BM / NW;        // rows of a block
+  constexpr int NJ = EROWS * LPR / 64, NC = (64 % LPR == 0) ? 1 : 3;
+  static_assert(EROWS * LPR == NJ * 64 && (NC == 1 || (64 * NC) % LPR == 0), "runs of an epilogue block");
+  static_assert(NC == 1 || EPI != EPI_DGELU, "column sums need one column place per lane");
+  constexpr int NBLK = KW == 1 ? WM / 32 : 1;
+  const int erow0 = m0 + (KW == 1 ? wm * WM : wave * EROWS), ecol0 = n0 + (KW == 1 ? wn * WN : 0);
+  auto run_row = [&](int j) { return (64 * j + lane) / LPR; };
+  auto run_col = [&](int j) { return 4 * ((64 * (j % NC) + lane) % LPR); };
+  float bv[NC][4];
+  // Side inputs are fetched one 32-row block ahead, all of a block's loads together.  Written as
+  // load - use - store per row, every load sits behind the previous row's store (the compiler
   // cannot know that the two tensors do not overlap) and the epilogue pays a memory latency per
   // row: 52 k cycles instead of 11 k for the residual form.
-  constexpr bool SIDE16 = (EPI == EPI_RESID || EPI == EPI_DGELU), SIDE32 = (EPI == EPI_F32_ACC);
-  constexpr int NJ = 32 / RPI;
-  const bf16* side16 = (EPI == EPI_RESID) ? resid : zin;
-  bf16x4 s16[2][SIDE16 ? NJ : 1];
-  f32x4 s32[2][SIDE32 ? NJ : 1];
-  auto fetch = [&](int mi, int buf) {
+  constexpr bool AHEAD = NBLK > 1 && !(Side<EPI>::F32 && NC > 1);   // two blocks' worth of registers
+  Side<EPI> side[AHEAD ? 2 : 1][NJ];
+  auto fetch = [&](int blk, int buf) {
+    if (blk == 0) {
+#pragma unroll
+      for (int c = 0; c < NC; c++) load_bias<EPI>(g, ecol0 + run_col(c), bv[c]);
+    }
+    if (!Side<EPI>::ANY) return;
 #pragma unroll
     for (int j = 0; j < NJ; j++) {
-      const int row = m0 + wm * WM + mi * 32 + RPI * j + lane / LPR;
-      if (row >= g.M || ecol >= g.N) continue;
-      const size_t idx = (size_t)row * g.ldc + ecol;
-      if (SIDE16) s16[buf][j] = *reinterpret_cast<const bf16x4*>(side16 + idx);
-      if (SIDE32) s32[buf][j] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(g.C) + idx);
-    }
-  };
-  char* sa = smem;                       // A[STAGES]
-  char* sb = smem + STAGES * A_BYTES;    // B[STAGES]
-  const int nk = (g.K + BK - 1) / BK;
-  // Fragments of sub-step ks+1 are requested before the products of sub-step ks are issued, also
-  // across tiles: the wait for the next tile's DMA and the workgroup barrier sit before the LAST
-  // sub-step's products, whose operands are already in registers, so the first fragments of the
-  // next tile are in flight while those products run and no wavefront starts a tile by waiting
-  // for LDS.  The stage the barrier has just retired receives the next tile to be fetched.
-  Frag fa[2][TM], fb[2][TN];
-  auto request = [&](const char* ta, const char* tb, int ks, int buf) {
-#pragma unroll
-    for (int mi = 0; mi < TM; mi++) {
-      if (A_K) fa[buf][mi].full = frag_k<BK>(ta, wm * WM + mi * 32 + l32, ks, grp);
-      else     frag_mn_issue<BM>(ta, wm * WM + mi * 32, ks, lane, fa[buf][mi]);
-    }
-#pragma unroll
-    for (int ni = 0; ni < TN; ni++) {
-      if (B_K) fb[buf][ni].full = frag_k<BK>(tb, wn * WN + ni * 32 + l32, ks, grp);
-      else     frag_mn_issue<BN>(tb, wn * WN + ni * 32, ks, lane, fb[buf][ni]);
-    }
-  };
-  // one sub-step: finish this sub-step's fragments, let `between` request the next ones (and do
-  // the tile hand-over on the last sub-step), then issue the products
-  auto substep = [&](int ks, auto between) {
-    const int buf = ks & 1;
-    bf16x8 af[TM], bfr[TN];
-    if (!A_K || !B_K || ks == KS - 1) lds_wait_all();
-#pragma unroll
-    for (int mi = 0; mi < TM; mi++) af[mi] = A_K ? fa[buf][mi].full : frag_mn_finish(fa[buf][mi]);
-#pragma unroll
-    for (int ni = 0; ni < TN; ni++) bfr[ni] = B_K ? fb[buf][ni].full : frag_mn_finish(fb[buf][ni]);
-    between(buf);
-#pragma unroll
-    for (int mi = 0; mi < TM; mi++)
-#pragma unroll
-      for (int ni = 0; ni < TN; ni++)
-        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ni], af[mi], acc[mi][ni], 0, 0, 0);
-    // ask the scheduler to place one LDS read after each matrix instruction instead of a block of
-    // reads ahead of a block of products (measured: 0.5 - 1.5 % on the NN and GELU' products, none
-    // slower; raising the wavefront's priority around the products or the compiler's canned
-    // matrix-loop schedules were 1 - 2 % slower)
-#pragma unroll
-    for (int i = 0; i < TM * TN; i++) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      const int row = erow0 + 32 * blk + run_row(j), col = ecol0 + run_col(j);
+      if (row < g.M && col < g.N) side[buf][j].fetch(g, (size_t)row * g.ldc + col);
     }
   };
 
-  if constexpr (STAGES == 2) {
-    // Double buffer, written as a fixed sequence of slots: every matrix instruction is followed by
-    // at most one fragment read and one tile load, and a scheduling barrier on either side keeps
-    // the compiler from regrouping them.  Left to itself it gathers a tile's loads and their address
-    // arithmetic into one block behind the workgroup barrier, during which both wavefronts of a
-    // SIMD leave the matrix pipe idle at the same moment (measured: 2 - 8 % per product).
-    //   sub-steps 0 .. KS-2: products of sub-step ks, fragments of sub-step ks + 1 requested
-    //   sub-step KS-1:       wait for tile kt + 1, workgroup barrier, then the products, the first
-    //                        fragments of tile kt + 1, and tile kt + 2 into the stage just retired
-    constexpr int SL = TM * TN, NF = TM + TN;
-    constexpr int PER = TileLoader<A_K, BM, BK>::PER;
-    static_assert(TileLoader<B_K, BN, BK>::PER == PER && 2 * PER <= SL && NF <= SL, "slots of a sub-step");
-    auto request_one = [&](const char* ta, const char* tb, int ks, int buf, int j) {
-      if (j < TM) {
-        if (A_K) fa[buf][j].full = frag_k<BK>(ta, wm * WM + j * 32 + l32, ks, grp);
-        else     frag_mn_issue<BM>(ta, wm * WM + j * 32, ks, lane, fa[buf][j]);
-      } else {
-        const int ni = j - TM;
-        if (B_K) fb[buf][ni].full = frag_k<BK>(tb, wn * WN + ni * 32 + l32, ks, grp);
-        else     frag_mn_issue<BN>(tb, wn * WN + ni * 32, ks, lane, fb[buf][ni]);
-      }
-    };
-    auto tile = [&](int kt, const bool inside) __attribute__((always_inline)) {
-      const int cur = kt & 1;
-      const char* ta = sa + cur * A_BYTES;
-      const char* tb = sb + cur * B_BYTES;
-      const char* na = sa + (cur ^ 1) * A_BYTES;
-      const char* nb = sb + (cur ^ 1) * B_BYTES;
-      const unsigned offa = la.tile_offset((kt + 2) * BK), offb = lb.tile_offset((kt + 2) * BK);
+  // The first block is fetched before the last tiles where the registers allow it (nothing may
+  // spill there: a fragment read in flight must not be moved), else after them.
+  constexpr int SIDE_VGPRS = 2 * NJ * (Side<EPI>::F32 ? 2 : Side<EPI>::B16) + 4 * NC;
+  constexpr bool EARLY = SIDE_VGPRS <= (TM * TN >= 32 ? 8 : 24);
+  char* sa = smem;                       // A[STAGES]
+  char* sb = smem + STAGES * A_BYTES;    // B[STAGES]
+  const int nk = (g.K + KE - 1) / KE;
+  // Fragments of a sub-step are requested during the one before it.  B fragments, which every row of
+  // products uses, alternate between two sets of registers; the A fragment of a row is requested
+  // into its own registers once the row's products are issued.
+  Frag fa[TM], fb[2][TN];
+  auto request_a = [&](const char* ta, int ks, int mi) {
+    if (A_K) fa[mi].full = frag_k<KE>(ta, wm * WM + mi * 16 + l16, kw * KS + ks, q4);
+    else     frag_mn_issue<BM>(ta, wm * WM + mi * 16, kw * KS + ks, lane, fa[mi]);
+  };
+  auto request_b = [&](const char* tb, int ks, int buf, int ni) {
+    if (B_K) fb[buf][ni].full = frag_k<KE>(tb, wn * WN + ni * 16 + l16, kw * KS + ks, q4);
+    else     frag_mn_issue<BN>(tb, wn * WN + ni * 16, kw * KS + ks, lane, fb[buf][ni]);
+  };
+  // The loop is written as a fixed sequence of slots: every matrix instruction is followed by its
+  // share of the fragment reads and tile loads, and a scheduling barrier on either side keeps the
+  // compiler from regrouping them.  Left to itself it gathers a tile's loads and their address
+  // arithmetic into one block behind the workgroup barrier, during which both wavefronts of a SIMD
+  // leave the matrix pipe idle at the same moment (measured: 2 - 8 % per product).
+  //   sub-step before the last: products; B fragments of the next sub-step in its first row, the A
+  //                        fragment of each row at the end of the row (an earlier row's at the same time)
+  //   last sub-step:       products of row 0; wait for tile kt + 1, workgroup barrier; the other rows'
+  //                        products, with the first fragments of tile kt + 1 requested in the same
+  //                        pattern, and tile kt + STAGES requested into the stage just retired
+  // The last tile requests nothing: a fragment read in flight whose destination nobody uses any
+  // more would land in registers that already hold something else.
+  constexpr int LA = TileLoader<A_K, BM, KE, NW>::PER, LPT = LA + TileLoader<B_K, BN, KE, NW>::PER;
+  constexpr int RA = A_K ? 1 : 2, RB = B_K ? 1 : 2;          // LDS reads per fragment
+  static_assert((STAGES - 1) * LPT < 64, "vmcnt immediate");
+  enum { INSIDE, CHECKED, LAST };
+  int slot = 0;
+  auto tile = [&](int kt, auto mode_tag, auto par_tag) __attribute__((always_inline)) {
+    constexpr int MODE = decltype(mode_tag)::value, PAR = decltype(par_tag)::value;
+    char* ta = sa + slot * A_BYTES;
+    char* tb = sb + slot * B_BYTES;
+    slot = (STAGES & (STAGES - 1)) == 0 ? (slot + 1) & (STAGES - 1) : (slot == STAGES - 1 ? 0 : slot + 1);
+    const char* na = sa + slot * A_BYTES;
+    const char* nb = sb + slot * B_BYTES;
+    const unsigned offa = la.tile_offset((kt + STAGES) * KE), offb = lb.tile_offset((kt + STAGES) * KE);
 #pragma unroll
-      for (int ks = 0; ks < KS; ks++) {
-        const int buf = ks & 1;
-        bf16x8 af[TM], bfr[TN];
-        if (!A_K || !B_K || ks == KS - 1) lds_wait_all();
+    for (int ks = 0; ks < KS; ks++) {
+      const int buf = (PAR + ks) & 1;
+      const bool last = ks == KS - 1, hand_over = MODE != LAST && last;
+      const bool requests = !last || hand_over;
+      const int row0 = hand_over ? 1 : 0;                    // first row that requests
+      const char* ra = last ? na : ta;
+      const char* rb = last ? nb : tb;
+      const int rks = last ? 0 : ks + 1;
+      bf16x8 bfr[TN];
 #pragma unroll
-        for (int mi = 0; mi < TM; mi++) af[mi] = A_K ? fa[buf][mi].full : frag_mn_finish(fa[buf][mi]);
-#pragma unroll
-        for (int ni = 0; ni < TN; ni++) bfr[ni] = B_K ? fb[buf][ni].full : frag_mn_finish(fb[buf][ni]);
-        if (ks == KS - 1) {
-          // every LDS read of tile kt by this wavefront has completed (lds_wait_all)
-          __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's share of tile kt + 1 has landed
-          __syncthreads();
+      for (int mi = 0; mi < TM; mi++) {
+        // untracked reads still outstanding that are younger than what this row needs: the A
+        // fragments of later rows, and this sub-step's requests so far
+        const int newer = (!requests || mi <= row0) ? 0 : TN * RB + mi * RA;
+        if (!(hand_over && mi >= 1)) {
+          if (!A_K || (!B_K && mi == 0)) lds_wait_most((TM - 1 - mi) * RA + newer);
+        } else if (mi == 1) {
+          // every LDS read of tile kt by this wavefront has completed; its share of tile kt + 1 has
+          // landed when only the younger tiles' requests are outstanding
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((STAGES - 2) * LPT) : "memory");
         }
+        if (mi == 0) {
+#pragma unroll
+          for (int ni = 0; ni < TN; ni++) bfr[ni] = B_K ? fb[buf][ni].full : frag_mn_finish(fb[buf][ni]);
+        }
+        const bf16x8 af = A_K ? fa[mi].full : frag_mn_finish(fa[mi]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int sl = 0; sl < SL; sl++) {
-          const int mi = sl / TN, ni = sl % TN;
-          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ni], af[mi], acc[mi][ni], 0, 0, 0);
+        for (int ni = 0; ni < TN; ni++) {
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[ni], af, acc[mi][ni], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
-          if (sl < NF) {
-            // past the last tile this reads a stage that holds zeros or a stale tile; never used
-            if (ks + 1 < KS) request_one(ta, tb, ks + 1, buf ^ 1, sl);
-            else request_one(na, nb, 0, buf ^ 1, sl);
+          if (requests && mi == row0) request_b(rb, rks, buf ^ 1, ni);
+          if (requests && mi >= row0 && ni == TN - 1) {
+            if (mi == row0) {
+#pragma unroll
+              for (int m = 0; m < row0; m++) request_a(ra, rks, m);
+            }
+            request_a(ra, rks, mi);
           }
-          if (ks == KS - 1 && sl >= SL - 2 * PER) {
-            const int i = sl - (SL - 2 * PER);
-            if (inside) {
-              if (i < PER) la.issue_inside(sa + cur * A_BYTES, offa, wave, i);
-              else lb.issue_inside(sb + cur * B_BYTES, offb, wave, i - PER);
-            } else {
-              // a ragged last tile, or nothing at all beyond K (every lane out of range: zeros, no
-              // memory traffic)
-              if (i < PER) la.issue_one(sa + cur * A_BYTES, (kt + 2) * BK, wave, i);
-              else lb.issue_one(sb + cur * B_BYTES, (kt + 2) * BK, wave, i - PER);
+          if (hand_over && mi >= 1) {
+            constexpr int SL = (TM - 1) * TN;
+            const int sl = (mi - 1) * TN + ni;
+#pragma unroll
+            for (int i = sl * LPT / SL; i < (sl + 1) * LPT / SL; i++) {
+              if (MODE == INSIDE) {
+                if (i < LA) la.issue_inside(ta, offa, wave, i);
+                else lb.issue_inside(tb, offb, wave, i - LA);
+              } else {
+                // a ragged last tile, or nothing at all beyond K (every lane out of range: zeros, no
+                // memory traffic; the count of loads in flight stays the same)
+                if (i < LA) la.issue_one(ta, (kt + STAGES) * KE, wave, i);
+                else lb.issue_one(tb, (kt + STAGES) * KE, wave, i - LA);
+              }
             }
           }
           __builtin_amdgcn_sched_barrier(0);
         }
       }
-    };
-    la.issue(sa, 0, wave);
-    lb.issue(sb, 0, wave);
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's LDS-DMA has landed
-    __syncthreads();
-    la.issue(sa + A_BYTES, BK, wave);
-    lb.issue(sb + B_BYTES, BK, wave);
-    request(sa, sb, 0, 0);
-    const int ninside = max(0, g.K / BK - 2);   // tiles kt whose prefetch target kt + 2 lies wholly inside K
-    for (int kt = 0; kt < ninside; kt++) tile(kt, true);
-    if (SIDE16 || SIDE32) fetch(0, 0);
-    for (int kt = ninside; kt < nk; kt++) tile(kt, false);
-    // the zero-fill requests of the last two tiles must have landed before the staging below reuses LDS
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    __syncthreads();
-  } else {
-    // ring of STAGES tiles, STAGES - 1 in flight.  Loads in flight are counted per wavefront, LPT
-    // per tile; tiles beyond K are requested like any other (every lane out of range: zeros, no
-    // memory traffic), so that the count at each wait is the same in every step.
-    constexpr int LPT = TileLoader<A_K, BM, BK>::PER + TileLoader<B_K, BN, BK>::PER;
-    static_assert((STAGES - 1) * LPT < 16, "vmcnt immediate");
-#pragma unroll
-    for (int t = 0; t < STAGES; t++) {
-      la.issue(sa + t * A_BYTES, t * BK, wave);
-      lb.issue(sb + t * B_BYTES, t * BK, wave);
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70 | ((STAGES - 1) * LPT));   // vmcnt: tile 0 has landed
-    __syncthreads();
-    request(sa, sb, 0, 0);
-    for (int kt = 0; kt < nk; kt++) {
-      const int cur = kt & (STAGES - 1), nxt = (kt + 1) & (STAGES - 1);
-      const char* ta = sa + cur * A_BYTES;
-      const char* tb = sb + cur * B_BYTES;
+  };
+#define GX_TILE(KT, MODE, PAR) tile(KT, std::integral_constant<int, MODE>(), std::integral_constant<int, PAR>())
 #pragma unroll
-      for (int ks = 0; ks < KS; ks++) {
-        substep(ks, [&](int buf) {
-          if (ks + 1 < KS) {
-            request(ta, tb, ks + 1, buf ^ 1);
-          } else {
-            // tile kt+1 has landed once at most STAGES-2 younger tiles are still in flight
-            __builtin_amdgcn_s_waitcnt(0x0F70 | ((STAGES - 2) * LPT));
-            __syncthreads();
-            la.issue(sa + cur * A_BYTES, (kt + STAGES) * BK, wave);
-            lb.issue(sb + cur * B_BYTES, (kt + STAGES) * BK, wave);
-            if (kt + 1 < nk) request(sa + nxt * A_BYTES, sb + nxt * B_BYTES, 0, buf ^ 1);
-          }
-        });
-      }
-    }
-    if (SIDE16 || SIDE32) fetch(0, 0);
-    // the zero-fill requests of the tail must have landed before the staging below reuses LDS
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    __syncthreads();
+  for (int t = 0; t < STAGES; t++) {
+    la.issue(sa + t * A_BYTES, t * KE, wave);
+    lb.issue(sb + t * B_BYTES, t * KE, wave);
   }
-  // every wavefront passed the last barrier with all its LDS reads complete, so the tile buffers
-  // are free to serve as staging space below
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((STAGES - 1) * LPT) : "memory");   // tile 0 is there
+#pragma unroll
+  for (int ni = 0; ni < TN; ni++) request_b(sb, 0, 0, ni);
+#pragma unroll
+  for (int mi = 0; mi < TM; mi++) request_a(sa, 0, mi);
+  const int ninside = max(0, g.K / KE - STAGES);   // tiles kt whose prefetch target kt + STAGES lies wholly inside K
+  int kt = 0;
+  if constexpr (KS == 2) {
+    for (; kt < ninside; kt++) GX_TILE(kt, INSIDE, 0);
+    if (EARLY) fetch(0, 0);
+    for (; kt < nk - 1; kt++) GX_TILE(kt, CHECKED, 0);
+    GX_TILE(nk - 1, LAST, 0);
+  } else {                                         // one sub-step per tile: the B registers alternate by tile
+    for (; kt + 1 < ninside; kt += 2) {
+      GX_TILE(kt, INSIDE, 0);
+      GX_TILE(kt + 1, INSIDE, 1);
+    }
+    if (EARLY) fetch(0, 0);
+    for (; kt + 2 < nk; kt += 2) {
+      GX_TILE(kt, CHECKED, 0);
+      GX_TILE(kt + 1, CHECKED, 1);
+    }
+    GX_TILE(kt, CHECKED, 0);
+    if (kt + 1 < nk) {
+      GX_TILE(kt + 1, LAST, 1);
+    } else {                                       // nothing left: see the reads of the next stage's zeros in
+      lds_wait_all();
+#pragma unroll
+      for (int mi = 0; mi < TM; mi++)
+        if (!A_K) lds_pin(fa[mi].lo), lds_pin(fa[mi].hi);
+#pragma unroll
+      for (int ni = 0; ni < TN; ni++)
+        if (!B_K) lds_pin(fb[1][ni].lo), lds_pin(fb[1][ni].hi);
+    }
+  }
+#undef GX_TILE
+  if (!EARLY) fetch(0, 0);
+  // the zero-fill requests beyond K must have landed, and every wavefront must be done with the
+  // tiles, before the staging below reuses LDS
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+  __syncthreads();
 
   // epilogue.  The MFMAs were issued with the B fragment as the row operand, so accumulator
-  // register v of lane l holds C[m = tile row l%32][n = 8*(v/4) + 4*(l/32) + v%4]: runs of 4
-  // consecutive columns.  Each wavefront passes its block through a private LDS region, 32 rows at
-  // a time (row stride WN + 4 floats keeps the 16 B writes conflict-free), and reads it back so
-  // that WN/4 lanes cover one row: every global access of the epilogue (C, residual,
-  // pre-activation, second output) is a 16 B or 8 B vector in fully used lines.
+  // register v of lane l holds C[m = l % 16][n = 4 * (l / 16) + v] of its block: a run of 4
+  // consecutive columns.  Blocks pass through LDS (row stride of 4 floats more than the columns
+  // keeps the 16 B writes conflict-free) and are read back so that consecutive lanes cover a row:
+  // every global access of the epilogue (C, residual, pre-activation, second output) is a 16 B
+  // or 8 B vector in fully used lines.
+  // EPI_DGELU may also leave partial column sums of what it stores (stage 1 of the bias gradient of
+  // the product that made z), one row of sums per block of 64 rows of C, by one writer each.
+  float cs[4] = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (KW == 1) {
+    static_assert(EPI != EPI_DGELU || WM % 64 == 0, "column-sum blocks of 64 rows");
+    constexpr int EPAD = WN + 4;
+    float* stage = reinterpret_cast<float*>(smem + wave * (32 * EPAD * 4));
 #pragma unroll
-  for (int mi = 0; mi < TM; mi++) {
-    if ((SIDE16 || SIDE32) && mi + 1 < TM) fetch(mi + 1, (mi + 1) & 1);
+    for (int mi = 0; mi < NBLK; mi++) {
+      if (AHEAD && mi + 1 < NBLK) fetch(mi + 1, (mi + 1) & 1);
+      if (!AHEAD && mi > 0) fetch(mi, 0);
 #pragma unroll
-    for (int ni = 0; ni < TN; ni++)
+      for (int h = 0; h < 2; h++)
 #pragma unroll
-      for (int q4 = 0; q4 < 4; q4++) {
-        const f32x16& a = acc[mi][ni];
-        *reinterpret_cast<f32x4*>(stage + l32 * EPAD + ni * 32 + 8 * q4 + 4 * grp) =
-            f32x4{a[4 * q4], a[4 * q4 + 1], a[4 * q4 + 2], a[4 * q4 + 3]};
+        for (int ni = 0; ni < TN; ni++)
+          *reinterpret_cast<f32x4*>(stage + (16 * h + l16) * EPAD + ni * 16 + 4 * q4) = acc[2 * mi + h][ni];
+#pragma unroll
+      for (int j = 0; j < NJ; j++) {
+        const f32x4 xv = *reinterpret_cast<const f32x4*>(stage + run_row(j) * EPAD + run_col(j));
+        const int row = erow0 + 32 * mi + run_row(j), col = ecol0 + run_col(j);
+        if (row >= g.M || col >= g.N) continue;            // N is a multiple of 4: whole run in or out
+        finish_run<EPI>(g, (size_t)row * g.ldc + col, xv, bv[j % NC], side[AHEAD ? mi & 1 : 0][j], cs);
       }
+      if (EPI == EPI_DGELU && (mi & 1) && g.colpart) {
+        // each lane has added its rows of the block; lanes that share columns combine by shuffles
 #pragma unroll
-    for (int j = 0; j < 32 / RPI; j++) {
-      const int r = RPI * j + lane / LPR;
-      const f32x4 xv = *reinterpret_cast<const f32x4*>(stage + r * EPAD + 4 * (lane % LPR));
-      const int row = m0 + wm * WM + mi * 32 + r;
-      if (row >= g.M || ecol >= g.N) continue;            // N is a multiple of 4: whole run in or out
-      const size_t idx = (size_t)row * g.ldc + ecol;
-      float x[4] = {xv[0] + bv[0], xv[1] + bv[1], xv[2] + bv[2], xv[3] + bv[3]};
-      if (EPI == EPI_F32) {
-        *reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + idx) = f32x4{x[0], x[1], x[2], x[3]};
-      } else if (EPI == EPI_F32_ACC) {
-        f32x4* cp = reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + idx);
-        const f32x4 old = s32[mi & 1][j];
-        *cp = f32x4{old[0] + x[0], old[1] + x[1], old[2] + x[2], old[3] + x[3]};
-      } else {
-        bf16x4 o;
-        if (EPI == EPI_RESID) {
-          if (aux) {
+        for (int e = 0; e < 4; e++) {
 #pragma unroll
-            for (int e = 0; e < 4; e++) o[e] = (bf16)x[e];
-            *reinterpret_cast<bf16x4*>(aux + idx) = o;
-          }
-          const bf16x4 rv = s16[mi & 1][j];
-#pragma unroll
-          for (int e = 0; e < 4; e++) x[e] += (float)rv[e];
-        } else if (EPI == EPI_GELU) {
-          bf16x4 ga;
-#pragma unroll
-          for (int e = 0; e < 4; e++) {
-            float y, dy;
-            if (g.gelu_tanh) gelu_tanh_both_fast(x[e], y, dy);
-            else gelu_both_fast(x[e], y, dy);
-            ga[e] = (bf16)y;
-            x[e] = dy;                                     // C receives gelu'(z)
-          }
-          *reinterpret_cast<bf16x4*>(aux + idx) = ga;
-        } else if (EPI == EPI_DGELU) {
-          const bf16x4 zv = s16[mi & 1][j];
-#pragma unroll
-          for (int e = 0; e < 4; e++) x[e] *= (float)zv[e];
+          for (int o = LPR; o < 64; o <<= 1) cs[e] += __shfl_xor(cs[e], o, 64);
         }
+        const int row0 = erow0 + (mi - 1) * 32, col = ecol0 + run_col(0);      // first row of this block of 64
+        if (lane < LPR && row0 < g.M && col < g.N)
+          *reinterpret_cast<f32x4*>(g.colpart + (size_t)(row0 >> 6) * g.N + col) = f32x4{cs[0], cs[1], cs[2], cs[3]};
 #pragma unroll
-        for (int e = 0; e < 4; e++) o[e] = (bf16)x[e];
-        *reinterpret_cast<bf16x4*>(static_cast<bf16*>(g.C) + idx) = o;
-        if (EPI == EPI_DGELU) {
-#pragma unroll
-          for (int e = 0; e < 4; e++) cs[e] += (float)o[e];
-        }
+        for (int e = 0; e < 4; e++) cs[e] = 0.f;
       }
     }
-    if (EPI == EPI_DGELU && (mi & 1) && g.colpart) {
+  } else {
+    constexpr int PADN = T::PADN;
+    float* park = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int mi = 0; mi < TM; mi++)
+#pragma unroll
+      for (int ni = 0; ni < TN; ni++)
+        *reinterpret_cast<f32x4*>(park + (kw * BM + wm * WM + mi * 16 + l16) * PADN + wn * WN + ni * 16 + 4 * q4) =
+            acc[mi][ni];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NJ; j++) {
+      const int r = wave * EROWS + run_row(j);
+      f32x4 xv = *reinterpret_cast<const f32x4*>(park + r * PADN + run_col(j));
+#pragma unroll
+      for (int k = 1; k < KW; k++) {
+        const f32x4 p = *reinterpret_cast<const f32x4*>(park + (k * BM + r) * PADN + run_col(j));
+#pragma unroll
+        for (int e = 0; e < 4; e++) xv[e] += p[e];
+      }
+      const int row = m0 + r, col = ecol0 + run_col(j);
+      if (row >= g.M || col >= g.N) continue;
+      finish_run<EPI>(g, (size_t)row * g.ldc + col, xv, bv[j % NC], side[0][j], cs);
+    }
+    if (EPI == EPI_DGELU && g.colpart) {
+      constexpr int WPB = 64 / EROWS;                                          // wavefronts per block of 64 rows
+      float* red = park + KW * BM * PADN;                                      // [NW][BN]
 #pragma unroll
       for (int e = 0; e < 4; e++) {
 #pragma unroll
         for (int o = LPR; o < 64; o <<= 1) cs[e] += __shfl_xor(cs[e], o, 64);
       }
-      const int row0 = m0 + wm * WM + (mi - 1) * 32;         // first row of this block of 64
-      if (lane < LPR && row0 < g.M && ecol < g.N)
-        *reinterpret_cast<f32x4*>(g.colpart + (size_t)(row0 >> 6) * g.N + ecol) = f32x4{cs[0], cs[1], cs[2], cs[3]};
+      if (lane < LPR) *reinterpret_cast<f32x4*>(red + wave * BN + run_col(0)) = f32x4{cs[0], cs[1], cs[2], cs[3]};
+      __syncthreads();
+      for (int i = threadIdx.x; i < BM / 64 * BN; i += T::THREADS) {
+        const int blk = i / BN, c = i % BN;
+        float t = red[blk * WPB * BN + c];
 #pragma unroll
-      for (int e = 0; e < 4; e++) cs[e] = 0.f;
+        for (int w = 1; w < WPB; w++) t += red[(blk * WPB + w) * BN + c];
+        if (m0 + 64 * blk < g.M && n0 + c < g.N) g.colpart[(size_t)((m0 >> 6) + blk) * g.N + n0 + c] = t;
+      }
     }
   }
 }
 
-template <int LAY, int EPI, int BM, int BN, int BK>
+template <int LAY, int EPI, class T>
 hipError_t launch_tile(const GemmArgs& g, hipStream_t s, int grid) {
-  constexpr int SMEM = ((BK == 64) ? 2 : 4) * (BM + BN) * BK * 2;
   static bool configured = false;
   if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<LAY, EPI, BM, BN, BK>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<LAY, EPI, T>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, T::SMEM);
     if (e != hipSuccess) return e;
     configured = true;
   }
-  hipLaunchKernelGGL((gemm_kernel<LAY, EPI, BM, BN, BK>), dim3(grid), dim3(NTHREADS), SMEM, s, g);
+  GemmArgs a = g;
+  if (!a.tail) a.group = grid > 256 ? 4 : 8;
+  hipLaunchKernelGGL((gemm_kernel<LAY, EPI, T>), dim3(grid), dim3(T::THREADS), T::SMEM, s, a);
   return hipGetLastError();
 }
-
-// 256 compute units, one large workgroup each.  Measured on this chip:
-//  - up to 144 large tiles the 128 x 128 tile is faster (128 large tiles: by 22 %; 160: large tile
-//    4-23 % faster);
-//  - beyond one round of 256 large tiles, a remainder of up to TAIL_MAX large tiles would hold the
-//    chip for a whole extra round at a fraction of its width: the whole rounds go to the large
-//    tile and the remainder region is cut into 128 x 128 tiles in a second launch.
-constexpr long ROUND = 256, TAIL_MAX = 128;
-template <int LAY, int EPI>
-hipError_t launch(const GemmArgs& g, hipStream_t s) {
-  const long big = (long)cdiv(g.M, 256) * cdiv(g.N, 256);
-  if (big <= 144) return launch_tile<LAY, EPI, 128, 128, 32>(g, s, cdiv(g.M, 128) * cdiv(g.N, 128));
-  const long rem = big % ROUND;
-  if (big < ROUND || rem == 0 || rem > TAIL_MAX) return launch_tile<LAY, EPI, 256, 256, 64>(g, s, (int)big);
-  hipError_t e = launch_tile<LAY, EPI, 256, 256, 64>(g, s, (int)(big - rem));
-  if (e != hipSuccess) return e;
-  GemmArgs t = g;
-  t.tail = 1;
-  t.tile_first = (int)(big - rem);
-  return launch_tile<LAY, EPI, 128, 128, 32>(t, s, (int)(4 * rem));
+template <int LAY, int EPI, class T>
+hipError_t launch_whole(const GemmArgs& g, hipStream_t s) {
+  return launch_tile<LAY, EPI, T>(g, s, cdiv(g.M, T::BM) * cdiv(g.N, T::BN));
 }
 
+// The tiles.  `fixed` and `per_k` price one round of a tile (at most 256 workgroups, one per compute
+// unit): microseconds that do not depend on K, and per 1024 reduction steps.
+struct Large : Tile<256, 256, 2, 4, 1, 64, 2> { static constexpr float fixed = 9.0f, per_k = 24.8f; };
+struct Wide : Tile<256, 192, 4, 2, 1, 64, 2> { static constexpr float fixed = 8.7f, per_k = 18.7f; };
+struct Tall : Tile<192, 256, 2, 4, 1, 64, 2> { static constexpr float fixed = 8.7f, per_k = 18.7f; };
+struct Half : Tile<256, 128, 4, 2, 1, 64, 3> { static constexpr float fixed = 6.5f, per_k = 14.5f; };
+struct Small : Tile<128, 128, 2, 2, 2, 64, 4> { static constexpr float fixed = 5.1f, per_k = 7.2f; };
+struct Flat : Tile<64, 128, 1, 2, 4, 128, 3> { static constexpr float fixed = 4.8f, per_k = 4.7f; };
+struct Tiny : Tile<64, 64, 1, 1, 4, 128, 4> { static constexpr float fixed = 3.8f, per_k = 3.4f; };
+
+// Which tile: the one whose rounds are cheapest.  A product's time is the number of rounds of 256
+// workgroups it takes times the price of a round, whether the last round is full or not, so the larger
+// tiles (less traffic per product) win where they fill the chip and the smaller ones where a larger
+// one would leave compute units without work.  The prices are fits to products of 1 to 4096 tiles
+// and K 768 to 10240; measured (us), chosen tile first:
+//   NN 4096 x 3072 x 4096   Wide 82.7 (256 tiles)  Large 89.0 (192)  Small 96.5   Half 103.8
+//   NT 2048 x 5120 x 10240  Wide 164 (216)         Large 191 (160)   Tall 179     Small 197
+//   NN 3003 x 4096 x 2048   Tall 44.1 (256)        Large 49.5 (192)  Wide 75.4    Half 57.7
+//   NT 2048 x 2560 x 5120   Half 57.4 (160)        Small 70.9 (320)  Flat 73.1    Large 92.6
+//   NT 4096 x 1024 x 4096   Small 32.0 (256)       Flat 42.9         Half 48.6    Large 72.6
+//   TN 512 x 4096 x 8192    Flat 44.4 (256)        Small 53.4 (128)  Tiny 60.7    Large 151
+//   TN 1024 x 1024 x 4096   Tiny 17.5 (256)        Flat 22.1 (128)   Small 27.7   Large 78.2
+//   NN 128 x 7680 x 5120    Tiny 22.8 (240)        Flat 28.3 (120)   Small 33.9   Large 85.5
+// Beyond whole rounds of large tiles, the remaining ones can also be cut into 128 x 128 tiles in a second
+// launch (TAIL is what that launch costs): NN 2048 x 10240 x 5120, 320 large tiles, 173 against 184
+// (Wide), 189 (Small) and 210 (Large alone).
+constexpr long ROUND = 256;
+constexpr float TAIL = 3.0f;
+template <class T>
+float price(long tiles, int K) {
+  return (float)((tiles + ROUND - 1) / ROUND) * (T::fixed + T::per_k * (float)K * (1.0f / 1024));
+}
+template <class T>
+float price(const GemmArgs& g) {
+  return price<T>((long)cdiv(g.M, T::BM) * cdiv(g.N, T::BN), g.K);
+}
+template <int LAY, int EPI>
+hipError_t launch(const GemmArgs& g, hipStream_t s) {
+  const long big = (long)cdiv(g.M, 256) * cdiv(g.N, 256), rem = big % ROUND;
+  typedef hipError_t (*Launcher)(const GemmArgs&, hipStream_t);
+  Launcher best = launch_whole<LAY, EPI, Large>;
+  float least = price<Large>(g);
+  auto consider = [&](Launcher l, float p) {
+    if (p < least) {
+      least = p;
+      best = l;
+    }
+  };
+  // the 192-wide tiles have no column sums: their wavefronts' parts are not whole blocks of 64 rows
+  if constexpr (EPI != EPI_DGELU) {
+    consider(launch_whole<LAY, EPI, Wide>, price<Wide>(g));
+    consider(launch_whole<LAY, EPI, Tall>, price<Tall>(g));
+  }
+  consider(launch_whole<LAY, EPI, Half>, price<Half>(g));
+  consider(launch_whole<LAY, EPI, Small>, price<Small>(g));
+  consider(launch_whole<LAY, EPI, Flat>, price<Flat>(g));
+  consider(launch_whole<LAY, EPI, Tiny>, price<Tiny>(g));
+  if (big > ROUND && rem && price<Large>(big - rem, g.K) + price<Small>(4 * rem, g.K) + TAIL < least) {
+    hipError_t e = launch_tile<LAY, EPI, Large>(g, s, (int)(big - rem));
+    if (e != hipSuccess) return e;
+    GemmArgs t = g;
+    t.tail = 1;
+    t.group = big - rem > 256 ? 4 : 8;           // the walk of the launch above
+    t.tile_first = (int)(big - rem);
+    return launch_tile<LAY, EPI, Small>(t, s, (int)(4 * rem));
+  }
+  return best(g, s);
+}
+
+// The combinations that the layer driver asks for.
 template <int LAY>
 hipError_t dispatch_epi(Epilogue epi, const GemmArgs& g, hipStream_t s) {
-  switch (epi) {
-    case EPI_STORE: return launch<LAY, EPI_STORE>(g, s);
-    case EPI_BIAS: return launch<LAY, EPI_BIAS>(g, s);
-    case EPI_RESID: return launch<LAY, EPI_RESID>(g, s);
-    case EPI_GELU: return launch<LAY, EPI_GELU>(g, s);
-    case EPI_DGELU: return launch<LAY, EPI_DGELU>(g, s);
-    case EPI_F32: return launch<LAY, EPI_F32>(g, s);
-    case EPI_F32_ACC: return launch<LAY, EPI_F32_ACC>(g, s);
+  if constexpr (LAY == LAY_NN) {
+    if (epi == EPI_BIAS) return launch<LAY, EPI_BIAS>(g, s);
+    if (epi == EPI_RESID) return launch<LAY, EPI_RESID>(g, s);
+    if (epi == EPI_GELU) return launch<LAY, EPI_GELU>(g, s);
+  } else if constexpr (LAY == LAY_NT) {
+    if (epi == EPI_STORE) return launch<LAY, EPI_STORE>(g, s);
+    if (epi == EPI_DGELU) return launch<LAY, EPI_DGELU>(g, s);
+  } else {
+    if (epi == EPI_F32) return launch<LAY, EPI_F32>(g, s);
+    if (epi == EPI_F32_ACC) return launch<LAY, EPI_F32_ACC>(g, s);
+    if (epi == EPI_STORE) return launch<LAY, EPI_STORE>(g, s);
+    if (epi == EPI_RESID) return launch<LAY, EPI_RESID>(g, s);
   }
   return hipErrorInvalidValue;
 }
@@ -527,7 +668,7 @@ hipError_t dispatch_epi(Epilogue epi, const GemmArgs& g, hipStream_t s) {
 
 hipError_t gemm_bf16(Layout lay, Epilogue epi, const GemmArgs& args, hipStream_t s) {
   GemmArgs g = args;
-  g.tail = g.tile_first = 0;                 // the launcher's own fields
+  g.tail = g.tile_first = g.group = 0;       // the launcher's own fields
   if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipErrorInvalidValue;
   // 16-byte chunks along each operand's contiguous index; 31-bit byte offsets in buffer loads
   const long a_rows = (lay == LAY_TN) ? g.K : g.M, b_rows = (lay == LAY_NT) ? g.N : g.K;

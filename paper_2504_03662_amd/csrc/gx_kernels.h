@@ -37,8 +37,9 @@ struct GemmArgs {
   float* colpart;      // bf16 EPI_DGELU only, optional: partial column sums of the stored C over blocks of 64
                        // rows, [ceil(M / 64)][N] fp32 (stage 1 of the bias gradient; finished by colsum_finish)
   // set by the bf16 launcher only (callers leave them 0): a launch that covers the super-tiles
-  // (2 x 2 kernel tiles) numbered tile_first onwards in the tile walk, four workgroups each
-  int tail, tile_first;
+  // (2 x 2 kernel tiles) numbered tile_first onwards in the tile walk, four workgroups each, and the
+  // tile-rows that the walk takes at a time
+  int tail, tile_first, group;
 };
 
 hipError_t gemm_bf16(Layout lay, Epilogue epi, const GemmArgs& g, hipStream_t s);
