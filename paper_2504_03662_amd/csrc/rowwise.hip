@@ -23,47 +23,57 @@ template <typename T> GX_DEVINL void store_vec(T* p, const float (&in)[Vec<T>::N
   *reinterpret_cast<typename Vec<T>::type*>(p) = v;
 }
 
-constexpr int LN_MAXC = 16;   // most 16 B chunks a lane keeps in registers (one wavefront per row)
+constexpr int LN_MAXC = 16;   // most 16 B chunks of a row per lane of one wavefront
 
-// One wavefront per row, the row held in registers (up to MAXC chunks per lane): mean, then
-// centred variance, then output.
-template <typename T, int MAXC>
+// G wavefronts per row (1 or 4), the row held in registers (up to MAXC chunks per lane): mean, then
+// centred variance, then output.  Four rows or one per workgroup.
+template <typename T, int MAXC, int G>
 __global__ void __launch_bounds__(256) ln_fwd_kernel(const T* __restrict__ x, const T* __restrict__ g,
                                                      const T* __restrict__ b, T* __restrict__ y,
                                                      float* __restrict__ mean, float* __restrict__ rstd, int rows,
                                                      int cols, float eps) {
   constexpr int V = Vec<T>::N;
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  __shared__ float red[2][4];
+  const int wave = threadIdx.x >> 6;
+  const int lane = (G == 1) ? threadIdx.x & 63 : threadIdx.x;      // place within the row's lanes
+  const int row = (G == 1) ? blockIdx.x * 4 + wave : blockIdx.x;
   if (row >= rows) return;
+  // sum over the row's lanes, in wavefront order
+  auto row_sum = [&](float v, int k) {
+    v = wave_sum(v);
+    if (G == 1) return v;
+    if ((threadIdx.x & 63) == 0) red[k][wave] = v;
+    __syncthreads();
+    return (red[k][0] + red[k][1]) + (red[k][2] + red[k][3]);
+  };
   const int nchunk = cols / V;
   const T* xr = x + (size_t)row * cols;
   float vals[MAXC][V];
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < MAXC; i++) {
-    const int c = lane + 64 * i;
+    const int c = lane + 64 * G * i;
     if (c < nchunk) {
       load_vec<T>(xr + c * V, vals[i]);
 #pragma unroll
       for (int e = 0; e < V; e++) s += vals[i][e];
     }
   }
-  const float mu = wave_sum(s) / (float)cols;
+  const float mu = row_sum(s, 0) / (float)cols;
   float q = 0.f;
 #pragma unroll
   for (int i = 0; i < MAXC; i++) {
-    if (lane + 64 * i < nchunk) {
+    if (lane + 64 * G * i < nchunk) {
 #pragma unroll
       for (int e = 0; e < V; e++) { const float d = vals[i][e] - mu; q += d * d; }
     }
   }
-  const float rs = rsqrtf(wave_sum(q) / (float)cols + eps);
+  const float rs = rsqrtf(row_sum(q, 1) / (float)cols + eps);
   if (lane == 0) { mean[row] = mu; rstd[row] = rs; }
   T* yr = y + (size_t)row * cols;
 #pragma unroll
   for (int i = 0; i < MAXC; i++) {
-    const int c = lane + 64 * i;
+    const int c = lane + 64 * G * i;
     if (c < nchunk) {
       float gv[V], bv[V], o[V];
       load_vec<T>(g + c * V, gv);
@@ -85,8 +95,8 @@ __global__ void __launch_bounds__(256) ln_fwd_kernel(const T* __restrict__ x, co
 // 8 / G row groups each take R rows per step; the next step's rows are fetched before this step's
 // are worked on, so loads, arithmetic and stores overlap.  Row sums cross the G wavefronts through
 // LDS (one barrier per step, double-buffered by step parity).
-// Every row group keeps its own column accumulators and writes its own partial row:
-// part[a][blockIdx.x * (8 / G) + group][cols] for a < NSUM.  Fixed order throughout.
+// Every row group keeps its own column accumulators; the groups of a workgroup are added through LDS
+// in order and leave one partial row, part[a][blockIdx.x][cols] for a < NSUM.  Fixed order throughout.
 template <typename T, int G, int CPT, int NSUM>
 __global__ void __launch_bounds__(512) ln_bwd_kernel(const T* __restrict__ dy, const T* __restrict__ x,
                                                      const T* __restrict__ g, const float* __restrict__ mean,
@@ -233,17 +243,38 @@ __global__ void __launch_bounds__(512) ln_bwd_kernel(const T* __restrict__ dy, c
     process(s1, base, 1);
     base += stride;
   }
-  const size_t nblk = (size_t)gridDim.x * NG, blk = (size_t)blockIdx.x * NG + grp;
+  constexpr int W = 64 * G * V;                        // columns per chunk index
+  __shared__ f32x4 sums[NG > 1 ? (NG - 1) * CPT * W / 4 : 1];
 #pragma unroll
-  for (int a = 0; a < NSUM; a++)
+  for (int a = 0; a < NSUM; a++) {
+    if (NG > 1) {
+      if (a) __syncthreads();
+      if (grp > 0)
+#pragma unroll
+        for (int i = 0; i < CPT; i++)
+#pragma unroll
+          for (int e = 0; e < V; e += 4)             // [group][chunk][quarter of a chunk][lane]: 16 B runs
+            sums[(((grp - 1) * CPT + i) * (V / 4) + e / 4) * (64 * G) + wg * 64 + lane] =
+                f32x4{acc[a][i][e], acc[a][i][e + 1], acc[a][i][e + 2], acc[a][i][e + 3]};
+      __syncthreads();
+      if (grp > 0) continue;
+    }
 #pragma unroll
     for (int i = 0; i < CPT; i++) {
       if (!live[i]) continue;
-      float* p = part + (a * nblk + blk) * cols + col[i];
+      float* p = part + ((size_t)a * gridDim.x + blockIdx.x) * cols + col[i];
 #pragma unroll
-      for (int e = 0; e < V; e += 4)
-        *reinterpret_cast<f32x4*>(p + e) = f32x4{acc[a][i][e], acc[a][i][e + 1], acc[a][i][e + 2], acc[a][i][e + 3]};
+      for (int e = 0; e < V; e += 4) {
+        f32x4 t = {acc[a][i][e], acc[a][i][e + 1], acc[a][i][e + 2], acc[a][i][e + 3]};
+#pragma unroll
+        for (int k = 0; k < NG - 1; k++) {
+          const f32x4 o = sums[((k * CPT + i) * (V / 4) + e / 4) * (64 * G) + wg * 64 + lane];
+          t = f32x4{t[0] + o[0], t[1] + o[1], t[2] + o[2], t[3] + o[3]};
+        }
+        *reinterpret_cast<f32x4*>(p + e) = t;
+      }
     }
+  }
 }
 
 // stage 1 of a column sum: workgroup (bx, by) adds rows [by*rpb, (by+1)*rpb) of 64 column chunks of
@@ -332,27 +363,36 @@ int ln_bwd_blocks(bool is_bf16, int rows, int cols) {
   int G, CPT;
   ln_bwd_shape(cols / (is_bf16 ? 8 : 4), G, CPT);
   const int per_step = (8 / G) * (4 / CPT);            // rows a workgroup takes per step
-  // one workgroup per compute unit, but at least four steps each: every row group leaves a partial
-  // row of `cols` sums, which should stay a small fraction of the rows read
-  const int want = cdiv(rows, 4 * per_step);
-  const int wgs = want < 256 ? want : 256;
-  return wgs * (8 / G);
+  // One workgroup per compute unit, but where a workgroup's wavefronts all share a row (G 8) at least four
+  // steps each, and two or one below: every workgroup leaves a partial row of `cols` sums, which should
+  // stay a small fraction of the rows read.  With 1024 rows of 768 (G 1) one step each: 17.6 us with a quarter of
+  // the workgroups and a partial row per wavefront, 9.3 now.
+  const int want = cdiv(rows, (G >= 4 ? G / 2 : 1) * per_step);
+  return want < 256 ? want : 256;
 }
 
 hipError_t ln_fwd(bool is_bf16, const void* x, const void* g, const void* b, void* y, float* mean, float* rstd,
                   int rows, int cols, float eps, hipStream_t s) {
   const int vec = is_bf16 ? 8 : 4;
   if (rows <= 0 || cols <= 0 || cols % vec || cols / vec > 64 * LN_MAXC) return hipErrorInvalidValue;
-  dim3 grid(cdiv(rows, 4)), block(256);
+  const dim3 block(256);
   const int per_lane = cdiv(cols / vec, 64);
-#define GX_LN_FWD(T, C)                                                                                          \
-  hipLaunchKernelGGL((ln_fwd_kernel<T, C>), grid, block, 0, s, (const T*)x, (const T*)g, (const T*)b, (T*)y, mean, \
-                     rstd, rows, cols, eps)
-  if (is_bf16) {
-    if (per_lane <= 4) GX_LN_FWD(bf16, 4); else if (per_lane <= 8) GX_LN_FWD(bf16, 8); else GX_LN_FWD(bf16, 16);
-  } else {
-    if (per_lane <= 4) GX_LN_FWD(float, 4); else if (per_lane <= 8) GX_LN_FWD(float, 8); else GX_LN_FWD(float, 16);
-  }
+#define GX_LN_FWD(T, C, G)                                                                                       \
+  hipLaunchKernelGGL((ln_fwd_kernel<T, C, G>), dim3(G == 1 ? cdiv(rows, 4) : rows), block, 0, s, (const T*)x,     \
+                     (const T*)g, (const T*)b, (T*)y, mean, rstd, rows, cols, eps)
+#define GX_LN_FWD_T(T)                                                                        \
+  do {                                                                                        \
+    if (per_lane <= 4) GX_LN_FWD(T, 4, 1);                                                    \
+    else if (per_lane <= 8) GX_LN_FWD(T, 2, 4);                                               \
+    else GX_LN_FWD(T, 4, 4);                                                                  \
+  } while (0)
+  // Rows of more than 4 chunks per lane are shared by four wavefronts: a wavefront that holds 8 to 16 chunks
+  // has too few others beside it to cover its loads.  bf16, one wavefront / four (us): 128 rows of 5120 6.6 / 3.8,
+  // 4096 of 4096 12.8 / 12.5, 8192 of 5120 38.2 / 26.9, 8192 of 8192 60.7 / 42.7; 2560 wide, 5 chunks per
+  // lane, 1024 rows 5.0 / 3.9, 4096 rows 8.6 / 9.2, 8192 rows 16.8 / 15.7.
+  if (is_bf16) GX_LN_FWD_T(bf16);
+  else GX_LN_FWD_T(float);
+#undef GX_LN_FWD_T
 #undef GX_LN_FWD
   return hipGetLastError();
 }
@@ -365,7 +405,7 @@ hipError_t ln_bwd(bool is_bf16, const void* dy, const void* x, const void* g, co
   int G, CPT;
   ln_bwd_shape(cols / vec, G, CPT);
   if (CPT > 2) return hipErrorInvalidValue;
-  const int wgs = ln_bwd_blocks(is_bf16, rows, cols) / (8 / G);
+  const int wgs = ln_bwd_blocks(is_bf16, rows, cols);
 #define GX_LN_BWD(T, GG, CC, NN)                                                                                  \
   hipLaunchKernelGGL((ln_bwd_kernel<T, GG, CC, NN>), dim3(wgs), dim3(512), 0, s, (const T*)dy, (const T*)x,        \
                      (const T*)g, mean, rstd, (const T*)resid, (T*)dx, rows, cols, part)
