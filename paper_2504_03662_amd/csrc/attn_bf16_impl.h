@@ -164,12 +164,6 @@ GX_DEVINL void tr_product(f32x16 (&acc)[DH / 32], unsigned ct, const unsigned (&
   }
 #undef GX_TR_GROUP
 }
-template <bool COLS_A>
-GX_DEVINL void tr_product4(f32x16 (&acc)[DH / 32], unsigned ct, const unsigned (&coff)[2][DH / 32],
-                           ColFrags (&cf)[2], const bf16x8 (&xf)[4]) {
-  tr_product<COLS_A, 4>(acc, ct, coff, cf, xf);
-}
-
 // ------------------------------------------------------------------------------- forward
 // A workgroup owns 32 NQ query rows of one (sample, head); its NQ * SPLIT wavefronts are NQ blocks
 // of 32 rows times SPLIT shares of the keys: every step brings SPLIT tiles of BKV keys (K and V)
@@ -564,25 +558,32 @@ __global__ void __launch_bounds__(256) attn_dsum_kernel(const bf16* __restrict__
 }
 
 // ------------------------------------------------------------------------------- backward: dK, dV
-// A workgroup owns 128 key rows as 4 blocks of 32; each block belongs to a PAIR of wavefronts on
-// the same SIMD that split the work by output: wavefront `pair` (role V) forms S = Q K^T, the
-// probabilities P and dV += P^T dO; wavefront `pair + 4` (role K) forms dP = dO V^T, then
-// dS = P (dP - D) and dK += dS^T Q.  P crosses from one to the other through LDS as bf16, in the
-// accumulator's own lane layout (16 B per lane per half sub-tile, conflict-free).  Each wavefront
-// thus keeps one operand (K or V) and one 32 x 128 accumulator in registers, which leaves room
-// for two wavefronts per SIMD.
+// A workgroup owns 64 key rows as 2 blocks of 32; each block belongs to a PAIR of wavefronts that split
+// the work by output: wavefront `pair` (role V) forms S = Q K^T, the probabilities P and dV += P^T dO;
+// wavefront `pair + 2` (role K) forms dP = dO V^T, then dS = P (dP - D) and dK += dS^T Q.  P crosses
+// from one to the other through LDS as bf16, in the accumulator's own lane layout (16 B per lane per
+// half sub-tile, conflict-free).  Each wavefront thus keeps one operand (K or V) and one 32 x DH
+// accumulator in registers.
 //
 // The roles are skewed so that the exponentials of one run under the matrix work of the other and
-// one barrier per query tile suffices.  In phase n
+// one barrier per query tile (32 rows) suffices.  In phase n
 //   role V: S(n), P(n) -> LDS, dV += P(n)^T dO(n)
 //   role K: dS(n-1) from P(n-1) and the dP(n-1) it kept in registers, dK += dS(n-1)^T Q(n-1), then dP(n)
 // Tiles n+1 and n+2 are in flight meanwhile (a tile has two phases to arrive from HBM).
-constexpr int KV_PAIRS = 4, KV_NW = 2 * KV_PAIRS, KV_BJ = 32 * KV_PAIRS, KV_BI = 64;
-// LDS: Q tiles (+ their D rows) in a ring of 4 (tiles n-1 .. n+2), dO tiles (+ lse rows) in a ring
-// of 3 (tiles n .. n+2), two P exchange buffers, and a 256 B sink (see stage_load).
-constexpr int KV_NQ = 4, KV_NDO = 3;
-constexpr int KV_TILE = KV_BI * ROWB + KV_BI * 4;            // 64 rows of Q or dO | 64 floats
-constexpr int KV_PX = KV_PAIRS * 4 * 1024;                   // P exchange: [pair][sub-tile, half][lane] x 16 B
+//
+// A phase is a chain (LDS reads, products, exponentials, exchange, barrier) that keeps the matrix pipe
+// busy for a third of its length, so what matters is a second, independent workgroup on the compute
+// unit (66 KB of LDS at DH 128) to fill the rest.  Against 128 key rows, query tiles of 64 and one workgroup
+// of 8 wavefronts per unit (us): 64 pairs of S 2048 at DH 128 336 -> 203, 16 pairs 95 -> 78, 4 pairs of S 8192
+// 265 -> 237; 64 pairs of S 1024 at DH 64 with dropout 70 -> 45.  One tile in flight instead of two is equal;
+// three workgroups per unit need 168 registers and spill (331 instead of 203).
+constexpr int KV_PAIRS = 2, KV_NW = 2 * KV_PAIRS, KV_BJ = 32 * KV_PAIRS, KV_BI = 32, KV_SUB = KV_BI / 32;
+// LDS: Q tiles (+ their D rows) in a ring (tiles n-1 .. n+2), dO tiles (+ lse rows) in a ring (tiles
+// n .. n+2), two P exchange buffers, and a 256 B sink (see stage_load).
+constexpr int KV_PAIRED = 512;                               // launches that are resident all at once
+constexpr int KV_AHEAD = 2, KV_NQ = KV_AHEAD + 2, KV_NDO = KV_AHEAD + 1;
+constexpr int KV_TILE = KV_BI * ROWB + 256;                  // rows of Q or dO | their D or lse (64 lanes' worth)
+constexpr int KV_PX = KV_PAIRS * 2 * KV_SUB * 1024;          // P exchange: [pair][sub-tile, half][lane] x 16 B
 constexpr int KV_OFF_DO = KV_NQ * KV_TILE, KV_OFF_PX = KV_OFF_DO + KV_NDO * KV_TILE;
 constexpr int KV_OFF_SINK = KV_OFF_PX + 2 * KV_PX, KV_SMEM = KV_OFF_SINK + 256;
 // direct-to-LDS loads per wavefront per tile: its share of the Q rows, of the dO rows (tile_load's
@@ -592,11 +593,11 @@ static_assert(KV_TILE_LOADS >= 1 && KV_TILE_LOADS * (64 / CPR) * KV_NW == KV_BI,
 constexpr int KV_LOADS = 2 * KV_TILE_LOADS + 1;
 
 template <bool DROP>
-__global__ void __launch_bounds__(64 * KV_NW) attn_bwd_dkv_kernel(const bf16* __restrict__ qkv,
+__global__ void __launch_bounds__(64 * KV_NW, 2) attn_bwd_dkv_kernel(const bf16* __restrict__ qkv,
                                                                   const bf16* __restrict__ dctx,
                                                                   const float* __restrict__ lse,
                                                                   const float* __restrict__ dsum,
-                                                                  bf16* __restrict__ dqkv, int S, int nl,
+                                                                  bf16* __restrict__ dqkv, int S, int nl, int npair,
                                                                   unsigned qkv_bytes, unsigned dctx_bytes,
                                                                   KeepArgs keep) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -604,9 +605,15 @@ __global__ void __launch_bounds__(64 * KV_NW) attn_bwd_dkv_kernel(const bf16* __
   const bool role_v = wave < KV_PAIRS;
   const int pair = wave & (KV_PAIRS - 1);
   const int g = lane >> 5, l32 = lane & 31;
-  const int h = blockIdx.y, b = blockIdx.z;
+  // Blocks with most query tiles (the first keys) first.  In a launch that is resident all at once, two
+  // workgroups per unit, the second half runs those with fewest first, as in the forward kernel (16 pairs
+  // of S 2048: 79 us against 81, 4 pairs of S 8192: 239 against 248; with four times as many workgroups
+  // as places, 203 in plain order against 220).
+  const int kp = blockIdx.x % npair, rk = blockIdx.x / npair, nkb = (S + KV_BJ - 1) / KV_BJ, hk = (nkb + 1) / 2;
+  const int kb = rk < hk || gridDim.x > KV_PAIRED ? rk : nkb - 1 - (rk - hk);
+  const int h = kp % nl, b = kp / nl;
   const int Hl = nl * DH, ld = 3 * Hl;
-  const int j0 = blockIdx.x * KV_BJ, jw = j0 + pair * 32;
+  const int j0 = kb * KV_BJ, jw = j0 + pair * 32;
   const unsigned eq = (unsigned)((size_t)b * S * ld + h * DH);
   const unsigned edo = (unsigned)((size_t)b * S * Hl + h * DH);
   const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(qkv), 0, qkv_bytes,
@@ -621,7 +628,7 @@ __global__ void __launch_bounds__(64 * KV_NW) attn_bwd_dkv_kernel(const bf16* __
   const float scale = rsqrtf((float)DH), c2 = scale * LOG2E;
   const float* lrow = lse + ((size_t)b * nl + h) * S;
   const float* drow = dsum + ((size_t)b * nl + h) * S;
-  char* px = smem + KV_OFF_PX + pair * 4096 + lane * 16;
+  char* px = smem + KV_OFF_PX + pair * (KV_PX / KV_PAIRS) + lane * 16;
   unsigned coff[2][DH / 32];
   cols_lane_offsets(lane, coff);
 
@@ -640,36 +647,36 @@ __global__ void __launch_bounds__(64 * KV_NW) attn_bwd_dkv_kernel(const bf16* __
     tile_load<KV_BI, KV_NW>(rdo, edo, Hl, t * KV_BI, S, ds, wave, lane);
     const int i = t * KV_BI + lane;
     char* ad = (wave == 0) ? ds + KV_BI * ROWB : (wave == 1) ? qs + KV_BI * ROWB : smem + KV_OFF_SINK;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(raux, (lds_void_ptr)ad, 4, (wave < 2 && i < S) ? (unsigned)i * 4u : OOB,
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(raux, (lds_void_ptr)ad, 4, (wave < 2 && lane < KV_BI && i < S) ? (unsigned)i * 4u : OOB,
                                              0, 0, 0);
   };
-  // first product of a role over both 32-row query sub-tiles: [query i][key j]
-  f32x16 sp[2];
+  // first product of a role over the 32-row query sub-tiles: [query i][key j]
+  f32x16 sp[KV_SUB];
   auto first_product = [&](const char* rows_of) {
-    bf16x8 fr[2][DH / 16];
+    bf16x8 fr[KV_SUB][DH / 16];
 #pragma unroll
     for (int s = 0; s < DH / 16; s++) fr[0][s] = frag_rows(rows_of, l32, s, g);
 #pragma unroll
-    for (int sub = 0; sub < 2; sub++) {
+    for (int sub = 0; sub < KV_SUB; sub++) {
       sp[sub] = zero16();
 #pragma unroll
       for (int s = 0; s < DH / 16; s++) {
-        if (sub == 0) fr[1][s] = frag_rows(rows_of, 32 + l32, s, g);
+        if (sub + 1 < KV_SUB) fr[sub + 1][s] = frag_rows(rows_of, 32 * (sub + 1) + l32, s, g);
         sp[sub] = MFMA(fr[sub][s], kvf[s], sp[sub]);
       }
     }
   };
-  stage_load(t0, 0, 0);
-  stage_load(t0 + 1, 1, 1);
-  __builtin_amdgcn_s_waitcnt(0x0F70 | KV_LOADS);                  // tile t0 has landed, t0 + 1 may be in flight
-  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < KV_AHEAD; a++) stage_load(t0 + a, a, a);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((KV_AHEAD - 1) * KV_LOADS) : "memory");   // tile t0 has landed
   const int j = jw + l32;
-  // dropout: this key's column of keep bits, one 64-bit word per query tile (both roles read it;
-  // a word is fetched one phase before its use, ahead of that phase's tile requests, so that
-  // waiting for it never waits for a tile)
+  // dropout: this key's column of keep bits, KV_BI bits per query tile (both roles read them; they are
+  // fetched one phase before their use, ahead of that phase's tile requests, so that waiting for
+  // them never waits for a tile)
   const unsigned* kcol = DROP ? keep.bits + (((size_t)b * nl + h) * S + min(j, S - 1)) * keep.wpr : nullptr;
   auto keep_word = [&](int t) -> unsigned long long {
-    return (t >= t0 && t < nt) ? *reinterpret_cast<const unsigned long long*>(kcol + 2 * t) : 0ull;
+    if (t < t0 || t >= nt) return 0ull;
+    return KV_SUB == 2 ? *reinterpret_cast<const unsigned long long*>(kcol + 2 * t) : kcol[t];
   };
   // One loop per role (the branch is wavefront-uniform and both loops pass the same number of
   // barriers), so that neither role carries the other's addresses and fragments in registers.
@@ -684,10 +691,11 @@ __global__ void __launch_bounds__(64 * KV_NW) attn_bwd_dkv_kernel(const bf16* __
         kw = kw_next;
         kw_next = keep_word(ROLE_V ? n + 1 : n);
       }
-      stage_load(n + 2, (qslot + 2) & (KV_NQ - 1), dslot == 0 ? 2 : dslot - 1);
+      stage_load(n + KV_AHEAD, qslot + KV_AHEAD < KV_NQ ? qslot + KV_AHEAD : qslot + KV_AHEAD - KV_NQ,
+                 dslot == 0 ? KV_NDO - 1 : dslot - 1);
       const char* qt = smem + qslot * KV_TILE;                    // Q rows of tile n, then their D
       const char* dot = smem + KV_OFF_DO + dslot * KV_TILE;       // dO rows of tile n, then their lse
-      bf16x8 xf[4];                                               // P or dS, 16 query rows per entry
+      bf16x8 xf[2 * KV_SUB];                                      // P or dS, 16 query rows per entry
       ColFrags cf[2];
       if (ROLE_V) {
         if (n < nt && n * KV_BI + KV_BI - 1 >= jw) {              // pair-uniform: some query of tile n sees a key
@@ -697,7 +705,7 @@ __global__ void __launch_bounds__(64 * KV_NW) attn_bwd_dkv_kernel(const bf16* __
           cols_issue<0>(ct, coff, cf[0]);
           cols_issue<1>(ct, coff, cf[1]);
 #pragma unroll
-          for (int sub = 0; sub < 2; sub++) {
+          for (int sub = 0; sub < KV_SUB; sub++) {
 #pragma unroll
             for (int q4 = 0; q4 < 4; q4++) {
               const f32x4 l4 = *reinterpret_cast<const f32x4*>(aux + 32 * sub + 8 * q4 + 4 * g);
@@ -720,14 +728,14 @@ __global__ void __launch_bounds__(64 * KV_NW) attn_bwd_dkv_kernel(const bf16* __
           if (DROP) {                                             // dV takes the dropped probabilities
             drop_unkept(sp, kw, g);
 #pragma unroll
-            for (int u = 0; u < 4; u++) xf[u] = pack_half(sp[u >> 1], u & 1);
+            for (int u = 0; u < 2 * KV_SUB; u++) xf[u] = pack_half(sp[u >> 1], u & 1);
           }
-          tr_product4<false>(acc, ct, coff, cf, xf);              // dV[j][d] += P^T dO
+          tr_product<false, 2 * KV_SUB>(acc, ct, coff, cf, xf);   // dV[j][d] += P^T dO
         }
       } else {
         const int m = n - 1;                                      // tile whose dP this wavefront holds
         if (m >= t0 && m * KV_BI + KV_BI - 1 >= jw) {
-          const char* qp = smem + ((qslot + KV_NQ - 1) & (KV_NQ - 1)) * KV_TILE;
+          const char* qp = smem + (qslot == 0 ? KV_NQ - 1 : qslot - 1) * KV_TILE;
           const float* dp = reinterpret_cast<const float*>(qp + KV_BI * ROWB);
           const unsigned ct = lds_addr(qp);
           cols_issue<0>(ct, coff, cf[0]);
@@ -735,12 +743,12 @@ __global__ void __launch_bounds__(64 * KV_NW) attn_bwd_dkv_kernel(const bf16* __
           if (DROP) {                                             // gradient w.r.t. the undropped probabilities
             drop_unkept(sp, kw, g);
 #pragma unroll
-            for (int sub = 0; sub < 2; sub++)
+            for (int sub = 0; sub < KV_SUB; sub++)
 #pragma unroll
               for (int v = 0; v < 16; v++) sp[sub][v] *= keep.scale;
           }
 #pragma unroll
-          for (int sub = 0; sub < 2; sub++) {
+          for (int sub = 0; sub < KV_SUB; sub++) {
             bf16x8 pb[2];
 #pragma unroll
             for (int u = 0; u < 2; u++)
@@ -757,14 +765,14 @@ __global__ void __launch_bounds__(64 * KV_NW) attn_bwd_dkv_kernel(const bf16* __
 #pragma unroll
             for (int u = 0; u < 2; u++) xf[2 * sub + u] = pack_half(sp[sub], u);
           }
-          tr_product4<false>(acc, ct, coff, cf, xf);              // dK[j][d] += dS^T Q
+          tr_product<false, 2 * KV_SUB>(acc, ct, coff, cf, xf);   // dK[j][d] += dS^T Q
         }
         if (n < nt && n * KV_BI + KV_BI - 1 >= jw) first_product(dot);   // dP = dO V^T, used in the next phase
       }
       // tile n+1 has landed (n+2 may still be in flight) and this wavefront's LDS traffic is
       // complete; then the workgroup meets
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(KV_LOADS) : "memory");
-      qslot = (qslot + 1) & (KV_NQ - 1);
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((KV_AHEAD - 1) * KV_LOADS) : "memory");
+      qslot = (qslot == KV_NQ - 1) ? 0 : qslot + 1;
       dslot = (dslot == KV_NDO - 1) ? 0 : dslot + 1;
     }
   };
@@ -1005,8 +1013,8 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s, hipStream_t s_dq, hipEvent_t fo
     if ((e = hipStreamWaitEvent(s_dq, fork, 0)) != hipSuccess) return e;
   }
   auto go_dkv = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, KV_BJ), a.nl, a.B), dim3(64 * KV_NW), KV_SMEM, s, (const bf16*)a.qkv,
-                       (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, qkv_bytes, dctx_bytes,
+    hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, KV_BJ) * a.nl * a.B), dim3(64 * KV_NW), KV_SMEM, s, (const bf16*)a.qkv,
+                       (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, a.nl * a.B, qkv_bytes, dctx_bytes,
                        keep_cols);
   };
   if (drop) go_dkv(attn_bwd_dkv_kernel<true>);
