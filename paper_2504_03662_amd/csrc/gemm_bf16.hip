@@ -630,31 +630,39 @@ hipError_t launch(const GemmArgs& g, hipStream_t s) {
   typedef hipError_t (*Launcher)(const GemmArgs&, hipStream_t);
   Launcher best = launch_whole<LAY, EPI, Large>;
   float least = price<Large>(g);
+  const float with_tail = big > ROUND && rem ? price<Large>(big - rem, g.K) + price<Small>(4 * rem, g.K) + TAIL : least;
+  const bool tail = with_tail < least;
+  if (tail) least = with_tail;
+  // Another tile has to be 3 % cheaper: where it only evens out, the large one leaves more to the
+  // product of the other stream that shares the chip (two products of 5466 x 6528 x 19584 and its transpose,
+  // equal alone, 1.5 % slower together with 256 x 192 tiles).  192 x 256 before 256 x 192: the same price, but
+  // its rows are read back from LDS without a remainder (6618 x 1216 x 16952 NT: 364 us against 430).
+  least *= 0.97f;
+  bool other = false;
   auto consider = [&](Launcher l, float p) {
     if (p < least) {
       least = p;
       best = l;
+      other = true;
     }
   };
   // the 192-wide tiles have no column sums: their wavefronts' parts are not whole blocks of 64 rows
   if constexpr (EPI != EPI_DGELU) {
-    consider(launch_whole<LAY, EPI, Wide>, price<Wide>(g));
     consider(launch_whole<LAY, EPI, Tall>, price<Tall>(g));
+    consider(launch_whole<LAY, EPI, Wide>, price<Wide>(g));
   }
   consider(launch_whole<LAY, EPI, Half>, price<Half>(g));
   consider(launch_whole<LAY, EPI, Small>, price<Small>(g));
   consider(launch_whole<LAY, EPI, Flat>, price<Flat>(g));
   consider(launch_whole<LAY, EPI, Tiny>, price<Tiny>(g));
-  if (big > ROUND && rem && price<Large>(big - rem, g.K) + price<Small>(4 * rem, g.K) + TAIL < least) {
-    hipError_t e = launch_tile<LAY, EPI, Large>(g, s, (int)(big - rem));
-    if (e != hipSuccess) return e;
-    GemmArgs t = g;
-    t.tail = 1;
-    t.group = big - rem > 256 ? 4 : 8;           // the walk of the launch above
-    t.tile_first = (int)(big - rem);
-    return launch_tile<LAY, EPI, Small>(t, s, (int)(4 * rem));
-  }
-  return best(g, s);
+  if (other || !tail) return best(g, s);
+  hipError_t e = launch_tile<LAY, EPI, Large>(g, s, (int)(big - rem));
+  if (e != hipSuccess) return e;
+  GemmArgs t = g;
+  t.tail = 1;
+  t.group = big - rem > 256 ? 4 : 8;             // the walk of the launch above
+  t.tile_first = (int)(big - rem);
+  return launch_tile<LAY, EPI, Small>(t, s, (int)(4 * rem));
 }
 
 // The combinations that the layer driver asks for.
