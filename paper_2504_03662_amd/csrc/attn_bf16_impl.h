@@ -165,6 +165,7 @@ GX_DEVINL void tr_product(f32x16 (&acc)[DH / 32], unsigned ct, const unsigned (&
 #undef GX_TR_GROUP
 }
 // ------------------------------------------------------------------------------- forward
+constexpr float MAX_SLACK = 8.0f;      // how far (in powers of 2) scores may exceed the reference maximum
 // A workgroup owns 32 NQ query rows of one (sample, head); its NQ * SPLIT wavefronts are NQ blocks
 // of 32 rows times SPLIT shares of the keys: every step brings SPLIT tiles of BKV keys (K and V)
 // into LDS and wavefront (q, part) works on tile `part`; the SPLIT partial softmax states
@@ -297,15 +298,18 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
 
   const int jend = min(S, i0 + BQ);                   // keys 0 .. jend-1 can be visible
   const int nt = (jend + ROWS - 1) / ROWS;
-  tile_load<ROWS, NW>(rsrc, eq + Hl, ld, 0, S, smem, wave, lane);
-  tile_load<ROWS, NW>(rsrc, eq + 2 * Hl, ld, 0, S, smem + ROWS * ROWB, wave, lane);
+  TileStream<ROWS, NW> ksrc, vsrc;
+  ksrc.init(eq + Hl, ld, wave, lane);
+  vsrc.init(eq + 2 * Hl, ld, wave, lane);
+  ksrc.load(rsrc, eq + Hl, ld, 0, S, smem, wave, lane);
+  vsrc.load(rsrc, eq + 2 * Hl, ld, 0, S, smem + ROWS * ROWB, wave, lane);
   WAIT_VM0();
   __syncthreads();
   for (int t = 0; t < nt; t++) {
     if (t + 1 < nt) {
       char* nxt = smem + ((t + 1) & 1) * STAGE;
-      tile_load<ROWS, NW>(rsrc, eq + Hl, ld, (t + 1) * ROWS, S, nxt, wave, lane);
-      tile_load<ROWS, NW>(rsrc, eq + 2 * Hl, ld, (t + 1) * ROWS, S, nxt + ROWS * ROWB, wave, lane);
+      ksrc.load(rsrc, eq + Hl, ld, (t + 1) * ROWS, S, nxt, wave, lane);
+      vsrc.load(rsrc, eq + 2 * Hl, ld, (t + 1) * ROWS, S, nxt + ROWS * ROWB, wave, lane);
     }
     const int j0 = t * ROWS + part * BKV;              // this wave's keys of the step
     // wave-uniform; j0 and iw are multiples of 32, so when it holds every row of the wave sees key j0
@@ -342,9 +346,10 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
       for (int jt = 0; jt < NJT; jt++)
 #pragma unroll
         for (int v = 0; v < 16; v++) mloc = fmaxf(mloc, sacc[jt][v]);
-      mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64)) * c2;
-      const float mnew = fmaxf(m, mloc);
-      if (__builtin_amdgcn_ballot_w64(mnew > m)) {     // wave-uniform: some row's running max moved
+      mloc = max_across_halves(mloc) * c2;
+      // the reference maximum follows the true one lazily (see attn_fwd_ahead_kernel); wave-uniform
+      if (__builtin_amdgcn_ballot_w64(mloc > m + MAX_SLACK)) {
+        const float mnew = fmaxf(m, mloc);
         const float alpha = __builtin_amdgcn_exp2f(m - mnew);
         m = mnew;
         lsum *= alpha;
@@ -417,7 +422,6 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
   for (int dt = 0; dt < DH / 32; dt++) o[dt] = zero16();
   float m = -INFINITY, lsum = 0.f;
   const float c2 = rsqrtf((float)DH) * LOG2E;
-  constexpr float MAX_SLACK = 8.0f;
   unsigned coff[2][DH / 32];
   cols_lane_offsets(lane, coff);
 
@@ -834,15 +838,18 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
 
   const int jend = min(S, i0 + BQ);
   const int nt = (jend + ROWS - 1) / ROWS;
-  tile_load<ROWS, NW>(rsrc, eq + Hl, ld, 0, S, smem, wave, lane);
-  tile_load<ROWS, NW>(rsrc, eq + 2 * Hl, ld, 0, S, smem + ROWS * ROWB, wave, lane);
+  TileStream<ROWS, NW> ksrc, vsrc;
+  ksrc.init(eq + Hl, ld, wave, lane);
+  vsrc.init(eq + 2 * Hl, ld, wave, lane);
+  ksrc.load(rsrc, eq + Hl, ld, 0, S, smem, wave, lane);
+  vsrc.load(rsrc, eq + 2 * Hl, ld, 0, S, smem + ROWS * ROWB, wave, lane);
   WAIT_VM0();
   __syncthreads();
   for (int t = 0; t < nt; t++) {
     if (t + 1 < nt) {
       char* nxt = smem + ((t + 1) & 1) * STAGE;
-      tile_load<ROWS, NW>(rsrc, eq + Hl, ld, (t + 1) * ROWS, S, nxt, wave, lane);
-      tile_load<ROWS, NW>(rsrc, eq + 2 * Hl, ld, (t + 1) * ROWS, S, nxt + ROWS * ROWB, wave, lane);
+      ksrc.load(rsrc, eq + Hl, ld, (t + 1) * ROWS, S, nxt, wave, lane);
+      vsrc.load(rsrc, eq + 2 * Hl, ld, (t + 1) * ROWS, S, nxt + ROWS * ROWB, wave, lane);
     }
     const int j0 = t * ROWS + part * BKV;
     if (j0 <= iw + 31) {
