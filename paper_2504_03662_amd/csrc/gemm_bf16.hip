@@ -3,8 +3,9 @@
 //
 // One workgroup computes a tile of C through LDS stages that loads fill straight from HBM
 // (buffer_load ... lds, 16 B per lane, no register staging): 256 x 256 by 8 wavefronts of 128 x 64 and a
-// double buffer of 64 reduction steps, or, for products with few tiles, 128 x 128 by two sets of 4
-// wavefronts of 64 x 64 that share every stage's reduction steps, and a ring of four stages.
+// double buffer of 64 reduction steps, and six smaller tiles for products that would leave compute
+// units without one, the smallest of them with several wavefronts per place that share every stage's
+// reduction steps (see the tiles and their prices below).
 // Products are v_mfma_f32_16x16x32_bf16: on this chip the large products run at the board's power
 // limit, and a register-only loop on normal data holds 1977 TFLOP/s with that instruction against
 // 1816 with 32x32x16 (on zeros 2420 and 2481): it reads and writes an accumulator half as often.
