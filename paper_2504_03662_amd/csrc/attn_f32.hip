@@ -200,6 +200,10 @@ struct Where {
   }
 };
 
+// What exponents are taken relative to.  The largest score that a part has seen is -inf while all of them
+// are (products that leave the fp32 range); such keys get weight 0, not that of -inf - -inf.
+GX_DEVINL float finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
+
 template <int DHP, bool EXACT>
 __global__ void __launch_bounds__(64 * PARTS, DHP <= 64 ? 2 : 1) attn_fwd_f32_kernel(Args a) {
   __shared__ float lds[lds_floats<DHP>()];
@@ -221,18 +225,18 @@ __global__ void __launch_bounds__(64 * PARTS, DHP <= 64 ? 2 : 1) attn_fwd_f32_ke
     load_rows<DHP, EXACT>(w.k + (size_t)min(j0 + l32, a.S - 1) * w.ld, a.dh, g, kf);
     f32x16 s = row_product<DHP>(kf, qf);                         // S^T[j][i]
     float mx = -INFINITY;
+    const float mold = m;
 #pragma unroll
     for (int v = 0; v < 16; v++) {
       s[v] = (j0 + acc_row(v, g) <= i) ? s[v] * scale : -INFINITY;
       mx = fmaxf(mx, s[v]);
     }
-    const float mnew = fmaxf(m, max_across_halves(mx));          // finite: every query sees key j0
-    const float alpha = expf(m - mnew);
-    m = mnew;
+    m = fmaxf(m, max_across_halves(mx));
+    const float ref = finite_ref(m), alpha = expf(mold - ref);
     float sum = 0.f;
 #pragma unroll
     for (int v = 0; v < 16; v++) {
-      s[v] = (j0 + acc_row(v, g) <= i) ? expf(s[v] - m) : 0.f;
+      s[v] = (j0 + acc_row(v, g) <= i) ? expf(s[v] - ref) : 0.f;
       sum += s[v];
     }
     l = l * alpha + sum;                                         // of the undropped probabilities
@@ -264,7 +268,7 @@ __global__ void __launch_bounds__(64 * PARTS, DHP <= 64 ? 2 : 1) attn_fwd_f32_ke
   if (part > 0) return;
   for (int pp = 0; pp < min(PARTS - 1, w.tile); pp++) {          // part 0 always has a tile; part p when tile >= p
     const float* p = lds + pp * VALS * 64 + lane;
-    const float mm = fmaxf(m, p[0]), a0 = expf(m - mm), a1 = expf(p[0] - mm);
+    const float mm = fmaxf(m, p[0]), ref = finite_ref(mm), a0 = expf(m - ref), a1 = expf(p[0] - ref);
     l = l * a0 + p[64] * a1;
     m = mm;
 #pragma unroll

@@ -8,7 +8,7 @@ import torch
 from oracle import layer as O
 from paper_2504_03662_amd import inputs as I
 from paper_2504_03662_amd.runtime import DeviceLayer, to_device, to_host
-from parity import TOL, compare, run_both
+from parity import TOL, check, compare, run_both
 
 pytestmark = pytest.mark.gpu
 
@@ -71,3 +71,53 @@ def test_fp32_values_that_are_not_finite_stay_behind_the_mask(heads, at):
     np.testing.assert_array_equal(y1[100:], y0[100:])
     np.testing.assert_array_equal(dx1[100:], dx0[100:])
     assert not np.isfinite(y1[at]).any()
+
+
+def _with_keys_out_of_range(hidden, heads, seq, keys):
+    """A layer whose scores are -inf in fp32 for the keys named, and ordinary for all others: component 0
+    of every query is 1e20, of those keys -1e20, of the others exactly 0 (a feature that is 0 there in tokens
+    of +1 and -1 with zero mean, which LayerNorm leaves 0)."""
+    shape = I.LayerShape(hidden, heads, 8, 1, 1, 0, seq, 2, "f32")
+    rng = np.random.default_rng(450)
+    half = rng.choice(np.array([-1.0, 1.0], np.float32), (shape.micro_batch, seq, hidden // 2))
+    half[:, :, 0] = np.isin(np.arange(seq), keys)
+    x = np.concatenate([half, -half], axis=2).reshape(shape.tokens, hidden)
+    p = I.full_params(shape, case=450, random_affine=True)
+    dh = hidden // heads
+    p["ln1_g"][:], p["ln1_b"][:] = 1.0, 0.0
+    p["w_qkv"][[0, hidden // 2]] = 0.0
+    p["w_qkv"][:, 0:2 * hidden:dh] = 0.0
+    p["w_qkv"][0, hidden:2 * hidden:dh] = -1e20
+    p["b_qkv"][0:hidden:dh] = 1e20
+    p["b_qkv"][hidden:2 * hidden:dh] = 0.0
+    return shape, p, x
+
+
+@pytest.mark.parametrize("hidden,heads", [(40, 2), (64, 2), (128, 2), (256, 2)])       # head dim 20, 32, 64, 128
+@pytest.mark.parametrize("keys", [[32], range(32, 64), [64, 65, 95, 129], range(0, 32), range(0, 64)])
+def test_fp32_keys_whose_scores_are_minus_infinity_get_no_weight(hidden, heads, keys):
+    # also where they are all that a wavefront sees of its first tile, or of every tile; a query that sees
+    # no other key has no result
+    keys = list(keys)
+    shape, p, x = _with_keys_out_of_range(hidden, heads, 160, keys)
+    first = 0 if keys[0] > 0 else keys[-1] + 1
+    dy = I.activations(shape, case=451)[1]
+    layer = DeviceLayer(shape, p)
+    xd, dyd = to_device(x, "f32"), to_device(dy, "f32")
+    got = to_host(layer.forward(xd, "attn")["p_attn"]).reshape(2, 160, hidden)
+    with np.errstate(over="ignore", invalid="ignore"):
+        ref = O.layer_fwd(shape, p, x, "attn")
+    check("p_attn", got[:, first:].reshape(-1, hidden), ref["p_attn"].reshape(2, 160, hidden)[:, first:].reshape(-1, hidden),
+          TOL["f32"])
+    if first:
+        assert not np.isfinite(got[:, :first]).any()
+        return
+    layer.backward(xd, dyd, "attn")
+    torch.cuda.synchronize()
+    with np.errstate(over="ignore", invalid="ignore"):
+        _, g = O.layer_bwd(shape, p, dy, ref["cache"], "attn")
+    kept = np.ones(3 * hidden, bool)               # without component 0 of Q and K, which holds the 1e20s
+    kept[0:2 * hidden:hidden // heads] = False
+    for n in ("w_qkv", "b_qkv"):
+        check("d" + n, to_host(layer.grads[n])[..., kept], g[n][..., kept], TOL["f32"])
+    check("dw_o", to_host(layer.grads["w_o"]), g["w_o"], TOL["f32"])
