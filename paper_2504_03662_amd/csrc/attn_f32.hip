@@ -94,11 +94,13 @@ GX_DEVINL void col_product(f32x16 (&acc)[DHP / 32], const f32x16& w, const float
 #pragma unroll
         for (int v = 0; v < 16; v++) x[c][v] = (src + (size_t)acc_row(v, 0) * ld)[off];
       } else {
-        // rows beyond the tensor have weight 0 and take the last row's values: where that row is
-        // not finite, so is the result of every column that sees it, and the diagonal form below
-        // keeps it from the others
+        // rows beyond the tensor count as zeros (their weight is 0 too, which alone would not do beside a
+        // last row that is not finite)
 #pragma unroll
-        for (int v = 0; v < 16; v++) x[c][v] = src[(unsigned)(min(acc_row(v, g), rows - 1) * ld + d)];
+        for (int v = 0; v < 16; v++) {
+          const float xv = src[(unsigned)(min(acc_row(v, g), rows - 1) * ld + d)];
+          x[c][v] = acc_row(v, g) < rows ? xv : 0.f;
+        }
       }
     }
     bool bad = false;

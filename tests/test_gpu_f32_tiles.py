@@ -121,3 +121,20 @@ def test_fp32_keys_whose_scores_are_minus_infinity_get_no_weight(hidden, heads, 
     for n in ("w_qkv", "b_qkv"):
         check("d" + n, to_host(layer.grads[n])[..., kept], g[n][..., kept], TOL["f32"])
     check("dw_o", to_host(layer.grads["w_o"]), g["w_o"], TOL["f32"])
+
+
+@pytest.mark.parametrize("hidden,heads", [(40, 2), (64, 2), (128, 2), (256, 2)])       # head dim 20, 32, 64, 128
+def test_fp32_infinite_upstream_gradient_in_a_partial_last_tile(hidden, heads):
+    # the last query's upstream gradient is infinite in one column, its gradient of the heads' outputs then
+    # in all of them, and so is dV = P^T dO of every key, with the sign that dO has: the rows that pad the
+    # last tile add nothing to it
+    shape = I.LayerShape(hidden, heads, 8, 1, 1, 0, 40, 1, "f32")
+    p = I.full_params(shape, case=460, random_affine=True)
+    x, dy = I.activations(shape, case=460)
+    dy[-1, 3] = np.inf
+    layer = DeviceLayer(shape, p)
+    xd = to_device(x, "f32")
+    layer.forward(xd, "attn")
+    layer.backward(xd, to_device(dy, "f32"), "attn")
+    got = to_host(layer.grads["b_qkv"])[2 * hidden:]
+    np.testing.assert_array_equal(got, np.sign(p["w_o"][:, 3]) * np.float32(np.inf))
