@@ -621,49 +621,63 @@ template <class T>
 float price(long tiles, int K) {
   return (float)((tiles + ROUND - 1) / ROUND) * (T::fixed + T::per_k * (float)K * (1.0f / 1024));
 }
-template <class T>
-float price(const GemmArgs& g) {
-  return price<T>((long)cdiv(g.M, T::BM) * cdiv(g.N, T::BN), g.K);
+// Another tile than the large one has to be 3 % cheaper: where it only evens out, the large one leaves more
+// to the product of the other stream that shares the chip (two products of 5466 x 6528 x 19584 and its
+// transpose, equal alone, 1.5 % slower together with 256 x 192 tiles).  192 x 256 before 256 x 192: the same
+// price, but its rows are read back from LDS without a remainder; where the two take as many rounds it was
+// faster on the mean of 70 products whichever of them has fewer tiles (2048 x 5120 x 10240 NT, operands not
+// cached, 215 us of 220 tiles against 218 of 216; 6618 x 1216 x 16952 NT 421 of 175 against 439 of 182).
+enum Pick { PICK_LARGE, PICK_WIDE, PICK_TALL, PICK_HALF, PICK_SMALL, PICK_FLAT, PICK_TINY, PICK_LARGE_TAIL };
+Pick pick(int M, int N, int K, bool column_sums) {
+  const long big = (long)cdiv(M, 256) * cdiv(N, 256), rem = big % ROUND;
+  Pick best = PICK_LARGE;
+  float least = price<Large>(big, K);
+  if (big > ROUND && rem) {
+    const float with_tail = price<Large>(big - rem, K) + price<Small>(4 * rem, K) + TAIL;
+    if (with_tail < least) least = with_tail, best = PICK_LARGE_TAIL;
+  }
+  least *= 0.97f;
+  auto consider = [&](Pick t, int bm, int bn, auto tile) {
+    const float p = price<decltype(tile)>((long)cdiv(M, bm) * cdiv(N, bn), K);
+    if (p < least) least = p, best = t;
+  };
+  // the 192-wide tiles have no column sums: their wavefronts' parts are not whole blocks of 64 rows
+  if (!column_sums) {
+    consider(PICK_TALL, Tall::BM, Tall::BN, Tall());
+    consider(PICK_WIDE, Wide::BM, Wide::BN, Wide());
+  }
+  consider(PICK_HALF, Half::BM, Half::BN, Half());
+  consider(PICK_SMALL, Small::BM, Small::BN, Small());
+  consider(PICK_FLAT, Flat::BM, Flat::BN, Flat());
+  consider(PICK_TINY, Tiny::BM, Tiny::BN, Tiny());
+  return best;
 }
 template <int LAY, int EPI>
 hipError_t launch(const GemmArgs& g, hipStream_t s) {
-  const long big = (long)cdiv(g.M, 256) * cdiv(g.N, 256), rem = big % ROUND;
-  typedef hipError_t (*Launcher)(const GemmArgs&, hipStream_t);
-  Launcher best = launch_whole<LAY, EPI, Large>;
-  float least = price<Large>(g);
-  const float with_tail = big > ROUND && rem ? price<Large>(big - rem, g.K) + price<Small>(4 * rem, g.K) + TAIL : least;
-  const bool tail = with_tail < least;
-  if (tail) least = with_tail;
-  // Another tile has to be 3 % cheaper: where it only evens out, the large one leaves more to the
-  // product of the other stream that shares the chip (two products of 5466 x 6528 x 19584 and its transpose,
-  // equal alone, 1.5 % slower together with 256 x 192 tiles).  192 x 256 before 256 x 192: the same price, but
-  // its rows are read back from LDS without a remainder (6618 x 1216 x 16952 NT: 364 us against 430).
-  least *= 0.97f;
-  bool other = false;
-  auto consider = [&](Launcher l, float p) {
-    if (p < least) {
-      least = p;
-      best = l;
-      other = true;
+  switch (pick(g.M, g.N, g.K, EPI == EPI_DGELU)) {
+    case PICK_LARGE: return launch_whole<LAY, EPI, Large>(g, s);
+    case PICK_WIDE:
+      if constexpr (EPI != EPI_DGELU) return launch_whole<LAY, EPI, Wide>(g, s);
+      break;
+    case PICK_TALL:
+      if constexpr (EPI != EPI_DGELU) return launch_whole<LAY, EPI, Tall>(g, s);
+      break;
+    case PICK_HALF: return launch_whole<LAY, EPI, Half>(g, s);
+    case PICK_SMALL: return launch_whole<LAY, EPI, Small>(g, s);
+    case PICK_FLAT: return launch_whole<LAY, EPI, Flat>(g, s);
+    case PICK_TINY: return launch_whole<LAY, EPI, Tiny>(g, s);
+    case PICK_LARGE_TAIL: {
+      const long big = (long)cdiv(g.M, 256) * cdiv(g.N, 256), rem = big % ROUND;
+      hipError_t e = launch_tile<LAY, EPI, Large>(g, s, (int)(big - rem));
+      if (e != hipSuccess) return e;
+      GemmArgs t = g;
+      t.tail = 1;
+      t.group = big - rem > 256 ? 4 : 8;             // the walk of the launch above
+      t.tile_first = (int)(big - rem);
+      return launch_tile<LAY, EPI, Small>(t, s, (int)(4 * rem));
     }
-  };
-  // the 192-wide tiles have no column sums: their wavefronts' parts are not whole blocks of 64 rows
-  if constexpr (EPI != EPI_DGELU) {
-    consider(launch_whole<LAY, EPI, Tall>, price<Tall>(g));
-    consider(launch_whole<LAY, EPI, Wide>, price<Wide>(g));
   }
-  consider(launch_whole<LAY, EPI, Half>, price<Half>(g));
-  consider(launch_whole<LAY, EPI, Small>, price<Small>(g));
-  consider(launch_whole<LAY, EPI, Flat>, price<Flat>(g));
-  consider(launch_whole<LAY, EPI, Tiny>, price<Tiny>(g));
-  if (other || !tail) return best(g, s);
-  hipError_t e = launch_tile<LAY, EPI, Large>(g, s, (int)(big - rem));
-  if (e != hipSuccess) return e;
-  GemmArgs t = g;
-  t.tail = 1;
-  t.group = big - rem > 256 ? 4 : 8;             // the walk of the launch above
-  t.tile_first = (int)(big - rem);
-  return launch_tile<LAY, EPI, Small>(t, s, (int)(4 * rem));
+  return hipErrorInvalidValue;
 }
 
 // The combinations that the layer driver asks for.
@@ -686,6 +700,8 @@ hipError_t dispatch_epi(Epilogue epi, const GemmArgs& g, hipStream_t s) {
 }
 
 }  // namespace
+
+extern "C" int gx_bf16_tile(int M, int N, int K, int column_sums) { return pick(M, N, K, column_sums != 0); }
 
 hipError_t gemm_bf16(Layout lay, Epilogue epi, const GemmArgs& args, hipStream_t s) {
   GemmArgs g = args;

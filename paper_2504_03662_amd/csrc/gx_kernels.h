@@ -43,6 +43,10 @@ struct GemmArgs {
 };
 
 hipError_t gemm_bf16(Layout lay, Epilogue epi, const GemmArgs& g, hipStream_t s);
+// Which tile gemm_bf16 takes for an M x N x K product (column_sums: EPI_DGELU), host code, so that tests can
+// tell what their sizes reach: 0 256x256, 1 256x192, 2 192x256, 3 256x128, 4 128x128, 5 64x128, 6 64x64,
+// 7 256x256 with the remainder in 128x128.
+extern "C" int gx_bf16_tile(int M, int N, int K, int column_sums);
 hipError_t gemm_f32(Layout lay, Epilogue epi, const GemmArgs& g, hipStream_t s);
 
 // Causal attention over the local heads.  qkv is [T, 3*Hl] with column blocks [Q | K | V], each
