@@ -603,18 +603,18 @@ struct Tiny : Tile<64, 64, 1, 1, 4, 128, 4> { static constexpr float fixed = 3.8
 // workgroups it takes times the price of a round, whether the last round is full or not, so the larger
 // tiles (less traffic per product) win where they fill the chip and the smaller ones where a larger
 // one would leave compute units without work.  The prices are fits to products of 1 to 4096 tiles
-// and K 768 to 10240; measured (us), chosen tile first:
-//   NN 4096 x 3072 x 4096   Wide 82.7 (256 tiles)  Large 89.0 (192)  Small 96.5   Half 103.8
-//   NT 2048 x 5120 x 10240  Wide 164 (216)         Large 191 (160)   Tall 179     Small 197
-//   NN 3003 x 4096 x 2048   Tall 44.1 (256)        Large 49.5 (192)  Wide 75.4    Half 57.7
-//   NT 2048 x 2560 x 5120   Half 57.4 (160)        Small 70.9 (320)  Flat 73.1    Large 92.6
-//   NT 4096 x 1024 x 4096   Small 32.0 (256)       Flat 42.9         Half 48.6    Large 72.6
-//   TN 512 x 4096 x 8192    Flat 44.4 (256)        Small 53.4 (128)  Tiny 60.7    Large 151
-//   TN 1024 x 1024 x 4096   Tiny 17.5 (256)        Flat 22.1 (128)   Small 27.7   Large 78.2
-//   NN 128 x 7680 x 5120    Tiny 22.8 (240)        Flat 28.3 (120)   Small 33.9   Large 85.5
+// and K 768 to 10240; measured (us, the same operands again and again), chosen tile first:
+//   NN 4096 x 3072 x 4096   Wide 79.0 (256 tiles)  Large 86.5 (192)  Small 90.4   Half 103
+//   NT 2048 x 5120 x 10240  Tall 164 (220)         Wide 161 (216)    Large 177    Small 190
+//   NN 3003 x 4096 x 2048   Tall 42.5 (256)        Large 44.4 (192)  Wide 73.8    Half 55.3
+//   NT 2048 x 2560 x 5120   Half 55.2 (160)        Small 66.5 (320)  Flat 72.7    Large 92.0
+//   NT 4096 x 1024 x 4096   Small 29.9 (256)       Flat 40.4         Half 43.9    Large 71.2
+//   TN 512 x 4096 x 8192    Flat 40.7 (256)        Small 49.7 (128)  Tiny 59.9    Large 150
+//   TN 1024 x 1024 x 4096   Tiny 17.1 (256)        Flat 21.6 (128)   Small 27.1   Large 78.5
+//   NN 128 x 7680 x 5120    Tiny 22.4 (240)        Flat 27.9 (120)   Small 35.2   Large 85.0
 // Beyond whole rounds of large tiles, the remaining ones can also be cut into 128 x 128 tiles in a second
-// launch (TAIL is what that launch costs): NN 2048 x 10240 x 5120, 320 large tiles, 173 against 184
-// (Wide), 189 (Small) and 210 (Large alone).
+// launch (TAIL is what that launch costs): NN 2048 x 10240 x 5120, 320 large tiles, 157 against 175
+// (Tall), 182 (Small) and 203 (Large alone).
 constexpr long ROUND = 256;
 constexpr float TAIL = 3.0f;
 template <class T>
@@ -624,9 +624,10 @@ float price(long tiles, int K) {
 // Another tile than the large one has to be 3 % cheaper: where it only evens out, the large one leaves more
 // to the product of the other stream that shares the chip (two products of 5466 x 6528 x 19584 and its
 // transpose, equal alone, 1.5 % slower together with 256 x 192 tiles).  192 x 256 before 256 x 192: the same
-// price, but its rows are read back from LDS without a remainder; where the two take as many rounds it was
-// faster on the mean of 70 products whichever of them has fewer tiles (2048 x 5120 x 10240 NT, operands not
-// cached, 215 us of 220 tiles against 218 of 216; 6618 x 1216 x 16952 NT 421 of 175 against 439 of 182).
+// price, but its rows are read back from LDS without a remainder.  Where both take the same number of rounds
+// 256 x 192 took 1.3 % longer on the mean of 70 products, whichever has fewer tiles (6618 x 1216 x 16952 NT, 175
+// and 182 tiles, 421 us against 439; 2048 x 5120 x 10240 NT, 220 and 216 tiles, 215 against 218, operands not
+// in the caches; a pipeline stage of hidden 5120 is 0.3 % faster than with the fewer tiles first).
 enum Pick { PICK_LARGE, PICK_WIDE, PICK_TALL, PICK_HALF, PICK_SMALL, PICK_FLAT, PICK_TINY, PICK_LARGE_TAIL };
 Pick pick(int M, int N, int K, bool column_sums) {
   const long big = (long)cdiv(M, 256) * cdiv(N, 256), rem = big % ROUND;
