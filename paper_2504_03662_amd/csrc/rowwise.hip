@@ -377,19 +377,24 @@ hipError_t ln_fwd(bool is_bf16, const void* x, const void* g, const void* b, voi
   if (rows <= 0 || cols <= 0 || cols % vec || cols / vec > 64 * LN_MAXC) return hipErrorInvalidValue;
   const dim3 block(256);
   const int per_lane = cdiv(cols / vec, 64);
+  // Rows of more than 4 chunks per lane are shared by four wavefronts: a wavefront that holds 8 to 16 chunks
+  // has too few others beside it to cover its loads.  bf16, one wavefront / four (us): 128 rows of 5120 6.6 / 3.8,
+  // 8192 of 5120 38.2 / 26.9, 8192 of 8192 60.7 / 42.7.  With 5 or 6 chunks per lane one wavefront per row is
+  // the faster as long as all rows are on the chip at once (at most 16 wavefronts of bf16 rows per compute unit, 28 of
+  // fp32 rows) and four per row are not (2048 rows): 2560 wide, 2048 rows 7.0 / 6.4, 2304 rows 7.2 / 7.7, 4096 rows
+  // 9.2 / 10.0, 4104 rows 12.0 / 9.9; fp32, 1280 wide, 2048 rows 6.3 / 6.2, 2560 rows 6.9 / 7.7, 7168 rows 16.6 / 18.2, 7176
+  // rows 22.7 / 18.6.
+  const int at_once = is_bf16 ? 4096 : 7168;
 #define GX_LN_FWD(T, C, G)                                                                                       \
   hipLaunchKernelGGL((ln_fwd_kernel<T, C, G>), dim3(G == 1 ? cdiv(rows, 4) : rows), block, 0, s, (const T*)x,     \
                      (const T*)g, (const T*)b, (T*)y, mean, rstd, rows, cols, eps)
 #define GX_LN_FWD_T(T)                                                                        \
   do {                                                                                        \
     if (per_lane <= 4) GX_LN_FWD(T, 4, 1);                                                    \
+    else if (per_lane <= 6 && rows > 2048 && rows <= at_once) GX_LN_FWD(T, 6, 1);             \
     else if (per_lane <= 8) GX_LN_FWD(T, 2, 4);                                               \
     else GX_LN_FWD(T, 4, 4);                                                                  \
   } while (0)
-  // Rows of more than 4 chunks per lane are shared by four wavefronts: a wavefront that holds 8 to 16 chunks
-  // has too few others beside it to cover its loads.  bf16, one wavefront / four (us): 128 rows of 5120 6.6 / 3.8,
-  // 4096 of 4096 12.8 / 12.5, 8192 of 5120 38.2 / 26.9, 8192 of 8192 60.7 / 42.7; 2560 wide, 5 chunks per
-  // lane, 1024 rows 5.0 / 3.9, 4096 rows 8.6 / 9.2, 8192 rows 16.8 / 15.7.
   if (is_bf16) GX_LN_FWD_T(bf16);
   else GX_LN_FWD_T(float);
 #undef GX_LN_FWD_T

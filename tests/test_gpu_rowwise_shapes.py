@@ -21,3 +21,12 @@ def test_layer_norm_launch_shapes(dtype, hidden, rows):
     x, dy = I.activations(shape, case=600 + rows)
     gpu, ref, _ = run_both(shape, params, x, dy, "mlp")
     compare(gpu, ref, TOL[dtype], "mlp")
+
+
+@pytest.mark.parametrize("dtype,hidden,rows", [
+    ("bf16", 2112, 2048), ("bf16", 2112, 2049), ("bf16", 3072, 4096), ("bf16", 2560, 4097), ("f32", 1028, 2049),
+    ("f32", 1536, 2050), ("f32", 1280, 7168), ("f32", 1028, 7169),
+])
+def test_layer_norm_rows_of_five_and_six_chunks_per_lane(dtype, hidden, rows):
+    # one wavefront per row or four, by the number of rows
+    test_layer_norm_launch_shapes(dtype, hidden, rows)
