@@ -48,8 +48,8 @@ def test_fp32_accumulation_and_dropout_with_padded_heads():
 @pytest.mark.parametrize("heads", [1, 2, 4, 8])
 @pytest.mark.parametrize("at", [40, 99])
 def test_fp32_values_that_are_not_finite_stay_behind_the_mask(heads, at):
-    # one token of one sample is not finite: rows before it (and the other sample) are untouched bit
-    # for bit, its own row is not finite
+    # one token of one sample is not finite: rows before it are untouched (up to the order of their sums),
+    # the other sample bit for bit, its own row is not finite
     shape = I.LayerShape(256, heads, 256, 1, 1, 0, 100, 2, "f32") if heads > 1 else \
         I.LayerShape(128, heads, 256, 1, 1, 0, 100, 2, "f32")
     params = I.full_params(shape, case=440, random_affine=True)
@@ -138,3 +138,67 @@ def test_fp32_infinite_upstream_gradient_in_a_partial_last_tile(hidden, heads):
     layer.backward(xd, to_device(dy, "f32"), "attn")
     got = to_host(layer.grads["b_qkv"])[2 * hidden:]
     np.testing.assert_array_equal(got, np.sign(p["w_o"][:, 3]) * np.float32(np.inf))
+
+
+def _one_token_layer(hidden, heads, at):
+    """A layer with a feature that is exactly 0 in every token but `at` (tokens of +1 and -1 with zero mean)."""
+    shape = I.LayerShape(hidden, heads, 8, 1, 1, 0, 100, 1, "f32")
+    half = np.random.default_rng(470).choice(np.array([-1.0, 1.0], np.float32), (100, hidden // 2))
+    half[:, 0] = 0.0
+    half[at, 0] = 4.0
+    p = I.full_params(shape, case=470, random_affine=True)
+    dh = hidden // heads
+    p["ln1_g"][:], p["ln1_b"][:] = 1.0, 0.0
+    p["w_qkv"][[0, hidden // 2]] = 0.0
+    p["w_qkv"][:, 0:2 * hidden:dh] = 0.0               # component 0 of every query and key: 0
+    p["b_qkv"][0:2 * hidden:dh] = 0.0
+    return shape, p, np.concatenate([half, -half], axis=1)
+
+
+def _run_attn(shape, p, x, dy):
+    layer = DeviceLayer(shape, p)
+    xd = to_device(x, "f32")
+    layer.forward(xd, "attn")
+    dx = to_host(layer.backward(xd, to_device(dy, "f32"), "attn"))
+    return dx, {n: to_host(layer.grads[n]) for n in ("w_qkv", "b_qkv")}
+
+
+@pytest.mark.parametrize("hidden,heads", [(40, 2), (64, 2), (128, 2), (256, 2)])       # head dim 20, 32, 64, 128
+@pytest.mark.parametrize("at", [40, 97])                                               # 97: in a partial tile
+@pytest.mark.parametrize("what", ["query", "upstream gradient"])
+def test_fp32_a_query_that_is_not_finite_stays_from_later_keys(hidden, heads, at, what):
+    # dK and dV of the keys after it, which it does not see, and with them dx of those tokens
+    shape, p, x = _one_token_layer(hidden, heads, at)
+    dy = I.activations(shape, case=470)[1]
+    dx0, _ = _run_attn(shape, p, x, dy)
+    if what == "query":
+        p["w_qkv"][0, 0:hidden:hidden // heads] = 3e38     # beyond the fp32 range at that token
+    else:
+        dy[at, 3] = np.inf
+    dx1, _ = _run_attn(shape, p, x, dy)
+    np.testing.assert_allclose(dx1[at + 1:], dx0[at + 1:], rtol=0, atol=1e-5 * np.abs(dx0).max())
+    assert not np.isfinite(dx1[:at + 1]).all(axis=1).any()
+
+
+@pytest.mark.parametrize("hidden,heads", [(40, 2), (64, 2), (128, 2), (256, 2)])
+@pytest.mark.parametrize("at", [40, 97])
+def test_fp32_a_key_that_is_not_finite_stays_from_earlier_queries(hidden, heads, at):
+    # component 0 of one key is -inf and every query's is 1: the key has weight 0, and only dQ of the queries
+    # that see it is not finite, in that component
+    shape, p, x = _one_token_layer(hidden, heads, at)
+    dh = hidden // heads
+    p["w_qkv"][0, hidden:2 * hidden:dh] = -3e38
+    p["b_qkv"][0:hidden:dh] = 1.0
+    dy = I.activations(shape, case=470)[1]
+    dx, g = _run_attn(shape, p, x, dy)
+    assert np.isfinite(dx[:at]).all()
+    with np.errstate(over="ignore", invalid="ignore"):
+        q = p.copy()
+        q["w_qkv"] = p["w_qkv"].astype(np.float64)
+        q["w_qkv"][0, hidden:2 * hidden:dh] = -1e308       # -inf in 64 bits as well
+        ref = O.layer_fwd(shape, q, x, "attn")
+        _, rg = O.layer_bwd(shape, q, dy, ref["cache"], "attn")
+    kept = np.ones(3 * hidden, bool)
+    kept[0:hidden:dh] = False
+    for n in ("w_qkv", "b_qkv"):
+        check("d" + n, g[n][..., kept], rg[n][..., kept], TOL["f32"])
