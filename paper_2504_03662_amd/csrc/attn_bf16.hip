@@ -43,9 +43,8 @@ hipError_t attn_fwd_bf16(const AttnArgs& a, hipStream_t s) {
   return a.dh == 128 ? dh128::fwd(a, s) : a.dh == 64 ? dh64::fwd(a, s) : hipErrorInvalidValue;
 }
 
-hipError_t attn_bwd_bf16(const AttnArgs& a, hipStream_t s, hipStream_t s_dq, hipEvent_t fork, hipEvent_t join) {
-  return a.dh == 128 ? dh128::bwd(a, s, s_dq, fork, join)
-                     : a.dh == 64 ? dh64::bwd(a, s, s_dq, fork, join) : hipErrorInvalidValue;
+hipError_t attn_bwd_bf16(const AttnArgs& a, hipStream_t s) {
+  return a.dh == 128 ? dh128::bwd(a, s) : a.dh == 64 ? dh64::bwd(a, s) : hipErrorInvalidValue;
 }
 
 }  // namespace gx

@@ -344,9 +344,9 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
         for (int v = 0; v < 16; v++) mloc = fmaxf(mloc, sacc[jt][v]);
       mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64)) * c2;
       // The reference is the running maximum itself, so that a row's largest probability is exactly 1 in
-      // bf16.  Letting it lag by up to 8 powers of 2 left the output 0.1 to 1.5 % further from the fp64 one
-      // and saved nothing (layer steps, us: hidden 2048 with 64 pairs of S 2048 2501 against 2500; hidden
-      // 1024 with head dim 64 and dropout 581 against 576 here).
+      // bf16.  Letting it lag by up to 8 powers of 2 left the output 0.1 to 1.5 % further from the fp64 one,
+      // and layer steps (hidden 2048, 64 pairs of S 2048; hidden 1024, head dim 64, dropout) differed by less
+      // than the 1 % that two builds of the same kernels do, in either direction.
       const float mnew = fmaxf(m, mloc);
       if (__builtin_amdgcn_ballot_w64(mnew > m)) {     // wave-uniform: some row's running max moved
         const float alpha = __builtin_amdgcn_exp2f(m - mnew);
@@ -984,11 +984,8 @@ hipError_t fwd(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// dK/dV and dQ are independent once D is known, and the dK/dV kernel is short of workgroups near
-// the end of the causal triangle (heavy key blocks come first): with a second stream the dQ
-// kernel runs beside it and fills the compute units it leaves idle.  `fork` / `join` are events
-// owned by the caller of this function.
-hipError_t bwd(const AttnArgs& a, hipStream_t s, hipStream_t s_dq, hipEvent_t fork, hipEvent_t join) {
+// D, then dK / dV, then dQ.
+hipError_t bwd(const AttnArgs& a, hipStream_t s) {
   if (!attn_shape_ok(a)) return hipErrorInvalidValue;
   static bool configured = false;
   if (!configured) {
@@ -1011,11 +1008,6 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s, hipStream_t s_dq, hipEvent_t fo
                      (const bf16*)a.dctx, a.dsum, a.B, a.S, a.nl);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const bool two = (s_dq != s);
-  if (two) {
-    if ((e = hipEventRecord(fork, s)) != hipSuccess) return e;
-    if ((e = hipStreamWaitEvent(s_dq, fork, 0)) != hipSuccess) return e;
-  }
   auto go_dkv = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, KV_BJ) * a.nl * a.B), dim3(64 * KV_NW), KV_SMEM, s, (const bf16*)a.qkv,
                        (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, a.nl * a.B, qkv_bytes, dctx_bytes,
@@ -1026,7 +1018,7 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s, hipStream_t s_dq, hipEvent_t fo
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int npair = a.nl * a.B;
   auto go_dq = [&](auto kernel, int bq, int threads, int smem) {
-    hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, bq) * npair), dim3(threads), smem, s_dq, (const bf16*)a.qkv,
+    hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, bq) * npair), dim3(threads), smem, s, (const bf16*)a.qkv,
                        (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, npair, qkv_bytes, keep_rows);
   };
   if (few_pairs(a)) {
@@ -1036,11 +1028,6 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s, hipStream_t s_dq, hipEvent_t fo
     if (drop) go_dq(attn_bwd_dq_kernel<4, 1, 64, true>, 128, 256, SMEM_MANY);
     else go_dq(attn_bwd_dq_kernel<4, 1, 64, false>, 128, 256, SMEM_MANY);
   }
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (two) {
-    if ((e = hipEventRecord(join, s_dq)) != hipSuccess) return e;
-    if ((e = hipStreamWaitEvent(s, join, 0)) != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return hipGetLastError();
 }
 

@@ -216,16 +216,19 @@ hipError_t launch(const GemmArgs& g, hipStream_t s) {
   return launch_tile<LAY, EPI, 64, 1, 3>(g, s);
 }
 
+// The combinations that the layer driver asks for.
 template <int LAY>
 hipError_t dispatch_epi(Epilogue epi, const GemmArgs& g, hipStream_t s) {
-  switch (epi) {
-    case EPI_STORE: return launch<LAY, EPI_F32>(g, s);
-    case EPI_BIAS: return launch<LAY, EPI_BIAS>(g, s);
-    case EPI_RESID: return launch<LAY, EPI_RESID>(g, s);
-    case EPI_GELU: return launch<LAY, EPI_GELU>(g, s);
-    case EPI_DGELU: return launch<LAY, EPI_DGELU>(g, s);
-    case EPI_F32: return launch<LAY, EPI_F32>(g, s);
-    case EPI_F32_ACC: return launch<LAY, EPI_F32_ACC>(g, s);
+  if constexpr (LAY == LAY_NN) {
+    if (epi == EPI_BIAS) return launch<LAY, EPI_BIAS>(g, s);
+    if (epi == EPI_RESID) return launch<LAY, EPI_RESID>(g, s);
+    if (epi == EPI_GELU) return launch<LAY, EPI_GELU>(g, s);
+  } else if constexpr (LAY == LAY_NT) {
+    if (epi == EPI_STORE) return launch<LAY, EPI_STORE>(g, s);
+    if (epi == EPI_DGELU) return launch<LAY, EPI_DGELU>(g, s);
+  } else {
+    if (epi == EPI_F32) return launch<LAY, EPI_F32>(g, s);
+    if (epi == EPI_F32_ACC) return launch<LAY, EPI_F32_ACC>(g, s);
   }
   return hipErrorInvalidValue;
 }

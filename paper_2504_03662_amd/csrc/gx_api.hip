@@ -282,10 +282,8 @@ hipError_t colsum_p(bool bf, const void* a, long rows, long cols, float* part, f
 // The backward pass has work whose inputs are ready long before anything consumes its results:
 // the bandwidth-bound column reductions (bias and LayerNorm parameter gradients) and every
 // weight-gradient product.  It runs on a second, library-owned stream beside the dependent chain
-// (input gradients, LayerNorm input gradients, attention) on the caller's stream, and a third
-// stream takes the dQ kernel beside the dK/dV kernel: fork with an event after the producer, join
-// once at the end of the call.  Created on first use, default priority, shared by all calls of the
-// process (calls from several host threads must not overlap).
+// (input gradients, LayerNorm input gradients, attention) on the caller's stream: fork with an event
+// after the producer, join once at the end of the call.  Default priority.
 struct SideStream {
   bool tried = false, ok = false;
   hipStream_t s = nullptr;
@@ -580,7 +578,7 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
     { ProfScope ps(GX_KC_ATTN_BWD, st);
     // the dQ kernel follows the dK / dV kernel on the caller's stream: a stream of its own for it
     // measured slightly slower (its workgroups cannot share a compute unit with the other kernel's)
-    GX_TRY(d.bf ? attn_bwd_bf16(a, st, st, nullptr, nullptr) : attn_bwd_f32(a, st));
+    GX_TRY(d.bf ? attn_bwd_bf16(a, st) : attn_bwd_f32(a, st));
     }
     if ((s = point(5)) != GX_OK) return s;
     GemmArgs dy1 = gargs(w.dqkv, p.w_qkv, w.dy1, d.T, d.H, 3 * d.Hl, 3 * d.Hl, 3 * d.Hl, d.H);
