@@ -223,8 +223,8 @@ int gx_prof_collect(int* kernel_class, float* ms, int capacity);
 
 /* Measured ceilings of the chip, to hold the layer's kernels against (benchmarks only; both calls
  * create two HIP events, queue their work on `hip_stream`, wait for it and destroy the events):
- *   gx_peak_mfma : `launches` launches of a register-only v_mfma_f32_32x32x16_bf16 loop (1024
- *                       workgroups of 4 wavefronts, 4 independent accumulators each, no memory
+ *   gx_peak_mfma : `launches` launches of a register-only v_mfma_f32_16x16x32_bf16 loop (1024
+ *                       workgroups of 4 wavefronts, 8 independent accumulators each, no memory
  *                       traffic); *tflops receives the sustained rate.  `scratch`: at least 64
  *                       bytes of device memory (never written in practice).
  *   gx_peak_copy      : `launches` copies of `bytes` (a multiple of 16) from src to dst, 16 bytes per
