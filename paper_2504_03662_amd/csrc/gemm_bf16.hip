@@ -7,8 +7,8 @@
 // units without one, the smallest of them with several wavefronts per place that share every stage's
 // reduction steps (see the tiles and their prices below).
 // Products are v_mfma_f32_16x16x32_bf16: on this chip the large products run at the board's power
-// limit, and a register-only loop on normal data holds 1977 TFLOP/s with that instruction against
-// 1816 with 32x32x16 (on zeros 2420 and 2481): it reads and writes an accumulator half as often.
+// limit, and a register-only loop on normal data holds 2030 TFLOP/s with that instruction against
+// 1811 with 32x32x16 (on zeros 2411 and 2472): it reads and writes an accumulator half as often.
 // Fragments come from ds_read_b128 when the reduction index is contiguous in memory ("K-major" tiles)
 // and from the transposing ds_read_b64_tr_b16 when it is strided ("MN-major" tiles), so no operand is
 // ever transposed in HBM.  LDS positions are XOR-swizzled on the global-address side because a

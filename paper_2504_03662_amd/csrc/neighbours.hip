@@ -239,8 +239,8 @@ gx_status gx_adamw_step(const gx_adamw_cfg* cfg, size_t n, float* master, float*
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const int out = !param_out ? 0 : (param_dtype == GX_BF16 ? 1 : 2);
   // Four fp32 arrays beyond what the 256 MB memory-side cache holds are streamed past it.  Through the
-  // caches / past them, us: 8 M elements 35.7 / 43.3, 16 M (256 MB) 72.4 / 82.3, 25 M 144 / 127, 50 M 289 / 250
-  // (6.0 TB/s; a plain copy reaches 5.7).
+  // caches / past them, us: 8 M elements 35.7 / 43.3, 16 M (256 MB) 72.4 / 82.3, 25 M 144 / 129, 50 M 288 / 250
+  // (6.0 TB/s; a plain copy reaches 5.8).  With the caches full of other data 25 M 155 / 142, 50 M 295 / 280.
   const bool stream = n * 16 > ((size_t)320 << 20);
   const dim3 grid((unsigned)wgs), block(256);
 #define GX_ADAMW(OUT)                                                                                              \
