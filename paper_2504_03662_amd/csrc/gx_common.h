@@ -94,7 +94,9 @@ GX_DEVINL bf16x4 lds_read_tr_issue(unsigned addr) {
 GX_DEVINL float max_across_halves(float x) {
   const unsigned u = __builtin_bit_cast(unsigned, x);
   const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fmaxf(__builtin_bit_cast(float, r[0]), __builtin_bit_cast(float, r[1]));
+  // through scalars: __builtin_bit_cast of a vector's element reads element 0 whatever the index
+  const unsigned lo = r[0], hi = r[1];
+  return fmaxf(__builtin_bit_cast(float, lo), __builtin_bit_cast(float, hi));
 }
 GX_DEVINL void lds_wait_all() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 // wait until at most N LDS operations of this wavefront are outstanding (they complete in order)

@@ -105,3 +105,38 @@ def test_scores_that_rise_along_the_keys(dh, heads, batch, drop):
     for n in ("w_qkv", "b_qkv"):
         check("d" + n, to_host(layer.grads[n]) * kept, rg[n] * kept, TOL["bf16"])
     check("dw_o", to_host(layer.grads["w_o"]), rg["w_o"], TOL["bf16"])
+
+
+@pytest.mark.parametrize("dtype,dh,heads,batch", [
+    ("bf16", 64, 8, 2), ("bf16", 128, 4, 1), ("bf16", 64, 16, 25), ("bf16", 128, 16, 25), ("f32", 32, 4, 2),
+    ("f32", 64, 4, 2), ("f32", 128, 2, 2), ("f32", 20, 4, 2),
+])
+@pytest.mark.parametrize("star", [1, 6, 66, 70, 93])
+def test_one_score_far_above_all_others(dtype, dh, heads, batch, star):
+    # 300 (natural) above every other: relative to anything but itself its exponential overflows.  Places 1 to 3
+    # of 8 keys are held by one half of a wavefront, 5 to 7 by the other.
+    shape = I.LayerShape(heads * dh, heads, 64, 1, 1, 0, 128, batch, dtype)
+    h = shape.hidden
+    feat = np.zeros((shape.seq, 1), np.float32)
+    feat[star] = 1.0
+    x = _signs(shape, feat, 720)
+    p = I.full_params(shape, case=721, random_affine=True)
+    p["ln1_g"][:], p["ln1_b"][:] = 1.0, 0.0
+    p["w_qkv"][:, 0:2 * h:dh] = 0.0
+    p["b_qkv"][0:2 * h:dh] = 0.0
+    p["b_qkv"][0:h:dh] = 16.0                                       # q component 0
+    p["w_qkv"][0, h:2 * h:dh] = I.bf16_round(np.float32([300 / 16 * np.sqrt(dh)]))[0]   # k component 0 of the one key
+    dy = I.activations(shape, case=722)[1]
+    layer = DeviceLayer(shape, p)
+    xd, dyd = to_device(x, dtype), to_device(dy, dtype)
+    got = to_host(layer.forward(xd, "attn")["p_attn"])
+    layer.backward(xd, dyd, "attn")
+    torch.cuda.synchronize()
+    ref = O.layer_fwd(shape, p, x, "attn")
+    _, rg = O.layer_bwd(shape, p, dy, ref["cache"], "attn")
+    check("p_attn", got, ref["p_attn"], TOL[dtype])
+    kept = np.ones(3 * h, np.float32)                               # as above, without component 0 of dQ and dK
+    kept[0:2 * h:dh] = 0.0
+    for n in ("w_qkv", "b_qkv"):
+        check("d" + n, to_host(layer.grads[n]) * kept, rg[n] * kept, TOL[dtype])
+    check("dw_o", to_host(layer.grads["w_o"]), rg["w_o"], TOL[dtype])
