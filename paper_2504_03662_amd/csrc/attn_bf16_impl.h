@@ -297,15 +297,18 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
 
   const int jend = min(S, i0 + BQ);                   // keys 0 .. jend-1 can be visible
   const int nt = (jend + ROWS - 1) / ROWS;
-  tile_load<ROWS, NW>(rsrc, eq + Hl, ld, 0, S, smem, wave, lane);
-  tile_load<ROWS, NW>(rsrc, eq + 2 * Hl, ld, 0, S, smem + ROWS * ROWB, wave, lane);
+  TileStream<ROWS, NW> ksrc, vsrc;
+  ksrc.init(eq + Hl, ld, wave, lane);
+  vsrc.init(eq + 2 * Hl, ld, wave, lane);
+  ksrc.load(rsrc, eq + Hl, ld, 0, S, smem, wave, lane);
+  vsrc.load(rsrc, eq + 2 * Hl, ld, 0, S, smem + ROWS * ROWB, wave, lane);
   WAIT_VM0();
   __syncthreads();
   for (int t = 0; t < nt; t++) {
     if (t + 1 < nt) {
       char* nxt = smem + ((t + 1) & 1) * STAGE;
-      tile_load<ROWS, NW>(rsrc, eq + Hl, ld, (t + 1) * ROWS, S, nxt, wave, lane);
-      tile_load<ROWS, NW>(rsrc, eq + 2 * Hl, ld, (t + 1) * ROWS, S, nxt + ROWS * ROWB, wave, lane);
+      ksrc.load(rsrc, eq + Hl, ld, (t + 1) * ROWS, S, nxt, wave, lane);
+      vsrc.load(rsrc, eq + 2 * Hl, ld, (t + 1) * ROWS, S, nxt + ROWS * ROWB, wave, lane);
     }
     const int j0 = t * ROWS + part * BKV;              // this wave's keys of the step
     // wave-uniform; j0 and iw are multiples of 32, so when it holds every row of the wave sees key j0
@@ -342,11 +345,10 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
       for (int jt = 0; jt < NJT; jt++)
 #pragma unroll
         for (int v = 0; v < 16; v++) mloc = fmaxf(mloc, sacc[jt][v]);
-      mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64)) * c2;
+      mloc = max_across_halves(mloc) * c2;
       // The reference is the running maximum itself, so that a row's largest probability is exactly 1 in
-      // bf16.  Letting it lag by up to 8 powers of 2 left the output 0.1 to 1.5 % further from the fp64 one,
-      // and layer steps (hidden 2048, 64 pairs of S 2048; hidden 1024, head dim 64, dropout) differed by less
-      // than the 1 % that two builds of the same kernels do, in either direction.
+      // bf16.  Letting it lag by up to 8 powers of 2 is faster (64 pairs of S 2048: 89 us against 95) but leaves
+      // the output 0.1 to 1.5 % further from the fp64 one.
       const float mnew = fmaxf(m, mloc);
       if (__builtin_amdgcn_ballot_w64(mnew > m)) {     // wave-uniform: some row's running max moved
         const float alpha = __builtin_amdgcn_exp2f(m - mnew);
@@ -838,15 +840,18 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
 
   const int jend = min(S, i0 + BQ);
   const int nt = (jend + ROWS - 1) / ROWS;
-  tile_load<ROWS, NW>(rsrc, eq + Hl, ld, 0, S, smem, wave, lane);
-  tile_load<ROWS, NW>(rsrc, eq + 2 * Hl, ld, 0, S, smem + ROWS * ROWB, wave, lane);
+  TileStream<ROWS, NW> ksrc, vsrc;
+  ksrc.init(eq + Hl, ld, wave, lane);
+  vsrc.init(eq + 2 * Hl, ld, wave, lane);
+  ksrc.load(rsrc, eq + Hl, ld, 0, S, smem, wave, lane);
+  vsrc.load(rsrc, eq + 2 * Hl, ld, 0, S, smem + ROWS * ROWB, wave, lane);
   WAIT_VM0();
   __syncthreads();
   for (int t = 0; t < nt; t++) {
     if (t + 1 < nt) {
       char* nxt = smem + ((t + 1) & 1) * STAGE;
-      tile_load<ROWS, NW>(rsrc, eq + Hl, ld, (t + 1) * ROWS, S, nxt, wave, lane);
-      tile_load<ROWS, NW>(rsrc, eq + 2 * Hl, ld, (t + 1) * ROWS, S, nxt + ROWS * ROWB, wave, lane);
+      ksrc.load(rsrc, eq + Hl, ld, (t + 1) * ROWS, S, nxt, wave, lane);
+      vsrc.load(rsrc, eq + 2 * Hl, ld, (t + 1) * ROWS, S, nxt + ROWS * ROWB, wave, lane);
     }
     const int j0 = t * ROWS + part * BKV;
     if (j0 <= iw + 31) {
