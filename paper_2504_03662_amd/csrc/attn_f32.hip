@@ -14,7 +14,7 @@
 // Head dimensions up to 128 are padded with zeros to 32, 64 or 128.  With 16 heads of 64, S 512, batch 2:
 // forward 1031 -> 25 us, dQ 2222 -> 41 us, dK / dV 2426 -> 47 us against one wavefront per row with
 // scalar multiply-adds; with 8 heads of 128 forward 1251 -> 43 us, backward 5448 -> 142 us, although dK / dV then
-// needs more than the 512 registers there are and spills 47 (184 bytes a lane).
+// needs more than the 512 registers there are and spills 43 (176 bytes a lane).
 #include "gx_kernels.h"
 
 namespace gx {
@@ -74,9 +74,10 @@ GX_DEVINL f32x16 row_product(const f32x4 (&a)[DHP / 8], const f32x4 (&b)[DHP / 8
 }
 
 // acc[dt][d][col] += sum over the 32 rows r of the tile of src[r][d] * w[r][col], w being an
-// accumulator.  On the tile that touches the diagonal some weights stand for masked pairs and are
-// 0; a value of src that is not finite must not reach the columns it is masked for (0 * inf), so
-// such a tile takes the second form: weights through LDS and one multiply-add per unmasked pair.
+// accumulator.  On the tile that touches the diagonal some weights stand for masked pairs, on a partial
+// last tile for rows that are not there, and are 0; a value of src that is not finite must not reach the
+// columns it is masked for (0 * inf), so such a tile then takes the second form: weights through LDS and
+// one multiply-add per pair that counts.
 // LATER: a row is masked for the columns below it (keys for queries); else for those above it.
 template <int DHP, bool EXACT, bool LATER>
 GX_DEVINL void col_product(f32x16 (&acc)[DHP / 32], const f32x16& w, const float* src, int ld, int rows, int dh,
@@ -95,17 +96,14 @@ GX_DEVINL void col_product(f32x16 (&acc)[DHP / 32], const f32x16& w, const float
 #pragma unroll
         for (int v = 0; v < 16; v++) x[c][v] = (src + (size_t)acc_row(v, 0) * ld)[off];
       } else {
-        // rows beyond the tensor count as zeros (their weight is 0 too, which alone would not do beside a
-        // last row that is not finite)
+        // rows beyond the tensor have weight 0 and take the last row's values; where that row is not finite
+        // the second form leaves them out
 #pragma unroll
-        for (int v = 0; v < 16; v++) {
-          const float xv = src[(unsigned)(min(acc_row(v, g), rows - 1) * ld + d)];
-          x[c][v] = acc_row(v, g) < rows ? xv : 0.f;
-        }
+        for (int v = 0; v < 16; v++) x[c][v] = src[(unsigned)(min(acc_row(v, g), rows - 1) * ld + d)];
       }
     }
     bool bad = false;
-    if (diagonal) {
+    if (diagonal || rows < 32) {
 #pragma unroll
       for (int c = 0; c < CH; c++)
 #pragma unroll
@@ -116,7 +114,7 @@ GX_DEVINL void col_product(f32x16 (&acc)[DHP / 32], const f32x16& w, const float
       for (int v = 0; v < 16; v++) spill[acc_row(v, g) * 33 + l32] = w[v];
       for (int r = 0; r < min(rows, 32); r++) {
         const float wr = spill[r * 33 + l32];
-        if (LATER ? r > l32 : r < l32) continue;
+        if (diagonal && (LATER ? r > l32 : r < l32)) continue;
 #pragma unroll
         for (int c = 0; c < CH; c++)
 #pragma unroll
