@@ -347,7 +347,7 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
         for (int v = 0; v < 16; v++) mloc = fmaxf(mloc, sacc[jt][v]);
       mloc = max_across_halves(mloc) * c2;
       // The reference is the running maximum itself, so that a row's largest probability is exactly 1 in
-      // bf16.  Letting it lag by up to 8 powers of 2 is faster (64 pairs of S 2048: 89 us against 95) but leaves
+      // bf16.  Letting it lag by up to 8 powers of 2 is faster (64 pairs of S 2048: 86 us against 92) but leaves
       // the output 0.1 to 1.5 % further from the fp64 one.
       const float mnew = fmaxf(m, mloc);
       if (__builtin_amdgcn_ballot_w64(mnew > m)) {     // wave-uniform: some row's running max moved
@@ -580,9 +580,10 @@ __global__ void __launch_bounds__(256) attn_dsum_kernel(const bf16* __restrict__
 // A phase is a chain (LDS reads, products, exponentials, exchange, barrier) that keeps the matrix pipe
 // busy for a third of its length, so what matters is a second, independent workgroup on the compute
 // unit (66 KB of LDS at DH 128) to fill the rest.  Against 128 key rows, query tiles of 64 and one workgroup
-// of 8 wavefronts per unit (us): 64 pairs of S 2048 at DH 128 336 -> 203, 16 pairs 95 -> 78, 4 pairs of S 8192
-// 265 -> 237; 64 pairs of S 1024 at DH 64 with dropout 70 -> 45.  One tile in flight instead of two is equal;
-// three workgroups per unit need 168 registers and spill (331 instead of 203).
+// of 8 wavefronts per unit, the whole backward pass (D, this kernel, dQ; nothing else on the chip, us): 64 pairs of
+// S 2048 at DH 128 394 -> 292 (this kernel 287 -> 173), 16 pairs 112 -> 101 (75 -> 62), 4 pairs of S 8192 372 -> 334;
+// 64 pairs of S 1024 at DH 64 with dropout 95 -> 74.  One tile in flight instead of two is equal; three
+// workgroups per unit need 168 registers and spill (1.6 times the time).
 constexpr int KV_PAIRS = 2, KV_NW = 2 * KV_PAIRS, KV_BJ = 32 * KV_PAIRS, KV_BI = 32, KV_SUB = KV_BI / 32;
 // LDS: Q tiles (+ their D rows) in a ring (tiles n-1 .. n+2), dO tiles (+ lse rows) in a ring (tiles
 // n .. n+2), two P exchange buffers, and a 256 B sink (see stage_load).
@@ -613,8 +614,8 @@ __global__ void __launch_bounds__(64 * KV_NW, 2) attn_bwd_dkv_kernel(const bf16*
   const int g = lane >> 5, l32 = lane & 31;
   // Blocks with most query tiles (the first keys) first.  In a launch that is resident all at once, two
   // workgroups per unit, the second half runs those with fewest first, as in the forward kernel (16 pairs
-  // of S 2048: 79 us against 81, 4 pairs of S 8192: 239 against 248; with four times as many workgroups
-  // as places, 203 in plain order against 220).
+  // of S 2048 2 % faster, 4 pairs of S 8192 4 %; with four times as many workgroups as places plain order is 8 %
+  // faster).
   const int kp = blockIdx.x % npair, rk = blockIdx.x / npair, nkb = (S + KV_BJ - 1) / KV_BJ, hk = (nkb + 1) / 2;
   const int kb = rk < hk || gridDim.x > KV_PAIRED ? rk : nkb - 1 - (rk - hk);
   const int h = kp % nl, b = kp / nl;
