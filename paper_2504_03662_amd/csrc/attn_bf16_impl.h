@@ -447,6 +447,7 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
 #pragma unroll
     for (int s = 0; s < NS; s++) s_even = MFMA(frag_rows(k0, l32, s, g), qf[s], s_even);
   }
+  __syncthreads();          // step 0 requests K(2) into the buffer that every wavefront has just read K(0) from
   // one step: `sacc` holds the scores of step t on entry, `snxt` those of step t + 1 on exit
   auto step = [&](int t, f32x16& sacc, f32x16& snxt) __attribute__((always_inline)) {
     if (t + 2 < nt) ksrc.load(rsrc, eq + Hl, ld, (t + 2) * ROWS, S, kst + (t & 1) * TILE, wave, lane);
