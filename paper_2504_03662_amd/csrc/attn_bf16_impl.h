@@ -38,36 +38,30 @@ GX_DEVINL void tile_load(__amdgpu_buffer_rsrc_t rsrc, unsigned elem0, int ld, in
   }
 }
 
-// The same load for a kernel that brings in many tiles of one column block: the lane's byte offsets
-// within a tile are worked out once, and a tile that lies wholly inside the rows puts its first
-// row into the instruction's scalar offset (which takes no part in the range check, hence the
-// condition), so that a load costs no vector arithmetic; a ragged last tile takes tile_load().
+// Tiles of column blocks of one sample's rows, for a loop: the buffer ends with the sample's last row, so that rows
+// beyond it read as zeros without a comparison, and the column block goes into the instruction's scalar offset.
+// Instruction i of this wave's share of the tile that starts at byte row0_bytes = first row * row bytes.
 template <int ROWS, int NW>
-struct TileStream {
+struct RowStream {
   static constexpr int RPI = 64 / CPR, PER_WAVE = ROWS / RPI / NW;
   static_assert(PER_WAVE >= 1, "tile too small for the workgroup");
   unsigned voff[PER_WAVE];
-  GX_DEVINL void init(unsigned elem0, int ld, int wave, int lane) {
+  GX_DEVINL void init(int ld, int wave, int lane) {
 #pragma unroll
     for (int i = 0; i < PER_WAVE; i++) {
       const int r = RPI * (wave * PER_WAVE + i) + lane / CPR;
       const int c = (lane % CPR) ^ swz(r);
-      voff[i] = (elem0 + (unsigned)(r * ld + c * 8)) * 2u;
+      voff[i] = (unsigned)(r * ld + c * 8) * 2u;
     }
   }
-  GX_DEVINL void load(__amdgpu_buffer_rsrc_t rsrc, unsigned elem0, int ld, int row0, int nrows, char* dst, int wave,
-                      int lane) const {
-    if (row0 + ROWS <= nrows) {
-      const unsigned so = (unsigned)(row0 * ld) * 2u;
+  GX_DEVINL void issue(__amdgpu_buffer_rsrc_t rsrc, unsigned row0_bytes, int col_bytes, char* dst, int wave, int i) const {
+    const unsigned off = voff[i] + row0_bytes;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(dst + (wave * PER_WAVE + i) * 1024), 16, off,
+                                             col_bytes, 0, 0);
+  }
+  GX_DEVINL void load(__amdgpu_buffer_rsrc_t rsrc, unsigned row0_bytes, int col_bytes, char* dst, int wave) const {
 #pragma unroll
-      for (int i = 0; i < PER_WAVE; i++) {
-        unsigned off = voff[i];
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(dst + (wave * PER_WAVE + i) * 1024), 16, off,
-                                                 so, 0, 0);
-      }
-    } else {
-      tile_load<ROWS, NW>(rsrc, elem0, ld, row0, nrows, dst, wave, lane);
-    }
+    for (int i = 0; i < PER_WAVE; i++) issue(rsrc, row0_bytes, col_bytes, dst, wave, i);
   }
 };
 
@@ -127,6 +121,33 @@ GX_DEVINL f32x16 zero16() {
   return z;
 }
 
+template <class F, int... I>
+GX_DEVINL void unroll_seq(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+// f(0) .. f(N - 1) with the index as a constant
+template <int N, class F>
+GX_DEVINL void unroll(F&& f) {
+  unroll_seq(f, std::make_integer_sequence<int, N>());
+}
+
+// N products whose LDS fragments are requested DEPTH products ahead: read(i) returns fragment i, mul(i, f)
+// issues product i.  Left to itself the compiler asks for a fragment one product ahead.
+template <int N, int DEPTH, class Read, class Mul>
+GX_DEVINL void streamed(Read read, Mul mul) {
+  bf16x8 f[DEPTH];
+#pragma unroll
+  for (int i = 0; i < DEPTH && i < N; i++) f[i] = read(i);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < N; i++) {
+    mul(i, f[i % DEPTH]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (i + DEPTH < N) f[i % DEPTH] = read(i + DEPTH);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // this lane's 8 steps of a 32-row operand read straight from global memory (row clamped)
 GX_DEVINL void load_row_frags(const bf16* base, int ld, int row, int nrows, int g, bf16x8 (&out)[DH / 16]) {
   const bf16* p = base + (size_t)min(row, nrows - 1) * ld + 8 * g;
@@ -170,15 +191,14 @@ GX_DEVINL void tr_product(f32x16 (&acc)[DH / 32], unsigned ct, const unsigned (&
 // into LDS and wavefront (q, part) works on tile `part`; the SPLIT partial softmax states
 // (max, sum, O) of a row block are merged through LDS at the end, in the order of `part`.
 //   many (sample, head) pairs : NQ 4, SPLIT 1, BKV 64 (4 wavefronts, two workgroups per compute unit)
-//   few pairs                 : NQ 2, SPLIT 2, BKV 32 (4 wavefronts, two workgroups per compute unit;
-//     the forward pass in the kernel after this one): the causal triangle gives query blocks
-//     between 1 and S / 32 NQ units of work, so with few pairs the chip is filled by short blocks
-//     cut fine, each with its keys spread over two wavefronts.  Two independent workgroups per
-//     unit matter more than wavefronts per workgroup: the wavefronts of one workgroup pass every
-//     step's barrier together and are then all in the matrix pipe or all in the vector units at
-//     once, while two workgroups drift apart and fill each other's gaps.
-// Workgroups are numbered longest query block first over the whole launch (all pairs' last blocks,
-// then all pairs' next-to-last blocks, ...): the hardware hands them out in that order.
+//   few pairs                 : NQ 2, SPLIT 2, BKV 32 (the same), or NQ 2, SPLIT 4, BKV 32 (8 wavefronts, one workgroup
+//     per unit: see keys_over_four()): the causal triangle gives query blocks between 1 and S / 32 NQ
+//     units of work, so with few pairs the chip is filled by short blocks cut fine, each with its keys spread
+//     over two or four wavefronts.
+// Workgroups are numbered longest query block first over the whole launch (all pairs' last blocks, then all pairs'
+// next-to-last blocks, ...): the hardware hands them out in that order.  With SPLIT 2 the second half of the
+// launch runs shortest first: with two workgroups per compute unit and a launch of twice the number of units,
+// workgroups x and x + gridDim.x / 2 tend to share a unit, and their work then adds up to the same total.
 // Dropout of the probabilities: keep bits (1 = kept) of the whole launch, `wpr` 32-bit words per
 // row; row-major (a query's keys) for the forward and dQ kernels, column-major (a key's queries)
 // for the dK / dV kernel.  Kept probabilities are multiplied by `scale`.
@@ -208,50 +228,86 @@ GX_DEVINL unsigned long long keep_bits_of_step(const unsigned* row_words, int j0
 
 // End of a forward workgroup: merge the SPLIT partial softmax states of each row block through LDS
 // (the tiles are no longer needed), then normalise and store the block's rows of ctx and lse.
+constexpr int FWD_REGION = (4 + DH / 2) * 64;          // a wavefront's parked state, in floats
+// LDS: two buffers for K and two for V, or what the merge parks
+constexpr int fwd_smem(int nq, int split, int bkv) {
+  const int tiles = 4 * bkv * split * ROWB, parked = split > 1 ? nq * split * FWD_REGION * 4 : 0;
+  return tiles > parked ? tiles : parked;
+}
 template <int NQ, int SPLIT, bool DROP>
 GX_DEVINL void fwd_merge_store(char* smem, f32x16 (&o)[DH / 32], float m, float lsum, int part, int qs, int lane,
                                int iw, int b, int h, int S, int nl, bf16* __restrict__ ctx,
                                float* __restrict__ lse, const KeepArgs& keep) {
+  constexpr int NDT = DH / 32, OWN = NDT / SPLIT > 0 ? NDT / SPLIT : 1, OWNERS = NDT / OWN;
   const int g = lane >> 5, l32 = lane & 31;
   const int Hl = nl * DH;
-  if (SPLIT > 1) {
-    // merge the parts' partial softmax states; the tiles are no longer needed, so parts 1.. park
-    // (m, l, O) in LDS as [part - 1][row block][2 + DH / 2 values][64 lanes] and part 0 folds them
-    // in, in order.  A part that saw no key has m = -inf, l = 0, O = 0 and folds in as nothing
-    // (part 0 always saw key 0, so the merged maximum is finite).
-    constexpr int REGION = (2 + DH / 2) * 64;
-    if (part > 0) {
-      float* park = reinterpret_cast<float*>(smem) + ((part - 1) * NQ + qs) * REGION + lane;
-      park[0] = m;
-      park[64] = lsum;
-#pragma unroll
-      for (int dt = 0; dt < DH / 32; dt++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) park[(2 + 16 * dt + v) * 64] = o[dt][v];
-    }
-    __syncthreads();
-    if (part > 0) return;
-#pragma unroll
-    for (int pp = 1; pp < SPLIT; pp++) {
-      const float* park = reinterpret_cast<const float*>(smem) + ((pp - 1) * NQ + qs) * REGION + lane;
-      const float m1 = park[0], l1 = park[64];
-      const float mm = fmaxf(m, m1);
-      const float a0 = __builtin_amdgcn_exp2f(m - mm), a1 = __builtin_amdgcn_exp2f(m1 - mm);
-      lsum = lsum * a0 + l1 * a1;
-      m = mm;
-#pragma unroll
-      for (int dt = 0; dt < DH / 32; dt++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) o[dt][v] = o[dt][v] * a0 + park[(2 + 16 * dt + v) * 64] * a1;
-    }
-  }
   lsum += __shfl_xor(lsum, 32, 64);
+  // Part p finishes the head-dim blocks p * OWN ..: every part parks its maximum, sum and blocks in LDS (the tiles
+  // are no longer needed) as [row block][part][2 values, then blocks of 16 values][64 lanes], 16 B per lane and write.
+  // A part that saw no key has m = -inf, l = 0, O = 0 and counts for nothing (part 0 always saw key 0).
+  if constexpr (SPLIT > 1) {
+    constexpr int REGION = FWD_REGION;
+    float* mine = reinterpret_cast<float*>(smem) + (qs * SPLIT + part) * REGION;
+    *reinterpret_cast<f32x2*>(mine + lane * 4) = f32x2{m, lsum};
+#pragma unroll
+    for (int dt = 0; dt < NDT; dt++)
+#pragma unroll
+      for (int q = 0; q < 4; q++)
+        if (dt / OWN != part)
+          *reinterpret_cast<f32x4*>(mine + 256 + ((dt * 4 + q) * 64 + lane) * 4) =
+              f32x4{o[dt][4 * q], o[dt][4 * q + 1], o[dt][4 * q + 2], o[dt][4 * q + 3]};
+    __syncthreads();
+    if (part >= OWNERS) return;
+    const float* all = reinterpret_cast<const float*>(smem) + qs * SPLIT * REGION;
+    float mp[SPLIT], lp[SPLIT], mm = -INFINITY;
+#pragma unroll
+    for (int p = 0; p < SPLIT; p++) {
+      const f32x2 v = *reinterpret_cast<const f32x2*>(all + p * REGION + lane * 4);
+      mp[p] = v[0];
+      lp[p] = v[1];
+      mm = fmaxf(mm, mp[p]);
+    }
+    lsum = 0.f;
+#pragma unroll
+    for (int p = 0; p < SPLIT; p++) {
+      mp[p] = __builtin_amdgcn_exp2f(mp[p] - mm);
+      lsum += lp[p] * mp[p];
+    }
+    m = mm;
+    f32x16 t[OWN];
+#pragma unroll
+    for (int k = 0; k < OWN; k++) {
+      t[k] = zero16();
+#pragma unroll
+      for (int p = 0; p < SPLIT; p++) {
+        // this part's own share comes from its registers
+        f32x16 x;
+        if (p == part) {
+#pragma unroll
+          for (int dt = 0; dt < NDT; dt++)
+            if (dt == part * OWN + k) x = o[dt];
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; q++) {
+            const f32x4 v = *reinterpret_cast<const f32x4*>(all + p * REGION + 256 +
+                                                            (((part * OWN + k) * 4 + q) * 64 + lane) * 4);
+#pragma unroll
+            for (int e = 0; e < 4; e++) x[4 * q + e] = v[e];
+          }
+        }
+#pragma unroll
+        for (int v = 0; v < 16; v++) t[k][v] += x[v] * mp[p];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < OWN; k++) o[k] = t[k];
+  }
   const int i = iw + l32;
   if (i < S) {
     const float inv = (DROP ? keep.scale : 1.0f) / lsum;
-    bf16* orow = ctx + ((size_t)b * S + i) * Hl + h * DH;
+    bf16* orow = ctx + ((size_t)b * S + i) * Hl + h * DH + 32 * (SPLIT > 1 ? part * OWN : 0);
 #pragma unroll
-    for (int dt = 0; dt < DH / 32; dt++)
+    for (int dt = 0; dt < (SPLIT > 1 ? OWN : NDT); dt++)
 #pragma unroll
       for (int q4 = 0; q4 < 4; q4++) {
         bf16x4 pk;
@@ -259,283 +315,275 @@ GX_DEVINL void fwd_merge_store(char* smem, f32x16 (&o)[DH / 32], float m, float 
         for (int e = 0; e < 4; e++) pk[e] = (bf16)(o[dt][4 * q4 + e] * inv);
         *reinterpret_cast<bf16x4*>(orow + 32 * dt + 8 * q4 + 4 * g) = pk;
       }
-    if (g == 0) lse[((size_t)b * nl + h) * S + i] = (m + __builtin_amdgcn_logf(lsum)) * LN2;
+    if (g == 0 && part == 0) lse[((size_t)b * nl + h) * S + i] = (m + __builtin_amdgcn_logf(lsum)) * LN2;
   }
 }
 
-template <int NQ, int SPLIT, int BKV, bool DROP>
-__global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
+// What bounds it: a score costs 512 (DH 128) FLOP of matrix work, 1/64 of 32 cycles per 64 scores, and about nine issue
+// slots of 4 cycles of vector work (an exponential alone takes four), so neither pipe may wait for the other.  The
+// wavefronts of a SIMD do not take turns by themselves: they pass the same barrier, then want the same pipe.  So one
+// wavefront's stream mixes the two: in step t the products of the step before (O += V P, t - 1) and the
+// scores of the next one (S, t + 1) are issued one by one, and behind each goes its share of the softmax of step t, held in
+// that order by scheduling barriers and by pinning the results (else the exponentials sink to their use).
+// K and V have two buffers each: step t requests K(t + 2) where K(t) was and V(t) where V(t - 2) was, in its first four
+// or eight slots (later, the step's end waits for them; all at once, the wavefronts queue for the load unit).
+// LAZY: the reference maximum m follows the true one only when some row exceeds it by more than 2^8, so exponentials
+// stay below 2^8 and the rescaling of O (as many multiplies as a step's vector work has otherwise) becomes rare; any
+// reference gives the same softmax up to rounding, and lse = m + log2(l) holds for any m.  Without it m is the
+// running maximum itself, so that a row's largest probability is exactly 1 in bf16, which leaves outputs 0.1 to 1.5 %
+// nearer to the fp64 ones (64 pairs of S 2048).
+// Measured against one kernel without the mix (many pairs) and one with only the scores ahead (few), us: 64 pairs of
+// S 2048 88 -> 85, 64 of S 1024 32 -> 30, 4 of S 8192 101 -> 89, 8 of S 2048 26.9 -> 21.6, 16 of S 2048 30.1 -> 28.8,
+// 20 of S 2048 36.9 -> 34.8, 20 of S 128 6.8 -> 6.3; DH 64: 64 of S 1024 20.9 -> 18.9, 12 of S 1024 11.7 -> 9.9.  Deeper
+// rings (80 KB) leave one workgroup per unit: 64 pairs of S 2048 take twice as long.
+template <int NQ, int SPLIT, int BKV, bool LAZY, bool DROP>
+__global__ void __launch_bounds__(64 * NQ * SPLIT, 2)
     attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ ctx, float* __restrict__ lse, int S, int nl,
-                    int npair, unsigned qkv_bytes, KeepArgs keep) {
+                    int npair, KeepArgs keep) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  constexpr int NW = NQ * SPLIT, BQ = 32 * NQ, ROWS = BKV * SPLIT, STAGE = 2 * ROWS * ROWB;   // K rows | V rows
-  constexpr int NJT = BKV / 32;
+  constexpr int NW = NQ * SPLIT, BQ = 32 * NQ, ROWS = BKV * SPLIT, TILE = ROWS * ROWB, NS = DH / 16;
+  constexpr int NJT = BKV / 32, NG = 2 * NJT, NDT = DH / 32;
   static_assert((NQ & (NQ - 1)) == 0 && (BKV == 32 || BKV == 64), "shape of the step");
-  static_assert((SPLIT - 1) * NQ * (2 + DH / 2) * 256 <= 2 * STAGE, "merge area fits the tile buffers");
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int qs = wave % NQ, part = wave / NQ;
   const int g = lane >> 5, l32 = lane & 31;
   const int nq = (S + BQ - 1) / BQ;
   const int pair = blockIdx.x % npair;
-  const int qt = nq - 1 - blockIdx.x / npair;         // longest rows first
-  const int h = pair % nl, b = pair / nl;
-  const int Hl = nl * DH, ld = 3 * Hl;
-  const int i0 = qt * BQ, iw = i0 + qs * 32;          // this wave's first query row
-  const unsigned eq = (unsigned)((size_t)b * S * ld + h * DH);
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(qkv), 0, qkv_bytes,
-                                                                        0x00020000);
-  bf16x8 qf[DH / 16];
-  load_row_frags(qkv + eq, ld, iw + l32, S, g, qf);
-
-  f32x16 o[DH / 32];
-#pragma unroll
-  for (int dt = 0; dt < DH / 32; dt++) o[dt] = zero16();
-  float m = -INFINITY, lsum = 0.f;
-  const float c2 = rsqrtf((float)DH) * LOG2E;
-  unsigned coff[2][DH / 32];
-  cols_lane_offsets(lane, coff);
-
-  const int jend = min(S, i0 + BQ);                   // keys 0 .. jend-1 can be visible
-  const int nt = (jend + ROWS - 1) / ROWS;
-  TileStream<ROWS, NW> ksrc, vsrc;
-  ksrc.init(eq + Hl, ld, wave, lane);
-  vsrc.init(eq + 2 * Hl, ld, wave, lane);
-  ksrc.load(rsrc, eq + Hl, ld, 0, S, smem, wave, lane);
-  vsrc.load(rsrc, eq + 2 * Hl, ld, 0, S, smem + ROWS * ROWB, wave, lane);
-  WAIT_VM0();
-  __syncthreads();
-  for (int t = 0; t < nt; t++) {
-    if (t + 1 < nt) {
-      char* nxt = smem + ((t + 1) & 1) * STAGE;
-      ksrc.load(rsrc, eq + Hl, ld, (t + 1) * ROWS, S, nxt, wave, lane);
-      vsrc.load(rsrc, eq + 2 * Hl, ld, (t + 1) * ROWS, S, nxt + ROWS * ROWB, wave, lane);
-    }
-    const int j0 = t * ROWS + part * BKV;              // this wave's keys of the step
-    // wave-uniform; j0 and iw are multiples of 32, so when it holds every row of the wave sees key j0
-    if (j0 <= iw + 31) {
-      const char* kt = smem + (t & 1) * STAGE + part * BKV * ROWB;
-      const char* vt = kt + ROWS * ROWB;
-      unsigned long long kw = ~0ull;                    // keep bits of this query's keys of the step
-      if (DROP && iw + l32 < S)
-        kw = keep_bits_of_step<NJT>(keep.bits + (((size_t)b * nl + h) * S + iw + l32) * keep.wpr, j0);
-      f32x16 sacc[NJT];
-#pragma unroll
-      for (int jt = 0; jt < NJT; jt++) {
-        sacc[jt] = zero16();
-#pragma unroll
-        for (int s = 0; s < DH / 16; s++) sacc[jt] = MFMA(frag_rows(kt, 32 * jt + l32, s, g), qf[s], sacc[jt]);
-      }
-      // transposed V fragments of the first 32 keys travel while the softmax runs
-      const unsigned ct = lds_addr(vt);
-      ColFrags cf[2];
-      cols_issue<0>(ct, coff, cf[0]);
-      cols_issue<1>(ct, coff, cf[1]);
-      // online softmax for query column i = iw + l32 (base-2 exponentials, scale folded into the
-      // exponent's multiply-add)
-      const int i = iw + l32;
-      if (j0 + BKV - 1 > iw) {                         // the tile touches the diagonal
-#pragma unroll
-        for (int jt = 0; jt < NJT; jt++)
-#pragma unroll
-          for (int v = 0; v < 16; v++)
-            if (j0 + 32 * jt + 8 * (v >> 2) + 4 * g + (v & 3) > i) sacc[jt][v] = -INFINITY;
-      }
-      float mloc = sacc[0][0];
-#pragma unroll
-      for (int jt = 0; jt < NJT; jt++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) mloc = fmaxf(mloc, sacc[jt][v]);
-      mloc = max_across_halves(mloc) * c2;
-      // The reference is the running maximum itself, so that a row's largest probability is exactly 1 in
-      // bf16.  Letting it lag by up to 8 powers of 2 is faster (64 pairs of S 2048: 86 us against 92) but leaves
-      // the output 0.1 to 1.5 % further from the fp64 one.
-      const float mnew = fmaxf(m, mloc);
-      if (__builtin_amdgcn_ballot_w64(mnew > m)) {     // wave-uniform: some row's running max moved
-        const float alpha = __builtin_amdgcn_exp2f(m - mnew);
-        m = mnew;
-        lsum *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < DH / 32; dt++)
-#pragma unroll
-          for (int v = 0; v < 16; v++) o[dt][v] *= alpha;
-      }
-      float psum = 0.f;
-#pragma unroll
-      for (int jt = 0; jt < NJT; jt++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) {
-          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[jt][v], c2, -m));
-          sacc[jt][v] = p;
-          psum += p;
-        }
-      lsum += psum;
-      if (DROP) drop_unkept<NJT>(sacc, kw, g);         // the row sum above is the undropped one
-      // O^T += V^T P^T, 16 keys per group
-      bf16x8 pf[2 * NJT];
-#pragma unroll
-      for (int u = 0; u < 2 * NJT; u++) pf[u] = pack_half(sacc[u >> 1], u & 1);
-      tr_product<true, 2 * NJT>(o, ct, coff, cf, pf);
-    }
-    WAIT_VM0();
-    __syncthreads();
-  }
-  fwd_merge_store<NQ, SPLIT, DROP>(smem, o, m, lsum, part, qs, lane, iw, b, h, S, nl, ctx, lse, keep);
-}
-
-// The split-key shape of the forward pass with the scores one step ahead: while the softmax of step
-// t runs on the vector units, the same wavefront's matrix instructions already compute the scores
-// of step t + 1 (one matrix instruction, then a share of the softmax, kept in that order by
-// scheduling barriers).  The two wavefronts of a SIMD pass the workgroup barrier together and so
-// are in the same phase of a step at the same time; without the interleave inside a wavefront the
-// matrix pipe idles through both softmaxes and the vector units through both score products.
-// K and V have separate double buffers because K runs a step ahead of V: at the top of step t,
-// K(t + 2) goes into the buffer of K(t) (its scores were taken during step t - 1) and V(t + 1)
-// into the buffer of V(t - 1).
-template <int NQ, int SPLIT, bool DROP>
-__global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
-    attn_fwd_ahead_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ ctx, float* __restrict__ lse, int S,
-                          int nl, int npair, unsigned qkv_bytes, KeepArgs keep) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  constexpr int NW = NQ * SPLIT, BQ = 32 * NQ, BKV = 32, ROWS = BKV * SPLIT, TILE = ROWS * ROWB, NS = DH / 16;
-  static_assert((NQ & (NQ - 1)) == 0 && SPLIT > 1, "shape of the step");
-  static_assert((SPLIT - 1) * NQ * (2 + DH / 2) * 256 <= 4 * TILE, "merge area fits the tile buffers");
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int qs = wave % NQ, part = wave / NQ;
-  const int g = lane >> 5, l32 = lane & 31;
-  const int nq = (S + BQ - 1) / BQ;
-  const int pair = blockIdx.x % npair;
-  // First half of the launch: longest blocks first; second half: shortest first.  With two
-  // workgroups per compute unit and a launch of twice the number of units, workgroups x and
-  // x + gridDim.x / 2 tend to share a unit, and their causal work then adds up to the same total.
   const int rq = blockIdx.x / npair, hq = (nq + 1) / 2;
-  const int qt = rq < hq ? nq - 1 - rq : rq - hq;
+  const int qt = (SPLIT != 2 || rq < hq) ? nq - 1 - rq : rq - hq;
   const int h = pair % nl, b = pair / nl;
   const int Hl = nl * DH, ld = 3 * Hl;
   const int i0 = qt * BQ, iw = i0 + qs * 32;          // this wave's first query row
-  const unsigned eq = (unsigned)((size_t)b * S * ld + h * DH);
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(qkv), 0, qkv_bytes,
-                                                                        0x00020000);
+  const bf16* sample = qkv + (size_t)b * S * ld;
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(sample), 0,
+                                                                        (unsigned)(S * ld) * 2u, 0x00020000);
   bf16x8 qf[NS];
-  load_row_frags(qkv + eq, ld, iw + l32, S, g, qf);
+  load_row_frags(sample + h * DH, ld, iw + l32, S, g, qf);
 
-  f32x16 o[DH / 32];
+  f32x16 o[NDT];
 #pragma unroll
-  for (int dt = 0; dt < DH / 32; dt++) o[dt] = zero16();
+  for (int dt = 0; dt < NDT; dt++) o[dt] = zero16();
   float m = -INFINITY, lsum = 0.f;
   const float c2 = rsqrtf((float)DH) * LOG2E;
-  constexpr float MAX_SLACK = 8.0f;
-  unsigned coff[2][DH / 32];
+  unsigned coff[2][NDT];
   cols_lane_offsets(lane, coff);
 
   char* const kst = smem;                             // K(t) at kst + (t & 1) * TILE
   char* const vst = smem + 2 * TILE;                  // V(t) at vst + (t & 1) * TILE
   const int jend = min(S, i0 + BQ);                   // keys 0 .. jend-1 can be visible
   const int nt = (jend + ROWS - 1) / ROWS;
-  TileStream<ROWS, NW> ksrc, vsrc;
-  ksrc.init(eq + Hl, ld, wave, lane);
-  vsrc.init(eq + 2 * Hl, ld, wave, lane);
-  ksrc.load(rsrc, eq + Hl, ld, 0, S, kst, wave, lane);
-  vsrc.load(rsrc, eq + 2 * Hl, ld, 0, S, vst, wave, lane);
-  if (nt > 1) ksrc.load(rsrc, eq + Hl, ld, ROWS, S, kst + TILE, wave, lane);
+  RowStream<ROWS, NW> src;
+  constexpr int PER = RowStream<ROWS, NW>::PER_WAVE;
+  src.init(ld, wave, lane);
+  const int kcol = (Hl + h * DH) * 2, vcol = (2 * Hl + h * DH) * 2;
+  const unsigned tile_bytes = (unsigned)(ROWS * ld) * 2u, none = (unsigned)(S * ld) * 2u;   // none: nothing but zeros
+  src.load(rsrc, 0, kcol, kst, wave);
+  src.load(rsrc, 0, vcol, vst, wave);
+  src.load(rsrc, nt > 1 ? tile_bytes : none, kcol, kst + TILE, wave);
+  const unsigned* kwords = DROP ? keep.bits + (((size_t)b * nl + h) * S + min(iw + l32, S - 1)) * keep.wpr : nullptr;
+  auto keep_of = [&](int t) -> unsigned long long {
+    const int j = t * ROWS + part * BKV;
+    return j <= iw + 31 && j < S ? keep_bits_of_step<NJT>(kwords, j) : 0ull;
+  };
+  unsigned long long kw = 0, kw_next = 0;
+  if (DROP) kw_next = keep_of(0);
   WAIT_VM0();
   __syncthreads();
-  // scores of step 0; a wavefront's keys of a step are visible when the step's first key is at or
-  // before the wavefront's last row (wave-uniform; both are multiples of 32 up to the 31)
-  f32x16 s_even = zero16(), s_odd;
+  f32x16 s_even[NJT], s_odd[NJT];                     // scores of an even and an odd step
+#pragma unroll
+  for (int jt = 0; jt < NJT; jt++) s_even[jt] = zero16();
   if (part * BKV <= iw + 31) {
     const char* k0 = kst + part * BKV * ROWB;
-#pragma unroll
-    for (int s = 0; s < NS; s++) s_even = MFMA(frag_rows(k0, l32, s, g), qf[s], s_even);
+    streamed<NJT * NS, 4>([&](int q) { return frag_rows(k0, 32 * (q / NS) + l32, q % NS, g); },
+                          [&](int q, bf16x8 f) { s_even[q / NS] = MFMA(f, qf[q % NS], s_even[q / NS]); });
   }
-  __syncthreads();          // step 0 requests K(2) into the buffer that every wavefront has just read K(0) from
-  // one step: `sacc` holds the scores of step t on entry, `snxt` those of step t + 1 on exit
-  auto step = [&](int t, f32x16& sacc, f32x16& snxt) __attribute__((always_inline)) {
-    if (t + 2 < nt) ksrc.load(rsrc, eq + Hl, ld, (t + 2) * ROWS, S, kst + (t & 1) * TILE, wave, lane);
-    if (t + 1 < nt) vsrc.load(rsrc, eq + 2 * Hl, ld, (t + 1) * ROWS, S, vst + ((t + 1) & 1) * TILE, wave, lane);
+  __syncthreads();                                    // K(2) goes into the buffer of K(0)
+  bf16x8 pf[NG];                                      // P of the step before, 16 keys per entry
+  struct VFrag { bf16x4 lo, hi; };
+  auto v_request = [&](unsigned vt, auto P, VFrag& f) __attribute__((always_inline)) {
+    constexpr int p = decltype(P)::value, dt = p / NG, u = p % NG;
+    f.lo = lds_read_tr_issue<u * 16 * ROWB>(vt + coff[0][dt]);
+    f.hi = lds_read_tr_issue<u * 16 * ROWB>(vt + coff[1][dt]);
+  };
+  auto v_get = [&](VFrag& f) __attribute__((always_inline)) {
+    lds_pin(f.lo);
+    lds_pin(f.hi);
+    return __builtin_shufflevector(f.lo, f.hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  constexpr int NPV = NG * NDT, NSC = NJT * NS, VD = 4 < NPV ? 4 : NPV, KD = 4 < NSC ? 4 : NSC;
+  auto flush = [&](unsigned vt) __attribute__((always_inline)) {       // O^T += V^T P^T of the step before, on its own
+    VFrag vf[VD];
+    unroll<VD>([&](auto P) __attribute__((always_inline)) { v_request(vt, P, vf[P]); });
+    unroll<NPV>([&](auto P) __attribute__((always_inline)) {
+      constexpr int p = decltype(P)::value, newer = 2 * ((p + VD < NPV ? p + VD : NPV) - p - 1);
+      lds_wait_le<newer>();
+      o[p / NG] = MFMA(v_get(vf[p % VD]), pf[p % NG], o[p / NG]);
+      if constexpr (p + VD < NPV) v_request(vt, std::integral_constant<int, p + VD>(), vf[p % VD]);
+    });
+  };
+  // this wave's steps with a visible key are 0 .. tv - 1 (wave-uniform)
+  const int ahead = iw + 31 - part * BKV, tv = ahead < 0 ? 0 : min(nt, ahead / ROWS + 1);
+  // request i of a step: first its share of K(t + 2), then of V(t)
+  auto request = [&](int t, int i) __attribute__((always_inline)) {
+    if (i < PER) src.issue(rsrc, t + 2 < nt ? (unsigned)(t + 2) * tile_bytes : none, kcol, kst + (t & 1) * TILE, wave, i);
+    else src.issue(rsrc, (unsigned)t * tile_bytes, vcol, vst + (t & 1) * TILE, wave, i - PER);
+  };
+  auto meet = [&]() __attribute__((always_inline)) {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  };
+  auto step = [&](int t, f32x16 (&sacc)[NJT], f32x16 (&snxt)[NJT], auto first_tag) __attribute__((always_inline)) {
+    constexpr bool FIRST = decltype(first_tag)::value;
+    if (DROP) {
+      kw = kw_next;
+      kw_next = keep_of(t + 1);
+    }
     const int j0 = t * ROWS + part * BKV;              // this wave's keys of the step
-    if (j0 <= iw + 31) {
-      // Scores of the next step are always taken, also when that step does not exist or is not
-      // visible to this wavefront: the buffer then holds an older tile (or nothing yet), the
-      // products are never looked at, and the loop body stays free of a second code path.
+    const unsigned vt = lds_addr(vst + ((t - 1) & 1) * TILE + part * BKV * ROWB);
+    {
       const char* kn = kst + ((t + 1) & 1) * TILE + part * BKV * ROWB;
-      const char* vt = vst + (t & 1) * TILE + part * BKV * ROWB;
-      unsigned long long kw = ~0ull;                    // keep bits of this query's keys of the step
-      if (DROP && iw + l32 < S)
-        kw = keep_bits_of_step<1>(keep.bits + (((size_t)b * nl + h) * S + iw + l32) * keep.wpr, j0);
-      bf16x8 kf[NS];
+      constexpr int NP = FIRST ? 0 : NPV, NM = NP + NSC, RS = NM / 4;
+      constexpr int NREQ = FIRST ? PER : 2 * PER;      // V(0) came with K(0)
+      VFrag vf[VD];
+      bf16x8 kf[KD];
+      if constexpr (!FIRST) unroll<VD>([&](auto P) __attribute__((always_inline)) { v_request(vt, P, vf[P]); });
+      if constexpr (FIRST) {
 #pragma unroll
-      for (int s = 0; s < NS; s++) kf[s] = frag_rows(kn, l32, s, g);
-      snxt = zero16();
+        for (int q = 0; q < KD; q++) kf[q] = frag_rows(kn, 32 * (q / NS) + l32, q % NS, g);
+      }
+#pragma unroll
+      for (int jt = 0; jt < NJT; jt++) snxt[jt] = zero16();
       const int i = iw + l32;
-      float psum = 0.f;
-      // the softmax of step t for query column i (base-2 exponentials, scale folded into the
-      // exponent's multiply-add), cut into pieces
-      auto piece = [&](int k) __attribute__((always_inline)) {
-        if (k == 0) {
+      float psum = 0.f, alpha = 1.f;
+      bool moved = false;
+      // the softmax of step t for query column i (base-2 exponentials, scale folded into the exponent's multiply-add)
+      // in pieces: 0 mask, 1 reference, then EPP scores each, a head-dim block of O to rescale each, 16 keys to round each
+      constexpr int EPP = 2;
+      constexpr int NE = 16 * NJT / EPP, P_E = 2, P_R = P_E + NE, P_P = P_R + NDT, NPIECE = P_P + NG;
+      auto piece = [&](auto K) __attribute__((always_inline)) {
+        constexpr int k = decltype(K)::value;
+        if constexpr (k == 0) {
           if (j0 + BKV - 1 > iw) {                     // the tile touches the diagonal
 #pragma unroll
-            for (int v = 0; v < 16; v++)
-              if (j0 + 8 * (v >> 2) + 4 * g + (v & 3) > i) sacc[v] = -INFINITY;
-          }
-        } else if (k == 1) {
-          float mloc = sacc[0];
+            for (int jt = 0; jt < NJT; jt++)
 #pragma unroll
-          for (int v = 1; v < 16; v++) mloc = fmaxf(mloc, sacc[v]);
+              for (int v = 0; v < 16; v++)
+                if (j0 + 32 * jt + 8 * (v >> 2) + 4 * g + (v & 3) > i) sacc[jt][v] = -INFINITY;
+          }
+        } else if constexpr (k == 1) {
+          float mloc = sacc[0][0];
+#pragma unroll
+          for (int jt = 0; jt < NJT; jt++)
+#pragma unroll
+            for (int v = 0; v < 16; v++) mloc = fmaxf(mloc, sacc[jt][v]);
           mloc = max_across_halves(mloc) * c2;
-          // The reference maximum m follows the true one lazily: it moves only when some row's new
-          // maximum exceeds it by more than MAX_SLACK (wave-uniform), so exponentials stay below
-          // 2^MAX_SLACK and the rescaling of O, four multiplies per score, becomes rare.  Any
-          // reference gives the same softmax up to rounding; lse = m + log2(l) is exact for any m.
-          if (__builtin_amdgcn_ballot_w64(mloc > m + MAX_SLACK)) {
-            const float mnew = fmaxf(m, mloc);
-            const float alpha = __builtin_amdgcn_exp2f(m - mnew);
-            m = mnew;
-            lsum *= alpha;
-#pragma unroll
-            for (int dt = 0; dt < DH / 32; dt++)
-#pragma unroll
-              for (int v = 0; v < 16; v++) o[dt][v] *= alpha;
+          float mnew = fmaxf(m, mloc);
+          if (LAZY) {
+            moved = __builtin_amdgcn_ballot_w64(mloc > m + 8.f) != 0;
+            mnew = moved ? mnew : m;
           }
-        } else if (k >= 2 && k < 6) {
+          alpha = __builtin_amdgcn_exp2f(m - mnew);
+          m = mnew;
+          lsum *= alpha;
+          asm volatile("" : "+v"(m), "+v"(alpha));
+        } else if constexpr (k < P_R) {
+          constexpr int e = EPP * (k - P_E), jt = e / 16, v0 = e % 16;
 #pragma unroll
-          for (int v = 4 * (k - 2); v < 4 * (k - 2) + 4; v++) {
-            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[v], c2, -m));
-            sacc[v] = p;
+          for (int v = v0; v < v0 + EPP; v++) {
+            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[jt][v], c2, -m));
+            sacc[jt][v] = p;
             psum += p;
           }
+          asm volatile("" : "+v"(psum));
+        } else if constexpr (k < P_P) {
+          constexpr int dt = k - P_R;
+          if constexpr (!LAZY && !FIRST) {
+#pragma unroll
+            for (int v = 0; v < 16; v++) o[dt][v] *= alpha;
+            asm volatile("" : "+v"(o[dt]));
+          } else if constexpr (LAZY && !FIRST && dt == 0) {
+            if (moved) {
+#pragma unroll
+              for (int d = 0; d < NDT; d++)
+#pragma unroll
+                for (int v = 0; v < 16; v++) o[d][v] *= alpha;
+            }
+          }
+        } else {
+          constexpr int u = k - P_P;
+          if constexpr (DROP && u == 0) {
+            lsum += psum;
+            drop_unkept<NJT>(sacc, kw, g);
+          }
+          pf[u] = pack_half(sacc[u >> 1], u & 1);
         }
       };
+      // cost of the pieces in issue slots, for spreading them over the matrix instructions
+      constexpr auto cost = [](int k) constexpr {
+        return k == 0 ? 4 : k == 1 ? 12 + 8 * NJT : k < P_R ? 6 * EPP : k < P_P ? (LAZY ? 1 : 16) : 4;
+      };
+      constexpr auto upto = [cost](int k) constexpr { int c = 0; for (int x = 0; x < k; x++) c += cost(x); return c; };
+      constexpr int TOTAL = upto(NPIECE);
+      // piece k goes behind matrix instruction slot_of(k); rescaling behind the last product into O
+      constexpr auto slot_of = [upto, cost](int k) constexpr {
+        int sl = (upto(k) + cost(k) / 2) * NM / TOTAL;
+        if (k >= P_R && sl < NP) sl = NP;
+        return sl < NM ? sl : NM - 1;
+      };
       __builtin_amdgcn_sched_barrier(0);
+      piece(std::integral_constant<int, 0>());
+      unroll<NM>([&](auto I) __attribute__((always_inline)) {
+        constexpr int x = decltype(I)::value;
+        if constexpr (x < NP) {
+          // untracked reads younger than this product's, and the K fragments requested so far
+          constexpr int newer = 2 * ((x + VD < NPV ? x + VD : NPV) - x - 1) + (x > NPV - KD ? x - (NPV - KD) : 0);
+          lds_wait_le<newer>();
+          o[x / NG] = MFMA(v_get(vf[x % VD]), pf[x % NG], o[x / NG]);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (x + VD < NPV) v_request(vt, std::integral_constant<int, x + VD>(), vf[x % VD]);
+          if constexpr (x >= NPV - KD) {
+            constexpr int q = x - (NPV - KD);
+            kf[q] = frag_rows(kn, 32 * (q / NS) + l32, q % NS, g);
+          }
+        } else {
+          constexpr int q = x - NP;
+          snxt[q / NS] = MFMA(kf[q % KD], qf[q % NS], snxt[q / NS]);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (q + KD < NSC) kf[q % KD] = frag_rows(kn, 32 * ((q + KD) / NS) + l32, (q + KD) % NS, g);
+        }
 #pragma unroll
-      for (int s = 0; s < NS; s++) {
-        snxt = MFMA(kf[s], qf[s], snxt);
+        for (int i = x * NREQ / RS; i < (x + 1) * NREQ / RS && i < NREQ; i++) request(t, i);
+        unroll<NPIECE>([&](auto K) __attribute__((always_inline)) {
+          if constexpr (decltype(K)::value > 0 && slot_of(decltype(K)::value) == x) piece(K);
+        });
         __builtin_amdgcn_sched_barrier(0);
+      });
+      if (!DROP) lsum += psum;
+      // also where no step follows: the waits above count the reads of these products
 #pragma unroll
-        for (int k = 0; k < 8; k++)
-          if (k * NS / 8 == s) piece(k);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      // transposed V fragments travel while the probabilities are rounded
-      const unsigned ct = lds_addr(vt);
-      ColFrags cf[2];
-      cols_issue<0>(ct, coff, cf[0]);
-      cols_issue<1>(ct, coff, cf[1]);
-      lsum += psum;
-      f32x16 pacc[1] = {sacc};
-      if (DROP) drop_unkept<1>(pacc, kw, g);           // the row sum above is the undropped one
-      // O^T += V^T P^T, 16 keys per group
-      bf16x8 pf[2];
-#pragma unroll
-      for (int u = 0; u < 2; u++) pf[u] = pack_half(pacc[0], u);
-      tr_product<true, 2>(o, ct, coff, cf, pf);
+      for (int jt = 0; jt < NJT; jt++) asm volatile("" : "+v"(snxt[jt]));
     }
-    WAIT_VM0();
-    __syncthreads();
+    meet();
   };
-  for (int t = 0; t < nt; t += 2) {
-    step(t, s_even, s_odd);
-    if (t + 1 < nt) step(t + 1, s_odd, s_even);
+  int t = 0;
+  if (tv > 0) {
+    step(0, s_even, s_odd, std::true_type());
+    for (t = 1; t + 1 < tv; t += 2) {
+      step(t, s_odd, s_even, std::false_type());
+      step(t + 1, s_even, s_odd, std::false_type());
+    }
+    if (t < tv) {
+      step(t, s_odd, s_even, std::false_type());
+      t++;
+    }
+    flush(lds_addr(vst + ((t - 1) & 1) * TILE + part * BKV * ROWB));
   }
+  for (; t < nt; t++) {                               // what the other wavefronts still need
+#pragma unroll
+    for (int i = 0; i < 2 * PER; i++)
+      if (i < PER || t > 0) request(t, i);
+    meet();
+  }
+  if (SPLIT > 1) __syncthreads();                     // the merge reuses the tile buffers
   fwd_merge_store<NQ, SPLIT, DROP>(smem, o, m, lsum, part, qs, lane, iw, b, h, S, nl, ctx, lse, keep);
 }
 
@@ -806,7 +854,7 @@ template <int NQ, int SPLIT, int BKV, bool DROP>
 __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
     attn_bwd_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dctx, const float* __restrict__ lse,
                        const float* __restrict__ dsum, bf16* __restrict__ dqkv, int S, int nl, int npair,
-                       unsigned qkv_bytes, KeepArgs keep) {
+                       KeepArgs keep) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int NW = NQ * SPLIT, BQ = 32 * NQ, ROWS = BKV * SPLIT, STAGE = 2 * ROWS * ROWB;
   constexpr int NJT = BKV / 32;
@@ -823,11 +871,11 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
   const int h = pair % nl, b = pair / nl;
   const int Hl = nl * DH, ld = 3 * Hl;
   const int i0 = qt * BQ, iw = i0 + qs * 32;
-  const unsigned eq = (unsigned)((size_t)b * S * ld + h * DH);
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(qkv), 0, qkv_bytes,
-                                                                        0x00020000);
+  const bf16* sample = qkv + (size_t)b * S * ld;
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(sample), 0,
+                                                                        (unsigned)(S * ld) * 2u, 0x00020000);
   bf16x8 qf[DH / 16], dof[DH / 16];
-  load_row_frags(qkv + eq, ld, iw + l32, S, g, qf);
+  load_row_frags(sample + h * DH, ld, iw + l32, S, g, qf);
   load_row_frags(dctx + (size_t)b * S * Hl + h * DH, Hl, iw + l32, S, g, dof);
   const int i = iw + l32;
   const int ic = min(i, S - 1);
@@ -842,18 +890,19 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
 
   const int jend = min(S, i0 + BQ);
   const int nt = (jend + ROWS - 1) / ROWS;
-  TileStream<ROWS, NW> ksrc, vsrc;
-  ksrc.init(eq + Hl, ld, wave, lane);
-  vsrc.init(eq + 2 * Hl, ld, wave, lane);
-  ksrc.load(rsrc, eq + Hl, ld, 0, S, smem, wave, lane);
-  vsrc.load(rsrc, eq + 2 * Hl, ld, 0, S, smem + ROWS * ROWB, wave, lane);
+  RowStream<ROWS, NW> src;
+  src.init(ld, wave, lane);
+  const int kcol = (Hl + h * DH) * 2, vcol = (2 * Hl + h * DH) * 2;
+  const unsigned tile_bytes = (unsigned)(ROWS * ld) * 2u;
+  src.load(rsrc, 0, kcol, smem, wave);
+  src.load(rsrc, 0, vcol, smem + ROWS * ROWB, wave);
   WAIT_VM0();
   __syncthreads();
   for (int t = 0; t < nt; t++) {
     if (t + 1 < nt) {
       char* nxt = smem + ((t + 1) & 1) * STAGE;
-      ksrc.load(rsrc, eq + Hl, ld, (t + 1) * ROWS, S, nxt, wave, lane);
-      vsrc.load(rsrc, eq + 2 * Hl, ld, (t + 1) * ROWS, S, nxt + ROWS * ROWB, wave, lane);
+      src.load(rsrc, (unsigned)(t + 1) * tile_bytes, kcol, nxt, wave);
+      src.load(rsrc, (unsigned)(t + 1) * tile_bytes, vcol, nxt + ROWS * ROWB, wave);
     }
     const int j0 = t * ROWS + part * BKV;
     if (j0 <= iw + 31) {
@@ -957,36 +1006,51 @@ bool attn_shape_ok(const AttnArgs& a) {
 // each block's keys over two wavefronts (see the forward kernel).
 bool few_pairs(const AttnArgs& a) { return (long)a.B * a.nl * cdiv(a.S, 128) <= 384; }
 
-// row-block kernels (forward, dQ) in their two shapes, <4, 1, 64> and <2, 2, 32>: both 4 wavefronts
+// Few pairs, forward: the keys of a step over four wavefronts instead of two where the workgroups of 64 query rows
+// then still find a compute unit each, or are at most two per unit and so long that a unit's two would spend most of
+// their time one after the other (a long and a short one together).  Each has a longer start and end, so the keys
+// must be many.  us, two / four: 12 pairs of S 1024 14.7 / 14.0, of S 512 10.0 / 10.5, 12 of S 2048 27.9 / 25.9,
+// 16 of S 2048 28.1 / 28.9, 8 of S 4096 50.1 / 46.6, 4 of S 8192 108 / 87.
+bool keys_over_four(const AttnArgs& a) {
+  const long blocks = (long)a.B * a.nl * cdiv(a.S, 64);
+  return a.S >= 768 && (blocks <= 256 || (blocks <= 512 && a.S > 4 * blocks));
+}
+
+// row-block kernels (dQ) in their two shapes, <4, 1, 64> and <2, 2, 32>: both 4 wavefronts
 // and two stages of 64 rows of K and of V
 constexpr int SMEM_MANY = 2 * 2 * 64 * ROWB, SMEM_FEW = 2 * 2 * 64 * ROWB;
 
 hipError_t fwd(const AttnArgs& a, hipStream_t s) {
   if (!attn_shape_ok(a)) return hipErrorInvalidValue;
   static bool configured = false;
+  constexpr int SMEM_MANY_FWD = fwd_smem(4, 1, 64), SMEM_TWO = fwd_smem(2, 2, 32), SMEM_FOUR = fwd_smem(2, 4, 32);
   if (!configured) {
-    hipError_t e = set_smem(attn_fwd_kernel<4, 1, 64, false>, SMEM_MANY);
-    if (e == hipSuccess) e = set_smem(attn_fwd_ahead_kernel<2, 2, false>, SMEM_FEW);
-    if (e == hipSuccess) e = set_smem(attn_fwd_kernel<4, 1, 64, true>, SMEM_MANY);
-    if (e == hipSuccess) e = set_smem(attn_fwd_ahead_kernel<2, 2, true>, SMEM_FEW);
+    hipError_t e = set_smem(attn_fwd_kernel<4, 1, 64, false, false>, SMEM_MANY_FWD);
+    if (e == hipSuccess) e = set_smem(attn_fwd_kernel<2, 2, 32, true, false>, SMEM_TWO);
+    if (e == hipSuccess) e = set_smem(attn_fwd_kernel<2, 4, 32, true, false>, SMEM_FOUR);
+    if (e == hipSuccess) e = set_smem(attn_fwd_kernel<4, 1, 64, false, true>, SMEM_MANY_FWD);
+    if (e == hipSuccess) e = set_smem(attn_fwd_kernel<2, 2, 32, true, true>, SMEM_TWO);
+    if (e == hipSuccess) e = set_smem(attn_fwd_kernel<2, 4, 32, true, true>, SMEM_FOUR);
     if (e != hipSuccess) return e;
     configured = true;
   }
-  const unsigned qkv_bytes = (unsigned)((size_t)a.B * a.S * 3 * a.nl * DH * 2);
   const KeepArgs keep{a.rowbits, a.wpr, a.keep_scale};
   const bool drop = a.rowbits != nullptr;
   if (drop && a.wpr != 2 * cdiv(a.S, 64)) return hipErrorInvalidValue;
   const int npair = a.nl * a.B;
   auto go = [&](auto kernel, int bq, int threads, int smem) {
     hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, bq) * npair), dim3(threads), smem, s, (const bf16*)a.qkv, (bf16*)a.ctx,
-                       a.lse, a.S, a.nl, npair, qkv_bytes, keep);
+                       a.lse, a.S, a.nl, npair, keep);
   };
-  if (few_pairs(a)) {
-    if (drop) go(attn_fwd_ahead_kernel<2, 2, true>, 64, 256, SMEM_FEW);
-    else go(attn_fwd_ahead_kernel<2, 2, false>, 64, 256, SMEM_FEW);
+  if (!few_pairs(a)) {
+    if (drop) go(attn_fwd_kernel<4, 1, 64, false, true>, 128, 256, SMEM_MANY_FWD);
+    else go(attn_fwd_kernel<4, 1, 64, false, false>, 128, 256, SMEM_MANY_FWD);
+  } else if (keys_over_four(a)) {
+    if (drop) go(attn_fwd_kernel<2, 4, 32, true, true>, 64, 512, SMEM_FOUR);
+    else go(attn_fwd_kernel<2, 4, 32, true, false>, 64, 512, SMEM_FOUR);
   } else {
-    if (drop) go(attn_fwd_kernel<4, 1, 64, true>, 128, 256, SMEM_MANY);
-    else go(attn_fwd_kernel<4, 1, 64, false>, 128, 256, SMEM_MANY);
+    if (drop) go(attn_fwd_kernel<2, 2, 32, true, true>, 64, 256, SMEM_TWO);
+    else go(attn_fwd_kernel<2, 2, 32, true, false>, 64, 256, SMEM_TWO);
   }
   return hipGetLastError();
 }
@@ -1026,7 +1090,7 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s) {
   const int npair = a.nl * a.B;
   auto go_dq = [&](auto kernel, int bq, int threads, int smem) {
     hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, bq) * npair), dim3(threads), smem, s, (const bf16*)a.qkv,
-                       (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, npair, qkv_bytes, keep_rows);
+                       (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, npair, keep_rows);
   };
   if (few_pairs(a)) {
     if (drop) go_dq(attn_bwd_dq_kernel<2, 2, 32, true>, 64, 256, SMEM_FEW);
