@@ -8,8 +8,9 @@
 // stages, one barrier per stage.  A matrix instruction holds the pipe for 64 cycles and needs one
 // or two LDS reads, so the matrix pipe is the bound as soon as every SIMD has a wavefront with data:
 // the tile is chosen to give the chip enough wavefronts, not to save LDS traffic.  Against a 64 x 64
-// tile of scalar multiply-adds: 256 x 256 x 1024 60 -> 9 us, 1024 x 1024 x 4096 (NT) 240 -> 76 us.
+// tile of scalar multiply-adds: 256 x 256 x 1024 60 -> 9 us, 1024 x 1024 x 4096 (NT) 240 -> 70 us.
 #include "gx_kernels.h"
+#include <type_traits>
 
 namespace gx {
 namespace {
@@ -92,37 +93,71 @@ __global__ void __launch_bounds__(BM * BM * KW / 16) gemm_f32_kernel(GemmArgs g)
   for (int v = 0; v < 16; v++) acc[v] = 0.f;
 
   constexpr int LPT = la.PER + lb.PER;                  // loads per wavefront and stage
-  static_assert((STAGES - 2) * LPT < 64, "vmcnt immediate");
+  static_assert((STAGES - 1) * LPT < 64, "vmcnt immediate");
+  constexpr bool AHEAD = BM > 32;                       // with a few stages in all the extra start costs more than it saves
   const int nk = (g.K + 32 * KW - 1) / (32 * KW);
-#pragma unroll
-  for (int t = 0; t < STAGES - 1; t++) {                // stages beyond K: out of range, zeros, no traffic
-    la.issue(smem + t * STAGE, t * 32 * KW, wave);
-    lb.issue(smem + t * STAGE + OPER, t * 32 * KW, wave);
-  }
-  int slot = 0;
-  for (int kt = 0; kt < nk; kt++) {
-    // stage kt has landed (STAGES - 2 younger ones may be in flight) and every wavefront has finished
-    // with stage kt - 1, whose slot takes the next request
-    // (__syncthreads() would wait for the younger requests too)
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((STAGES - 2) * LPT) : "memory");
-    {
-      char* nxt = smem + (slot == 0 ? STAGES - 1 : slot - 1) * STAGE;
-      la.issue(nxt, (kt + STAGES - 1) * 32 * KW, wave);
-      lb.issue(nxt + OPER, (kt + STAGES - 1) * 32 * KW, wave);
-    }
+  auto request = [&](int t, int slot) __attribute__((always_inline)) {   // stages beyond K: out of range, zeros, no traffic
+    la.issue(smem + slot * STAGE, t * 32 * KW, wave);
+    lb.issue(smem + slot * STAGE + OPER, t * 32 * KW, wave);
+  };
+  f32x4 fa[AHEAD ? 2 : 1][4], fb[AHEAD ? 2 : 1][4];
+  auto read = [&](int slot, int set, int c) __attribute__((always_inline)) {
     const char* ta = smem + slot * STAGE + kw * SUB;
-    const char* tb = ta + OPER;
-    f32x4 fa[4], fb[4];
+    fa[set][c] = frag<A_K, BM>(ta, 32 * wm + l32, c, grp);
+    fb[set][c] = frag<B_K, BM>(ta + OPER, 32 * wn + l32, c, grp);
+  };
+  auto products = [&](int set, int c) __attribute__((always_inline)) {
 #pragma unroll
-    for (int c = 0; c < 4; c++) {
-      fa[c] = frag<A_K, BM>(ta, 32 * wm + l32, c, grp);
-      fb[c] = frag<B_K, BM>(tb, 32 * wn + l32, c, grp);
+    for (int e = 0; e < 4; e++)
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[set][c][e], fb[set][c][e], acc, 0, 0, 0);
+  };
+  // (__syncthreads() would wait for the younger requests too)
+  int slot = 0;
+  if constexpr (AHEAD) {
+    // The fragments of stage kt + 1 are read between the products of stage kt, so that no product waits for LDS;
+    // a stage's slot is free for stage kt + STAGES as soon as every wavefront holds its fragments.
+#pragma unroll
+    for (int t = 0; t < STAGES; t++) request(t, t);
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 1) * LPT) : "memory");
+#pragma unroll
+    for (int c = 0; c < 4; c++) read(0, 0, c);
+    auto stage = [&](int kt, auto set_tag) __attribute__((always_inline)) {
+      constexpr int SET = decltype(set_tag)::value;
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        if (c == 1) {
+          // this wavefront holds stage kt, and its share of stage kt + 1 has landed
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((STAGES - 2) * LPT) : "memory");
+          request(kt + STAGES, slot);
+          slot = (slot == STAGES - 1) ? 0 : slot + 1;
+          read(slot, SET ^ 1, 0);
+        }
+        if (c > 0) read(slot, SET ^ 1, c);
+        __builtin_amdgcn_sched_barrier(0);
+        products(SET, c);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    int kt = 0;
+    for (; kt + 1 < nk; kt += 2) {
+      stage(kt, std::integral_constant<int, 0>());
+      stage(kt + 1, std::integral_constant<int, 1>());
     }
+    if (kt < nk) stage(kt, std::integral_constant<int, 0>());
+  } else {
 #pragma unroll
-    for (int c = 0; c < 4; c++)
+    for (int t = 0; t < STAGES - 1; t++) request(t, t);
+    for (int kt = 0; kt < nk; kt++) {
+      // stage kt has landed (STAGES - 2 younger ones may be in flight) and every wavefront has finished
+      // with stage kt - 1, whose slot takes the next request
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((STAGES - 2) * LPT) : "memory");
+      request(kt + STAGES - 1, slot == 0 ? STAGES - 1 : slot - 1);
 #pragma unroll
-      for (int e = 0; e < 4; e++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[c][e], fb[c][e], acc, 0, 0, 0);
-    slot = (slot == STAGES - 1) ? 0 : slot + 1;
+      for (int c = 0; c < 4; c++) read(slot, 0, c);
+#pragma unroll
+      for (int c = 0; c < 4; c++) products(0, c);
+      slot = (slot == STAGES - 1) ? 0 : slot + 1;
+    }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // requests beyond K must not land in what follows
   __syncthreads();
@@ -201,19 +236,20 @@ hipError_t launch_tile(const GemmArgs& g, hipStream_t s) {
 }
 
 // The smaller tile is for products that leave most of the 256 compute units without one of 64 x 64;
-// two wavefronts per block for products of at most one 64 x 64 tile per unit, which would leave a
-// wavefront per SIMD; beyond that the smallest stages, so that three workgroups share a unit.
-// Measured (NN, us; <32, KW 4> / <64, KW 2> / <64, KW 1>):
-//   tiles of 64 x 64      64               128              256              320              4096
-//   (M, N, K)             512 512 1024     512 1024 1024    1024 1024 1024   1024 1280 1024   4096 4096 1024
-//                         9.7/21.2/23.6    18.0/21.6/23.8   32.8/22.4/24.2   41.1/41.4/38.7   502/321/279
-// and at 192 tiles 25.1/21.6/23.8.  The largest is 123 TFLOP/s of a peak of 157.
+// two wavefronts per block while that gives no unit more than three tiles, one beyond.  Two stages are enough with
+// the fragments of the next one in registers, and leave room for two or four workgroups per unit, so that the last
+// ones do not run alone.  Measured (NN, us; <32, KW 4> / <64, KW 2> / <64, KW 1>):
+//   tiles of 64 x 64      64               128              256              320             1024             4096
+//   (M, N, K)             512 512 1024     512 1024 1024    1024 1024 1024   1024 1280 1024  1024 4096 1024   4096 4096 1024
+//                         9.8/20.0/22.0    18.0/20/22       31/20.4/21.6     42/36.5/37.1    130/71/69.5      502/276/270
+// and at 768 tiles 99/54.0/54.3.  With fragments read at the start of their own stage, three and four stages: 768 tiles 58,
+// 1024 tiles 77, 4096 tiles 280, 1024 1024 4096 (NT) 75.6 against 70.  The largest is 127 TFLOP/s of a peak of 157.
 template <int LAY, int EPI>
 hipError_t launch(const GemmArgs& g, hipStream_t s) {
   const long t64 = (long)cdiv(g.M, 64) * cdiv(g.N, 64);
   if (t64 <= 128) return launch_tile<LAY, EPI, 32, 4, 4>(g, s);
-  if (t64 <= 256) return launch_tile<LAY, EPI, 64, 2, 4>(g, s);
-  return launch_tile<LAY, EPI, 64, 1, 3>(g, s);
+  if (t64 <= 768) return launch_tile<LAY, EPI, 64, 2, 2>(g, s);
+  return launch_tile<LAY, EPI, 64, 1, 2>(g, s);
 }
 
 // The combinations that the layer driver asks for.
