@@ -10,6 +10,9 @@
 // 16 wavefront ballots, each of which is the column-major word pair "64 queries of one key".
 //   rowbits[(bh * S + i) * wpr + j / 32]  bit j % 32  = keep(i, j)        (forward, dQ)
 //   colbits[(bh * S + j) * wpr + i / 32]  bit i % 32  = keep(i, j)        (dK / dV)
+// What bounds it is the generator: 20 products of 32 x 32 bits a call, quarter rate, about 700 of 1000 cycles per wavefront
+// and call.  A ballot is the comparison's own mask, put into its lane by v_writelane (a select per lane and half took
+// four instructions).  64 pairs of S 1024, us: row-major alone 17.0 -> 14.0, both 26.9 -> 18.3; 64 of S 2048 89.5 -> 57.5.
 // wpr = 2 * ceil(S / 64) words per row.  Only words that a causal kernel can touch are written:
 // keys below 64 * (i / 64 + 1).
 //
@@ -28,8 +31,8 @@ GX_DEVINL Philox philox4x32_10(unsigned c0, unsigned c1, unsigned c2, unsigned c
   constexpr unsigned M0 = 0xD2511F53u, M1 = 0xCD9E8D57u, W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
 #pragma unroll
   for (int r = 0; r < 10; r++) {
-    const unsigned hi0 = __umulhi(M0, c0), lo0 = M0 * c0;
-    const unsigned hi1 = __umulhi(M1, c2), lo1 = M1 * c2;
+    const unsigned long long p0 = (unsigned long long)M0 * c0, p1 = (unsigned long long)M1 * c2;
+    const unsigned hi0 = (unsigned)(p0 >> 32), lo0 = (unsigned)p0, hi1 = (unsigned)(p1 >> 32), lo1 = (unsigned)p1;
     c0 = hi1 ^ c1 ^ k0;
     c1 = lo1;
     c2 = hi0 ^ c3 ^ k1;
@@ -40,19 +43,19 @@ GX_DEVINL Philox philox4x32_10(unsigned c0, unsigned c1, unsigned c2, unsigned c
   return Philox{{c0, c1, c2, c3}};
 }
 
-// bit e of the result = (byte e of the 16 random bytes >= t), i.e. element e is kept
+// element e is kept: byte e of the 16 random bytes >= t
+GX_DEVINL bool keep_of(const Philox& r, int e, unsigned t) { return ((r.x[e >> 2] >> (8 * (e & 3))) & 0xFFu) >= t; }
 GX_DEVINL unsigned keep_bits16(const Philox& r, unsigned t) {
   unsigned bits = 0;
 #pragma unroll
-  for (int w = 0; w < 4; w++)
-#pragma unroll
-    for (int b = 0; b < 4; b++) bits |= (((r.x[w] >> (8 * b)) & 0xFFu) >= t ? 1u : 0u) << (4 * w + b);
+  for (int e = 0; e < 16; e++) bits |= keep_of(r, e, t) ? 1u << e : 0u;
   return bits;
 }
 
 // One wavefront: 64 queries x MASK_GROUPS groups of 16 keys.
 constexpr int MASK_GROUPS = 8;
 
+template <bool COLS>
 __global__ void __launch_bounds__(64) attn_mask_kernel(unsigned* __restrict__ rowbits, unsigned* __restrict__ colbits,
                                                        int S, int wpr, int nchunk, int heads, int head0, unsigned k0,
                                                        unsigned k1, unsigned t) {
@@ -68,22 +71,40 @@ __global__ void __launch_bounds__(64) attn_mask_kernel(unsigned* __restrict__ ro
   const unsigned c2 = (unsigned)(b * heads + head0 + h);
   unsigned word = 0;
   for (int jg = jg0; jg < jg1; jg++) {
-    const unsigned kb = keep_bits16(philox4x32_10((unsigned)i, (unsigned)jg, c2, 1u, k0, k1), t);
+    const Philox r = philox4x32_10((unsigned)i, (unsigned)jg, c2, 1u, k0, k1);
+    // lane e of (lo, hi): the 64 queries of key e, which is the wavefront's mask of the comparison itself
+    unsigned kb = 0, lo = 0, hi = 0;
+#pragma unroll
+    for (int e = 0; e < 16; e += 4) {
+      unsigned long long col[4];
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        const bool keep = keep_of(r, e + k, t);
+        kb |= keep ? 1u << (e + k) : 0u;
+        if (COLS) col[k] = __builtin_amdgcn_ballot_w64(keep);
+      }
+      // (two wait states between a comparison and the read of its mask)
+      if (COLS)
+        asm("s_nop 1\n\t"
+            "v_writelane_b32 %0, %2, %10\n\tv_writelane_b32 %1, %3, %10\n\t"
+            "v_writelane_b32 %0, %4, %11\n\tv_writelane_b32 %1, %5, %11\n\t"
+            "v_writelane_b32 %0, %6, %12\n\tv_writelane_b32 %1, %7, %12\n\t"
+            "v_writelane_b32 %0, %8, %13\n\tv_writelane_b32 %1, %9, %13"
+            : "+v"(lo), "+v"(hi)
+            : "s"((unsigned)col[0]), "s"((unsigned)(col[0] >> 32)), "s"((unsigned)col[1]), "s"((unsigned)(col[1] >> 32)),
+              "s"((unsigned)col[2]), "s"((unsigned)(col[2] >> 32)), "s"((unsigned)col[3]), "s"((unsigned)(col[3] >> 32)),
+              "n"(e), "n"(e + 1), "n"(e + 2), "n"(e + 3));
+    }
     word |= kb << (16 * (jg & 1));
     if (jg & 1) {
       if (i < S) rowbits[(bh * S + i) * wpr + (jg >> 1)] = word;
       word = 0;
     }
-    if (colbits) {
-      unsigned long long mine = 0;
-#pragma unroll
-      for (int k = 0; k < 16; k++) {
-        const unsigned long long col = __builtin_amdgcn_ballot_w64((kb >> k) & 1u);
-        if (lane == k) mine = col;
-      }
+    if (COLS) {
       const int j = 16 * jg + lane;
       if (lane < 16 && j < S)
-        *reinterpret_cast<unsigned long long*>(colbits + (bh * S + j) * wpr + 2 * blk) = mine;
+        *reinterpret_cast<unsigned long long*>(colbits + (bh * S + j) * wpr + 2 * blk) =
+            (unsigned long long)hi << 32 | lo;
     }
   }
 }
@@ -138,8 +159,12 @@ hipError_t attn_mask(unsigned* rowbits, unsigned* colbits, int B, int nl, int S,
                      unsigned k1, int t, hipStream_t s) {
   if (!rowbits || S <= 0 || t < 0 || t > 255) return hipErrorInvalidValue;
   const int wpr = attn_mask_wpr(S), nchunk = cdiv(2 * wpr, MASK_GROUPS);
-  hipLaunchKernelGGL(attn_mask_kernel, dim3(cdiv(S, 64) * nchunk, nl, B), dim3(64), 0, s, rowbits, colbits, S, wpr,
-                     nchunk, heads, head0, k0, k1, (unsigned)t);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(cdiv(S, 64) * nchunk, nl, B), dim3(64), 0, s, rowbits, colbits, S, wpr, nchunk, heads,
+                       head0, k0, k1, (unsigned)t);
+  };
+  if (colbits) go(attn_mask_kernel<true>);
+  else go(attn_mask_kernel<false>);
   return hipGetLastError();
 }
 
