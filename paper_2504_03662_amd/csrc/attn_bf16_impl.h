@@ -587,31 +587,6 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, 2)
   fwd_merge_store<NQ, SPLIT, DROP>(smem, o, m, lsum, part, qs, lane, iw, b, h, S, nl, ctx, lse, keep);
 }
 
-// ------------------------------------------------------------------------------- backward: D
-// D[b, h, s] = sum_d dO * O; DH / 8 lanes per (token, head), 8 elements each
-__global__ void __launch_bounds__(256) attn_dsum_kernel(const bf16* __restrict__ ctx, const bf16* __restrict__ dctx,
-                                                        float* __restrict__ dsum, int B, int S, int nl) {
-  const long gid = (long)blockIdx.x * 256 + threadIdx.x;
-  const long pair = gid / CPR;                // (token, head) index
-  const int sub = (int)(gid % CPR);
-  const long npair = (long)B * S * nl;
-  float acc = 0.f;
-  if (pair < npair) {
-    const bf16x8 a = *reinterpret_cast<const bf16x8*>(ctx + pair * DH + sub * 8);
-    const bf16x8 d = *reinterpret_cast<const bf16x8*>(dctx + pair * DH + sub * 8);
-#pragma unroll
-    for (int e = 0; e < 8; e++) acc += (float)a[e] * (float)d[e];
-  }
-#pragma unroll
-  for (int o = CPR / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-  if (pair < npair && sub == 0) {
-    const long tok = pair / nl;
-    const int h = (int)(pair % nl);
-    const long b = tok / S, s = tok % S;
-    dsum[(b * nl + h) * S + s] = acc;
-  }
-}
-
 // ------------------------------------------------------------------------------- backward: dK, dV
 // A workgroup owns 64 key rows as 2 blocks of 32; each block belongs to a PAIR of wavefronts that split
 // the work by output: wavefront `pair` (role V) forms S = Q K^T, the probabilities P and dV += P^T dO;
@@ -849,12 +824,15 @@ __global__ void __launch_bounds__(64 * KV_NW, 2) attn_bwd_dkv_kernel(const bf16*
 
 // ------------------------------------------------------------------------------- backward: dQ
 // Shapes and workgroup order as in the forward kernel; the parts' dQ partial sums are added
-// through LDS in the order of `part`.
+// through LDS in the order of `part`.  It runs before the dK / dV kernel and leaves D[b, h, s] = sum_d dO * O for it:
+// the rows of dO are here anyway, so D costs one read of O and no launch of its own (that one took 3 to 10 us, up to
+// 250 beside the weight gradients of the other stream; layer steps, us: hidden 768, 1024 tokens 198.5 -> 193, hidden
+// 2048, 8192 tokens 2486 -> 2465, attention half of 4 heads and S 8192 958 -> 934).
 template <int NQ, int SPLIT, int BKV, bool DROP>
 __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
-    attn_bwd_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ dctx, const float* __restrict__ lse,
-                       const float* __restrict__ dsum, bf16* __restrict__ dqkv, int S, int nl, int npair,
-                       KeepArgs keep) {
+    attn_bwd_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ ctx, const bf16* __restrict__ dctx,
+                       const float* __restrict__ lse, float* __restrict__ dsum, bf16* __restrict__ dqkv, int S, int nl,
+                       int npair, KeepArgs keep) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int NW = NQ * SPLIT, BQ = 32 * NQ, ROWS = BKV * SPLIT, STAGE = 2 * ROWS * ROWB;
   constexpr int NJT = BKV / 32;
@@ -877,11 +855,12 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
   bf16x8 qf[DH / 16], dof[DH / 16];
   load_row_frags(sample + h * DH, ld, iw + l32, S, g, qf);
   load_row_frags(dctx + (size_t)b * S * Hl + h * DH, Hl, iw + l32, S, g, dof);
+  bf16x8 of[DH / 16];
+  load_row_frags(ctx + (size_t)b * S * Hl + h * DH, Hl, iw + l32, S, g, of);
   const int i = iw + l32;
   const int ic = min(i, S - 1);
   const float scale = rsqrtf((float)DH), c2 = scale * LOG2E;
   const float lse2 = lse[((size_t)b * nl + h) * S + ic] * LOG2E;
-  const float dd = dsum[((size_t)b * nl + h) * S + ic];
   unsigned coff[2][DH / 32];
   cols_lane_offsets(lane, coff);
   f32x16 dq[DH / 32];
@@ -896,6 +875,14 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
   const unsigned tile_bytes = (unsigned)(ROWS * ld) * 2u;
   src.load(rsrc, 0, kcol, smem, wave);
   src.load(rsrc, 0, vcol, smem + ROWS * ROWB, wave);
+  float d4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < DH / 16; s++)
+#pragma unroll
+    for (int e = 0; e < 8; e++) d4[e & 3] = __builtin_fmaf((float)of[s][e], (float)dof[s][e], d4[e & 3]);
+  float dd = (d4[0] + d4[1]) + (d4[2] + d4[3]);
+  dd += __shfl_xor(dd, 32, 64);
+  if (part == 0 && g == 0 && i < S) dsum[((size_t)b * nl + h) * S + i] = dd;
   WAIT_VM0();
   __syncthreads();
   for (int t = 0; t < nt; t++) {
@@ -1055,7 +1042,7 @@ hipError_t fwd(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// D, then dK / dV, then dQ.
+// dQ with D, then dK / dV.
 hipError_t bwd(const AttnArgs& a, hipStream_t s) {
   if (!attn_shape_ok(a)) return hipErrorInvalidValue;
   static bool configured = false;
@@ -1074,23 +1061,10 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s) {
   const KeepArgs keep_rows{a.rowbits, a.wpr, a.keep_scale}, keep_cols{a.colbits, a.wpr, a.keep_scale};
   const unsigned qkv_bytes = (unsigned)((size_t)a.B * a.S * 3 * a.nl * DH * 2);
   const unsigned dctx_bytes = qkv_bytes / 3;
-  const long npairs = (long)a.B * a.S * a.nl;
-  hipLaunchKernelGGL(attn_dsum_kernel, dim3(cdiv(npairs * CPR, 256)), dim3(256), 0, s, (const bf16*)a.ctx,
-                     (const bf16*)a.dctx, a.dsum, a.B, a.S, a.nl);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  auto go_dkv = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, KV_BJ) * a.nl * a.B), dim3(64 * KV_NW), KV_SMEM, s, (const bf16*)a.qkv,
-                       (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, a.nl * a.B, qkv_bytes, dctx_bytes,
-                       keep_cols);
-  };
-  if (drop) go_dkv(attn_bwd_dkv_kernel<true>);
-  else go_dkv(attn_bwd_dkv_kernel<false>);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   const int npair = a.nl * a.B;
   auto go_dq = [&](auto kernel, int bq, int threads, int smem) {
     hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, bq) * npair), dim3(threads), smem, s, (const bf16*)a.qkv,
-                       (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, npair, keep_rows);
+                       (const bf16*)a.ctx, (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, npair, keep_rows);
   };
   if (few_pairs(a)) {
     if (drop) go_dq(attn_bwd_dq_kernel<2, 2, 32, true>, 64, 256, SMEM_FEW);
@@ -1099,6 +1073,15 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s) {
     if (drop) go_dq(attn_bwd_dq_kernel<4, 1, 64, true>, 128, 256, SMEM_MANY);
     else go_dq(attn_bwd_dq_kernel<4, 1, 64, false>, 128, 256, SMEM_MANY);
   }
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  auto go_dkv = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, KV_BJ) * a.nl * a.B), dim3(64 * KV_NW), KV_SMEM, s, (const bf16*)a.qkv,
+                       (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, a.nl * a.B, qkv_bytes, dctx_bytes,
+                       keep_cols);
+  };
+  if (drop) go_dkv(attn_bwd_dkv_kernel<true>);
+  else go_dkv(attn_bwd_dkv_kernel<false>);
   return hipGetLastError();
 }
 

@@ -576,8 +576,8 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
     a.B = (int)d.B; a.S = (int)d.S; a.nl = (int)d.nl; a.dh = (int)d.dh;
     set_attn_drop(a, d, dr, db);
     { ProfScope ps(GX_KC_ATTN_BWD, st);
-    // the dQ kernel follows the dK / dV kernel on the caller's stream: a stream of its own for it
-    // measured slightly slower (its workgroups cannot share a compute unit with the other kernel's)
+    // the dK / dV kernel follows the dQ kernel, which leaves D for it, on the caller's stream (streams of their
+    // own measured slightly slower when D had a launch: their workgroups cannot share a compute unit)
     GX_TRY(d.bf ? attn_bwd_bf16(a, st) : attn_bwd_f32(a, st));
     }
     if ((s = point(5)) != GX_OK) return s;
