@@ -595,43 +595,40 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, 2)
 // half sub-tile, conflict-free).  Each wavefront thus keeps one operand (K or V) and one 32 x DH
 // accumulator in registers.
 //
-// The roles are skewed so that the exponentials of one run under the matrix work of the other and
-// one barrier per query tile (32 rows) suffices.  In phase n
-//   role V: S(n), P(n) -> LDS, dV += P(n)^T dO(n)
-//   role K: dS(n-1) from P(n-1) and the dP(n-1) it kept in registers, dK += dS(n-1)^T Q(n-1), then dP(n)
-// Tiles n+1 and n+2 are in flight meanwhile (a tile has two phases to arrive from HBM).
-//
-// A phase is a chain (LDS reads, products, exponentials, exchange, barrier) that keeps the matrix pipe
-// busy for a third of its length, so what matters is a second, independent workgroup on the compute
-// unit (66 KB of LDS at DH 128) to fill the rest.  Against 128 key rows, query tiles of 64 and one workgroup
-// of 8 wavefronts per unit, the whole backward pass (D, this kernel, dQ; nothing else on the chip, us): 64 pairs of
-// S 2048 at DH 128 394 -> 292 (this kernel 287 -> 173), 16 pairs 112 -> 101 (75 -> 62), 4 pairs of S 8192 372 -> 334;
-// 64 pairs of S 1024 at DH 64 with dropout 95 -> 74.  One tile in flight instead of two is equal; three
-// workgroups per unit need 168 registers and spill (1.6 times the time).
-constexpr int KV_PAIRS = 2, KV_NW = 2 * KV_PAIRS, KV_BJ = 32 * KV_PAIRS, KV_BI = 32, KV_SUB = KV_BI / 32;
-// LDS: Q tiles (+ their D rows) in a ring (tiles n-1 .. n+2), dO tiles (+ lse rows) in a ring (tiles
-// n .. n+2), two P exchange buffers, and a 256 B sink (see stage_load).
+// What bounds it: a phase (one query tile of 32 rows) written as a chain (LDS reads, products, exponentials,
+// exchange, barrier) keeps the matrix pipe busy for a third of its length.  So a wavefront's stream mixes the
+// first products of the next tile with the vector work of its own, product by product, as in the forward kernel, and a
+// second, independent workgroup on the compute unit (76 KB of LDS at DH 128) fills the rest.  In phase n
+//   role V: S(n+1) = Q(n+1) K^T, mixed with P(n) -> LDS; then dV += P(n)^T dO(n)
+//   role K: dP(n) = dO(n) V^T, mixed with dS(n-1) from P(n-1) and dP(n-1); then dK += dS(n-1)^T Q(n-1)
+// with one barrier per phase; Q(n+3) and dO(n+2) are requested in its first slots.  Tiles need two phases to arrive:
+// with one (and the second products a phase later, mixed too, in the same LDS) every phase waited for them.
+// This kernel alone, us, as a chain / mixed with one phase to arrive / as it is: 64 pairs of S 2048 197 / 190 / 183, 16 pairs
+// 72 / 68 / 65, 4 pairs of S 8192 238 / 229 / 216; DH 64: 12 pairs of S 1024 23.1 / 22.0 / 19.8, 64 pairs of S 1024 with
+// dropout 42.9 / 50.7 / 45.1 (there three workgroups share a unit instead of four; the second needed 169 registers, two).
+// The chain with two workgroups per unit against 128 key rows, query tiles of 64 and one workgroup of 8 wavefronts (the whole
+// backward pass, nothing else on the chip, us): 64 pairs of S 2048 at DH 128 394 -> 292, 16 pairs 112 -> 101, 4 pairs of
+// S 8192 372 -> 334.
+constexpr int KV_PAIRS = 2, KV_NW = 2 * KV_PAIRS, KV_BJ = 32 * KV_PAIRS, KV_BI = 32;
+// LDS: Q tiles (+ their D rows) in a ring (tiles n-1 .. n+3), dO tiles (+ lse rows) in a ring (tiles
+// n .. n+2), two P exchange buffers, and a 256 B sink (see the requests).
 constexpr int KV_PAIRED = 512;                               // launches that are resident all at once
-constexpr int KV_AHEAD = 2, KV_NQ = KV_AHEAD + 2, KV_NDO = KV_AHEAD + 1;
+constexpr int KV_NQ = 5, KV_NDO = 3;
 constexpr int KV_TILE = KV_BI * ROWB + 256;                  // rows of Q or dO | their D or lse (64 lanes' worth)
-constexpr int KV_PX = KV_PAIRS * 2 * KV_SUB * 1024;          // P exchange: [pair][sub-tile, half][lane] x 16 B
+constexpr int KV_PX = KV_PAIRS * 2 * 1024;                   // P exchange: [pair][half][lane] x 16 B
 constexpr int KV_OFF_DO = KV_NQ * KV_TILE, KV_OFF_PX = KV_OFF_DO + KV_NDO * KV_TILE;
 constexpr int KV_OFF_SINK = KV_OFF_PX + 2 * KV_PX, KV_SMEM = KV_OFF_SINK + 256;
-// direct-to-LDS loads per wavefront per tile: its share of the Q rows, of the dO rows (tile_load's
-// PER_WAVE each, which depends on the row length) and one lse / D / sink load
-constexpr int KV_TILE_LOADS = KV_BI / (64 / CPR) / KV_NW;
-static_assert(KV_TILE_LOADS >= 1 && KV_TILE_LOADS * (64 / CPR) * KV_NW == KV_BI, "tile_load<KV_BI, KV_NW> split");
-constexpr int KV_LOADS = 2 * KV_TILE_LOADS + 1;
+static_assert(2 * KV_SMEM <= 160 * 1024, "two workgroups per compute unit");
 
 template <bool DROP>
-__global__ void __launch_bounds__(64 * KV_NW, 2) attn_bwd_dkv_kernel(const bf16* __restrict__ qkv,
+__global__ void __launch_bounds__(64 * KV_NW, DH == 64 ? 3 : 2) attn_bwd_dkv_kernel(const bf16* __restrict__ qkv,
                                                                   const bf16* __restrict__ dctx,
                                                                   const float* __restrict__ lse,
                                                                   const float* __restrict__ dsum,
                                                                   bf16* __restrict__ dqkv, int S, int nl, int npair,
-                                                                  unsigned qkv_bytes, unsigned dctx_bytes,
                                                                   KeepArgs keep) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
+  constexpr int NS = DH / 16, NDT = DH / 32;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool role_v = wave < KV_PAIRS;
   const int pair = wave & (KV_PAIRS - 1);
@@ -645,176 +642,245 @@ __global__ void __launch_bounds__(64 * KV_NW, 2) attn_bwd_dkv_kernel(const bf16*
   const int h = kp % nl, b = kp / nl;
   const int Hl = nl * DH, ld = 3 * Hl;
   const int j0 = kb * KV_BJ, jw = j0 + pair * 32;
-  const unsigned eq = (unsigned)((size_t)b * S * ld + h * DH);
-  const unsigned edo = (unsigned)((size_t)b * S * Hl + h * DH);
-  const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(qkv), 0, qkv_bytes,
-                                                                      0x00020000);
-  const __amdgpu_buffer_rsrc_t rdo = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(dctx), 0, dctx_bytes,
-                                                                       0x00020000);
-  bf16x8 kvf[DH / 16];                      // role V: this block's K rows; role K: its V rows
-  load_row_frags(qkv + eq + (role_v ? Hl : 2 * Hl), ld, jw + l32, S, g, kvf);
-  f32x16 acc[DH / 32];                      // role V: dV; role K: dK
+  const bf16* sample = qkv + (size_t)b * S * ld;
+  const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(sample), 0,
+                                                                      (unsigned)(S * ld) * 2u, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rdo = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<bf16*>(dctx + (size_t)b * S * Hl), 0, (unsigned)(S * Hl) * 2u, 0x00020000);
+  bf16x8 kvf[NS];                           // role V: this block's K rows; role K: its V rows
+  load_row_frags(sample + h * DH + (role_v ? Hl : 2 * Hl), ld, jw + l32, S, g, kvf);
+  f32x16 acc[NDT];                          // role V: dV; role K: dK
 #pragma unroll
-  for (int dt = 0; dt < DH / 32; dt++) acc[dt] = zero16();
+  for (int dt = 0; dt < NDT; dt++) acc[dt] = zero16();
   const float scale = rsqrtf((float)DH), c2 = scale * LOG2E;
   const float* lrow = lse + ((size_t)b * nl + h) * S;
   const float* drow = dsum + ((size_t)b * nl + h) * S;
-  char* px = smem + KV_OFF_PX + pair * (KV_PX / KV_PAIRS) + lane * 16;
-  unsigned coff[2][DH / 32];
+  char* const px = smem + KV_OFF_PX + pair * (KV_PX / KV_PAIRS) + lane * 16;
+  unsigned coff[2][NDT];
   cols_lane_offsets(lane, coff);
 
-  const int t0 = j0 / KV_BI, nt = (S + KV_BI - 1) / KV_BI;     // query tiles t0 .. nt-1 see these keys
+  // query tiles t0 .. nt - 1 see these keys, tiles tp .. nt - 1 those of this pair of wavefronts
+  const int t0 = j0 / KV_BI, tp = t0 + pair, nt = (S + KV_BI - 1) / KV_BI;
   // lse and D rows of a query tile go to LDS by the same direct path, 4 B per lane (wavefront 0:
-  // lse, wavefront 1: D; the others send an out-of-range load to a sink so that every wavefront
-  // has the same number of loads in flight per tile).  Rows beyond the sequence read as 0
+  // lse, wavefront 1: D; the others send an out-of-range load to a sink, so that every wavefront has the same
+  // number of loads in flight).  Rows beyond the sequence read as 0
   // everywhere (Q, dO, lse, D): their probabilities are 1 but their contributions to dV and dK
   // are exactly 0, and whole tiles beyond the sequence may be requested harmlessly.
   const __amdgpu_buffer_rsrc_t raux = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<float*>(wave == 0 ? lrow : drow), 0, (unsigned)S * 4u, 0x00020000);
-  auto stage_load = [&](int t, int qslot, int dslot) {
-    char* qs = smem + qslot * KV_TILE;
-    char* ds = smem + KV_OFF_DO + dslot * KV_TILE;
-    tile_load<KV_BI, KV_NW>(rq, eq, ld, t * KV_BI, S, qs, wave, lane);
-    tile_load<KV_BI, KV_NW>(rdo, edo, Hl, t * KV_BI, S, ds, wave, lane);
+  RowStream<KV_BI, KV_NW> srcq, srcdo;
+  constexpr int PER = RowStream<KV_BI, KV_NW>::PER_WAVE, NREQ = 2 * PER + 1;
+  srcq.init(ld, wave, lane);
+  srcdo.init(Hl, wave, lane);
+  const unsigned q_bytes = (unsigned)(KV_BI * ld) * 2u, do_bytes = (unsigned)(KV_BI * Hl) * 2u;
+  const int col = h * DH * 2;
+  auto q_slot = [&](int slot) { return smem + slot * KV_TILE; };
+  auto do_slot = [&](int slot) { return smem + KV_OFF_DO + slot * KV_TILE; };
+  auto aux_load = [&](int t, char* dst, bool on) {
     const int i = t * KV_BI + lane;
-    char* ad = (wave == 0) ? ds + KV_BI * ROWB : (wave == 1) ? qs + KV_BI * ROWB : smem + KV_OFF_SINK;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(raux, (lds_void_ptr)ad, 4, (wave < 2 && lane < KV_BI && i < S) ? (unsigned)i * 4u : OOB,
-                                             0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(raux, (lds_void_ptr)(on ? dst : smem + KV_OFF_SINK), 4,
+                                             (on && lane < KV_BI && i < S) ? (unsigned)i * 4u : OOB, 0, 0, 0);
   };
-  // first product of a role over the 32-row query sub-tiles: [query i][key j]
-  f32x16 sp[KV_SUB];
-  auto first_product = [&](const char* rows_of) {
-    bf16x8 fr[KV_SUB][DH / 16];
-#pragma unroll
-    for (int s = 0; s < DH / 16; s++) fr[0][s] = frag_rows(rows_of, l32, s, g);
-#pragma unroll
-    for (int sub = 0; sub < KV_SUB; sub++) {
-      sp[sub] = zero16();
-#pragma unroll
-      for (int s = 0; s < DH / 16; s++) {
-        if (sub + 1 < KV_SUB) fr[sub + 1][s] = frag_rows(rows_of, 32 * (sub + 1) + l32, s, g);
-        sp[sub] = MFMA(fr[sub][s], kvf[s], sp[sub]);
-      }
-    }
-  };
-#pragma unroll
-  for (int a = 0; a < KV_AHEAD; a++) stage_load(t0 + a, a, a);
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((KV_AHEAD - 1) * KV_LOADS) : "memory");   // tile t0 has landed
+  srcq.load(rq, (unsigned)t0 * q_bytes, col, q_slot(0), wave);
+  srcq.load(rq, (unsigned)(t0 + 1) * q_bytes, col, q_slot(1), wave);
+  srcdo.load(rdo, (unsigned)t0 * do_bytes, col, do_slot(0), wave);
+  aux_load(t0, wave == 0 ? do_slot(0) + KV_BI * ROWB : q_slot(0) + KV_BI * ROWB, wave < 2);
+  aux_load(t0 + 1, q_slot(1) + KV_BI * ROWB, wave == 1);
+  srcq.load(rq, (unsigned)(t0 + 2) * q_bytes, col, q_slot(2), wave);
+  srcdo.load(rdo, (unsigned)(t0 + 1) * do_bytes, col, do_slot(1), wave);
+  aux_load(wave == 0 ? t0 + 1 : t0 + 2, (wave == 0 ? do_slot(1) : q_slot(2)) + KV_BI * ROWB, wave < 2);
   const int j = jw + l32;
   // dropout: this key's column of keep bits, KV_BI bits per query tile (both roles read them; they are
-  // fetched one phase before their use, ahead of that phase's tile requests, so that waiting for
-  // them never waits for a tile)
+  // fetched one phase before their use)
   const unsigned* kcol = DROP ? keep.bits + (((size_t)b * nl + h) * S + min(j, S - 1)) * keep.wpr : nullptr;
-  auto keep_word = [&](int t) -> unsigned long long {
-    if (t < t0 || t >= nt) return 0ull;
-    return KV_SUB == 2 ? *reinterpret_cast<const unsigned long long*>(kcol + 2 * t) : kcol[t];
+  auto keep_word = [&](int t) -> unsigned long long { return t < t0 || t >= nt ? 0ull : kcol[t]; };
+  // all that was requested before this phase has landed, and this wavefront is done with its reads
+  auto meet = [&]() __attribute__((always_inline)) {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NREQ) : "memory");
   };
-  // One loop per role (the branch is wavefront-uniform and both loops pass the same number of
-  // barriers), so that neither role carries the other's addresses and fragments in registers.
-  auto run = [&](auto role_tag) {
-    constexpr bool ROLE_V = decltype(role_tag)::value;
-    int qslot = 0, dslot = 0;                                     // ring positions of tile n
-    unsigned long long kw = 0, kw_next = 0;                       // role V: tile n; role K: tile n - 1
-    if (DROP && ROLE_V) kw_next = keep_word(t0);
-#pragma unroll 1
-    for (int n = t0; n <= nt; n++) {
-      if (DROP) {
-        kw = kw_next;
-        kw_next = keep_word(ROLE_V ? n + 1 : n);
-      }
-      stage_load(n + KV_AHEAD, qslot + KV_AHEAD < KV_NQ ? qslot + KV_AHEAD : qslot + KV_AHEAD - KV_NQ,
-                 dslot == 0 ? KV_NDO - 1 : dslot - 1);
-      const char* qt = smem + qslot * KV_TILE;                    // Q rows of tile n, then their D
-      const char* dot = smem + KV_OFF_DO + dslot * KV_TILE;       // dO rows of tile n, then their lse
-      bf16x8 xf[2 * KV_SUB];                                      // P or dS, 16 query rows per entry
-      ColFrags cf[2];
-      if (ROLE_V) {
-        if (n < nt && n * KV_BI + KV_BI - 1 >= jw) {              // pair-uniform: some query of tile n sees a key
-          const float* aux = reinterpret_cast<const float*>(dot + KV_BI * ROWB);
-          first_product(qt);                                      // S = Q K^T
-          const unsigned ct = lds_addr(dot);
-          cols_issue<0>(ct, coff, cf[0]);
-          cols_issue<1>(ct, coff, cf[1]);
+  meet();
+
+  int qs = 0, ds = 0;                       // ring positions of tile n
+  auto q_of = [&](int d) { return q_slot(qs + d < KV_NQ ? qs + d : qs + d - KV_NQ); };       // tile n + d, d in 0 .. 4
+  auto do_of = [&](int d) { return do_slot(ds + d < KV_NDO ? ds + d : ds + d - KV_NDO); };   // tile n + d, d in 0 .. 2
+  // request i of phase n: this wavefront's share of Q(n + 3), of dO(n + 2), then D(n + 3) or lse(n + 2)
+  auto request = [&](int n, int i) __attribute__((always_inline)) {
+    if (i < PER) srcq.issue(rq, (unsigned)(n + 3) * q_bytes, col, q_of(3), wave, i);
+    else if (i < 2 * PER) srcdo.issue(rdo, (unsigned)(n + 2) * do_bytes, col, do_of(2), wave, i - PER);
+    else aux_load(wave == 0 ? n + 2 : n + 3, (wave == 0 ? do_of(2) : q_of(3)) + KV_BI * ROWB, wave < 2);
+  };
+  auto request_all = [&](int n) __attribute__((always_inline)) {
 #pragma unroll
-          for (int sub = 0; sub < KV_SUB; sub++) {
+    for (int i = 0; i < NREQ; i++) request(n, i);
+  };
+  auto advance = [&]() __attribute__((always_inline)) {
+    qs = qs == KV_NQ - 1 ? 0 : qs + 1;
+    ds = ds == KV_NDO - 1 ? 0 : ds + 1;
+  };
+  struct CFrag { bf16x4 lo, hi; };
+  constexpr int NPC = 2 * NDT, VD = 4, KD = 4;       // products with a transposed tile; fragments requested ahead
+  static_assert(NPC >= VD && NS >= KD && NREQ <= NS, "slots of a phase");
+  // product p takes head-dim block p % NDT and rows 16 (p / NDT) .. + 15 of the tile
+  auto c_request = [&](unsigned ct, auto P, CFrag& f) __attribute__((always_inline)) {
+    constexpr int p = decltype(P)::value, dt = p % NDT, u = p / NDT;
+    f.lo = lds_read_tr_issue<u * 16 * ROWB>(ct + coff[0][dt]);
+    f.hi = lds_read_tr_issue<u * 16 * ROWB>(ct + coff[1][dt]);
+  };
+  auto c_get = [&](CFrag& f) __attribute__((always_inline)) {
+    lds_pin(f.lo);
+    lds_pin(f.hi);
+    return __builtin_shufflevector(f.lo, f.hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  // S or dP of one tile on its own
+  auto first_product = [&](const char* rows, f32x16& out) __attribute__((always_inline)) {
+    out = zero16();
+    streamed<NS, KD>([&](int s) { return frag_rows(rows, l32, s, g); },
+                     [&](int s, bf16x8 f) { out = MFMA(f, kvf[s], out); });
+  };
+  unsigned long long kw = 0, kw_next = 0;   // keep bits: role V: tile n; role K: tile n - 1
+  // One phase.  cur: S(n) (role V) or dP(n - 1) (role K), worked on in place; nxt: S(n + 1) or dP(n).  DIAGONAL: role
+  // V's tile has keys behind their queries.
+  auto phase = [&](int n, f32x16& cur, f32x16& nxt, auto role_tag, auto diagonal_tag) __attribute__((always_inline)) {
+    constexpr bool ROLE_V = decltype(role_tag)::value, DIAGONAL = decltype(diagonal_tag)::value;
+    if (DROP) {
+      kw = kw_next;
+      kw_next = keep_word(ROLE_V ? n + 1 : n);
+    }
+    const char* rows = ROLE_V ? q_of(1) : do_of(0);
+    const char* own = ROLE_V ? do_of(0) : q_of(4);                    // dO(n) and lse(n), or Q(n - 1) and D(n - 1)
+    const unsigned ct = lds_addr(own);
+    const float* aux = reinterpret_cast<const float*>(own + KV_BI * ROWB);
+    char* const pxn = px + ((ROLE_V ? n : n - 1) & 1) * KV_PX;
+    f32x4 row_value[4];
 #pragma unroll
-            for (int q4 = 0; q4 < 4; q4++) {
-              const f32x4 l4 = *reinterpret_cast<const f32x4*>(aux + 32 * sub + 8 * q4 + 4 * g);
+    for (int q4 = 0; q4 < 4; q4++) row_value[q4] = *reinterpret_cast<const f32x4*>(aux + 8 * q4 + 4 * g);
+    bf16x8 pb[2];
+    if (!ROLE_V) {
 #pragma unroll
-              for (int e = 0; e < 4; e++)
-                sp[sub][4 * q4 + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sp[sub][4 * q4 + e], c2, -LOG2E * l4[e]));
-            }
-            const int it0 = n * KV_BI + 32 * sub;
-            if (it0 < jw + 31) {                                  // the sub-tile touches the diagonal
+      for (int u = 0; u < 2; u++) pb[u] = *reinterpret_cast<const bf16x8*>(pxn + u * 1024);
+    }
+    CFrag cf[VD];
+    bf16x8 rf[KD], xf[2];                   // xf: P or dS, 16 query rows per entry
 #pragma unroll
-              for (int v = 0; v < 16; v++)
-                if (j > it0 + 8 * (v >> 2) + 4 * g + (v & 3)) sp[sub][v] = 0.f;
-            }
+    for (int q = 0; q < KD; q++) rf[q] = frag_rows(rows, l32, q, g);
+    nxt = zero16();
+    // the vector work in pieces: two values each, then 16 query rows to round each
+    constexpr int EPP = 2, NE = 16 / EPP, NPIECE = NE + 2;
+    auto piece = [&](auto K) __attribute__((always_inline)) {
+      constexpr int k = decltype(K)::value;
+      if constexpr (k < NE) {
+        constexpr int v0 = EPP * k;
+        if constexpr (ROLE_V) {
 #pragma unroll
-            for (int u = 0; u < 2; u++) {
-              xf[2 * sub + u] = pack_half(sp[sub], u);
-              *reinterpret_cast<bf16x8*>(px + (n & 1) * KV_PX + (2 * sub + u) * 1024) = xf[2 * sub + u];
-            }
+          for (int v = v0; v < v0 + EPP; v++) {
+            float p = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[v], c2, -LOG2E * row_value[v >> 2][v & 3]));
+            if (DIAGONAL && j > n * KV_BI + 8 * (v >> 2) + 4 * g + (v & 3)) p = 0.f;
+            cur[v] = p;
           }
-          if (DROP) {                                             // dV takes the dropped probabilities
-            drop_unkept(sp, kw, g);
-#pragma unroll
-            for (int u = 0; u < 2 * KV_SUB; u++) xf[u] = pack_half(sp[u >> 1], u & 1);
+        } else {
+          if (DROP && k == 0) {                                   // gradient w.r.t. the undropped probabilities
+            f32x16 (&one)[1] = reinterpret_cast<f32x16 (&)[1]>(cur);
+            drop_unkept<1>(one, kw, g);
           }
-          tr_product<false, 2 * KV_SUB>(acc, ct, coff, cf, xf);   // dV[j][d] += P^T dO
+#pragma unroll
+          for (int v = v0; v < v0 + EPP; v++) {
+            const float dp = DROP ? cur[v] * keep.scale : cur[v];
+            cur[v] = (float)pb[v >> 3][v & 7] * (dp - row_value[v >> 2][v & 3]);
+          }
         }
       } else {
-        const int m = n - 1;                                      // tile whose dP this wavefront holds
-        if (m >= t0 && m * KV_BI + KV_BI - 1 >= jw) {
-          const char* qp = smem + (qslot == 0 ? KV_NQ - 1 : qslot - 1) * KV_TILE;
-          const float* dp = reinterpret_cast<const float*>(qp + KV_BI * ROWB);
-          const unsigned ct = lds_addr(qp);
-          cols_issue<0>(ct, coff, cf[0]);
-          cols_issue<1>(ct, coff, cf[1]);
-          if (DROP) {                                             // gradient w.r.t. the undropped probabilities
-            drop_unkept(sp, kw, g);
+        constexpr int u = k - NE;
+        xf[u] = pack_half(cur, u);
+        if constexpr (ROLE_V) *reinterpret_cast<bf16x8*>(pxn + u * 1024) = xf[u];
+        if constexpr (ROLE_V && DROP && u == 1) {                 // dV takes the dropped probabilities
+          f32x16 (&one)[1] = reinterpret_cast<f32x16 (&)[1]>(cur);
+          drop_unkept<1>(one, kw, g);
 #pragma unroll
-            for (int sub = 0; sub < KV_SUB; sub++)
-#pragma unroll
-              for (int v = 0; v < 16; v++) sp[sub][v] *= keep.scale;
-          }
-#pragma unroll
-          for (int sub = 0; sub < KV_SUB; sub++) {
-            bf16x8 pb[2];
-#pragma unroll
-            for (int u = 0; u < 2; u++)
-              pb[u] = *reinterpret_cast<const bf16x8*>(px + (m & 1) * KV_PX + (2 * sub + u) * 1024);
-#pragma unroll
-            for (int q4 = 0; q4 < 4; q4++) {
-              const f32x4 d4 = *reinterpret_cast<const f32x4*>(dp + 32 * sub + 8 * q4 + 4 * g);
-#pragma unroll
-              for (int e = 0; e < 4; e++) {
-                const int v = 4 * q4 + e;
-                sp[sub][v] = (float)pb[v >> 3][v & 7] * (sp[sub][v] - d4[e]);
-              }
-            }
-#pragma unroll
-            for (int u = 0; u < 2; u++) xf[2 * sub + u] = pack_half(sp[sub], u);
-          }
-          tr_product<false, 2 * KV_SUB>(acc, ct, coff, cf, xf);   // dK[j][d] += dS^T Q
+          for (int w = 0; w < 2; w++) xf[w] = pack_half(cur, w);
         }
-        if (n < nt && n * KV_BI + KV_BI - 1 >= jw) first_product(dot);   // dP = dO V^T, used in the next phase
       }
-      // tile n+1 has landed (n+2 may still be in flight) and this wavefront's LDS traffic is
-      // complete; then the workgroup meets
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((KV_AHEAD - 1) * KV_LOADS) : "memory");
-      qslot = (qslot == KV_NQ - 1) ? 0 : qslot + 1;
-      dslot = (dslot == KV_NDO - 1) ? 0 : dslot + 1;
-    }
+    };
+    constexpr auto cost = [](int k) constexpr { return k < NE ? (ROLE_V ? 7 : 3) * EPP : 6; };
+    constexpr auto upto = [cost](int k) constexpr { int c = 0; for (int x = 0; x < k; x++) c += cost(x); return c; };
+    constexpr int TOTAL = upto(NPIECE);
+    // piece k goes behind first product slot_of(k)
+    constexpr auto slot_of = [upto, cost](int k) constexpr { return (upto(k) + cost(k) / 2) * NS / TOTAL; };
+    __builtin_amdgcn_sched_barrier(0);
+    unroll<NS>([&](auto I) __attribute__((always_inline)) {
+      constexpr int x = decltype(I)::value;
+      nxt = MFMA(rf[x % KD], kvf[x], nxt);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (x + KD < NS) rf[x % KD] = frag_rows(rows, l32, x + KD, g);
+      if constexpr (x >= NS - VD) c_request(ct, std::integral_constant<int, x - (NS - VD)>(), cf[x - (NS - VD)]);
+      if constexpr (x < NREQ) request(n, x);
+      unroll<NPIECE>([&](auto K) __attribute__((always_inline)) {
+        if constexpr (slot_of(decltype(K)::value) == x) piece(K);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    unroll<NPC>([&](auto P) __attribute__((always_inline)) {
+      constexpr int p = decltype(P)::value, newer = 2 * ((p + VD < NPC ? p + VD : NPC) - p - 1);   // untracked, younger
+      lds_wait_le<newer>();
+      acc[p % NDT] = MFMA(xf[p / NDT], c_get(cf[p % VD]), acc[p % NDT]);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (p + VD < NPC) c_request(ct, std::integral_constant<int, p + VD>(), cf[p % VD]);
+    });
+    asm volatile("" : "+v"(nxt));           // also where no tile follows
   };
-  if (role_v) run(std::true_type{});
-  else run(std::false_type{});
+  // One loop per role (the branch is wavefront-uniform; both pass a barrier after each of the phases t0 .. nt - 1).
+  f32x16 sa, sb;
+  int n = t0;
+  if (role_v) {
+    if (DROP) kw_next = keep_word(tp);
+    if (tp == t0) first_product(q_of(0), sa);
+    for (; n < tp && n < nt; n++) {
+      request_all(n);
+      if (n + 1 == tp) first_product(q_of(1), sa);
+      meet();
+      advance();
+    }
+    if (n < nt) {
+      auto next = [&](f32x16& cur, f32x16& nxt, auto diagonal_tag) __attribute__((always_inline)) {
+        phase(n, cur, nxt, std::true_type(), diagonal_tag);
+        meet();
+        advance();
+        n++;
+      };
+      next(sa, sb, std::true_type());
+      while (n + 1 < nt) {
+        next(sb, sa, std::false_type());
+        next(sa, sb, std::false_type());
+      }
+      if (n < nt) next(sb, sa, std::false_type());
+    }
+  } else {
+    for (; n <= tp && n < nt; n++) {
+      request_all(n);
+      if (n == tp) first_product(do_of(0), sa);
+      meet();
+      advance();
+    }
+    if (tp < nt) {                          // n is tp + 1; phases up to nt
+      if (DROP) kw_next = keep_word(tp);
+      auto next = [&](f32x16& cur, f32x16& nxt) __attribute__((always_inline)) {
+        phase(n, cur, nxt, std::false_type(), std::false_type());
+        if (n < nt) meet();
+        advance();
+        n++;
+      };
+      while (n < nt) {
+        next(sa, sb);
+        next(sb, sa);
+      }
+      if (n <= nt) next(sa, sb);
+    }
+  }
   WAIT_VM0();   // requests for tiles beyond the last one (zero fill) must not outlive the workgroup's LDS
   // accumulator register v of lane l is row 8 (v/4) + 4 g + v%4, column l%32 of its 32x32 tile
   const float oscale = role_v ? (DROP ? keep.scale : 1.f) : scale;
   bf16* obase = dqkv + (size_t)b * S * ld + h * DH + (role_v ? 2 * Hl : Hl);
 #pragma unroll
-  for (int dt = 0; dt < DH / 32; dt++)
+  for (int dt = 0; dt < NDT; dt++)
 #pragma unroll
     for (int v = 0; v < 16; v++) {
       const int jr = jw + 8 * (v >> 2) + 4 * g + (v & 3);
@@ -1059,8 +1125,6 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s) {
   const bool drop = a.rowbits != nullptr;
   if (drop && (!a.colbits || a.wpr != 2 * cdiv(a.S, 64))) return hipErrorInvalidValue;
   const KeepArgs keep_rows{a.rowbits, a.wpr, a.keep_scale}, keep_cols{a.colbits, a.wpr, a.keep_scale};
-  const unsigned qkv_bytes = (unsigned)((size_t)a.B * a.S * 3 * a.nl * DH * 2);
-  const unsigned dctx_bytes = qkv_bytes / 3;
   const int npair = a.nl * a.B;
   auto go_dq = [&](auto kernel, int bq, int threads, int smem) {
     hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, bq) * npair), dim3(threads), smem, s, (const bf16*)a.qkv,
@@ -1077,8 +1141,7 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s) {
   if (e != hipSuccess) return e;
   auto go_dkv = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, KV_BJ) * a.nl * a.B), dim3(64 * KV_NW), KV_SMEM, s, (const bf16*)a.qkv,
-                       (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, a.nl * a.B, qkv_bytes, dctx_bytes,
-                       keep_cols);
+                       (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, a.nl * a.B, keep_cols);
   };
   if (drop) go_dkv(attn_bwd_dkv_kernel<true>);
   else go_dkv(attn_bwd_dkv_kernel<false>);

@@ -1,0 +1,28 @@
+"""The dK / dV kernel works on three query tiles of 32 at once: lengths for which a pair of wavefronts has no tile, one,
+two, three, or an odd or even number of them, with a last tile of one row, of all but one, or whole; more than one sample,
+so that a tile beyond a sample's end may not read the next one's rows; repeated, the same bits."""
+import pytest
+import torch
+
+from paper_2504_03662_amd import inputs as I
+from paper_2504_03662_amd.runtime import to_device
+from parity import TOL, compare, run_both
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("drop", [0, 26])
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("seq", [1, 31, 32, 33, 64, 65, 95, 96, 97, 128, 129, 161, 255])
+def test_query_tile_counts_against_the_oracle(seq, dh, drop):
+    shape = I.LayerShape(2 * dh, 2, 64, 1, 1, 0, seq, 2, "bf16", drop_attn=drop, drop_seed=5 if drop else 0)
+    params = I.full_params(shape, case=700 + seq, random_affine=True)
+    x, dy = I.activations(shape, case=700 + seq)
+    gpu, ref, layer = run_both(shape, params, x, dy, "attn")
+    compare(gpu, ref, TOL["bf16"], "attn")
+    xd, dyd = to_device(x, "bf16"), to_device(dy, "bf16")
+    first = layer.backward(xd, dyd, "attn").clone()
+    grad = layer.grads["w_qkv"].clone()
+    for _ in range(3):
+        assert torch.equal(layer.backward(xd, dyd, "attn"), first)
+        assert torch.equal(layer.grads["w_qkv"], grad)
