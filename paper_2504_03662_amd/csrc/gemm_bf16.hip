@@ -243,6 +243,33 @@ GX_DEVINL void finish_run(const GemmArgs& g, size_t idx, const f32x4& xv, const 
   }
 }
 
+// Workgroups beyond the tiles read the next product's weights, so that it finds them in the memory-side cache.  With few
+// tokens a product is bound by what one compute unit can have in flight (20 GB/s of weights from memory, 30 from that cache,
+// for a 64 x 64 tile with 4 stages of 32 KB), and has fewer tiles than the chip has units: 128 x 5120 x 10240 on 160 of
+// them 64 -> 44 us.  Forward passes, us: hidden 5120, degree 2: 64 tokens 178 -> 162, 128 183 -> 161, 256 224 -> 195, 512
+// 280 -> 257, 768 305 -> 294, 1024 396 -> 374, 2048 (where operands are read for longer than weights) 663 / 663; hidden
+// 2048: 256 tokens 117 -> 112, 1024 178 -> 175; hidden 4096, degree 4: 256 tokens 100.6 / 100.2.
+// A workgroup reads at most what one with a tile reads, so that it does not outlast the product.
+// The values go to LDS, where nobody reads them: no registers, and nothing that could be optimised away.
+template <class T>
+GX_DEVINL void read_ahead(const GemmArgs& g, char* smem, int wave, int lane) {
+  constexpr int U = 8, CHUNK = U * T::THREADS * 16;
+  static_assert(CHUNK <= T::SMEM, "landing area");
+  const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(g.next, g.next_bytes);
+  const unsigned n = gridDim.x - g.tiles, me = blockIdx.x - g.tiles;
+  const unsigned chunks = g.next_bytes / CHUNK + 1, most = (unsigned)((long)g.K * ((T::BM + T::BN) * 2) / CHUNK);
+  const unsigned mine = min((chunks + n - 1 - me) / n, most);
+  for (unsigned k = 0; k < mine; k++) {
+#pragma unroll
+    for (int i = 0; i < U; i++)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(smem + (wave * U + i) * 1024), 16,
+                                               (me + k * n) * CHUNK + (unsigned)((wave * U + i) * 1024 + lane * 16), 0,
+                                               0, 0);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(U) : "memory");
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);                // nothing may land after this workgroup's LDS is given away
+}
+
 template <int LAY, int EPI, class T>
 __global__ void __launch_bounds__(T::THREADS, 2) gemm_kernel(GemmArgs g) {
   constexpr int BM = T::BM, BN = T::BN, KE = T::KE, KS = T::KS, STAGES = T::STAGES, TM = T::TM, TN = T::TN;
@@ -262,8 +289,9 @@ __global__ void __launch_bounds__(T::THREADS, 2) gemm_kernel(GemmArgs g) {
   // where a launch takes several rounds (8192^3 NT 779 -> 748 us, NN 807 -> 791; 28672 x 8192 x 4096 TN
   // 1606 -> 1554; within one round the two are equal).  Grids that are not a multiple of 8 are spread too
   // (2327 x 9752 x 7168 NT with GELU', 1463 tiles: 447 -> 353 us against consecutive numbering).
+  if (LAY == LAY_NN && (int)blockIdx.x >= g.tiles) return read_ahead<T>(g, smem, wave, lane);
   int pid = blockIdx.x;
-  const int nwg = gridDim.x;
+  const int nwg = g.tiles;
   const int xcd = pid & 7;
   pid = xcd * (nwg >> 3) + min(xcd, nwg & 7) + (pid >> 3);      // XCD's share: nwg / 8, one more for the first nwg % 8
   // tail launch: the walk runs over super-tiles of 2BM x 2BN (the tiles of the large-tile launch
@@ -570,6 +598,11 @@ __global__ void __launch_bounds__(T::THREADS, 2) gemm_kernel(GemmArgs g) {
   }
 }
 
+constexpr int ROUND = 256;                     // workgroups at work at once: one per compute unit
+// beyond 1024 tokens nothing is gained (see read_ahead), below 8 MB of weights (hidden 768: steps 0.4 % slower with) neither
+constexpr int READ_AHEAD_TOKENS = 1024;
+constexpr unsigned READ_AHEAD_BYTES = 8u << 20;
+
 template <int LAY, int EPI, class T>
 hipError_t launch_tile(const GemmArgs& g, hipStream_t s, int grid) {
   static bool configured = false;
@@ -581,6 +614,8 @@ hipError_t launch_tile(const GemmArgs& g, hipStream_t s, int grid) {
   }
   GemmArgs a = g;
   if (!a.tail) a.group = grid > 256 ? 4 : 8;
+  a.tiles = grid;
+  if (LAY == LAY_NN && a.next_bytes >= READ_AHEAD_BYTES && !a.tail && a.M <= READ_AHEAD_TOKENS && grid < ROUND) grid = ROUND;
   hipLaunchKernelGGL((gemm_kernel<LAY, EPI, T>), dim3(grid), dim3(T::THREADS), T::SMEM, s, a);
   return hipGetLastError();
 }
@@ -615,7 +650,6 @@ struct Tiny : Tile<64, 64, 1, 1, 4, 128, 4> { static constexpr float fixed = 3.8
 // Beyond whole rounds of large tiles, the remaining ones can also be cut into 128 x 128 tiles in a second
 // launch (TAIL is what that launch costs): NN 2048 x 10240 x 5120, 320 large tiles, 157 against 175
 // (Tall), 182 (Small) and 203 (Large alone).
-constexpr long ROUND = 256;
 constexpr float TAIL = 3.0f;
 template <class T>
 float price(long tiles, int K) {
@@ -706,7 +740,7 @@ extern "C" int gx_bf16_tile(int M, int N, int K, int column_sums) { return pick(
 
 hipError_t gemm_bf16(Layout lay, Epilogue epi, const GemmArgs& args, hipStream_t s) {
   GemmArgs g = args;
-  g.tail = g.tile_first = g.group = 0;       // the launcher's own fields
+  g.tail = g.tile_first = g.group = g.tiles = 0;       // the launcher's own fields
   if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipErrorInvalidValue;
   // 16-byte chunks along each operand's contiguous index; 31-bit byte offsets in buffer loads
   const long a_rows = (lay == LAY_TN) ? g.K : g.M, b_rows = (lay == LAY_NT) ? g.N : g.K;

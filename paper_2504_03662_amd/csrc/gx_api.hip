@@ -390,11 +390,16 @@ gx_status run_fwd(const gx_layer_cfg& c, const gx_params& p, const void* x, void
   const Drop dr = drop_of(c);
   const bool attn = c.flags & GX_PHASE_ATTN, mlp = c.flags & GX_PHASE_MLP;
   const void* h1 = x;
+  auto read_next = [&](GemmArgs& g, const void* w, long elements) {
+    g.next = w;
+    g.next_bytes = (unsigned)(elements * d.e);
+  };
   if (attn) {
     { ProfScope ps(GX_KC_LN_FWD, st);
     GX_TRY(ln_fwd(d.bf, x, p.ln1_g, p.ln1_b, sv.y1, sv.mean1, sv.rstd1, (int)d.T, (int)d.H, c.ln_eps, st)); }
     GemmArgs g = gargs(sv.y1, p.w_qkv, sv.qkv, d.T, 3 * d.Hl, d.H, d.H, 3 * d.Hl, 3 * d.Hl);
     g.bias = p.b_qkv;
+    if (mlp || !for_backward_only) read_next(g, p.w_o, d.Hl * d.H);
     GX_TRY(gemm(d, LAY_NN, EPI_BIAS, g, st));
     AttnArgs a;
     memset(&a, 0, sizeof(a));
@@ -408,6 +413,7 @@ gx_status run_fwd(const gx_layer_cfg& c, const gx_params& p, const void* x, void
       void* pa = p_attn ? p_attn : db.partial;
       GemmArgs o = gargs(sv.ctx, p.w_o, pa, d.T, d.H, d.Hl, d.Hl, d.H, d.H);
       o.bias = (c.flags & GX_ROW_BIAS_ATTN) ? p.b_o : nullptr;
+      read_next(o, p.w_fc1, d.H * d.Fl);
       GX_TRY(gemm(d, LAY_NN, EPI_BIAS, o, st));
       GX_TRY(dropout_p(d, dr, pa, x, sv.h1, DROP_STREAM_ATTN_OUT, st));
       h1 = sv.h1;
@@ -416,6 +422,7 @@ gx_status run_fwd(const gx_layer_cfg& c, const gx_params& p, const void* x, void
       o.bias = (c.flags & GX_ROW_BIAS_ATTN) ? p.b_o : nullptr;
       o.resid = x;
       o.aux = p_attn;
+      read_next(o, p.w_fc1, d.H * d.Fl);
       GX_TRY(gemm(d, LAY_NN, EPI_RESID, o, st));
       h1 = sv.h1;
     } else if (!for_backward_only) {
@@ -431,6 +438,7 @@ gx_status run_fwd(const gx_layer_cfg& c, const gx_params& p, const void* x, void
     f1.bias = p.b_fc1;
     f1.aux = sv.act;
     f1.gelu_tanh = (c.flags & GX_GELU_TANH) ? 1 : 0;
+    if (!for_backward_only) read_next(f1, p.w_fc2, d.Fl * d.H);
     GX_TRY(gemm(d, LAY_NN, EPI_GELU, f1, st));
     if (!for_backward_only) {
       void* pm = p_mlp ? p_mlp : db.partial;

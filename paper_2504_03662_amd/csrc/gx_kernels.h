@@ -36,10 +36,12 @@ struct GemmArgs {
   int gelu_tanh;       // EPI_GELU: tanh form of GELU instead of the erf form
   float* colpart;      // bf16 EPI_DGELU only, optional: partial column sums of the stored C over blocks of 64
                        // rows, [ceil(M / 64)][N] fp32 (stage 1 of the bias gradient; finished by colsum_finish)
+  const void* next;    // bf16 NN only, optional: weights that the next product of the chain reads (its B), 16-byte
+  unsigned next_bytes; // aligned; compute units that this product leaves idle may bring them nearer
   // set by the bf16 launcher only (callers leave them 0): a launch that covers the super-tiles
-  // (2 x 2 kernel tiles) numbered tile_first onwards in the tile walk, four workgroups each, and the
-  // tile-rows that the walk takes at a time
-  int tail, tile_first, group;
+  // (2 x 2 kernel tiles) numbered tile_first onwards in the tile walk, four workgroups each, the
+  // tile-rows that the walk takes at a time, and how many workgroups have a tile
+  int tail, tile_first, group, tiles;
 };
 
 hipError_t gemm_bf16(Layout lay, Epilogue epi, const GemmArgs& g, hipStream_t s);
