@@ -1069,9 +1069,17 @@ bool keys_over_four(const AttnArgs& a) {
   return a.S >= 768 && (blocks <= 256 || (blocks <= 512 && a.S > 4 * blocks));
 }
 
-// row-block kernels (dQ) in their two shapes, <4, 1, 64> and <2, 2, 32>: both 4 wavefronts
-// and two stages of 64 rows of K and of V
-constexpr int SMEM_MANY = 2 * 2 * 64 * ROWB, SMEM_FEW = 2 * 2 * 64 * ROWB;
+// The same for the dQ kernel, whose steps are longer, so that the start and the end matter more.  us, two / four, head dim
+// 128: 12 pairs of S 1024 21.4 / 22.1, 4 of S 1024 20.2 / 20.7, 8 of S 2048 35.8 / 34.3, 12 of S 2048 39.5 / 40.4, 8 of
+// S 4096 75.2 / 74.6, 4 of S 8192 142 / 135; head dim 64: 12 of S 1024 14.8 / 14.7, 8 of S 2048 22.8 / 20.2, 4 of S 8192
+// 81 / 72.
+bool dq_keys_over_four(const AttnArgs& a) {
+  const long blocks = (long)a.B * a.nl * cdiv(a.S, 64);
+  return a.S >= 2048 && (blocks <= 256 || a.S > 8 * blocks);
+}
+
+// the dQ kernel in its three shapes, <4, 1, 64>, <2, 2, 32> and <2, 4, 32>: two stages of 64 or 128 rows of K and of V
+constexpr int SMEM_MANY = 2 * 2 * 64 * ROWB, SMEM_FEW = 2 * 2 * 64 * ROWB, SMEM_FOUR_DQ = 2 * 2 * 128 * ROWB;
 
 hipError_t fwd(const AttnArgs& a, hipStream_t s) {
   if (!attn_shape_ok(a)) return hipErrorInvalidValue;
@@ -1117,6 +1125,8 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s) {
     if (e == hipSuccess) e = set_smem(attn_bwd_dkv_kernel<true>, KV_SMEM);
     if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<4, 1, 64, false>, SMEM_MANY);
     if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<2, 2, 32, false>, SMEM_FEW);
+    if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<2, 4, 32, false>, SMEM_FOUR_DQ);
+    if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<2, 4, 32, true>, SMEM_FOUR_DQ);
     if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<4, 1, 64, true>, SMEM_MANY);
     if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<2, 2, 32, true>, SMEM_FEW);
     if (e != hipSuccess) return e;
@@ -1130,7 +1140,10 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, bq) * npair), dim3(threads), smem, s, (const bf16*)a.qkv,
                        (const bf16*)a.ctx, (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, npair, keep_rows);
   };
-  if (few_pairs(a)) {
+  if (few_pairs(a) && dq_keys_over_four(a)) {
+    if (drop) go_dq(attn_bwd_dq_kernel<2, 4, 32, true>, 64, 512, SMEM_FOUR_DQ);
+    else go_dq(attn_bwd_dq_kernel<2, 4, 32, false>, 64, 512, SMEM_FOUR_DQ);
+  } else if (few_pairs(a)) {
     if (drop) go_dq(attn_bwd_dq_kernel<2, 2, 32, true>, 64, 256, SMEM_FEW);
     else go_dq(attn_bwd_dq_kernel<2, 2, 32, false>, 64, 256, SMEM_FEW);
   } else {

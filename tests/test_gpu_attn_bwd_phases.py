@@ -26,3 +26,15 @@ def test_query_tile_counts_against_the_oracle(seq, dh, drop):
     for _ in range(3):
         assert torch.equal(layer.backward(xd, dyd, "attn"), first)
         assert torch.equal(layer.grads["w_qkv"], grad)
+
+
+@pytest.mark.parametrize("drop", [0, 26])
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("seq", [2047, 2048, 2113])
+def test_dq_key_shares_against_the_oracle(seq, dh, drop):
+    # from 2048 keys on the dQ kernel spreads few pairs' keys over four wavefronts instead of two
+    shape = I.LayerShape(dh, 1, 64, 1, 1, 0, seq, 1, "bf16", drop_attn=drop, drop_seed=5 if drop else 0)
+    params = I.full_params(shape, case=900 + seq, random_affine=True)
+    x, dy = I.activations(shape, case=900 + seq)
+    gpu, ref, layer = run_both(shape, params, x, dy, "attn")
+    compare(gpu, ref, TOL["bf16"], "attn")
