@@ -246,9 +246,7 @@ GX_DEVINL void finish_run(const GemmArgs& g, size_t idx, const f32x4& xv, const 
 // Workgroups beyond the tiles read the next product's weights, so that it finds them in the memory-side cache.  With few
 // tokens a product is bound by what one compute unit can have in flight (20 GB/s of weights from memory, 30 from that cache,
 // for a 64 x 64 tile with 4 stages of 32 KB), and has fewer tiles than the chip has units: 128 x 5120 x 10240 on 160 of
-// them 64 -> 44 us.  Forward passes, us: hidden 5120, degree 2: 64 tokens 178 -> 162, 128 183 -> 161, 256 224 -> 195, 512
-// 280 -> 257, 768 305 -> 294, 1024 396 -> 374, 2048 (where operands are read for longer than weights) 663 / 663; hidden
-// 2048: 256 tokens 117 -> 112, 1024 178 -> 175; hidden 4096, degree 4: 256 tokens 100.6 / 100.2.
+// them 64 -> 44 us.  Where this is done: read_ahead_workgroups().
 // A workgroup reads at most what one with a tile reads, so that it does not outlast the product.
 // The values go to LDS, where nobody reads them: no registers, and nothing that could be optimised away.
 template <class T>
@@ -599,9 +597,26 @@ __global__ void __launch_bounds__(T::THREADS, 2) gemm_kernel(GemmArgs g) {
 }
 
 constexpr int ROUND = 256;                     // workgroups at work at once: one per compute unit
-// beyond 1024 tokens nothing is gained (see read_ahead), below 8 MB of weights (hidden 768: steps 0.4 % slower with) neither
-constexpr int READ_AHEAD_TOKENS = 1024;
-constexpr unsigned READ_AHEAD_BYTES = 8u << 20;
+// How many workgroups read ahead.  They cost the product bandwidth, and other streams the compute units that they hold, so:
+//  - the weights of the whole call exceed the memory-side cache; smaller ones may still be in it from the call before (one
+//    layer again and again: hidden 2048 64 tokens 79.6 us with nothing read ahead, 86.6 with, hidden 4096 degree 4 74.3 / 81.1,
+//    hidden 8192 degree 8 105.8 / 115.7; other layers in between 106.6 / 94.2, 100.4 / 92.4 and 152.8 / 145.3 are given up).
+//  - this product's weights and the next one's fit the cache together, or what is read ahead is gone by the time it is used
+//    (hidden 8192, degree 2: 512 tokens 428 / 442, 1024 701 / 714; hidden 5120, degree 1: 200 tokens 328 / 340).
+//  - more than 64 tokens and up to 256: fewer are bound by the bandwidth itself (1 token of hidden 4096 4.5 % slower, a stage
+//    of two blocks and two streams, 64 tokens, hidden 8192 degree 4, 2 %); more mostly by operands (hidden 8192, degree 4: 400
+//    tokens 238 / 253; hidden 6144, degree 2: 312 / 323; hidden 5120, degree 2: 512 tokens 280 / 254 are given up).
+//  - a quarter of the compute units at least has no tile: with fewer a stage loses (same stage, 256 tokens, 0.7 %).
+// Forward passes within that, other layers in between, without / with, us: hidden 5120, degree 2: 100 tokens 173 / 155, 256
+// 226 / 194; hidden 4096: 160 203 / 198; hidden 8192, degree 4: 160 214 / 203; hidden 6144, degree 2: 230 262 / 253;
+// stages of two blocks within 0.5 % either way.  One layer's 300 to 400 MB again and again, which the cache half holds, can still lose: hidden
+// 3584, 100 tokens 2.6 %, forward and backward of hidden 4096, 100 tokens 2.6 % (with other layers in between 4.5 and 2 % faster).
+constexpr long CACHE = 256L << 20;
+int read_ahead_workgroups(const GemmArgs& g, long tiles) {
+  if (g.M <= 64 || g.M > 256 || tiles > ROUND / 4 * 3) return 0;
+  if (g.call_weights <= CACHE || (long)g.N * g.K * 2 + g.next_bytes > CACHE / 8 * 7) return 0;
+  return ROUND - (int)tiles;
+}
 
 template <int LAY, int EPI, class T>
 hipError_t launch_tile(const GemmArgs& g, hipStream_t s, int grid) {
@@ -615,7 +630,7 @@ hipError_t launch_tile(const GemmArgs& g, hipStream_t s, int grid) {
   GemmArgs a = g;
   if (!a.tail) a.group = grid > 256 ? 4 : 8;
   a.tiles = grid;
-  if (LAY == LAY_NN && a.next_bytes >= READ_AHEAD_BYTES && !a.tail && a.M <= READ_AHEAD_TOKENS && grid < ROUND) grid = ROUND;
+  if (LAY == LAY_NN && a.next && !a.tail) grid += read_ahead_workgroups(a, grid);
   hipLaunchKernelGGL((gemm_kernel<LAY, EPI, T>), dim3(grid), dim3(T::THREADS), T::SMEM, s, a);
   return hipGetLastError();
 }
@@ -737,6 +752,27 @@ hipError_t dispatch_epi(Epilogue epi, const GemmArgs& g, hipStream_t s) {
 }  // namespace
 
 extern "C" int gx_bf16_tile(int M, int N, int K, int column_sums) { return pick(M, N, K, column_sums != 0); }
+
+extern "C" int gx_bf16_read_ahead(int M, int N, int K, long next_bytes, long call_weights) {
+  GemmArgs g = {};
+  g.M = M; g.N = N; g.K = K;
+  g.next_bytes = (unsigned)next_bytes;
+  g.call_weights = call_weights;
+  auto of = [&](auto tile) {
+    return read_ahead_workgroups(g, (long)cdiv(M, decltype(tile)::BM) * cdiv(N, decltype(tile)::BN));
+  };
+  switch (pick(M, N, K, false)) {
+    case PICK_LARGE: return of(Large());
+    case PICK_WIDE: return of(Wide());
+    case PICK_TALL: return of(Tall());
+    case PICK_HALF: return of(Half());
+    case PICK_SMALL: return of(Small());
+    case PICK_FLAT: return of(Flat());
+    case PICK_TINY: return of(Tiny());
+    case PICK_LARGE_TAIL: break;                 // more than a round of tiles
+  }
+  return 0;
+}
 
 hipError_t gemm_bf16(Layout lay, Epilogue epi, const GemmArgs& args, hipStream_t s) {
   GemmArgs g = args;

@@ -390,16 +390,20 @@ gx_status run_fwd(const gx_layer_cfg& c, const gx_params& p, const void* x, void
   const Drop dr = drop_of(c);
   const bool attn = c.flags & GX_PHASE_ATTN, mlp = c.flags & GX_PHASE_MLP;
   const void* h1 = x;
+  const long call_weights = ((attn ? 4 * d.H * d.Hl : 0) + (mlp ? 2 * d.H * d.Fl : 0)) * d.e;
   auto read_next = [&](GemmArgs& g, const void* w, long elements) {
+    // recomputation runs beside a backward pass, which has work for the compute units that a product leaves idle
+    if (for_backward_only) return;
     g.next = w;
     g.next_bytes = (unsigned)(elements * d.e);
+    g.call_weights = call_weights;
   };
   if (attn) {
     { ProfScope ps(GX_KC_LN_FWD, st);
     GX_TRY(ln_fwd(d.bf, x, p.ln1_g, p.ln1_b, sv.y1, sv.mean1, sv.rstd1, (int)d.T, (int)d.H, c.ln_eps, st)); }
     GemmArgs g = gargs(sv.y1, p.w_qkv, sv.qkv, d.T, 3 * d.Hl, d.H, d.H, 3 * d.Hl, 3 * d.Hl);
     g.bias = p.b_qkv;
-    if (mlp || !for_backward_only) read_next(g, p.w_o, d.Hl * d.H);
+    read_next(g, p.w_o, d.Hl * d.H);
     GX_TRY(gemm(d, LAY_NN, EPI_BIAS, g, st));
     AttnArgs a;
     memset(&a, 0, sizeof(a));
@@ -438,7 +442,7 @@ gx_status run_fwd(const gx_layer_cfg& c, const gx_params& p, const void* x, void
     f1.bias = p.b_fc1;
     f1.aux = sv.act;
     f1.gelu_tanh = (c.flags & GX_GELU_TANH) ? 1 : 0;
-    if (!for_backward_only) read_next(f1, p.w_fc2, d.Fl * d.H);
+    read_next(f1, p.w_fc2, d.Fl * d.H);
     GX_TRY(gemm(d, LAY_NN, EPI_GELU, f1, st));
     if (!for_backward_only) {
       void* pm = p_mlp ? p_mlp : db.partial;

@@ -38,6 +38,7 @@ struct GemmArgs {
                        // rows, [ceil(M / 64)][N] fp32 (stage 1 of the bias gradient; finished by colsum_finish)
   const void* next;    // bf16 NN only, optional: weights that the next product of the chain reads (its B), 16-byte
   unsigned next_bytes; // aligned; compute units that this product leaves idle may bring them nearer
+  long call_weights;   // with `next`: bytes of all the weights that the call reads
   // set by the bf16 launcher only (callers leave them 0): a launch that covers the super-tiles
   // (2 x 2 kernel tiles) numbered tile_first onwards in the tile walk, four workgroups each, the
   // tile-rows that the walk takes at a time, and how many workgroups have a tile
@@ -49,6 +50,9 @@ hipError_t gemm_bf16(Layout lay, Epilogue epi, const GemmArgs& g, hipStream_t s)
 // tell what their sizes reach: 0 256x256, 1 256x192, 2 192x256, 3 256x128, 4 128x128, 5 64x128, 6 64x64,
 // 7 256x256 with the remainder in 128x128.
 extern "C" int gx_bf16_tile(int M, int N, int K, int column_sums);
+// Workgroups without a tile with which gemm_bf16 launches an NN product whose successor reads next_bytes of weights, in
+// a call that reads call_weights bytes of them (host code, for tests)
+extern "C" int gx_bf16_read_ahead(int M, int N, int K, long next_bytes, long call_weights);
 hipError_t gemm_f32(Layout lay, Epilogue epi, const GemmArgs& g, hipStream_t s);
 
 // Causal attention over the local heads.  qkv is [T, 3*Hl] with column blocks [Q | K | V], each

@@ -1,12 +1,13 @@
-"""Forward products of few tokens have workgroups that only read the next product's weights, from 8 MB of them on: a
-last chunk that is not whole, either side of the 8 MB and of the 1024 tokens up to which it is done, in each phase;
-repeated, the same bits."""
+"""Forward products of few tokens in calls with many weights have workgroups that only read the next product's weights
+(the rule is host code: test_bf16_read_ahead_rule.py): all three products with and without it, last chunks that are not
+whole, and calls of other sizes and phases around it, which read nothing ahead; repeated, the same bits."""
 import pytest
 import torch
 
 from paper_2504_03662_amd import inputs as I
 from paper_2504_03662_amd.runtime import to_device
 from parity import TOL, compare, run_both
+from test_bf16_read_ahead_rule import forward_workgroups
 
 pytestmark = pytest.mark.gpu
 
@@ -25,3 +26,17 @@ def test_few_tokens_against_the_oracle(hidden, ffn, tokens, phase, recompute):
     first = layer.forward(xd, phase)[out].clone()
     for _ in range(3):
         assert torch.equal(layer.forward(xd, phase)[out], first)
+
+
+@pytest.mark.parametrize("tokens,expected", [(65, (64, 128, 124)), (144, (64, 64, 0)), (256, (64, 0, 124))])
+def test_products_that_read_ahead_against_the_oracle(tokens, expected):
+    shape = I.LayerShape(4096, 32, 8328, 1, 1, 0, tokens, 1, "bf16")        # weights of 270 MB
+    assert forward_workgroups(4096, 4096, 8328, tokens) == expected
+    params = I.full_params(shape, case=850 + tokens, random_affine=True)
+    x, dy = I.activations(shape, case=850 + tokens)
+    gpu, ref, layer = run_both(shape, params, x, dy, "both", recompute=tokens == 144)
+    compare(gpu, ref, TOL["bf16"], "both")
+    xd = to_device(x, "bf16")
+    first = layer.forward(xd, "both")["y"].clone()
+    for _ in range(3):
+        assert torch.equal(layer.forward(xd, "both")["y"], first)
