@@ -246,7 +246,7 @@ GX_DEVINL void finish_run(const GemmArgs& g, size_t idx, const f32x4& xv, const 
 // Workgroups beyond the tiles read the next product's weights, so that it finds them in the memory-side cache.  With few
 // tokens a product is bound by what one compute unit can have in flight (20 GB/s of weights from memory, 30 from that cache,
 // for a 64 x 64 tile with 4 stages of 32 KB), and has fewer tiles than the chip has units: 128 x 5120 x 10240 on 160 of
-// them 64 -> 44 us.  Where this is done: read_ahead_workgroups().
+// them 64 -> 44 us.  Where: read_ahead_pays(), read_ahead_workgroups().
 // A workgroup reads at most what one with a tile reads, so that it does not outlast the product.
 // The values go to LDS, where nobody reads them: no registers, and nothing that could be optimised away.
 template <class T>
@@ -268,7 +268,10 @@ GX_DEVINL void read_ahead(const GemmArgs& g, char* smem, int wave, int lane) {
   __builtin_amdgcn_s_waitcnt(0x0F70);                // nothing may land after this workgroup's LDS is given away
 }
 
-template <int LAY, int EPI, class T>
+// READ_AHEAD: the instance with workgroups beyond the tiles.  One of its own, because products of a few microseconds feel the
+// branch (forward half of hidden 768, 423 tokens, two products: 19.4 us, 19.9 with it in every instance and 136 bytes of
+// arguments instead of 112, which a launch copies).
+template <int LAY, int EPI, class T, bool READ_AHEAD>
 __global__ void __launch_bounds__(T::THREADS, 2) gemm_kernel(GemmArgs g) {
   constexpr int BM = T::BM, BN = T::BN, KE = T::KE, KS = T::KS, STAGES = T::STAGES, TM = T::TM, TN = T::TN;
   constexpr int WM = T::WM, WN = T::WN, NW = T::NW, KW = T::KW;
@@ -287,7 +290,8 @@ __global__ void __launch_bounds__(T::THREADS, 2) gemm_kernel(GemmArgs g) {
   // where a launch takes several rounds (8192^3 NT 779 -> 748 us, NN 807 -> 791; 28672 x 8192 x 4096 TN
   // 1606 -> 1554; within one round the two are equal).  Grids that are not a multiple of 8 are spread too
   // (2327 x 9752 x 7168 NT with GELU', 1463 tiles: 447 -> 353 us against consecutive numbering).
-  if (LAY == LAY_NN && (int)blockIdx.x >= g.tiles) return read_ahead<T>(g, smem, wave, lane);
+  if constexpr (READ_AHEAD)
+    if ((int)blockIdx.x >= g.tiles) return read_ahead<T>(g, smem, wave, lane);
   int pid = blockIdx.x;
   const int nwg = g.tiles;
   const int xcd = pid & 7;
@@ -612,27 +616,33 @@ constexpr int ROUND = 256;                     // workgroups at work at once: on
 // stages of two blocks within 0.5 % either way.  One layer's 300 to 400 MB again and again, which the cache half holds, can still lose: hidden
 // 3584, 100 tokens 2.6 %, forward and backward of hidden 4096, 100 tokens 2.6 % (with other layers in between 4.5 and 2 % faster).
 constexpr long CACHE = 256L << 20;
-int read_ahead_workgroups(const GemmArgs& g, long tiles) {
-  if (g.M <= 64 || g.M > 256 || tiles > ROUND / 4 * 3) return 0;
-  if (g.call_weights <= CACHE || (long)g.N * g.K * 2 + g.next_bytes > CACHE / 8 * 7) return 0;
-  return ROUND - (int)tiles;
+constexpr int READ_AHEAD_TILE = 128 * 128;     // so few tokens do not take larger ones in calls of so many weights
+template <class T>
+int read_ahead_workgroups(int M, int tiles) {
+  return T::BM * T::BN <= READ_AHEAD_TILE && M > 64 && M <= 256 && tiles <= ROUND / 4 * 3 ? ROUND - tiles : 0;
 }
 
-template <int LAY, int EPI, class T>
-hipError_t launch_tile(const GemmArgs& g, hipStream_t s, int grid) {
+template <int LAY, int EPI, class T, bool READ_AHEAD>
+hipError_t start(const GemmArgs& g, hipStream_t s, int grid) {
   static bool configured = false;
   if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<LAY, EPI, T>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_kernel<LAY, EPI, T, READ_AHEAD>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, T::SMEM);
     if (e != hipSuccess) return e;
     configured = true;
   }
+  hipLaunchKernelGGL((gemm_kernel<LAY, EPI, T, READ_AHEAD>), dim3(grid), dim3(T::THREADS), T::SMEM, s, g);
+  return hipGetLastError();
+}
+template <int LAY, int EPI, class T>
+hipError_t launch_tile(const GemmArgs& g, hipStream_t s, int grid) {
   GemmArgs a = g;
   if (!a.tail) a.group = grid > 256 ? 4 : 8;
   a.tiles = grid;
-  if (LAY == LAY_NN && a.next && !a.tail) grid += read_ahead_workgroups(a, grid);
-  hipLaunchKernelGGL((gemm_kernel<LAY, EPI, T>), dim3(grid), dim3(T::THREADS), T::SMEM, s, a);
-  return hipGetLastError();
+  if constexpr (LAY == LAY_NN && T::BM * T::BN <= READ_AHEAD_TILE)
+    if (a.next && !a.tail)
+      if (const int more = read_ahead_workgroups<T>(a.M, grid)) return start<LAY, EPI, T, true>(a, s, grid + more);
+  return start<LAY, EPI, T, false>(a, s, grid);
 }
 template <int LAY, int EPI, class T>
 hipError_t launch_whole(const GemmArgs& g, hipStream_t s) {
@@ -753,13 +763,15 @@ hipError_t dispatch_epi(Epilogue epi, const GemmArgs& g, hipStream_t s) {
 
 extern "C" int gx_bf16_tile(int M, int N, int K, int column_sums) { return pick(M, N, K, column_sums != 0); }
 
-extern "C" int gx_bf16_read_ahead(int M, int N, int K, long next_bytes, long call_weights) {
-  GemmArgs g = {};
-  g.M = M; g.N = N; g.K = K;
-  g.next_bytes = (unsigned)next_bytes;
-  g.call_weights = call_weights;
+bool read_ahead_pays(long own_bytes, long next_bytes, long call_bytes) {
+  return call_bytes > CACHE && own_bytes + next_bytes <= CACHE / 8 * 7;
+}
+
+extern "C" int gx_bf16_read_ahead(int M, int N, int K, long next_bytes, long call_bytes) {
+  if (!read_ahead_pays((long)N * K * 2, next_bytes, call_bytes)) return 0;
   auto of = [&](auto tile) {
-    return read_ahead_workgroups(g, (long)cdiv(M, decltype(tile)::BM) * cdiv(N, decltype(tile)::BN));
+    using T = decltype(tile);
+    return read_ahead_workgroups<T>(M, cdiv(M, T::BM) * cdiv(N, T::BN));
   };
   switch (pick(M, N, K, false)) {
     case PICK_LARGE: return of(Large());

@@ -390,13 +390,12 @@ gx_status run_fwd(const gx_layer_cfg& c, const gx_params& p, const void* x, void
   const Drop dr = drop_of(c);
   const bool attn = c.flags & GX_PHASE_ATTN, mlp = c.flags & GX_PHASE_MLP;
   const void* h1 = x;
-  const long call_weights = ((attn ? 4 * d.H * d.Hl : 0) + (mlp ? 2 * d.H * d.Fl : 0)) * d.e;
+  const long call_bytes = ((attn ? 4 * d.H * d.Hl : 0) + (mlp ? 2 * d.H * d.Fl : 0)) * d.e;
   auto read_next = [&](GemmArgs& g, const void* w, long elements) {
     // recomputation runs beside a backward pass, which has work for the compute units that a product leaves idle
-    if (for_backward_only) return;
+    if (!d.bf || for_backward_only || !read_ahead_pays((long)g.N * g.K * d.e, elements * d.e, call_bytes)) return;
     g.next = w;
     g.next_bytes = (unsigned)(elements * d.e);
-    g.call_weights = call_weights;
   };
   if (attn) {
     { ProfScope ps(GX_KC_LN_FWD, st);

@@ -32,27 +32,30 @@ struct GemmArgs {
   const void* bias;    // [N], storage type
   const void* resid;   // [M, ldc], storage type
   void* aux;           // [M, ldc], storage type
-  const void* z;       // [M, ldc], storage type: EPI_DGELU's multiplier
+  union {
+    const void* z;     // [M, ldc], storage type: EPI_DGELU's multiplier
+    const void* next;  // bf16 NN only, optional: weights that the next product of the chain reads (its B), 16-byte
+  };                   // aligned; compute units that this product leaves idle may bring them nearer
   int gelu_tanh;       // EPI_GELU: tanh form of GELU instead of the erf form
+  unsigned next_bytes;
   float* colpart;      // bf16 EPI_DGELU only, optional: partial column sums of the stored C over blocks of 64
                        // rows, [ceil(M / 64)][N] fp32 (stage 1 of the bias gradient; finished by colsum_finish)
-  const void* next;    // bf16 NN only, optional: weights that the next product of the chain reads (its B), 16-byte
-  unsigned next_bytes; // aligned; compute units that this product leaves idle may bring them nearer
-  long call_weights;   // with `next`: bytes of all the weights that the call reads
   // set by the bf16 launcher only (callers leave them 0): a launch that covers the super-tiles
   // (2 x 2 kernel tiles) numbered tile_first onwards in the tile walk, four workgroups each, the
   // tile-rows that the walk takes at a time, and how many workgroups have a tile
   int tail, tile_first, group, tiles;
 };
+static_assert(sizeof(GemmArgs) == 112, "a launch copies it: 136 bytes cost a product 0.2 us");
 
 hipError_t gemm_bf16(Layout lay, Epilogue epi, const GemmArgs& g, hipStream_t s);
 // Which tile gemm_bf16 takes for an M x N x K product (column_sums: EPI_DGELU), host code, so that tests can
 // tell what their sizes reach: 0 256x256, 1 256x192, 2 192x256, 3 256x128, 4 128x128, 5 64x128, 6 64x64,
 // 7 256x256 with the remainder in 128x128.
 extern "C" int gx_bf16_tile(int M, int N, int K, int column_sums);
-// Workgroups without a tile with which gemm_bf16 launches an NN product whose successor reads next_bytes of weights, in
-// a call that reads call_weights bytes of them (host code, for tests)
-extern "C" int gx_bf16_read_ahead(int M, int N, int K, long next_bytes, long call_weights);
+// Whether reading ahead can pay for a product of own_bytes of weights before one of next_bytes in a call of call_bytes
+bool read_ahead_pays(long own_bytes, long next_bytes, long call_bytes);
+// Workgroups without a tile with which gemm_bf16 then launches an NN product (host code, for tests)
+extern "C" int gx_bf16_read_ahead(int M, int N, int K, long next_bytes, long call_bytes);
 hipError_t gemm_f32(Layout lay, Epilogue epi, const GemmArgs& g, hipStream_t s);
 
 // Causal attention over the local heads.  qkv is [T, 3*Hl] with column blocks [Q | K | V], each
