@@ -949,6 +949,7 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
   float dd = (d4[0] + d4[1]) + (d4[2] + d4[3]);
   dd += __shfl_xor(dd, 32, 64);
   if (part == 0 && g == 0 && i < S) dsum[((size_t)b * nl + h) * S + i] = dd;
+  const unsigned* kwords = DROP ? keep.bits + (((size_t)b * nl + h) * S + ic) * keep.wpr : nullptr;
   WAIT_VM0();
   __syncthreads();
   for (int t = 0; t < nt; t++) {
@@ -961,9 +962,8 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
     if (j0 <= iw + 31) {
       const char* kt = smem + (t & 1) * STAGE + part * BKV * ROWB;
       const char* vt = kt + ROWS * ROWB;
-      unsigned long long kw = ~0ull;                    // keep bits of this query's keys of the step
-      if (DROP && i < S)
-        kw = keep_bits_of_step<NJT>(keep.bits + (((size_t)b * nl + h) * S + i) * keep.wpr, j0);
+      unsigned long long kw = 0;                        // keep bits of this query's keys of the step
+      if (DROP) kw = keep_bits_of_step<NJT>(kwords, j0);
       f32x16 sacc[NJT], pacc[NJT];
 #pragma unroll
       for (int jt = 0; jt < NJT; jt++) {
@@ -976,11 +976,15 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
         }
       }
       if (DROP) {                                      // gradient w.r.t. the undropped probabilities
+        // Left to mix the masks into the products the compiler needs 12 registers more than there are at head dim 128
+        // (64 pairs of S 2048: 209 us, 150 as it is) and 175 at head dim 64, two wavefronts per SIMD (128 pairs 176, 160).
+        asm volatile("" : "+v"(kw));                   // the keep bits are waited for here, after the products (164 without)
         drop_unkept<NJT>(pacc, kw, g);
 #pragma unroll
         for (int jt = 0; jt < NJT; jt++)
 #pragma unroll
           for (int v = 0; v < 16; v++) pacc[jt][v] *= keep.scale;
+        __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
       for (int jt = 0; jt < NJT; jt++)
