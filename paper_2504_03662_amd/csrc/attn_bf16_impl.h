@@ -219,6 +219,12 @@ GX_DEVINL void drop_unkept(f32x16 (&a)[NJT], unsigned long long kw, int g) {
       if (!((w >> (8 * (v >> 2) + (v & 3))) & 1u)) a[jt][v] = 0.f;
   }
 }
+// registers 8 h .. 8 h + 7 of one tile, w = its word shifted down by 4 g
+GX_DEVINL void drop_unkept_half(f32x16& a, unsigned w, int h) {
+#pragma unroll
+  for (int v = 8 * h; v < 8 * h + 8; v++)
+    if (!((w >> (8 * (v >> 2) + (v & 3))) & 1u)) a[v] = 0.f;
+}
 // this lane's keep bits of the BKV keys starting at key j0 of one query row (bits: the row's words)
 template <int NJT>
 GX_DEVINL unsigned long long keep_bits_of_step(const unsigned* row_words, int j0) {
@@ -457,6 +463,10 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, 2)
       bool moved = false;
       // the softmax of step t for query column i (base-2 exponentials, scale folded into the exponent's multiply-add)
       // in pieces: 0 mask, 1 reference, then EPP scores each, a head-dim block of O to rescale each, 16 keys to round each
+      // SPREAD: the keep bits of each 16 keys where these are rounded, not all at once.  At head dim 64 that also takes 166
+      // registers instead of 173, three wavefronts per SIMD instead of two (128 pairs of S 2048 118 -> 111 us); at 128
+      // it is slower (64 pairs of S 2048 98.0, 99.7).
+      constexpr bool SPREAD = DROP && DH == 64;
       constexpr int EPP = 2;
       constexpr int NE = 16 * NJT / EPP, P_E = 2, P_R = P_E + NE, P_P = P_R + NDT, NPIECE = P_P + NG;
       auto piece = [&](auto K) __attribute__((always_inline)) {
@@ -510,16 +520,15 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, 2)
           }
         } else {
           constexpr int u = k - P_P;
-          if constexpr (DROP && u == 0) {
-            lsum += psum;
-            drop_unkept<NJT>(sacc, kw, g);
-          }
+          if (DROP && u == 0) lsum += psum;            // the undropped sum
+          if constexpr (SPREAD) drop_unkept_half(sacc[u >> 1], (unsigned)(kw >> (32 * (u >> 1))) >> (4 * g), u & 1);
+          else if (DROP && u == 0) drop_unkept<NJT>(sacc, kw, g);
           pf[u] = pack_half(sacc[u >> 1], u & 1);
         }
       };
       // cost of the pieces in issue slots, for spreading them over the matrix instructions
       constexpr auto cost = [](int k) constexpr {
-        return k == 0 ? 4 : k == 1 ? 12 + 8 * NJT : k < P_R ? 6 * EPP : k < P_P ? (LAZY ? 1 : 16) : 4;
+        return k == 0 ? 4 : k == 1 ? 12 + 8 * NJT : k < P_R ? 6 * EPP : k < P_P ? (LAZY ? 1 : 16) : SPREAD ? 20 : 4;
       };
       constexpr auto upto = [cost](int k) constexpr { int c = 0; for (int x = 0; x < k; x++) c += cost(x); return c; };
       constexpr int TOTAL = upto(NPIECE);

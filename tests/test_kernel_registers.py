@@ -45,13 +45,13 @@ def _of(kernels, dh, name):
 
 
 @pytest.mark.parametrize("dh", [64, 128])
-@pytest.mark.parametrize("name", ["attn_bwd_dq_kernel"])
+@pytest.mark.parametrize("name", ["attn_bwd_dq_kernel", "attn_bwd_dkv_kernel", "attn_fwd_kernel"])
 def test_attention_kernels_do_not_spill(kernels, dh, name):
     for n, k in _of(kernels, dh, name).items():
         assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, n
 
 
-@pytest.mark.parametrize("name", ["attn_bwd_dq_kernel"])
+@pytest.mark.parametrize("name", ["attn_bwd_dq_kernel", "attn_bwd_dkv_kernel", "attn_fwd_kernel"])
 def test_three_wavefronts_per_simd_at_head_dim_64(kernels, name):
     for n, k in _of(kernels, 64, name).items():
         if k[".max_flat_workgroup_size"] == 256:
