@@ -43,6 +43,13 @@ hipError_t attn_fwd_bf16(const AttnArgs& a, hipStream_t s) {
   return a.dh == 128 ? dh128::fwd(a, s) : a.dh == 64 ? dh64::fwd(a, s) : hipErrorInvalidValue;
 }
 
+extern "C" int gx_attn_key_shares(int B, int S, int nl, int dh, int backward) {
+  AttnArgs a = {};
+  a.B = B; a.S = S; a.nl = nl; a.dh = dh;
+  if (dh == 128) return backward ? dh128::dq_key_shares(a) : dh128::fwd_key_shares(a);
+  return backward ? dh64::dq_key_shares(a) : dh64::fwd_key_shares(a);
+}
+
 hipError_t attn_bwd_bf16(const AttnArgs& a, hipStream_t s) {
   return a.dh == 128 ? dh128::bwd(a, s) : a.dh == 64 ? dh64::bwd(a, s) : hipErrorInvalidValue;
 }

@@ -1069,27 +1069,33 @@ bool attn_shape_ok(const AttnArgs& a) {
 }
 
 // With few (sample, head) pairs the chip is filled by cutting the query blocks fine and spreading
-// each block's keys over two wavefronts (see the forward kernel).
+// each block's keys over two or four wavefronts (see the forward kernel).
 bool few_pairs(const AttnArgs& a) { return (long)a.B * a.nl * cdiv(a.S, 128) <= 384; }
 
 // Few pairs, forward: the keys of a step over four wavefronts instead of two where the workgroups of 64 query rows
-// then still find a compute unit each, or are at most two per unit and so long that a unit's two would spend most of
-// their time one after the other (a long and a short one together).  Each has a longer start and end, so the keys
-// must be many.  us, two / four: 12 pairs of S 1024 14.7 / 14.0, of S 512 10.0 / 10.5, 12 of S 2048 27.9 / 25.9,
-// 16 of S 2048 28.1 / 28.9, 8 of S 4096 50.1 / 46.6, 4 of S 8192 108 / 87.
+// then still find a compute unit each, or are at most two per unit of fewer than 16 pairs, whose sequences are then so long
+// that a unit's two would spend most of their time one after the other (a long and a short one together).  Each has a longer
+// start and end, so the keys must be many.  us, two / four: 12 pairs of S 1024 14.7 / 14.0, of S 512 10.0 / 10.5, 12 of S 2048
+// 27.9 / 25.9, 16 of S 2048 28.1 / 28.9, 8 of S 4096 50.1 / 46.6, 4 of S 8192 108 / 87.
 bool keys_over_four(const AttnArgs& a) {
-  const long blocks = (long)a.B * a.nl * cdiv(a.S, 64);
-  return a.S >= 768 && (blocks <= 256 || (blocks <= 512 && a.S > 4 * blocks));
+  const long pairs = (long)a.B * a.nl, blocks = pairs * cdiv(a.S, 64);
+  return a.S >= 768 && (blocks <= 256 || (blocks <= 512 && pairs < 16));
 }
 
 // The same for the dQ kernel, whose steps are longer, so that the start and the end matter more.  us, two / four, head dim
-// 128: 12 pairs of S 1024 21.4 / 22.1, 4 of S 1024 20.2 / 20.7, 8 of S 2048 35.8 / 34.3, 12 of S 2048 39.5 / 40.4, 8 of
-// S 4096 75.2 / 74.6, 4 of S 8192 142 / 135; head dim 64: 12 of S 1024 14.8 / 14.7, 8 of S 2048 22.8 / 20.2, 4 of S 8192
-// 81 / 72.
+// 128: 12 pairs of S 1024 21.4 / 22.1, 4 of S 1024 20.2 / 20.7, 2 of S 2048 33.5 / 30.6, 8 of S 2048 34.8 / 33.6, 12 of S 2048
+// 40.9 / 40.0, 4 of S 4096 61.4 / 55.2, 7 of S 4096 73.6 / 68.3, 8 of S 4096 76.4 / 77.1, 4 of S 8192 140.5 / 132.3, 5 of S 8192
+// (640 workgroups, one per unit: a third round) 153.7 / 183.2, 6 184.3 / 198.1, with dropout 226 / 251.  Head dim 64, where two
+// share a unit: 12 of S 1024 14.8 / 14.7, 8 of S 2048 22.6 / 19.4, 7 of S 4096 43.5 / 37.9, 4, 5, 6 of S 8192 81.5 / 71.2, 89.5 /
+// 81.1, 95.0 / 92.5.
 bool dq_keys_over_four(const AttnArgs& a) {
-  const long blocks = (long)a.B * a.nl * cdiv(a.S, 64);
-  return a.S >= 2048 && (blocks <= 256 || a.S > 8 * blocks);
+  const long pairs = (long)a.B * a.nl, blocks = pairs * cdiv(a.S, 64);
+  return a.S >= 2048 && (blocks <= 256 || (pairs < 8 && (blocks <= 512 || DH == 64)));
 }
+
+// over how many wavefronts the keys of a query block are spread (1: many pairs)
+int fwd_key_shares(const AttnArgs& a) { return !few_pairs(a) ? 1 : keys_over_four(a) ? 4 : 2; }
+int dq_key_shares(const AttnArgs& a) { return !few_pairs(a) ? 1 : dq_keys_over_four(a) ? 4 : 2; }
 
 // the dQ kernel in its three shapes, <4, 1, 64>, <2, 2, 32> and <2, 4, 32>: two stages of 64 or 128 rows of K and of V
 constexpr int SMEM_MANY = 2 * 2 * 64 * ROWB, SMEM_FEW = 2 * 2 * 64 * ROWB, SMEM_FOUR_DQ = 2 * 2 * 128 * ROWB;
@@ -1116,10 +1122,11 @@ hipError_t fwd(const AttnArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, bq) * npair), dim3(threads), smem, s, (const bf16*)a.qkv, (bf16*)a.ctx,
                        a.lse, a.S, a.nl, npair, keep);
   };
-  if (!few_pairs(a)) {
+  const int shares = fwd_key_shares(a);
+  if (shares == 1) {
     if (drop) go(attn_fwd_kernel<4, 1, 64, false, true>, 128, 256, SMEM_MANY_FWD);
     else go(attn_fwd_kernel<4, 1, 64, false, false>, 128, 256, SMEM_MANY_FWD);
-  } else if (keys_over_four(a)) {
+  } else if (shares == 4) {
     if (drop) go(attn_fwd_kernel<2, 4, 32, true, true>, 64, 512, SMEM_FOUR);
     else go(attn_fwd_kernel<2, 4, 32, true, false>, 64, 512, SMEM_FOUR);
   } else {
@@ -1153,10 +1160,11 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, bq) * npair), dim3(threads), smem, s, (const bf16*)a.qkv,
                        (const bf16*)a.ctx, (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, npair, keep_rows);
   };
-  if (few_pairs(a) && dq_keys_over_four(a)) {
+  const int shares = dq_key_shares(a);
+  if (shares == 4) {
     if (drop) go_dq(attn_bwd_dq_kernel<2, 4, 32, true>, 64, 512, SMEM_FOUR_DQ);
     else go_dq(attn_bwd_dq_kernel<2, 4, 32, false>, 64, 512, SMEM_FOUR_DQ);
-  } else if (few_pairs(a)) {
+  } else if (shares == 2) {
     if (drop) go_dq(attn_bwd_dq_kernel<2, 2, 32, true>, 64, 256, SMEM_FEW);
     else go_dq(attn_bwd_dq_kernel<2, 2, 32, false>, 64, 256, SMEM_FEW);
   } else {
