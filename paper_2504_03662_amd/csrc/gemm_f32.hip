@@ -65,7 +65,8 @@ GX_DEVINL f32x4 frag(const char* sub, int row, int c, int g) {
   return f32x4{p[0], p[BM], p[2 * BM], p[3 * BM]};
 }
 
-template <int LAY, int EPI, int BM, int KW, int STAGES>
+// AHEAD: the next stage's fragments are read between the products; else at the start of their own stage (see pick()).
+template <int LAY, int EPI, int BM, int KW, int STAGES, bool AHEAD>
 __global__ void __launch_bounds__(BM * BM * KW / 16) gemm_f32_kernel(GemmArgs g) {
   constexpr bool A_K = (LAY != LAY_TN), B_K = (LAY == LAY_NT);
   constexpr int WR = BM / 32, NW = WR * WR * KW, NT = 64 * NW;
@@ -94,7 +95,6 @@ __global__ void __launch_bounds__(BM * BM * KW / 16) gemm_f32_kernel(GemmArgs g)
 
   constexpr int LPT = la.PER + lb.PER;                  // loads per wavefront and stage
   static_assert((STAGES - 1) * LPT < 64, "vmcnt immediate");
-  constexpr bool AHEAD = BM > 32;                       // with a few stages in all the extra start costs more than it saves
   const int nk = (g.K + 32 * KW - 1) / (32 * KW);
   auto request = [&](int t, int slot) __attribute__((always_inline)) {   // stages beyond K: out of range, zeros, no traffic
     la.issue(smem + slot * STAGE, t * 32 * KW, wave);
@@ -220,17 +220,17 @@ __global__ void __launch_bounds__(BM * BM * KW / 16) gemm_f32_kernel(GemmArgs g)
   }
 }
 
-template <int LAY, int EPI, int BM, int KW, int STAGES>
+template <int LAY, int EPI, int BM, int KW, int STAGES, bool AHEAD>
 hipError_t launch_tile(const GemmArgs& g, hipStream_t s) {
   constexpr int SMEM = STAGES * 2 * KW * BM * 128;
   static bool configured = false;
   if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_kernel<LAY, EPI, BM, KW, STAGES>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_kernel<LAY, EPI, BM, KW, STAGES, AHEAD>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
     if (e != hipSuccess) return e;
     configured = true;
   }
-  hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI, BM, KW, STAGES>), dim3(cdiv(g.M, BM) * cdiv(g.N, BM)),
+  hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI, BM, KW, STAGES, AHEAD>), dim3(cdiv(g.M, BM) * cdiv(g.N, BM)),
                      dim3(BM * BM * KW / 16), SMEM, s, g);
   return hipGetLastError();
 }
@@ -244,12 +244,28 @@ hipError_t launch_tile(const GemmArgs& g, hipStream_t s) {
 //                         9.8/20.0/22.0    18.0/20/22       31/20.4/21.6     42/36.5/37.1    130/71/69.5      502/276/270
 // and at 768 tiles 99/54.0/54.3.  With fragments read at the start of their own stage, three and four stages: 768 tiles 58,
 // 1024 tiles 77, 4096 tiles 280, 1024 1024 4096 (NT) 75.6 against 70.  The largest is 127 TFLOP/s of a peak of 157.
+// Short reductions, the weight gradients of few tokens, end before the extra start has paid and keep that older form
+// (forward and backward, us, without / with it: hidden 768, 128 tokens 217 / 210, hidden 1024, 128 tokens 255 / 248, hidden
+// 2048, 33 tokens 428 / 410; with it from 192 tokens on hidden 768 is 2 to 5 % slower).  Hidden 512, whose weight gradients
+// are one round of tiles beside the other stream, would be 1 to 2 % faster with it up to 512 tokens (256 tokens 205 / 201),
+// hidden 768 and 1024 1 to 2 % slower, by the same tiles.
+enum Pick { PICK_32, PICK_64_TWO, PICK_64_ONE, PICK_64_TWO_SHORT, PICK_64_ONE_SHORT };
+Pick pick(int M, int N, int K) {
+  const long t64 = (long)cdiv(M, 64) * cdiv(N, 64);
+  if (t64 <= 128) return PICK_32;
+  if (K <= 160) return t64 <= 256 ? PICK_64_TWO_SHORT : PICK_64_ONE_SHORT;
+  return t64 <= 768 ? PICK_64_TWO : PICK_64_ONE;
+}
 template <int LAY, int EPI>
 hipError_t launch(const GemmArgs& g, hipStream_t s) {
-  const long t64 = (long)cdiv(g.M, 64) * cdiv(g.N, 64);
-  if (t64 <= 128) return launch_tile<LAY, EPI, 32, 4, 4>(g, s);
-  if (t64 <= 768) return launch_tile<LAY, EPI, 64, 2, 2>(g, s);
-  return launch_tile<LAY, EPI, 64, 1, 2>(g, s);
+  switch (pick(g.M, g.N, g.K)) {
+    case PICK_32: return launch_tile<LAY, EPI, 32, 4, 4, false>(g, s);
+    case PICK_64_TWO: return launch_tile<LAY, EPI, 64, 2, 2, true>(g, s);
+    case PICK_64_ONE: return launch_tile<LAY, EPI, 64, 1, 2, true>(g, s);
+    case PICK_64_TWO_SHORT: return launch_tile<LAY, EPI, 64, 2, 4, false>(g, s);
+    case PICK_64_ONE_SHORT: return launch_tile<LAY, EPI, 64, 1, 3, false>(g, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 // The combinations that the layer driver asks for.
@@ -270,6 +286,8 @@ hipError_t dispatch_epi(Epilogue epi, const GemmArgs& g, hipStream_t s) {
 }
 
 }  // namespace
+
+extern "C" int gx_f32_tile(int M, int N, int K) { return pick(M, N, K); }
 
 hipError_t gemm_f32(Layout lay, Epilogue epi, const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipErrorInvalidValue;

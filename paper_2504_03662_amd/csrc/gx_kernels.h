@@ -56,6 +56,9 @@ extern "C" int gx_bf16_tile(int M, int N, int K, int column_sums);
 bool read_ahead_pays(long own_bytes, long next_bytes, long call_bytes);
 // Workgroups without a tile with which gemm_bf16 then launches an NN product (host code, for tests)
 extern "C" int gx_bf16_read_ahead(int M, int N, int K, long next_bytes, long call_bytes);
+// Which kernel gemm_f32 takes (host code, for tests): 0 32x32 tiles with four wavefronts, 64x64 with 1 two and 2 one per 32x32
+// block, 3 and 4 the same for short reductions
+extern "C" int gx_f32_tile(int M, int N, int K);
 hipError_t gemm_f32(Layout lay, Epilogue epi, const GemmArgs& g, hipStream_t s);
 
 // Causal attention over the local heads.  qkv is [T, 3*Hl] with column blocks [Q | K | V], each

@@ -1,11 +1,14 @@
 """fp32 products and attention at the edges of their tiles: remainders of the 32 / 64 row tiles and of
 the reduction stages, head dimensions that are padded, every tile size of the dispatch, and values
 that are not finite in positions that the causal mask hides."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 from oracle import layer as O
+from paper_2504_03662_amd import binding as gx
 from paper_2504_03662_amd import inputs as I
 from paper_2504_03662_amd.runtime import DeviceLayer, to_device, to_host
 from parity import TOL, check, compare, run_both
@@ -20,8 +23,8 @@ pytestmark = pytest.mark.gpu
     (100, 2, 200, 65, 2),       # head dim 50: rows that are not multiples of 16 bytes
     (96, 1, 324, 129, 2),       # head dim 96, five key tiles: one wavefront takes two
     (256, 2, 516, 160, 2),      # head dim 128
-    (768, 12, 772, 700, 1),     # 64-row tiles, one and two wavefronts per block
-    (512, 8, 2052, 1030, 2),    # more 64-row tiles than compute units, 33 key tiles
+    (768, 12, 772, 700, 1),     # 64-row tiles, two wavefronts per block
+    (512, 8, 2052, 1030, 2),    # 64-row tiles, more than three per compute unit too (one wavefront per block), 33 key tiles
 ])
 def test_fp32_tile_edges(hidden, heads, ffn, seq, batch):
     shape = I.LayerShape(hidden, heads, ffn, 1, 1, 0, seq, batch, "f32")
@@ -29,6 +32,45 @@ def test_fp32_tile_edges(hidden, heads, ffn, seq, batch):
     x, dy = I.activations(shape, case=400 + seq)
     gpu, ref, _ = run_both(shape, params, x, dy, want_partials=True)
     compare(gpu, ref, TOL["f32"], want_partials=True)
+
+
+def _tile(m, n, k):
+    f = gx.lib().gx_f32_tile
+    f.argtypes, f.restype = [ctypes.c_int] * 3, ctypes.c_int
+    return f(m, n, k)
+
+
+def test_fp32_one_wavefront_per_block_ragged_reductions():
+    # 64-row tiles with one wavefront per block in all three layouts, each with an odd number of stages of 32 reduction
+    # steps whose last one is not whole, and a weight gradient of four stages; stored and added to
+    shape = I.LayerShape(1036, 14, 4100, 1, 1, 0, 1030, 1, "f32")
+    t, h, f = shape.tokens, shape.hidden, shape.ffn
+    assert {_tile(t, 3 * h, h), _tile(t, f, h), _tile(h, f, t)} == {2}      # NN; NN and NT; TN
+    assert all(-(-k // 32) % 2 == 1 and k % 32 for k in (h, t))
+    params = I.full_params(shape, case=480, random_affine=True)
+    x, dy = I.activations(shape, case=480)
+    gpu, ref, layer = run_both(shape, params, x, dy, want_partials=True)
+    compare(gpu, ref, TOL["f32"], want_partials=True)
+    layer.backward(to_device(x, "f32"), to_device(dy, "f32"), accumulate=True)
+    torch.cuda.synchronize()
+    for n in I.PARAM_NAMES:
+        np.testing.assert_array_equal(to_host(layer.grads[n]), 2 * gpu["grads"][n])
+
+
+@pytest.mark.parametrize("tokens", [1, 31, 64, 97, 160, 161])
+def test_fp32_weight_gradients_of_few_tokens(tokens):
+    # the kernels for short reductions, one to five stages of 32 or 64 steps, whole and not, and one token beyond
+    shape = I.LayerShape(516, 6, 2060, 1, 1, 0, tokens, 1, "f32")
+    long = tokens > 160
+    assert _tile(516, 1548, tokens) == (1 if long else 3) and _tile(516, 2060, tokens) == (1 if long else 4)
+    params = I.full_params(shape, case=490 + tokens, random_affine=True)
+    x, dy = I.activations(shape, case=490 + tokens)
+    gpu, ref, layer = run_both(shape, params, x, dy, want_partials=True)
+    compare(gpu, ref, TOL["f32"], want_partials=True)
+    layer.backward(to_device(x, "f32"), to_device(dy, "f32"), accumulate=True)
+    torch.cuda.synchronize()
+    for n in I.PARAM_NAMES:
+        np.testing.assert_array_equal(to_host(layer.grads[n]), 2 * gpu["grads"][n])
 
 
 def test_fp32_accumulation_and_dropout_with_padded_heads():
