@@ -19,26 +19,7 @@ GX_DEVINL int swz(int r) {
   return ((x & 1) << 2) | (x >> 1);
 }
 
-// direct-to-LDS load of ROWS x DH starting at global row `row0` of one (sample, head, q|k|v)
-// column block; rows at or beyond `nrows` are zero-filled.  elem0 = element offset of (row 0,
-// first column) from the tensor start; ld = row stride in elements.
-template <int ROWS, int NW>
-GX_DEVINL void tile_load(__amdgpu_buffer_rsrc_t rsrc, unsigned elem0, int ld, int row0, int nrows, char* dst,
-                         int wave, int lane) {
-  constexpr int RPI = 64 / CPR;                        // rows per 64-lane instruction
-  constexpr int PER_WAVE = ROWS / RPI / NW;
-  static_assert(PER_WAVE >= 1, "tile too small for the workgroup");
-#pragma unroll
-  for (int i = 0; i < PER_WAVE; i++) {
-    const int q = wave * PER_WAVE + i;
-    const int r = RPI * q + lane / CPR;
-    const int c = (lane % CPR) ^ swz(r);
-    const unsigned off = (row0 + r < nrows) ? (elem0 + (unsigned)((row0 + r) * ld + c * 8)) * 2u : OOB;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(dst + q * 1024), 16, off, 0, 0, 0);
-  }
-}
-
-// Tiles of column blocks of one sample's rows, for a loop: the buffer ends with the sample's last row, so that rows
+// Direct-to-LDS loads of tiles of ROWS x DH, column blocks of one sample's rows: the buffer ends with the sample's last row, so that rows
 // beyond it read as zeros without a comparison, and the column block goes into the instruction's scalar offset.
 // Instruction i of this wave's share of the tile that starts at byte row0_bytes = first row * row bytes.
 template <int ROWS, int NW>
@@ -156,18 +137,16 @@ GX_DEVINL void load_row_frags(const bf16* base, int ld, int row, int nrows, int 
 }
 
 
-// acc[dt] += product of the transposed fragments of a tile of 16 * NG16 rows (groups of 16 rows at
-// LDS address `ct`) with xf[group]; COLS_A puts the transposed fragment first (rows of the result =
-// head-dim columns).  Groups 0 and 1 must have been issued into cf[0], cf[1] by the caller (as
-// early as it likes, to cover LDS latency with its own work); with four groups, groups 2 and 3
+// acc[dt] += product of the transposed fragments of a tile of 16 * NG16 rows (groups of 16 rows at LDS address `ct`)
+// with xf[group]; rows of the result are head-dim columns.  Groups 0 and 1 must have been issued into cf[0], cf[1] by the
+// caller (as early as it likes, to cover LDS latency with its own work); with four groups, groups 2 and 3
 // are issued here, so that two groups are always in flight.
-template <bool COLS_A, int NG16>
+template <int NG16>
 GX_DEVINL void tr_product(f32x16 (&acc)[DH / 32], unsigned ct, const unsigned (&coff)[2][DH / 32],
                           ColFrags (&cf)[2], const bf16x8 (&xf)[NG16]) {
   static_assert(NG16 == 2 || NG16 == 4, "tiles of 32 or 64 rows");
-#define GX_TR_GROUP(U, BUF)                                                                              \
-  _Pragma("unroll") for (int dt = 0; dt < DH / 32; dt++)                                                 \
-      acc[dt] = COLS_A ? MFMA(cols_get(cf[BUF], dt), xf[U], acc[dt]) : MFMA(xf[U], cols_get(cf[BUF], dt), acc[dt])
+#define GX_TR_GROUP(U, BUF) \
+  _Pragma("unroll") for (int dt = 0; dt < DH / 32; dt++) acc[dt] = MFMA(cols_get(cf[BUF], dt), xf[U], acc[dt])
   lds_wait_le<2 * (DH / 32)>();
   GX_TR_GROUP(0, 0);
   if (NG16 == 4) {
@@ -1017,7 +996,7 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
       bf16x8 dsf[2 * NJT];
 #pragma unroll
       for (int u = 0; u < 2 * NJT; u++) dsf[u] = pack_half(pacc[u >> 1], u & 1);
-      tr_product<true, 2 * NJT>(dq, ct, coff, cf, dsf);       // dQ^T[d][i] += K^T dS^T
+      tr_product<2 * NJT>(dq, ct, coff, cf, dsf);       // dQ^T[d][i] += K^T dS^T
     }
     WAIT_VM0();
     __syncthreads();
