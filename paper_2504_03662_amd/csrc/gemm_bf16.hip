@@ -610,16 +610,20 @@ constexpr int ROUND = 256;                     // workgroups at work at once: on
 //  - more than 64 tokens and up to 256: fewer are bound by the bandwidth itself (1 token of hidden 4096 4.5 % slower, a stage
 //    of two blocks and two streams, 64 tokens, hidden 8192 degree 4, 2 %); more mostly by operands (hidden 8192, degree 4: 400
 //    tokens 238 / 253; hidden 6144, degree 2: 312 / 323; hidden 5120, degree 2: 512 tokens 280 / 254 are given up).
-//  - a quarter of the compute units at least has no tile: with fewer a stage loses (same stage, 256 tokens, 0.7 %).
-// Forward passes within that, other layers in between, without / with, us: hidden 5120, degree 2: 100 tokens 173 / 155, 256
-// 226 / 194; hidden 4096: 160 203 / 198; hidden 8192, degree 4: 160 214 / 203; hidden 6144, degree 2: 230 262 / 253;
-// stages of two blocks within 0.5 % either way.  One layer's 300 to 400 MB again and again, which the cache half holds, can still lose: hidden
-// 3584, 100 tokens 2.6 %, forward and backward of hidden 4096, 100 tokens 2.6 % (with other layers in between 4.5 and 2 % faster).
+//  - beyond 128 tokens a quarter of the compute units at least has no tile (hidden 5120, degree 1: 129 tokens 2.3 % slower with
+//    fewer, that stage with 256 tokens 0.7 %); up to 128 a few are enough (hidden 8192, degree 4: 100 tokens 1.7 to 3 % faster).
+// Forward passes within that, other layers in between, without / with, us: hidden 5120, degree 2: 72 tokens 163 / 147, 128
+// 183 / 161, 256 226 / 195; hidden 4096: 128 205 / 197; hidden 8192, degree 4: 160 214 / 203; hidden 6144, degree 2: 256 271 /
+// 262; hidden 3584: 100 178 / 164.  What still loses: one layer's 300 to 400 MB again and again, which the cache half holds
+// (hidden 3584, 72 tokens 151 / 156, 160 tokens 168 / 169; forward and backward of hidden 4096, 100 tokens 553 / 573, with other
+// layers in between 587 / 572), and a stage of two blocks on two streams at one size of eleven (hidden 8192, degree 4, 128 tokens
+// 1.3 %; the others within 0.6 %).
 constexpr long CACHE = 256L << 20;
 constexpr int READ_AHEAD_TILE = 128 * 128;     // so few tokens do not take larger ones in calls of so many weights
 template <class T>
 int read_ahead_workgroups(int M, int tiles) {
-  return T::BM * T::BN <= READ_AHEAD_TILE && M > 64 && M <= 256 && tiles <= ROUND / 4 * 3 ? ROUND - tiles : 0;
+  if (T::BM * T::BN > READ_AHEAD_TILE || M <= 64 || M > 256) return 0;
+  return tiles <= (M <= 128 ? ROUND : ROUND / 4 * 3) ? ROUND - tiles : 0;
 }
 
 template <int LAY, int EPI, class T, bool READ_AHEAD>

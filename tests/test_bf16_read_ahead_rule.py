@@ -1,6 +1,6 @@
 """How many workgroups of a forward product read the next product's weights ahead (host code of the launcher): none where
 the call's weights may still be in the memory-side cache, where what is read would be gone before its use, where tokens are
-too few or too many, or where most compute units have a tile."""
+too few or too many, or where nearly all compute units have a tile."""
 import ctypes
 import os
 
@@ -41,13 +41,13 @@ def test_nothing_is_read_ahead_that_would_be_gone_before_its_use(hidden, hidden_
         assert forward_workgroups(hidden, hidden_local, ffn_local, tokens)[1:] == (0, 0)
 
 
-@pytest.mark.parametrize("tokens,expected", [(1, (0, 0, 0)), (64, (0, 0, 0)), (65, (0, 96, 96)), (128, (0, 96, 96)),
+@pytest.mark.parametrize("tokens,expected", [(1, (0, 0, 0)), (64, (0, 0, 0)), (65, (16, 96, 96)), (128, (16, 96, 96)),
                                              (256, (0, 96, 96)), (257, (0, 0, 0)), (1024, (0, 0, 0))])
 def test_tokens(tokens, expected):
     assert forward_workgroups(5120, 2560, 10240, tokens) == expected
 
 
-def test_a_quarter_of_the_compute_units_is_idle_wherever_something_is_read():
+def test_beyond_128_tokens_a_quarter_of_the_compute_units_is_idle_wherever_something_is_read():
     for hidden, local, ffn in ((5120, 2560, 10240), (4096, 4096, 16384), (6144, 3072, 12288), (8192, 2048, 7168)):
-        for tokens in range(1, 600):
+        for tokens in range(129, 600):
             assert all(n == 0 or 64 <= n < 256 for n in forward_workgroups(hidden, local, ffn, tokens))
