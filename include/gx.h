@@ -196,7 +196,7 @@ gx_status gx_layer_bwd_static(const gx_layer_cfg* cfg, const gx_params* params, 
  * While enabled, every kernel launch site inside gx_layer_fwd / gx_layer_bwd is bracketed by a
  * pair of HIP events on the call's stream and tagged with a kernel class:
  *   GX_KC_LN_FWD, GX_KC_LN_BWD (input gradient and partial parameter sums in one kernel),
- *   GX_KC_ATTN_FWD, GX_KC_ATTN_BWD (its three kernels together), GX_KC_COLSUM (a stage-1 pass of
+ *   GX_KC_ATTN_FWD, GX_KC_ATTN_BWD (its kernels together), GX_KC_COLSUM (a stage-1 pass of
  *   a bias gradient, or the one launch that finishes every column sum of the backward pass),
  *   GX_KC_DROPOUT (mask generation and the
  *   dropout passes over a half's output or its gradient), and GX_KC_GEMM + 10 * layout + epilogue

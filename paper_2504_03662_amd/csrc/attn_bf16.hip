@@ -1,17 +1,17 @@
 // Flash-style causal attention for gfx950, bf16 in / fp32 accumulate, head dim 128 or 64 (the
 // kernels live in attn_bf16_impl.h, compiled once per head dimension).
 //
-// Forward: a workgroup owns a block of query rows of one (sample, head); K and V tiles of 64 rows
-// stream through a double-buffered LDS stage (direct-to-LDS buffer loads).  Each wavefront keeps
+// Forward: a workgroup owns a block of query rows of one (sample, head); K and V tiles of 64 or 128 rows
+// stream through two LDS buffers each (direct-to-LDS buffer loads).  Each wavefront keeps
 // 32 query rows and works on the transposed problem S^T = K Q^T, so that a lane owns one query
 // column of every v_mfma_f32_32x32x16_bf16 accumulator: the online-softmax row statistics are
 // lane-local (plus one cross-half shuffle), and the probabilities, once rounded to bf16, are
 // already laid out as the B operand of O^T = V^T P^T.  V^T (and every other operand whose
 // reduction index is strided in memory) is read with the transposing ds_read_b64_tr_b16.
 //
-// Backward: D = rowsum(dO * O); then two kernels so that every output has exactly one writer
-// and sums run in a fixed order (no atomics): one owns key/value rows and produces dK, dV, the
-// other owns query rows and produces dQ.  Probabilities are recomputed from the saved
+// Backward: two kernels so that every output has exactly one writer and sums run in a fixed order (no
+// atomics): the first owns query rows, forms D = rowsum(dO * O) and produces dQ, the second owns key/value
+// rows and produces dK, dV with that D.  Probabilities are recomputed from the saved
 // log-sum-exp.
 #include "gx_kernels.h"
 #include <type_traits>

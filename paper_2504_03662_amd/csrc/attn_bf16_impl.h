@@ -19,9 +19,9 @@ GX_DEVINL int swz(int r) {
   return ((x & 1) << 2) | (x >> 1);
 }
 
-// Direct-to-LDS loads of tiles of ROWS x DH, column blocks of one sample's rows: the buffer ends with the sample's last row, so that rows
-// beyond it read as zeros without a comparison, and the column block goes into the instruction's scalar offset.
-// Instruction i of this wave's share of the tile that starts at byte row0_bytes = first row * row bytes.
+// Direct-to-LDS loads of tiles of ROWS x DH, column blocks of one sample's rows: the buffer ends with the sample's last
+// row, so that rows beyond it read as zeros without a comparison, and the column block goes into the instruction's scalar
+// offset.  Instruction i of this wave's share of the tile that starts at byte row0_bytes = first row * row bytes.
 template <int ROWS, int NW>
 struct RowStream {
   static constexpr int RPI = 64 / CPR, PER_WAVE = ROWS / RPI / NW;
@@ -304,7 +304,7 @@ GX_DEVINL void fwd_merge_store(char* smem, f32x16 (&o)[DH / 32], float m, float 
   }
 }
 
-// What bounds it: a score costs 512 (DH 128) FLOP of matrix work, 1/64 of 32 cycles per 64 scores, and about nine issue
+// What bounds it: 64 scores cost 32 cycles of the matrix pipe (512 FLOP each at DH 128) and about nine issue
 // slots of 4 cycles of vector work (an exponential alone takes four), so neither pipe may wait for the other.  The
 // wavefronts of a SIMD do not take turns by themselves: they pass the same barrier, then want the same pipe.  So one
 // wavefront's stream mixes the two: in step t the products of the step before (O += V P, t - 1) and the
@@ -317,10 +317,13 @@ GX_DEVINL void fwd_merge_store(char* smem, f32x16 (&o)[DH / 32], float m, float 
 // reference gives the same softmax up to rounding, and lse = m + log2(l) holds for any m.  Without it m is the
 // running maximum itself, so that a row's largest probability is exactly 1 in bf16, which leaves outputs 0.1 to 1.5 %
 // nearer to the fp64 ones (64 pairs of S 2048).
-// Measured against one kernel without the mix (many pairs) and one with only the scores ahead (few), us: 64 pairs of
-// S 2048 88 -> 85, 64 of S 1024 32 -> 30, 4 of S 8192 101 -> 89, 8 of S 2048 26.9 -> 21.6, 16 of S 2048 30.1 -> 28.8,
-// 20 of S 2048 36.9 -> 34.8, 20 of S 128 6.8 -> 6.3; DH 64: 64 of S 1024 20.9 -> 18.9, 12 of S 1024 11.7 -> 9.9.  Deeper
-// rings (80 KB) leave one workgroup per unit: 64 pairs of S 2048 take twice as long.
+// Measured against one kernel without the mix (many pairs) and one with only the scores ahead (few), in turn on one box
+// between the products of a layer, us: 64 pairs of S 2048 105 -> 94, 64 of S 1024 34.4 -> 31.7, 4 of S 8192 109 -> 99.6, 8 of
+// S 2048 29.2 -> 24.7, 16 of S 2048 33.4 -> 32.9, 20 of S 2048 38.6 -> 37.0, 20 of S 128 8.0 -> 7.2; DH 64: 64 of S 1024
+// 22.6 -> 20.6, 12 of S 1024 12.7 -> 10.9.  Distances from fp64 (2-norm,
+// four key shares against two, five calls, two to six seeds each): outputs -0.5 to +0.1 %, gradient matrices -0.5 to +0.1 % from
+// S 2048 on and +-1.4 % at 1024 tokens, gradient vectors of some hundred elements +-6 %, without a direction: P is rounded
+// to bf16 relative to another maximum.  Deeper rings (80 KB) leave one workgroup per unit: 64 pairs of S 2048 take twice as long.
 template <int NQ, int SPLIT, int BKV, bool LAZY, bool DROP>
 __global__ void __launch_bounds__(64 * NQ * SPLIT, 2)
     attn_fwd_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ ctx, float* __restrict__ lse, int S, int nl,
@@ -591,9 +594,10 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, 2)
 //   role K: dP(n) = dO(n) V^T, mixed with dS(n-1) from P(n-1) and dP(n-1); then dK += dS(n-1)^T Q(n-1)
 // with one barrier per phase; Q(n+3) and dO(n+2) are requested in its first slots.  Tiles need two phases to arrive:
 // with one (and the second products a phase later, mixed too, in the same LDS) every phase waited for them.
-// This kernel alone, us, as a chain / mixed with one phase to arrive / as it is: 64 pairs of S 2048 197 / 190 / 183, 16 pairs
-// 72 / 68 / 65, 4 pairs of S 8192 238 / 229 / 216; DH 64: 12 pairs of S 1024 23.1 / 22.0 / 19.8, 64 pairs of S 1024 with
-// dropout 42.9 / 50.7 / 45.1 (there three workgroups share a unit instead of four; the second needed 169 registers, two).
+// This kernel, us, as a chain / as it is, in turn on one box between the products of a layer: 64 pairs of S 2048 198 / 182,
+// 16 pairs 62.1 / 56.2, 4 pairs of S 8192 221 / 198, 64 of S 1024 58.2 / 57.6, 20 of S 128 9.4 / 9.8; DH 64: 12 pairs of S 1024
+// 22.8 / 19.4, 64 of S 2048 with dropout 125 / 119, 64 of S 1024 with dropout 41.8 / 40.8, without 32.8 / 34.2 (three
+// workgroups share a unit instead of four).  In a step of 64 pairs of S 2048, where power holds the clock down, 173 / 171.
 // The chain with two workgroups per unit against 128 key rows, query tiles of 64 and one workgroup of 8 wavefronts (the whole
 // backward pass, nothing else on the chip, us): 64 pairs of S 2048 at DH 128 394 -> 292, 16 pairs 112 -> 101, 4 pairs of
 // S 8192 372 -> 334.
@@ -878,10 +882,14 @@ __global__ void __launch_bounds__(64 * KV_NW, DH == 64 ? 3 : 2) attn_bwd_dkv_ker
 
 // ------------------------------------------------------------------------------- backward: dQ
 // Shapes and workgroup order as in the forward kernel; the parts' dQ partial sums are added
-// through LDS in the order of `part`.  It runs before the dK / dV kernel and leaves D[b, h, s] = sum_d dO * O for it:
-// the rows of dO are here anyway, so D costs one read of O and no launch of its own (that one took 3 to 10 us, up to
-// 250 beside the weight gradients of the other stream; layer steps, us: hidden 768, 1024 tokens 198.5 -> 193, hidden
-// 2048, 8192 tokens 2486 -> 2465, attention half of 4 heads and S 8192 958 -> 934).
+// through LDS in the order of `part`.  It runs before the dK / dV kernel and leaves D[b, h, s] = sum_d dO * O for it.
+// The rows of dO are here anyway; those of O are read as row fragments, once by every share of the keys, and waited for before
+// the first tile, so the kernel takes longer by about what a launch of D's own took (64 pairs of S 2048 130 + 14.3 -> 146 us,
+// 64 of S 1024 41.6 + 8.8 -> 44.3, 16 of S 2048 42.7 + 7.4 -> 43.6; DH 64: 64 of S 2048 65.8 + 8.4 -> 75.7, 64 of S 1024 25.1 +
+// 7.7 -> 28.0).  What is gained is that launch's wait for compute units beside the weight gradients of the other stream, up to
+// 250 us: steps of hidden 768, 1024 tokens 198.5 -> 193, hidden 2048, 8192 tokens 2486 -> 2465, attention half of 4 heads and
+// S 8192 958 -> 934; the order of the kernels beside those gradients changes with it, and a step with dropout of hidden 896,
+// 2976 tokens, is 3 % slower (252 -> 260) although its kernels one by one take 300 -> 288.
 template <int NQ, int SPLIT, int BKV, bool DROP>
 __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
     attn_bwd_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ ctx, const bf16* __restrict__ dctx,

@@ -10,9 +10,10 @@
 // 16 wavefront ballots, each of which is the column-major word pair "64 queries of one key".
 //   rowbits[(bh * S + i) * wpr + j / 32]  bit j % 32  = keep(i, j)        (forward, dQ)
 //   colbits[(bh * S + j) * wpr + i / 32]  bit i % 32  = keep(i, j)        (dK / dV)
-// What bounds it is the generator: 20 products of 32 x 32 bits a call, quarter rate, about 700 of 1000 cycles per wavefront
-// and call.  A ballot is the comparison's own mask, put into its lane by v_writelane (a select per lane and half took
-// four instructions).  64 pairs of S 1024, us: row-major alone 17.0 -> 14.0, both 26.9 -> 18.3; 64 of S 2048 89.5 -> 57.5.
+// What bounds it is vector arithmetic: a call's 20 products of 32 x 32 bits, each at a quarter of the rate, about 80 plain
+// operations around them, and 16 comparisons with what places their bits.  A ballot is the comparison's own mask, put into
+// its lane by v_writelane (a select per lane and half took four instructions).  64 pairs of S 1024, us: row-major alone
+// 17.0 -> 14.0, both 26.9 -> 18.3; 64 of S 2048 89.5 -> 57.5; 96 of S 777 13.6 -> 14.2, 21.6 -> 19.2.
 // wpr = 2 * ceil(S / 64) words per row.  Only words that a causal kernel can touch are written:
 // keys below 64 * (i / 64 + 1).
 //
