@@ -317,7 +317,7 @@ GX_DEVINL void fwd_merge_store(char* smem, f32x16 (&o)[DH / 32], float m, float 
 // reference gives the same softmax up to rounding, and lse = m + log2(l) holds for any m.  Without it m is the
 // running maximum itself, so that a row's largest probability is exactly 1 in bf16, which leaves outputs 0.1 to 1.5 %
 // nearer to the fp64 ones (64 pairs of S 2048).
-// Measured against one kernel without the mix (many pairs) and one with only the scores ahead (few), in turn on one box
+// Measured against one kernel without the mix (many pairs) and one with only the scores ahead (few), in turn
 // between the products of a layer, us: 64 pairs of S 2048 105 -> 94, 64 of S 1024 34.4 -> 31.7, 4 of S 8192 109 -> 99.6, 8 of
 // S 2048 29.2 -> 24.7, 16 of S 2048 33.4 -> 32.9, 20 of S 2048 38.6 -> 37.0, 20 of S 128 8.0 -> 7.2; DH 64: 64 of S 1024
 // 22.6 -> 20.6, 12 of S 1024 12.7 -> 10.9.  Distances from fp64 (2-norm,
@@ -594,7 +594,7 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, 2)
 //   role K: dP(n) = dO(n) V^T, mixed with dS(n-1) from P(n-1) and dP(n-1); then dK += dS(n-1)^T Q(n-1)
 // with one barrier per phase; Q(n+3) and dO(n+2) are requested in its first slots.  Tiles need two phases to arrive:
 // with one (and the second products a phase later, mixed too, in the same LDS) every phase waited for them.
-// This kernel, us, as a chain / as it is, in turn on one box between the products of a layer: 64 pairs of S 2048 198 / 182,
+// This kernel, us, as a chain / as it is, in turn between the products of a layer: 64 pairs of S 2048 198 / 182,
 // 16 pairs 62.1 / 56.2, 4 pairs of S 8192 221 / 198, 64 of S 1024 58.2 / 57.6, 20 of S 128 9.4 / 9.8; DH 64: 12 pairs of S 1024
 // 22.8 / 19.4, 64 of S 2048 with dropout 125 / 119, 64 of S 1024 with dropout 41.8 / 40.8, without 32.8 / 34.2 (three
 // workgroups share a unit instead of four).  In a step of 64 pairs of S 2048, where power holds the clock down, 173 / 171.
