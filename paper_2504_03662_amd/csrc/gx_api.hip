@@ -554,10 +554,14 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
     GX_TRY(gemm(d, LAY_NT, EPI_STORE, dy2, st));
     if ((s = point(2)) != GX_OK) return s;
     void* out = attn ? w.dh1 : dx;
+    // A lone feed-forward half has nothing left after this kernel but the two weight gradients, which are most of what
+    // remains: they stay on the caller's stream, and it is the LayerNorm that runs beside them (hidden 4096, degree 8, 3003 tokens,
+    // forward and backward: 392 us with the gradients on the side stream behind it, 380).
     {
-      ProfScope ps(GX_KC_LN_BWD, st);
+      const hipStream_t ln = attn ? st : fk.branch();
+      ProfScope ps(GX_KC_LN_BWD, ln);
       GX_TRY(ln_bwd(d.bf, w.dy2, h1, p.ln2_g, sv.mean2, sv.rstd2, attn ? dy : nullptr, out, (int)d.T, (int)d.H,
-                    ln2_sums_biases ? 4 : 2, w.part_ln2, st));
+                    ln2_sums_biases ? 4 : 2, w.part_ln2, ln));
     }
     const size_t stride = (size_t)lnb * d.H;
     fin.add(w.part_ln2, lnb, d.H, gr.ln2_g, acc);
@@ -567,9 +571,9 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
       if (c.flags & GX_ROW_BIAS_ATTN) fin.add(w.part_ln2 + 3 * stride, lnb, d.H, gr.b_o, acc);
     }
     dcur = w.dh1;
-    if (!attn)                       // a lone feed-forward half: no later point will come
-      for (int k = 3; k <= 6; k++)
-        if ((s = point(k)) != GX_OK) return s;
+    if (!attn)                       // no later point will come
+      for (int t = 0; t < 2; t++)
+        if ((s = task(t, st)) != GX_OK) return s;
   }
   if (attn) {
     dp_attn = dcur;
