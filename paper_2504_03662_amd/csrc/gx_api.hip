@@ -502,24 +502,30 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
   const int lnb = ln_bwd_blocks(d.bf, (int)d.T, (int)d.H);
   const void* dp_mlp = dy;
   const void* dp_attn = nullptr;
+  // The bias gradient that goes with weight gradient g, the column sums of its B: with fp32 the product adds them up itself.
+  auto bias_sums = [&](GemmArgs& g, float* part, float* out, hipStream_t sd) -> hipError_t {
+    if (d.bf) return colsum_p(true, g.B, g.K, g.N, part, out, acc, fin, sd);
+    g.colpart = out;
+    return hipSuccess;
+  };
   auto task = [&](int t, hipStream_t sd) -> gx_status {
     if (t == 0) {        // dW2 (+ b_fc2)
-      if (!(c.flags & GX_ROW_BIAS_MLP)) { if ((s = zero_grad(acc, gr.b_fc2, d.H, sd)) != GX_OK) return s; }
-      else if (!ln2_sums_biases) GX_TRY(colsum_p(d.bf, dp_mlp, d.T, d.H, w.part_fc2, gr.b_fc2, acc, fin, sd));
       GemmArgs w2 = gargs(sv.act, dp_mlp, gr.w_fc2, d.Fl, d.H, d.T, d.Fl, d.H, d.H);
+      if (!(c.flags & GX_ROW_BIAS_MLP)) { if ((s = zero_grad(acc, gr.b_fc2, d.H, sd)) != GX_OK) return s; }
+      else if (!ln2_sums_biases) GX_TRY(bias_sums(w2, w.part_fc2, gr.b_fc2, sd));
       GX_TRY(wgrad(w2, sd));
-    } else if (t == 1) { // dW1
-      if (!d.bf) GX_TRY(colsum_p(d.bf, w.dz, d.T, d.Fl, w.part_fc1, gr.b_fc1, acc, fin, sd));
+    } else if (t == 1) { // dW1 (+ b_fc1; bf16: the product that makes dz leaves its column sums)
       GemmArgs w1 = gargs(sv.y2, w.dz, gr.w_fc1, d.H, d.Fl, d.T, d.H, d.Fl, d.Fl);
+      if (!d.bf) GX_TRY(bias_sums(w1, nullptr, gr.b_fc1, sd));
       GX_TRY(wgrad(w1, sd));
     } else if (t == 2) { // dWo (+ b_o)
-      if (!(c.flags & GX_ROW_BIAS_ATTN)) { if ((s = zero_grad(acc, gr.b_o, d.H, sd)) != GX_OK) return s; }
-      else if (!ln2_sums_biases) GX_TRY(colsum_p(d.bf, dp_attn, d.T, d.H, w.part_o, gr.b_o, acc, fin, sd));
       GemmArgs wo = gargs(sv.ctx, dp_attn, gr.w_o, d.Hl, d.H, d.T, d.Hl, d.H, d.H);
+      if (!(c.flags & GX_ROW_BIAS_ATTN)) { if ((s = zero_grad(acc, gr.b_o, d.H, sd)) != GX_OK) return s; }
+      else if (!ln2_sums_biases) GX_TRY(bias_sums(wo, w.part_o, gr.b_o, sd));
       GX_TRY(wgrad(wo, sd));
     } else {             // dWqkv (+ b_qkv)
-      GX_TRY(colsum_p(d.bf, w.dqkv, d.T, 3 * d.Hl, w.part_qkv, gr.b_qkv, acc, fin, sd));
       GemmArgs wq = gargs(sv.y1, w.dqkv, gr.w_qkv, d.H, 3 * d.Hl, d.T, d.H, 3 * d.Hl, 3 * d.Hl);
+      GX_TRY(bias_sums(wq, w.part_qkv, gr.b_qkv, sd));
       GX_TRY(wgrad(wq, sd));
     }
     return GX_OK;
