@@ -202,7 +202,8 @@ gx_status gx_layer_bwd_static(const gx_layer_cfg* cfg, const gx_params* params, 
  *   dropout passes over a half's output or its gradient), and GX_KC_GEMM + 10 * layout + epilogue
  *   with layout 0 = A[M,K] B[K,N], 1 = A[M,K] B[N,K], 2 = A[K,M] B[K,N] and epilogue 0 = store,
  *   1 = +bias, 2 = +bias +residual, 3 = +bias then GELU, 4 = times GELU', 5 = fp32 store,
- *   6 = fp32 accumulate.
+ *   6 = fp32 accumulate.  In small fp32 layers a launch may hold an input gradient and a weight gradient
+ *   together; it counts as the input gradient's class.
  * gx_prof_enable(1) creates the events on first use (the only allocation the library ever makes)
  * and clears the record; gx_prof_enable(0) stops recording.  gx_prof_collect waits for the
  * recorded events, writes up to `capacity` (class, milliseconds) pairs to HOST arrays in launch

@@ -470,6 +470,16 @@ gx_status zero_grad(bool acc, float* out, long cols, hipStream_t st) {
   return GX_OK;
 }
 
+// Whether the backward pass puts each weight gradient into the launch of an input gradient instead of on the side stream: fp32
+// layers all of whose products take the smallest tile.
+bool pair_products(const Dims& d, bool attn, bool mlp) {
+  if (d.bf) return false;
+  auto smallest = [](long m, long n, long k) { return gx_f32_tile((int)m, (int)n, (int)k) == 0; };
+  if (mlp && !(smallest(d.T, d.Fl, d.H) && smallest(d.T, d.H, d.Fl) && smallest(d.Fl, d.H, d.T))) return false;
+  return !attn || (smallest(d.T, d.Hl, d.H) && smallest(d.T, d.H, 3 * d.Hl) && smallest(d.Hl, d.H, d.T) &&
+                   smallest(d.H, 3 * d.Hl, d.T));
+}
+
 gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, const void* dy, void* dx,
                   const gx_grads& gr, const Saved& sv, const Work& w, const DropBufs& db, hipStream_t st,
                   bool allow_side) {
@@ -477,16 +487,22 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
   const Drop dr = drop_of(c);
   const bool attn = c.flags & GX_PHASE_ATTN, mlp = c.flags & GX_PHASE_MLP;
   const bool acc = c.flags & GX_ACCUM_WGRAD;
+  const bool paired = pair_products(d, attn, mlp);
+  GemmArgs beside;                 // paired: the weight gradient that goes into the next input gradient's launch
   // weight gradient A^T B into fp32 (store or add) or, on request, into bf16: a plain rounding
   // store, or the residual epilogue reading the old value from the output itself (every lane
   // reads exactly the four elements it then writes, so in place is safe)
   auto wgrad = [&](GemmArgs g, hipStream_t s) -> hipError_t {
+    if (paired) {
+      beside = g;
+      return hipSuccess;
+    }
     if (!(c.flags & GX_WGRAD_BF16)) return gemm(d, LAY_TN, acc ? EPI_F32_ACC : EPI_F32, g, s);
     if (!acc) return gemm(d, LAY_TN, EPI_STORE, g, s);
     g.resid = g.C;
     return gemm(d, LAY_TN, EPI_RESID, g, s);
   };
-  Fork fk(st, allow_side);
+  Fork fk(st, allow_side && !paired);
   Finisher fin;
   gx_status s;
   // The weight-gradient products only consume finished tensors, so they are handed to the side
@@ -530,7 +546,19 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
     }
     return GX_OK;
   };
+  // An input gradient, paired with weight gradient t, whose operands are ready by then.
+  auto input_gradient = [&](Epilogue epi, const GemmArgs& g, int t) -> gx_status {
+    if (!paired) {
+      GX_TRY(gemm(d, LAY_NT, epi, g, st));
+      return GX_OK;
+    }
+    if ((s = task(t, st)) != GX_OK) return s;
+    ProfScope ps(gemm_class(LAY_NT, epi), st);
+    GX_TRY(gemm_f32_pair(epi, g, acc, beside, st));
+    return GX_OK;
+  };
   auto point = [&](int k) -> gx_status {
+    if (paired) return GX_OK;
     hipStream_t sd = nullptr;
     for (int t = 0; t < 4; t++) {
       if (sched[t] - '0' != k) continue;
@@ -554,10 +582,10 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
       dz.colpart = w.part_fc1;
       fin.add(w.part_fc1, cdiv(d.T, 64), d.Fl, gr.b_fc1, acc);
     }
-    GX_TRY(gemm(d, LAY_NT, EPI_DGELU, dz, st));
+    if ((s = input_gradient(EPI_DGELU, dz, 0)) != GX_OK) return s;
     if ((s = point(1)) != GX_OK) return s;
     GemmArgs dy2 = gargs(w.dz, p.w_fc1, w.dy2, d.T, d.H, d.Fl, d.Fl, d.Fl, d.H);
-    GX_TRY(gemm(d, LAY_NT, EPI_STORE, dy2, st));
+    if ((s = input_gradient(EPI_STORE, dy2, 1)) != GX_OK) return s;
     if ((s = point(2)) != GX_OK) return s;
     void* out = attn ? w.dh1 : dx;
     // A lone feed-forward half has nothing left after this kernel but the two weight gradients, which are most of what
@@ -577,7 +605,7 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
       if (c.flags & GX_ROW_BIAS_ATTN) fin.add(w.part_ln2 + 3 * stride, lnb, d.H, gr.b_o, acc);
     }
     dcur = w.dh1;
-    if (!attn)                       // no later point will come
+    if (!attn && !paired)            // no later point will come
       for (int t = 0; t < 2; t++)
         if ((s = task(t, st)) != GX_OK) return s;
   }
@@ -589,7 +617,7 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
     }
     if ((s = point(3)) != GX_OK) return s;
     GemmArgs dc = gargs(dp_attn, p.w_o, w.dctx, d.T, d.Hl, d.H, d.H, d.H, d.Hl);
-    GX_TRY(gemm(d, LAY_NT, EPI_STORE, dc, st));
+    if ((s = input_gradient(EPI_STORE, dc, 2)) != GX_OK) return s;
     if ((s = point(4)) != GX_OK) return s;
     AttnArgs a;
     memset(&a, 0, sizeof(a));
@@ -603,7 +631,7 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
     }
     if ((s = point(5)) != GX_OK) return s;
     GemmArgs dy1 = gargs(w.dqkv, p.w_qkv, w.dy1, d.T, d.H, 3 * d.Hl, 3 * d.Hl, 3 * d.Hl, d.H);
-    GX_TRY(gemm(d, LAY_NT, EPI_STORE, dy1, st));
+    if ((s = input_gradient(EPI_STORE, dy1, 3)) != GX_OK) return s;
     if ((s = point(6)) != GX_OK) return s;
     {
       ProfScope ps(GX_KC_LN_BWD, st);

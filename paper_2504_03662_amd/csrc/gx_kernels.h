@@ -61,6 +61,8 @@ extern "C" int gx_bf16_read_ahead(int M, int N, int K, long next_bytes, long cal
 // block, 3 and 4 the same for short reductions
 extern "C" int gx_f32_tile(int M, int N, int K);
 hipError_t gemm_f32(Layout lay, Epilogue epi, const GemmArgs& g, hipStream_t s);
+// An NT product and a TN product (fp32, stored or added to) in one launch, both in 32 x 32 tiles
+hipError_t gemm_f32_pair(Epilogue nt_epi, const GemmArgs& nt, bool accumulate, const GemmArgs& tn, hipStream_t s);
 
 // Causal attention over the local heads.  qkv is [T, 3*Hl] with column blocks [Q | K | V], each
 // head's dh columns contiguous; ctx / dctx are [T, Hl]; lse and dsum are [B, nl, S] fp32.
