@@ -185,12 +185,12 @@ struct Args {
   int wpr;
   float keep_scale;
 };
-// this workgroup's (sample, head) pair and tile; the tiles with most work come first in the launch
+// the (sample, head) pair and tile of workgroup `blk`; the tiles with most work come first
 struct Where {
   int b, h, tile, ld;
   const float *q, *k, *v;
-  GX_DEVINL Where(const Args& a, bool last_first) {
-    const int pair = blockIdx.x % a.npair, n = gridDim.x / a.npair, i = blockIdx.x / a.npair;
+  GX_DEVINL Where(const Args& a, int blk, bool last_first) {
+    const int pair = blk % a.npair, n = (a.S + 31) / 32, i = blk / a.npair;
     tile = last_first ? n - 1 - i : i;
     h = pair % a.nl;
     b = pair / a.nl;
@@ -210,7 +210,7 @@ __global__ void __launch_bounds__(64 * PARTS, DHP <= 64 ? 2 : 1) attn_fwd_f32_ke
   __shared__ float lds[lds_floats<DHP>()];
   const int lane = threadIdx.x & 63, part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 5, l32 = lane & 31;
-  const Where w(a, true);
+  const Where w(a, blockIdx.x, true);
   const int i0 = 32 * w.tile, i = i0 + l32;
   const float scale = rsqrtf((float)a.dh);
   const size_t row = ((size_t)w.b * a.nl + w.h) * a.S + min(i, a.S - 1);
@@ -285,11 +285,10 @@ __global__ void __launch_bounds__(64 * PARTS, DHP <= 64 ? 2 : 1) attn_fwd_f32_ke
 
 // D_i = dO_i . O_i, dS_ij = P_ij (dO_i . V_j - D_i), dQ_i = scale sum_j dS_ij K_j
 template <int DHP, bool EXACT>
-__global__ void __launch_bounds__(64 * PARTS, DHP <= 64 ? 2 : 1) attn_bwd_dq_f32_kernel(Args a) {
-  __shared__ float lds[lds_floats<DHP>()];
+GX_DEVINL void dq_block(const Args& a, int blk, float* lds) {
   const int lane = threadIdx.x & 63, part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 5, l32 = lane & 31;
-  const Where w(a, true);
+  const Where w(a, blk, true);
   const int i0 = 32 * w.tile, i = i0 + l32, ic = min(i, a.S - 1);
   const float scale = rsqrtf((float)a.dh);
   const size_t row = ((size_t)w.b * a.nl + w.h) * a.S + ic;
@@ -340,17 +339,19 @@ __global__ void __launch_bounds__(64 * PARTS, DHP <= 64 ? 2 : 1) attn_bwd_dq_f32
 }
 
 // dV_j = sum_{i >= j} P_ij dO_i, dK_j = scale sum_{i >= j} dS_ij Q_i
-template <int DHP, bool EXACT>
-__global__ void __launch_bounds__(64 * PARTS, 1) attn_bwd_dkv_f32_kernel(Args a) {
-  __shared__ float lds[lds_floats<DHP>()];
+// OWN_D: D is formed here once more, from the rows of dO that are in registers and those of O, in the order of the dQ
+// kernel; else it is what that kernel has left.
+template <int DHP, bool EXACT, bool OWN_D>
+GX_DEVINL void dkv_block(const Args& a, int blk, float* lds) {
   const int lane = threadIdx.x & 63, part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 5, l32 = lane & 31;
-  const Where w(a, false);
+  const Where w(a, blk, false);
   const int j0 = 32 * w.tile, j = j0 + l32, jc = min(j, a.S - 1);
   const float scale = rsqrtf((float)a.dh);
   const size_t pair_row = ((size_t)w.b * a.nl + w.h) * a.S;
   const int Hl = a.nl * a.dh;
   const float* dob = a.dctx + (size_t)w.b * a.S * Hl + w.h * a.dh;
+  const float* ob = a.ctx + (size_t)w.b * a.S * Hl + w.h * a.dh;
   f32x4 kf[DHP / 8], vf[DHP / 8];
   load_rows<DHP, EXACT>(w.k + (size_t)jc * w.ld, a.dh, g, kf);
   load_rows<DHP, EXACT>(w.v + (size_t)jc * w.ld, a.dh, g, vf);
@@ -361,6 +362,7 @@ __global__ void __launch_bounds__(64 * PARTS, 1) attn_bwd_dkv_f32_kernel(Args a)
   for (int t = w.tile + part; t < nt; t += PARTS) {
     const int i0 = 32 * t, ir = min(i0 + l32, a.S - 1);
     f32x16 p, ds;
+    float dd = 0.f;                        // OWN_D: D of row i0 + l32
     {
       f32x4 xf[DHP / 8];
       load_rows<DHP, EXACT>(w.q + (size_t)ir * w.ld, a.dh, g, xf);
@@ -368,6 +370,15 @@ __global__ void __launch_bounds__(64 * PARTS, 1) attn_bwd_dkv_f32_kernel(Args a)
       if (DHP > 64) __builtin_amdgcn_sched_barrier(0);           // one operand in registers at a time
       load_rows<DHP, EXACT>(dob + (size_t)ir * Hl, a.dh, g, xf);
       ds = row_product<DHP>(xf, vf);                             // dP[i][j]
+      if (OWN_D) {
+        f32x4 of[DHP / 8];
+        load_rows<DHP, EXACT>(ob + (size_t)ir * Hl, a.dh, g, of);
+#pragma unroll
+        for (int c = 0; c < DHP / 8; c++)
+#pragma unroll
+          for (int e = 0; e < 4; e++) dd = fmaf(xf[c][e], of[c][e], dd);
+        dd += __shfl_xor(dd, 32, 64);
+      }
     }
     float st[16];
     load_row_stats(a.lse + pair_row + i0, a.S - i0, g, st);
@@ -386,7 +397,12 @@ __global__ void __launch_bounds__(64 * PARTS, 1) attn_bwd_dkv_f32_kernel(Args a)
         ds[v] = ((kept >> v) & 1u) ? ds[v] * a.keep_scale : 0.f;
       }
     }
-    load_row_stats(a.dsum + pair_row + i0, a.S - i0, g, st);
+    if (OWN_D) {
+#pragma unroll
+      for (int v = 0; v < 16; v++) st[v] = __shfl(dd, acc_row(v, g), 64);
+    } else {
+      load_row_stats(a.dsum + pair_row + i0, a.S - i0, g, st);
+    }
 #pragma unroll
     for (int v = 0; v < 16; v++) {
       const int i = i0 + acc_row(v, g);
@@ -410,9 +426,43 @@ __global__ void __launch_bounds__(64 * PARTS, 1) attn_bwd_dkv_f32_kernel(Args a)
   store_column<DHP, EXACT>(dv, dst + Hl, 1.0f, a.dh, g);
 }
 
+template <int DHP, bool EXACT>
+__global__ void __launch_bounds__(64 * PARTS, DHP <= 64 ? 2 : 1) attn_bwd_dq_f32_kernel(Args a) {
+  __shared__ float lds[lds_floats<DHP>()];
+  dq_block<DHP, EXACT>(a, blockIdx.x, lds);
+}
+template <int DHP, bool EXACT>
+__global__ void __launch_bounds__(64 * PARTS, 1) attn_bwd_dkv_f32_kernel(Args a) {
+  __shared__ float lds[lds_floats<DHP>()];
+  dkv_block<DHP, EXACT, false>(a, blockIdx.x, lds);
+}
+// Both in one launch, first the blocks of dK / dV, which have more to do.
+template <int DHP, bool EXACT>
+__global__ void __launch_bounds__(64 * PARTS, 1) attn_bwd_f32_kernel(Args a) {
+  __shared__ float lds[lds_floats<DHP>()];
+  const int blk = blockIdx.x, n = gridDim.x / 2;
+  if (blk < n) dkv_block<DHP, EXACT, true>(a, blk, lds);
+  else dq_block<DHP, EXACT>(a, blk - n, lds);
+}
+
 bool shape_ok(const AttnArgs& a) {
   return a.S > 0 && a.S <= 8192 && a.dh > 0 && a.dh <= 128 && a.nl > 0 && a.B > 0 &&
          (long)a.B * a.nl * cdiv(a.S, 32) < (1L << 31) && (!a.rowbits || a.wpr >= cdiv(a.S, 32));
+}
+
+// Whether dQ and dK / dV share a launch: where their blocks find places at the same time, so that neither waits for the
+// other's longest.  One workgroup per compute unit (two at head dim 32, which takes fewer registers); many pairs of short
+// sequences fill the chip with each kernel alone, and forming D twice then costs more than it saves.  Layers forward and
+// backward, us, two launches / one (blocks of 32 rows, pairs):
+//   256 x 4 heads of 64, 2 x 128 tokens (32, 8) 107 / 98    512 x 8 of 64, 512 tokens (128, 8) 252 / 228
+//   128 x 2 of 64, 1024 tokens (64, 2) 224 / 185            200 x 4 of 50, 900 tokens (116, 4) 322 / 273
+//   768 x 6 of 128, 1024 tokens (192, 6) 720 / 693          640 x 10 of 64, 512 tokens (160, 10) 341 / 335
+//   512 x 8 of 64, 1024 tokens (256, 8) 403 / 390           512 x 8 of 64, 4 x 256 tokens (256, 32) 329 / 334
+//   256 x 8 of 32, 2 x 512 tokens (256, 16) 179 / 166       256 x 8 of 32, 4 x 256 tokens (256, 32) 159 / 163
+//   512 x 16 of 32, 1024 tokens (512, 16) 384 / 382         1024 x 16 of 64, 2 x 512 tokens (512, 32) 782 / 802
+bool one_launch(const AttnArgs& a) {
+  const long pairs = (long)a.B * a.nl, blocks = pairs * cdiv(a.S, 32);
+  return blocks <= 128 || (pairs <= 16 && blocks <= (a.dh <= 32 ? 512 : 256));
 }
 
 Args make_args(const AttnArgs& a, float* out) {
@@ -422,9 +472,9 @@ Args make_args(const AttnArgs& a, float* out) {
 
 // Head dimensions of exactly 32, 64 or 128 read rows 16 B at a time; every other one takes the next
 // larger of the three, padded.
-#define GX_F32_ATTN(KERNEL, ARGS)                                                                  \
+#define GX_F32_ATTN(KERNEL, ARGS, TIMES)                                                           \
   do {                                                                                             \
-    const dim3 grid((unsigned)((ARGS).npair * cdiv((ARGS).S, 32))), block(64 * PARTS);              \
+    const dim3 grid((unsigned)((TIMES) * (ARGS).npair * cdiv((ARGS).S, 32))), block(64 * PARTS);    \
     switch ((ARGS).dh) {                                                                           \
       case 32: hipLaunchKernelGGL((KERNEL<32, true>), grid, block, 0, s, (ARGS)); break;            \
       case 64: hipLaunchKernelGGL((KERNEL<64, true>), grid, block, 0, s, (ARGS)); break;            \
@@ -441,17 +491,21 @@ Args make_args(const AttnArgs& a, float* out) {
 hipError_t attn_fwd_f32(const AttnArgs& a, hipStream_t s) {
   if (!shape_ok(a)) return hipErrorInvalidValue;
   const Args f = make_args(a, (float*)a.ctx);
-  GX_F32_ATTN(attn_fwd_f32_kernel, f);
+  GX_F32_ATTN(attn_fwd_f32_kernel, f, 1);
   return hipGetLastError();
 }
 
 hipError_t attn_bwd_f32(const AttnArgs& a, hipStream_t s) {
   if (!shape_ok(a)) return hipErrorInvalidValue;
   const Args f = make_args(a, (float*)a.dqkv);
-  GX_F32_ATTN(attn_bwd_dq_f32_kernel, f);      // also leaves D for the next kernel
+  if (one_launch(a)) {
+    GX_F32_ATTN(attn_bwd_f32_kernel, f, 2);
+    return hipGetLastError();
+  }
+  GX_F32_ATTN(attn_bwd_dq_f32_kernel, f, 1);      // also leaves D for the next kernel
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  GX_F32_ATTN(attn_bwd_dkv_f32_kernel, f);
+  GX_F32_ATTN(attn_bwd_dkv_f32_kernel, f, 1);
   return hipGetLastError();
 }
 
