@@ -471,13 +471,22 @@ gx_status zero_grad(bool acc, float* out, long cols, hipStream_t st) {
 }
 
 // Whether the backward pass puts each weight gradient into the launch of an input gradient instead of on the side stream: fp32
-// layers all of whose products take the smallest tile.
+// layers whose products are at most 128 tiles of 64 x 64, or at most 256 with up to 256 tokens.  Forward and backward, us, side
+// stream / pairs: hidden 256 256 tokens 140 / 99, 1024 tokens 171 / 162; hidden 384 128 tokens 140 / 118, 256 165 / 146, 512
+// 197 / 202; hidden 512 64 tokens 147 / 128, 128 151 / 134, 256 184 / 178, 384 210 / 215; hidden 768 128 tokens 199 / 211, 256
+// 240 / 275.  Pairs in tiles of 64 x 64 gain and lose by turns (hidden 768: 512 tokens 396 / 369, 1024 602 / 617; hidden 1024:
+// 512 535 / 491, 1024 785 / 771, 1200 1198 / 1222; hidden 256, 4096 tokens 430 / 617) and are not taken.
 bool pair_products(const Dims& d, bool attn, bool mlp) {
   if (d.bf) return false;
-  auto smallest = [](long m, long n, long k) { return gx_f32_tile((int)m, (int)n, (int)k) == 0; };
-  if (mlp && !(smallest(d.T, d.Fl, d.H) && smallest(d.T, d.H, d.Fl) && smallest(d.Fl, d.H, d.T))) return false;
-  return !attn || (smallest(d.T, d.Hl, d.H) && smallest(d.T, d.H, 3 * d.Hl) && smallest(d.Hl, d.H, d.T) &&
-                   smallest(d.H, 3 * d.Hl, d.T));
+  auto tiles = [](long m, long n) { return (long)cdiv(m, 64) * cdiv(n, 64); };
+  long most = 0;
+  auto product = [&](long m, long n) {
+    const long t = tiles(m, n);
+    if (t > most) most = t;
+  };
+  if (mlp) product(d.T, d.Fl), product(d.T, d.H), product(d.H, d.Fl);
+  if (attn) product(d.T, d.Hl), product(d.T, d.H), product(d.Hl, d.H), product(d.H, 3 * d.Hl);
+  return most <= 128 || (most <= 256 && d.T <= 256);
 }
 
 gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, const void* dy, void* dx,
