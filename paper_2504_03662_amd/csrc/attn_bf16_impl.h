@@ -612,14 +612,25 @@ constexpr int KV_OFF_DO = KV_NQ * KV_TILE, KV_OFF_PX = KV_OFF_DO + KV_NDO * KV_T
 constexpr int KV_OFF_SINK = KV_OFF_PX + 2 * KV_PX, KV_SMEM = KV_OFF_SINK + 256;
 static_assert(2 * KV_SMEM <= 160 * 1024, "two workgroups per compute unit");
 
-template <bool DROP>
-__global__ void __launch_bounds__(64 * KV_NW, DH == 64 ? 3 : 2) attn_bwd_dkv_kernel(const bf16* __restrict__ qkv,
-                                                                  const bf16* __restrict__ dctx,
-                                                                  const float* __restrict__ lse,
-                                                                  const float* __restrict__ dsum,
-                                                                  bf16* __restrict__ dqkv, int S, int nl, int npair,
-                                                                  KeepArgs keep) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
+// What both kernels of the backward pass are given.
+struct BwdArgs {
+  const bf16 *qkv, *ctx, *dctx;
+  const float* lse;
+  float* dsum;
+  bf16* dqkv;
+  int S, nl, npair;
+};
+
+// Block `blk` of the launch order.  PAIRED: the second half of the blocks runs those with fewest tiles first.
+// OWN_D: D of the rows that see these keys is formed here first, from dO and O, into LDS behind the rings; else it is what the
+// dQ kernel has left.
+template <bool DROP, bool OWN_D>
+GX_DEVINL void dkv_block(const BwdArgs& a, const KeepArgs& keep, int blk, bool paired, char* smem) {
+  const bf16* __restrict__ const qkv = a.qkv;
+  const bf16* __restrict__ const dctx = a.dctx;
+  const float* __restrict__ const lse = a.lse;
+  bf16* __restrict__ const dqkv = a.dqkv;
+  const int S = a.S, nl = a.nl, npair = a.npair;
   constexpr int NS = DH / 16, NDT = DH / 32;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool role_v = wave < KV_PAIRS;
@@ -629,8 +640,8 @@ __global__ void __launch_bounds__(64 * KV_NW, DH == 64 ? 3 : 2) attn_bwd_dkv_ker
   // workgroups per unit, the second half runs those with fewest first, as in the forward kernel (16 pairs
   // of S 2048 2 % faster, 4 pairs of S 8192 4 %; with four times as many workgroups as places plain order is 8 %
   // faster).
-  const int kp = blockIdx.x % npair, rk = blockIdx.x / npair, nkb = (S + KV_BJ - 1) / KV_BJ, hk = (nkb + 1) / 2;
-  const int kb = rk < hk || gridDim.x > KV_PAIRED ? rk : nkb - 1 - (rk - hk);
+  const int kp = blk % npair, rk = blk / npair, nkb = (S + KV_BJ - 1) / KV_BJ, hk = (nkb + 1) / 2;
+  const int kb = rk < hk || !paired ? rk : nkb - 1 - (rk - hk);
   const int h = kp % nl, b = kp / nl;
   const int Hl = nl * DH, ld = 3 * Hl;
   const int j0 = kb * KV_BJ, jw = j0 + pair * 32;
@@ -646,7 +657,7 @@ __global__ void __launch_bounds__(64 * KV_NW, DH == 64 ? 3 : 2) attn_bwd_dkv_ker
   for (int dt = 0; dt < NDT; dt++) acc[dt] = zero16();
   const float scale = rsqrtf((float)DH), c2 = scale * LOG2E;
   const float* lrow = lse + ((size_t)b * nl + h) * S;
-  const float* drow = dsum + ((size_t)b * nl + h) * S;
+  const float* drow = a.dsum + ((size_t)b * nl + h) * S;
   char* const px = smem + KV_OFF_PX + pair * (KV_PX / KV_PAIRS) + lane * 16;
   unsigned coff[2][NDT];
   cols_lane_offsets(lane, coff);
@@ -676,11 +687,38 @@ __global__ void __launch_bounds__(64 * KV_NW, DH == 64 ? 3 : 2) attn_bwd_dkv_ker
   srcq.load(rq, (unsigned)t0 * q_bytes, col, q_slot(0), wave);
   srcq.load(rq, (unsigned)(t0 + 1) * q_bytes, col, q_slot(1), wave);
   srcdo.load(rdo, (unsigned)t0 * do_bytes, col, do_slot(0), wave);
-  aux_load(t0, wave == 0 ? do_slot(0) + KV_BI * ROWB : q_slot(0) + KV_BI * ROWB, wave < 2);
-  aux_load(t0 + 1, q_slot(1) + KV_BI * ROWB, wave == 1);
+  const bool lse_or_d = wave < (OWN_D ? 1 : 2), d_too = !OWN_D && wave == 1;
+  aux_load(t0, wave == 0 ? do_slot(0) + KV_BI * ROWB : q_slot(0) + KV_BI * ROWB, lse_or_d);
+  aux_load(t0 + 1, q_slot(1) + KV_BI * ROWB, d_too);
   srcq.load(rq, (unsigned)(t0 + 2) * q_bytes, col, q_slot(2), wave);
   srcdo.load(rdo, (unsigned)(t0 + 1) * do_bytes, col, do_slot(1), wave);
-  aux_load(wave == 0 ? t0 + 1 : t0 + 2, (wave == 0 ? do_slot(1) : q_slot(2)) + KV_BI * ROWB, wave < 2);
+  aux_load(wave == 0 ? t0 + 1 : t0 + 2, (wave == 0 ? do_slot(1) : q_slot(2)) + KV_BI * ROWB, lse_or_d);
+  float* const own_d = reinterpret_cast<float*>(smem + KV_SMEM);     // of rows j0 .. 32 nt - 1
+  if constexpr (OWN_D) {
+    // CPR lanes to a row, 16 bytes of it each
+    constexpr int RPS = 64 * KV_NW / CPR, AHEAD = 4;
+    const int rows = nt * KV_BI - j0, r0 = threadIdx.x / CPR, c = threadIdx.x % CPR;
+    const size_t at = ((size_t)b * S + j0) * Hl + h * DH + c * 8;
+    for (int base = 0; base < rows; base += AHEAD * RPS) {
+      bf16x8 x[AHEAD], y[AHEAD];
+#pragma unroll
+      for (int k = 0; k < AHEAD; k++) {
+        const size_t row = at + (size_t)min(base + k * RPS + r0, S - 1 - j0) * Hl;
+        x[k] = *reinterpret_cast<const bf16x8*>(dctx + row);
+        y[k] = *reinterpret_cast<const bf16x8*>(a.ctx + row);
+      }
+#pragma unroll
+      for (int k = 0; k < AHEAD; k++) {
+        float d = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; e++) d = __builtin_fmaf((float)x[k][e], (float)y[k][e], d);
+#pragma unroll
+        for (int o = CPR / 2; o > 0; o >>= 1) d += __shfl_xor(d, o, 64);
+        const int r = base + k * RPS + r0;
+        if (c == 0 && r < rows) own_d[r] = j0 + r < S ? d : 0.f;
+      }
+    }
+  }
   const int j = jw + l32;
   // dropout: this key's column of keep bits, KV_BI bits per query tile (both roles read them; they are
   // fetched one phase before their use)
@@ -699,7 +737,7 @@ __global__ void __launch_bounds__(64 * KV_NW, DH == 64 ? 3 : 2) attn_bwd_dkv_ker
   auto request = [&](int n, int i) __attribute__((always_inline)) {
     if (i < PER) srcq.issue(rq, (unsigned)(n + 3) * q_bytes, col, q_of(3), wave, i);
     else if (i < 2 * PER) srcdo.issue(rdo, (unsigned)(n + 2) * do_bytes, col, do_of(2), wave, i - PER);
-    else aux_load(wave == 0 ? n + 2 : n + 3, (wave == 0 ? do_of(2) : q_of(3)) + KV_BI * ROWB, wave < 2);
+    else aux_load(wave == 0 ? n + 2 : n + 3, (wave == 0 ? do_of(2) : q_of(3)) + KV_BI * ROWB, lse_or_d);
   };
   auto request_all = [&](int n) __attribute__((always_inline)) {
 #pragma unroll
@@ -741,7 +779,7 @@ __global__ void __launch_bounds__(64 * KV_NW, DH == 64 ? 3 : 2) attn_bwd_dkv_ker
     const char* rows = ROLE_V ? q_of(1) : do_of(0);
     const char* own = ROLE_V ? do_of(0) : q_of(4);                    // dO(n) and lse(n), or Q(n - 1) and D(n - 1)
     const unsigned ct = lds_addr(own);
-    const float* aux = reinterpret_cast<const float*>(own + KV_BI * ROWB);
+    const float* aux = OWN_D && !ROLE_V ? own_d + (n - 1) * KV_BI - j0 : reinterpret_cast<const float*>(own + KV_BI * ROWB);
     char* const pxn = px + ((ROLE_V ? n : n - 1) & 1) * KV_PX;
     f32x4 row_value[4];
 #pragma unroll
@@ -890,12 +928,16 @@ __global__ void __launch_bounds__(64 * KV_NW, DH == 64 ? 3 : 2) attn_bwd_dkv_ker
 // 250 us: steps of hidden 768, 1024 tokens 198.5 -> 193, hidden 2048, 8192 tokens 2486 -> 2465, attention half of 4 heads and
 // S 8192 958 -> 934; the order of the kernels beside those gradients changes with it, and a step with dropout of hidden 896,
 // 2976 tokens, is 3 % slower (252 -> 260) although its kernels one by one take 300 -> 288.
+// Block `blk` of the launch order; PAIRED as in the other kernel.
 template <int NQ, int SPLIT, int BKV, bool DROP>
-__global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
-    attn_bwd_dq_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ ctx, const bf16* __restrict__ dctx,
-                       const float* __restrict__ lse, float* __restrict__ dsum, bf16* __restrict__ dqkv, int S, int nl,
-                       int npair, KeepArgs keep) {
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
+GX_DEVINL void dq_block(const BwdArgs& a, const KeepArgs& keep, int blk, bool paired, char* smem) {
+  const bf16* __restrict__ const qkv = a.qkv;
+  const bf16* __restrict__ const ctx = a.ctx;
+  const bf16* __restrict__ const dctx = a.dctx;
+  const float* __restrict__ const lse = a.lse;
+  float* __restrict__ const dsum = a.dsum;
+  bf16* __restrict__ const dqkv = a.dqkv;
+  const int S = a.S, nl = a.nl, npair = a.npair;
   constexpr int NW = NQ * SPLIT, BQ = 32 * NQ, ROWS = BKV * SPLIT, STAGE = 2 * ROWS * ROWB;
   constexpr int NJT = BKV / 32;
   static_assert((SPLIT - 1) * NQ * (DH / 2) * 256 <= 2 * STAGE, "merge area fits the tile buffers");
@@ -903,11 +945,11 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
   const int qs = wave % NQ, part = wave / NQ;
   const int g = lane >> 5, l32 = lane & 31;
   const int nq = (S + BQ - 1) / BQ;
-  const int pair = blockIdx.x % npair;
+  const int pair = blk % npair;
   // longest blocks first; with two workgroups per compute unit (4 wavefronts each), the second
   // half of the launch runs shortest first, as in the forward kernel
-  const int rq = blockIdx.x / npair, hq = (nq + 1) / 2;
-  const int qt = (NW == 4 && rq >= hq) ? rq - hq : nq - 1 - rq;
+  const int rq = blk / npair, hq = (nq + 1) / 2;
+  const int qt = (paired && rq >= hq) ? rq - hq : nq - 1 - rq;
   const int h = pair % nl, b = pair / nl;
   const int Hl = nl * DH, ld = 3 * Hl;
   const int i0 = qt * BQ, iw = i0 + qs * 32;
@@ -1043,6 +1085,26 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1)
   }
 }
 
+// ------------------------------------------------------------------------------- backward: launches
+template <bool DROP>
+__global__ void __launch_bounds__(64 * KV_NW, DH == 64 ? 3 : 2) attn_bwd_dkv_kernel(BwdArgs a, KeepArgs keep) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  dkv_block<DROP, false>(a, keep, blockIdx.x, gridDim.x <= KV_PAIRED, smem);
+}
+template <int NQ, int SPLIT, int BKV, bool DROP>
+__global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1) attn_bwd_dq_kernel(BwdArgs a, KeepArgs keep) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  dq_block<NQ, SPLIT, BKV, DROP>(a, keep, blockIdx.x, NQ * SPLIT == 4, smem);
+}
+// Both in one launch (see one_launch()), first the blocks of dK / dV, which have more to do.
+template <bool DROP>
+__global__ void __launch_bounds__(256, 2) attn_bwd_both_kernel(BwdArgs a, KeepArgs rows, KeepArgs cols) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int blk = blockIdx.x, n = gridDim.x / 2;
+  if (blk < n) dkv_block<DROP, true>(a, cols, blk, false, smem);
+  else dq_block<2, 2, 32, DROP>(a, rows, blk - n, false, smem);
+}
+
 template <typename K>
 hipError_t set_smem(K kernel, int bytes) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1123,6 +1185,21 @@ hipError_t fwd(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Whether dQ and dK / dV share a launch: where nothing of another stream runs beside them, all of their workgroups find a place
+// at once, and forming D twice takes less than the dQ kernel.  Forward and backward on one stream, us, two launches / one: hidden
+// 512 (head dim 64) 64 tokens 117.6 / 112.8, 256 131 / 126.5, 1024 166 / 161.5, 2048 212.6 / 213.2; hidden 1024, degree 4, 1024
+// tokens 161.6 / 156.8; attention half of hidden 768, 1024 tokens 114 / 110.  Beside the weight gradients of larger layers it
+// gains (hidden 1024, 1024 tokens 237 / 227) and loses (hidden 2048, 1024 tokens 454 / 467; hidden 768, degree 2, 2 x 1024 191 /
+// 197) and is not taken.
+constexpr int ONE_LAUNCH_S = 1024;
+bool one_launch(const AttnArgs& a) {
+  return a.alone && a.S <= ONE_LAUNCH_S && (long)a.B * a.nl * cdiv(a.S, KV_BJ) <= 256;
+}
+int one_launch_smem(int S) {
+  const int kv = KV_SMEM + 4 * KV_BI * cdiv(S, KV_BI);
+  return kv > SMEM_FEW ? kv : SMEM_FEW;
+}
+
 // dQ with D, then dK / dV.
 hipError_t bwd(const AttnArgs& a, hipStream_t s) {
   if (!attn_shape_ok(a)) return hipErrorInvalidValue;
@@ -1130,6 +1207,8 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s) {
   if (!configured) {
     hipError_t e = set_smem(attn_bwd_dkv_kernel<false>, KV_SMEM);
     if (e == hipSuccess) e = set_smem(attn_bwd_dkv_kernel<true>, KV_SMEM);
+    if (e == hipSuccess) e = set_smem(attn_bwd_both_kernel<false>, one_launch_smem(ONE_LAUNCH_S));
+    if (e == hipSuccess) e = set_smem(attn_bwd_both_kernel<true>, one_launch_smem(ONE_LAUNCH_S));
     if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<4, 1, 64, false>, SMEM_MANY);
     if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<2, 2, 32, false>, SMEM_FEW);
     if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<2, 4, 32, false>, SMEM_FOUR_DQ);
@@ -1143,9 +1222,20 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s) {
   if (drop && (!a.colbits || a.wpr != 2 * cdiv(a.S, 64))) return hipErrorInvalidValue;
   const KeepArgs keep_rows{a.rowbits, a.wpr, a.keep_scale}, keep_cols{a.colbits, a.wpr, a.keep_scale};
   const int npair = a.nl * a.B;
+  const BwdArgs args{(const bf16*)a.qkv, (const bf16*)a.ctx, (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv,
+                     a.S, a.nl, npair};
+  if (one_launch(a)) {
+    static_assert(KV_BJ == 64, "as many blocks of keys as of queries");
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(2 * cdiv(a.S, KV_BJ) * npair), dim3(256), one_launch_smem(a.S), s, args, keep_rows,
+                         keep_cols);
+    };
+    if (drop) go(attn_bwd_both_kernel<true>);
+    else go(attn_bwd_both_kernel<false>);
+    return hipGetLastError();
+  }
   auto go_dq = [&](auto kernel, int bq, int threads, int smem) {
-    hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, bq) * npair), dim3(threads), smem, s, (const bf16*)a.qkv,
-                       (const bf16*)a.ctx, (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, npair, keep_rows);
+    hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, bq) * npair), dim3(threads), smem, s, args, keep_rows);
   };
   const int shares = dq_key_shares(a);
   if (shares == 4) {
@@ -1161,8 +1251,7 @@ hipError_t bwd(const AttnArgs& a, hipStream_t s) {
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   auto go_dkv = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, KV_BJ) * a.nl * a.B), dim3(64 * KV_NW), KV_SMEM, s, (const bf16*)a.qkv,
-                       (const bf16*)a.dctx, a.lse, a.dsum, (bf16*)a.dqkv, a.S, a.nl, a.nl * a.B, keep_cols);
+    hipLaunchKernelGGL(kernel, dim3(cdiv(a.S, KV_BJ) * npair), dim3(64 * KV_NW), KV_SMEM, s, args, keep_cols);
   };
   if (drop) go_dkv(attn_bwd_dkv_kernel<true>);
   else go_dkv(attn_bwd_dkv_kernel<false>);

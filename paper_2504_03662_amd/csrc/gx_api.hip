@@ -489,6 +489,17 @@ bool pair_products(const Dims& d, bool attn, bool mlp) {
   return most <= 128 || (most <= 256 && d.T <= 256);
 }
 
+// Whether a bf16 backward pass stays on one stream: by its multiply-adds per pass over the weights, tokens times weights.  Below
+// the line handing work over (an event recorded, one waited for, twice, and the host's part in it) costs more than what runs
+// side by side saves.  Forward and backward, us, two streams / one (with dQ and dK / dV in one launch): hidden 512 64 tokens (0.2
+// G) 139 / 113, 256 (0.8 G) 138 / 126, 1024 (3.2 G) 171 / 161, 2048 (6.4 G) 211 / 213; hidden 768 256 tokens (1.8 G) 147 / 145,
+// 512 (3.6 G) 162 / 163, 1024 192 / 195; hidden 1024 64 tokens 153 / 145, degree 4 1024 tokens (3.2 G) 168 / 157; hidden 2048 64
+// tokens (3.2 G) 227 / 225, degree 8 256 tokens (1.6 G) 156 / 147; hidden 768, halves alone: attention 1024 tokens (2.4 G) 120 /
+// 110, feed-forward 512 (2.4 G) 86 / 79.
+bool one_stream(const Dims& d, bool attn, bool mlp) {
+  return d.bf && d.T * ((attn ? 4 * d.H * d.Hl : 0) + (mlp ? 2 * d.H * d.Fl : 0)) <= 3250000000L;
+}
+
 gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, const void* dy, void* dx,
                   const gx_grads& gr, const Saved& sv, const Work& w, const DropBufs& db, hipStream_t st,
                   bool allow_side) {
@@ -511,7 +522,8 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
     g.resid = g.C;
     return gemm(d, LAY_TN, EPI_RESID, g, s);
   };
-  Fork fk(st, allow_side && !paired);
+  const bool serial = one_stream(d, attn, mlp);
+  Fork fk(st, allow_side && !paired && !serial);
   Finisher fin;
   gx_status s;
   // The weight-gradient products only consume finished tensors, so they are handed to the side
@@ -632,6 +644,7 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
     memset(&a, 0, sizeof(a));
     a.qkv = sv.qkv; a.ctx = sv.ctx; a.lse = sv.lse; a.dctx = w.dctx; a.dqkv = w.dqkv; a.dsum = w.dsum;
     a.B = (int)d.B; a.S = (int)d.S; a.nl = (int)d.nl; a.dh = (int)d.dh;
+    a.alone = serial;
     set_attn_drop(a, d, dr, db);
     { ProfScope ps(GX_KC_ATTN_BWD, st);
     // the dK / dV kernel follows the dQ kernel, which leaves D for it, on the caller's stream (streams of their

@@ -74,6 +74,7 @@ struct AttnArgs {
   void* dqkv;         // bwd out, same layout as qkv
   float* dsum;        // bwd scratch: rowsum(dctx * ctx)
   int B, S, nl, dh;
+  bool alone;         // bf16 bwd: no weight gradient runs beside it (a rule on sizes: it may decide which kernel is taken)
   // dropout of the probabilities (rowbits == nullptr: none): keep bits from attn_mask, row-major for
   // the forward and dQ kernels, column-major for dK / dV (bf16 path; the fp32 path reads rowbits
   // throughout), wpr words per row, kept probabilities multiplied by keep_scale
