@@ -360,9 +360,11 @@ __global__ void __launch_bounds__(T::THREADS, 2) gemm_kernel(GemmArgs g) {
   };
 
   // The first block is fetched before the last tiles where the registers allow it (nothing may
-  // spill there: a fragment read in flight must not be moved), else after them.
+  // spill there: a fragment read in flight must not be moved), else after them.  Gradients added to on 256 x 128 tiles, operands
+  // not in the caches, us: 4096 x 2048 x 3003 57.5 without, 56.0 with it, 2048 x 4096 x 3003 55.5 / 54.1; on 128 x 128
+  // 1024 x 3072 x 4096 31.2 / 30.2.
   constexpr int SIDE_VGPRS = 2 * NJ * (Side<EPI>::F32 ? 2 : Side<EPI>::B16) + 4 * NC;
-  constexpr bool EARLY = SIDE_VGPRS <= (TM * TN >= 32 ? 8 : 24);
+  constexpr bool EARLY = SIDE_VGPRS <= (TM * TN >= 32 ? 8 : TM * TN >= 24 ? 24 : 40);
   char* sa = smem;                       // A[STAGES]
   char* sb = smem + STAGES * A_BYTES;    // B[STAGES]
   const int nk = (g.K + KE - 1) / KE;
