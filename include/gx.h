@@ -160,7 +160,9 @@ size_t gx_layer_workspace_bytes(const gx_layer_cfg* cfg, int is_backward);
  *   ATTN only   : x in, p_attn out (required); y, p_mlp ignored.
  *   MLP only    : x holds h1, p_mlp out (required); y, p_attn ignored.
  * `saved` (gx_layer_saved_bytes) receives the activations gx_layer_bwd needs; `workspace` may be
- * NULL when gx_layer_workspace_bytes(cfg, 0) is 0. */
+ * NULL when gx_layer_workspace_bytes(cfg, 0) is 0, and also where it is not 0 without dropout (few
+ * tokens: the reductions of the products are cut into parts there; without it each product is one
+ * launch, and results differ by the order of additions). */
 gx_status gx_layer_fwd(const gx_layer_cfg* cfg, const gx_params* params, const void* x, void* y, void* p_attn,
                        void* p_mlp, void* saved, void* workspace, void* hip_stream);
 

@@ -198,6 +198,10 @@ GX_DEVINL void finish_run(const GemmArgs& g, size_t idx, const f32x4& xv, const 
                           float (&cs)[4]) {
   float x[4] = {xv[0] + bv[0], xv[1] + bv[1], xv[2] + bv[2], xv[3] + bv[3]};
   bf16* aux = static_cast<bf16*>(g.aux);
+  if (EPI == EPI_PART) {
+    *reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + idx) = f32x4{x[0], x[1], x[2], x[3]};
+    return;
+  }
   if (EPI == EPI_F32) {
     __builtin_nontemporal_store(f32x4{x[0], x[1], x[2], x[3]},
                                 reinterpret_cast<f32x4*>(static_cast<float*>(g.C) + idx));
@@ -294,6 +298,15 @@ __global__ void __launch_bounds__(T::THREADS, 2) gemm_kernel(GemmArgs g) {
     if ((int)blockIdx.x >= g.tiles) return read_ahead<T>(g, smem, wave, lane);
   int pid = blockIdx.x;
   const int nwg = g.tiles;
+  if constexpr (EPI == EPI_PART) {
+    // parts of a tile are consecutive workgroups; each is a product of its own over its share of the reduction
+    const int parts = gridDim.x / nwg, part = pid % parts, k0 = part * g.tile_first;
+    pid /= parts;
+    g.A = static_cast<const bf16*>(g.A) + k0;
+    g.B = static_cast<const bf16*>(g.B) + (size_t)k0 * g.ldb;
+    g.C = static_cast<float*>(g.C) + (size_t)part * g.M * g.ldc;
+    g.K = min(g.K - k0, g.tile_first);
+  }
   const int xcd = pid & 7;
   pid = xcd * (nwg >> 3) + min(xcd, nwg & 7) + (pid >> 3);      // XCD's share: nwg / 8, one more for the first nwg % 8
   // tail launch: the walk runs over super-tiles of 2BM x 2BN (the tiles of the large-tile launch
@@ -746,6 +759,46 @@ hipError_t launch(const GemmArgs& g, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+// Few tokens: the reduction is cut into parts, so that every compute unit streams weights, and a second launch adds the parts in
+// order and does the epilogue.  A unit takes 40 to 50 bytes per ns of weights and operands from memory, whatever the tile (rows of
+// weights lie tens of KB apart; reading 128 columns instead of 64 and deeper rings change little), so what counts is how little
+// each has to take: wide tiles on as many units as there are.  Without the second launch, weights not in the caches, us,
+// one launch of the best tile / parts of 128 x 128 tiles: 128 x 10240 x 5120 45 / 27 (3 parts), 128 x 5120 x 10240 63 / 28 (6),
+// 128 x 7680 x 5120 33 / 22 (4); the second takes 4 to 5.
+template <int EPI>
+__global__ void __launch_bounds__(256) split_finish_kernel(GemmArgs g, const float* __restrict__ part, int parts) {
+  const long run = (long)blockIdx.x * 256 + threadIdx.x, per_row = g.N / 4;
+  if (run >= g.M * per_row) return;
+  const int row = (int)(run / per_row), col = 4 * (int)(run % per_row);
+  const size_t idx = (size_t)row * g.ldc + col, stride = (size_t)g.M * g.ldc;
+  Side<EPI> side;
+  if (Side<EPI>::ANY) side.fetch(g, idx);
+  float bv[4], cs[4];
+  load_bias<EPI>(g, col, bv);
+  f32x4 x = *reinterpret_cast<const f32x4*>(part + idx);
+#pragma unroll 4
+  for (int k = 1; k < parts; k++) {
+    const f32x4 p = *reinterpret_cast<const f32x4*>(part + k * stride + idx);
+    x = f32x4{x[0] + p[0], x[1] + p[1], x[2] + p[2], x[3] + p[3]};
+  }
+  finish_run<LAY_NN, EPI>(g, idx, x, bv, side, cs);
+}
+// steps of a part: whole stages of every tile used; parts that are at least SPLIT_K long
+constexpr int SPLIT_UNIT = 128, SPLIT_K = 256, SPLIT_TOKENS = 256, SPLIT_N = 128;
+int split_steps(int N, int K) {
+  const int most = ROUND / cdiv(N, SPLIT_N);
+  if (most < 2) return K;
+  const int steps = cdiv(cdiv(K, most), SPLIT_UNIT) * SPLIT_UNIT;
+  return steps < SPLIT_K ? SPLIT_K : steps;
+}
+template <class T>
+hipError_t launch_parts(const GemmArgs& g, int parts, hipStream_t s) {
+  GemmArgs a = g;
+  a.group = 8;
+  a.tiles = cdiv(a.M, T::BM) * cdiv(a.N, T::BN);
+  return start<LAY_NN, EPI_PART, T, false>(a, s, a.tiles * parts);
+}
+
 // The combinations that the layer driver asks for.
 template <int LAY>
 hipError_t dispatch_epi(Epilogue epi, const GemmArgs& g, hipStream_t s) {
@@ -792,26 +845,63 @@ extern "C" int gx_bf16_read_ahead(int M, int N, int K, long next_bytes, long cal
   return 0;
 }
 
+namespace {
+bool args_ok(Layout lay, const GemmArgs& g) {
+  if (g.M <= 0 || g.N <= 0 || g.K <= 0) return false;
+  // 16-byte chunks along each operand's contiguous index; 31-bit byte offsets in buffer loads
+  const long a_rows = (lay == LAY_TN) ? g.K : g.M, b_rows = (lay == LAY_NT) ? g.N : g.K;
+  if ((g.lda & 7) || (g.ldb & 7)) return false;
+  if (lay != LAY_TN && (g.K & 7)) return false;
+  if (lay == LAY_TN && (g.M & 7)) return false;
+  if (lay != LAY_NT && (g.N & 7)) return false;
+  // the epilogue moves runs of 4 columns as one vector
+  if ((g.N & 3) || (g.ldc & 3) || (reinterpret_cast<uintptr_t>(g.C) & 15)) return false;
+  if (a_rows * g.lda * 2 >= (1L << 31) || b_rows * g.ldb * 2 >= (1L << 31)) return false;
+  return !((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B)) & 15);
+}
+}  // namespace
+
 hipError_t gemm_bf16(Layout lay, Epilogue epi, const GemmArgs& args, hipStream_t s) {
   GemmArgs g = args;
   g.tail = g.tile_first = g.group = g.tiles = 0;       // the launcher's own fields
-  if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipErrorInvalidValue;
-  // 16-byte chunks along each operand's contiguous index; 31-bit byte offsets in buffer loads
-  const long a_rows = (lay == LAY_TN) ? g.K : g.M, b_rows = (lay == LAY_NT) ? g.N : g.K;
-  if ((g.lda & 7) || (g.ldb & 7)) return hipErrorInvalidValue;
-  if (lay != LAY_TN && (g.K & 7)) return hipErrorInvalidValue;
-  if (lay == LAY_TN && (g.M & 7)) return hipErrorInvalidValue;
-  if (lay != LAY_NT && (g.N & 7)) return hipErrorInvalidValue;
-  // the epilogue moves runs of 4 columns as one vector
-  if ((g.N & 3) || (g.ldc & 3) || (reinterpret_cast<uintptr_t>(g.C) & 15)) return hipErrorInvalidValue;
-  if (a_rows * g.lda * 2 >= (1L << 31) || b_rows * g.ldb * 2 >= (1L << 31)) return hipErrorInvalidValue;
-  if ((reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B)) & 15) return hipErrorInvalidValue;
+  if (!args_ok(lay, g)) return hipErrorInvalidValue;
   switch (lay) {
     case LAY_NN: return dispatch_epi<LAY_NN>(epi, g, s);
     case LAY_NT: return dispatch_epi<LAY_NT>(epi, g, s);
     case LAY_TN: return dispatch_epi<LAY_TN>(epi, g, s);
   }
   return hipErrorInvalidValue;
+}
+
+extern "C" int gx_bf16_split(int M, int N, int K) {
+  if (M > SPLIT_TOKENS) return 1;
+  return cdiv(K, split_steps(N, K));
+}
+size_t gemm_bf16_split_bytes(int M, int N, int K) {
+  const int parts = gx_bf16_split(M, N, K);
+  return parts > 1 ? (size_t)parts * M * N * 4 : 0;
+}
+
+hipError_t gemm_bf16_split(Epilogue epi, const GemmArgs& args, float* scratch, hipStream_t s) {
+  const int parts = gx_bf16_split(args.M, args.N, args.K);
+  if (parts < 2 || !scratch || !args_ok(LAY_NN, args) || args.ldc != args.N) return hipErrorInvalidValue;
+  GemmArgs p = args;
+  p.C = scratch;
+  p.bias = p.resid = p.next = nullptr;
+  p.aux = nullptr;
+  p.tail = 0;
+  p.tile_first = split_steps(args.N, args.K);
+  hipError_t e = p.M <= 64 ? launch_parts<Flat>(p, parts, s) : p.M <= 128 ? launch_parts<Small>(p, parts, s)
+                                                                        : launch_parts<Half>(p, parts, s);
+  if (e != hipSuccess) return e;
+  const dim3 grid((unsigned)cdiv((long)args.M * (args.N / 4), 256L));
+  switch (epi) {
+    case EPI_BIAS: hipLaunchKernelGGL(split_finish_kernel<EPI_BIAS>, grid, dim3(256), 0, s, args, scratch, parts); break;
+    case EPI_RESID: hipLaunchKernelGGL(split_finish_kernel<EPI_RESID>, grid, dim3(256), 0, s, args, scratch, parts); break;
+    case EPI_GELU: hipLaunchKernelGGL(split_finish_kernel<EPI_GELU>, grid, dim3(256), 0, s, args, scratch, parts); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 }  // namespace gx

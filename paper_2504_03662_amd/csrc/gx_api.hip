@@ -192,6 +192,38 @@ DropBufs plan_drop(const gx_layer_cfg& c, Arena& a, bool bwd) {
   return b;
 }
 
+// Forward passes of few tokens stream weights, and a compute unit streams them at 30 to 50 bytes per ns whatever its tile: with
+// the reductions of the products cut into parts (gemm_bf16_split) all units do.  It costs a launch per product, which only
+// weights beyond what the memory-side cache delivers quickly repay.  Forward, one launch per product (reading ahead) / parts,
+// us, one layer again and again; others in between:
+//   up to 64 tokens : hidden 1024 (25 MB) 64 tokens 52 / 53; 65 / 57      hidden 4096, degree 8 (50 MB) 64 tokens 64 / 64; 90 / 68
+//                     hidden 768 (14 MB) 64 tokens 45 / 48; 46 / 49       hidden 2048 (101 MB) 64 tokens 79 / 67; 113 / 76
+//                     hidden 5120, degree 2 (315 MB) 1 token 149 / 97, 16 154 / 99, 64 177 / 110; 178 / 114
+//   up to 128       : hidden 4096, degree 8 (50 MB) 65 / 78; 88 / 81      degree 4 (101 MB) 100 tokens 73 / 73; 99 / 83
+//                     hidden 2048 (101 MB) 128 tokens 80 / 80; 110 / 90   hidden 8192, degree 8 (185 MB) 104 / 94; 147 / 112
+//                     hidden 5120, degree 2 161 / 132; 162 / 136          hidden 4096 (403 MB) 196 / 147; 196 / 150
+//   up to 256       : hidden 4096, degree 2 (201 MB) 200 tokens 102 / 116; 135 / 129     hidden 4096 204 / 172; 205 / 172
+//                     hidden 5120, degree 2 256 tokens 191 / 175; 194 / 174   hidden 2048 (101 MB) 256 tokens 88 / 103; 120 / 115
+bool split_pays(const gx_layer_cfg& c) {
+  const Dims d = dims_of(c);
+  if (!d.bf || (c.flags & GX_FWD_SAVED_ONLY)) return false;
+  const long weights = (((c.flags & GX_PHASE_ATTN) ? 4 * d.H * d.Hl : 0) + ((c.flags & GX_PHASE_MLP) ? 2 * d.H * d.Fl : 0)) * 2;
+  return weights >= (d.T <= 64 ? 32L << 20 : d.T <= 128 ? 90L << 20 : 256L << 20);
+}
+// The scratch that takes, for one product at a time.  A caller that gives no workspace gets one launch per product.
+size_t split_bytes(const gx_layer_cfg& c) {
+  if (!split_pays(c)) return 0;
+  const Dims d = dims_of(c);
+  size_t most = 0;
+  auto product = [&](long n, long k) {
+    const size_t b = gemm_bf16_split_bytes((int)d.T, (int)n, (int)k);
+    if (b > most) most = b;
+  };
+  if (c.flags & GX_PHASE_ATTN) product(3 * d.Hl, d.H), product(d.H, d.Hl);
+  if (c.flags & GX_PHASE_MLP) product(d.Fl, d.H), product(d.H, d.Fl);
+  return most;
+}
+
 gx_status validate(const gx_layer_cfg* c) {
   if (!c) return GX_ERR_NULL;
   if (c->dtype != GX_F32 && c->dtype != GX_BF16) return GX_ERR_DTYPE;
@@ -385,7 +417,7 @@ void set_attn_drop(AttnArgs& a, const Dims& d, const Drop& dr, const DropBufs& d
 // Forward kernel sequence.  `for_backward_only` skips the products whose results the backward
 // pass does not need (used when recomputing activations).
 gx_status run_fwd(const gx_layer_cfg& c, const gx_params& p, const void* x, void* y, void* p_attn, void* p_mlp,
-                  const Saved& sv, const DropBufs& db, bool for_backward_only, hipStream_t st) {
+                  const Saved& sv, const DropBufs& db, float* split, bool for_backward_only, hipStream_t st) {
   const Dims d = dims_of(c);
   const Drop dr = drop_of(c);
   const bool attn = c.flags & GX_PHASE_ATTN, mlp = c.flags & GX_PHASE_MLP;
@@ -393,9 +425,14 @@ gx_status run_fwd(const gx_layer_cfg& c, const gx_params& p, const void* x, void
   const long call_bytes = ((attn ? 4 * d.H * d.Hl : 0) + (mlp ? 2 * d.H * d.Fl : 0)) * d.e;
   auto read_next = [&](GemmArgs& g, const void* w, long elements) {
     // recomputation runs beside a backward pass, which has work for the compute units that a product leaves idle
-    if (!d.bf || for_backward_only || !read_ahead_pays((long)g.N * g.K * d.e, elements * d.e, call_bytes)) return;
+    if (!d.bf || split || for_backward_only || !read_ahead_pays((long)g.N * g.K * d.e, elements * d.e, call_bytes)) return;
     g.next = w;
     g.next_bytes = (unsigned)(elements * d.e);
+  };
+  auto product = [&](Epilogue epi, const GemmArgs& g) -> hipError_t {
+    if (!split || gx_bf16_split(g.M, g.N, g.K) < 2) return gemm(d, LAY_NN, epi, g, st);
+    ProfScope ps(gemm_class(LAY_NN, epi), st);
+    return gemm_bf16_split(epi, g, split, st);
   };
   if (attn) {
     { ProfScope ps(GX_KC_LN_FWD, st);
@@ -403,7 +440,7 @@ gx_status run_fwd(const gx_layer_cfg& c, const gx_params& p, const void* x, void
     GemmArgs g = gargs(sv.y1, p.w_qkv, sv.qkv, d.T, 3 * d.Hl, d.H, d.H, 3 * d.Hl, 3 * d.Hl);
     g.bias = p.b_qkv;
     read_next(g, p.w_o, d.Hl * d.H);
-    GX_TRY(gemm(d, LAY_NN, EPI_BIAS, g, st));
+    GX_TRY(product(EPI_BIAS, g));
     AttnArgs a;
     memset(&a, 0, sizeof(a));
     a.qkv = sv.qkv; a.ctx = sv.ctx; a.lse = sv.lse;
@@ -417,7 +454,7 @@ gx_status run_fwd(const gx_layer_cfg& c, const gx_params& p, const void* x, void
       GemmArgs o = gargs(sv.ctx, p.w_o, pa, d.T, d.H, d.Hl, d.Hl, d.H, d.H);
       o.bias = (c.flags & GX_ROW_BIAS_ATTN) ? p.b_o : nullptr;
       read_next(o, p.w_fc1, d.H * d.Fl);
-      GX_TRY(gemm(d, LAY_NN, EPI_BIAS, o, st));
+      GX_TRY(product(EPI_BIAS, o));
       GX_TRY(dropout_p(d, dr, pa, x, sv.h1, DROP_STREAM_ATTN_OUT, st));
       h1 = sv.h1;
     } else if (mlp) {
@@ -426,12 +463,12 @@ gx_status run_fwd(const gx_layer_cfg& c, const gx_params& p, const void* x, void
       o.resid = x;
       o.aux = p_attn;
       read_next(o, p.w_fc1, d.H * d.Fl);
-      GX_TRY(gemm(d, LAY_NN, EPI_RESID, o, st));
+      GX_TRY(product(EPI_RESID, o));
       h1 = sv.h1;
     } else if (!for_backward_only) {
       GemmArgs o = gargs(sv.ctx, p.w_o, p_attn, d.T, d.H, d.Hl, d.Hl, d.H, d.H);
       o.bias = (c.flags & GX_ROW_BIAS_ATTN) ? p.b_o : nullptr;
-      GX_TRY(gemm(d, LAY_NN, EPI_BIAS, o, st));
+      GX_TRY(product(EPI_BIAS, o));
     }
   }
   if (mlp) {
@@ -442,20 +479,20 @@ gx_status run_fwd(const gx_layer_cfg& c, const gx_params& p, const void* x, void
     f1.aux = sv.act;
     f1.gelu_tanh = (c.flags & GX_GELU_TANH) ? 1 : 0;
     read_next(f1, p.w_fc2, d.Fl * d.H);
-    GX_TRY(gemm(d, LAY_NN, EPI_GELU, f1, st));
+    GX_TRY(product(EPI_GELU, f1));
     if (!for_backward_only) {
       void* pm = p_mlp ? p_mlp : db.partial;
       GemmArgs f2 = gargs(sv.act, p.w_fc2, dr.hidden ? pm : attn ? y : p_mlp, d.T, d.H, d.Fl, d.Fl, d.H, d.H);
       f2.bias = (c.flags & GX_ROW_BIAS_MLP) ? p.b_fc2 : nullptr;
       if (dr.hidden) {
-        GX_TRY(gemm(d, LAY_NN, EPI_BIAS, f2, st));
+        GX_TRY(product(EPI_BIAS, f2));
         GX_TRY(dropout_p(d, dr, pm, h1, y, DROP_STREAM_MLP_OUT, st));
       } else if (attn) {
         f2.resid = h1;
         f2.aux = p_mlp;
-        GX_TRY(gemm(d, LAY_NN, EPI_RESID, f2, st));
+        GX_TRY(product(EPI_RESID, f2));
       } else {
-        GX_TRY(gemm(d, LAY_NN, EPI_BIAS, f2, st));
+        GX_TRY(product(EPI_BIAS, f2));
       }
     }
   }
@@ -722,7 +759,7 @@ gx_status layer_bwd(const gx_layer_cfg* cfg, const gx_params* params, const void
   const Saved sv = plan_saved(*cfg, sa);
   if ((s = make_attn_mask(*cfg, db, st)) != GX_OK) return s;
   if (recompute) {
-    s = run_fwd(*cfg, *params, x, nullptr, nullptr, nullptr, sv, db, true, st);
+    s = run_fwd(*cfg, *params, x, nullptr, nullptr, nullptr, sv, db, nullptr, true, st);
     if (s != GX_OK) return s;
   }
   return run_bwd(*cfg, *params, x, dy, dx, *grads, sv, w, db, st, allow_side);
@@ -761,6 +798,7 @@ size_t gx_layer_workspace_bytes(const gx_layer_cfg* cfg, int is_backward) {
   Arena a(nullptr);
   if (is_backward) plan_work(*cfg, a);
   plan_drop(*cfg, a, is_backward != 0);
+  if (!is_backward) a.take(split_bytes(*cfg));
   return a.off;
 }
 
@@ -769,7 +807,9 @@ gx_status gx_layer_fwd(const gx_layer_cfg* cfg, const gx_params* params, const v
   gx_status s = validate(cfg);
   if (s != GX_OK) return s;
   if (!params || !x || !saved) return GX_ERR_NULL;
-  if (!workspace && gx_layer_workspace_bytes(cfg, 0) != 0) return GX_ERR_NULL;
+  Arena need(nullptr);
+  plan_drop(*cfg, need, false);
+  if (!workspace && need.off != 0) return GX_ERR_NULL;
   if (misaligned(workspace)) return GX_ERR_ALIGN;
   const bool attn = cfg->flags & GX_PHASE_ATTN, mlp = cfg->flags & GX_PHASE_MLP;
   const bool saved_only = cfg->flags & GX_FWD_SAVED_ONLY;
@@ -786,10 +826,11 @@ gx_status gx_layer_fwd(const gx_layer_cfg* cfg, const gx_params* params, const v
   const Saved sv = plan_saved(*cfg, a);
   Arena wa(workspace);
   const DropBufs db = plan_drop(*cfg, wa, false);
+  float* split = workspace && split_bytes(*cfg) ? static_cast<float*>(wa.take(0)) : nullptr;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   if ((s = make_attn_mask(*cfg, db, st)) != GX_OK) return s;
-  if (saved_only) return run_fwd(*cfg, *params, x, nullptr, nullptr, nullptr, sv, db, true, st);
-  return run_fwd(*cfg, *params, x, y, p_attn, p_mlp, sv, db, false, st);
+  if (saved_only) return run_fwd(*cfg, *params, x, nullptr, nullptr, nullptr, sv, db, nullptr, true, st);
+  return run_fwd(*cfg, *params, x, y, p_attn, p_mlp, sv, db, split, false, st);
 }
 
 gx_status gx_layer_bwd(const gx_layer_cfg* cfg, const gx_params* params, const void* x, const void* dy, void* dx,

@@ -20,7 +20,8 @@ enum Epilogue {
   EPI_GELU,        // z = acc + bias[n]; C = gelu'(z); aux = gelu(z)  (erf form, or tanh form if gelu_tanh)
   EPI_DGELU,       // C = acc * z[m,n], z holding what EPI_GELU left in C
   EPI_F32,         // C (fp32) = acc
-  EPI_F32_ACC      // C (fp32) += acc
+  EPI_F32_ACC,     // C (fp32) += acc
+  EPI_PART         // C[part] (fp32) = acc over the part's reduction steps (the bf16 launcher's own: gemm_bf16_split)
 };
 
 struct GemmArgs {
@@ -43,7 +44,8 @@ struct GemmArgs {
                        // fp32 TN, optional: column sums of B, [N], stored or, with EPI_F32_ACC, added to
   // set by the bf16 launcher only (callers leave them 0): a launch that covers the super-tiles
   // (2 x 2 kernel tiles) numbered tile_first onwards in the tile walk, four workgroups each, the
-  // tile-rows that the walk takes at a time, and how many workgroups have a tile
+  // tile-rows that the walk takes at a time, and how many workgroups have a tile; EPI_PART: tile_first holds
+  // the reduction steps of a part
   int tail, tile_first, group, tiles;
 };
 static_assert(sizeof(GemmArgs) == 112, "a launch copies it: 136 bytes cost a product 0.2 us");
@@ -57,6 +59,12 @@ extern "C" int gx_bf16_tile(int M, int N, int K, int column_sums);
 bool read_ahead_pays(long own_bytes, long next_bytes, long call_bytes);
 // Workgroups without a tile with which gemm_bf16 then launches an NN product (host code, for tests)
 extern "C" int gx_bf16_read_ahead(int M, int N, int K, long next_bytes, long call_bytes);
+// Forward products of few tokens: into how many parts gemm_bf16_split cuts the reduction (1: it is not for this product),
+// and the scratch that takes, one fp32 copy of C per part.  extern "C": host code, for tests.
+extern "C" int gx_bf16_split(int M, int N, int K);
+size_t gemm_bf16_split_bytes(int M, int N, int K);
+// The NN product with its reduction cut into parts, and a second launch that adds them in order and does the epilogue
+hipError_t gemm_bf16_split(Epilogue epi, const GemmArgs& g, float* scratch, hipStream_t s);
 // Which kernel gemm_f32 takes (host code, for tests): 0 32x32 tiles with four wavefronts, 64x64 with 1 two and 2 one per 32x32
 // block, 3 and 4 the same for short reductions
 extern "C" int gx_f32_tile(int M, int N, int K);

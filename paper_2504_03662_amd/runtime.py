@@ -89,7 +89,9 @@ class DeviceLayer:
         else:
             p_mlp = out if out is not None else self.empty_act()
         nws = gx.layer_workspace_bytes(cfg, False)
-        ws = self._buf(workspace_key, nws) if nws else None
+        # without dropout the workspace belongs to the saved block: passes that overlap have one of each
+        ws = self._buf(workspace_key if self.shape.drop_attn or self.shape.drop_hidden else (workspace_key, saved_key),
+                       nws) if nws else None
         gx.layer_fwd(cfg, self.params, x, y, p_attn, p_mlp, saved, ws, torch.cuda.current_stream().cuda_stream)
         return dict(y=y, p_attn=p_attn, p_mlp=p_mlp)
 
