@@ -582,11 +582,13 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
     g.colpart = out;
     return hipSuccess;
   };
+  hipStream_t b_fc2_stream = nullptr;      // where the pass for b_fc2 goes, if not with dW2
   auto task = [&](int t, hipStream_t sd) -> gx_status {
     if (t == 0) {        // dW2 (+ b_fc2)
       GemmArgs w2 = gargs(sv.act, dp_mlp, gr.w_fc2, d.Fl, d.H, d.T, d.Fl, d.H, d.H);
+      const hipStream_t bs = b_fc2_stream ? b_fc2_stream : sd;
       if (!(c.flags & GX_ROW_BIAS_MLP)) { if ((s = zero_grad(acc, gr.b_fc2, d.H, sd)) != GX_OK) return s; }
-      else if (!ln2_sums_biases) GX_TRY(bias_sums(w2, w.part_fc2, gr.b_fc2, sd));
+      else if (!ln2_sums_biases) GX_TRY(bias_sums(w2, w.part_fc2, gr.b_fc2, bs));
       GX_TRY(wgrad(w2, sd));
     } else if (t == 1) { // dW1 (+ b_fc1; bf16: the product that makes dz leaves its column sums)
       GemmArgs w1 = gargs(sv.y2, w.dz, gr.w_fc1, d.H, d.Fl, d.T, d.H, d.Fl, d.Fl);
@@ -647,10 +649,12 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
     if ((s = point(2)) != GX_OK) return s;
     void* out = attn ? w.dh1 : dx;
     // A lone feed-forward half has nothing left after this kernel but the two weight gradients, which are most of what
-    // remains: they stay on the caller's stream, and it is the LayerNorm that runs beside them (hidden 4096, degree 8, 3003 tokens,
-    // forward and backward: 392 us with the gradients on the side stream behind it, 380).
+    // remains: they stay on the caller's stream, and it is the LayerNorm and the sums for b_fc2 that run beside them (hidden
+    // 4096, degree 8, 3003 tokens, forward and backward: 405 us with the gradients on the side stream behind it, 390, and with
+    // the sums there too 377).
     {
       const hipStream_t ln = attn ? st : fk.branch();
+      if (!attn) b_fc2_stream = ln;
       ProfScope ps(GX_KC_LN_BWD, ln);
       GX_TRY(ln_bwd(d.bf, w.dy2, h1, p.ln2_g, sv.mean2, sv.rstd2, attn ? dy : nullptr, out, (int)d.T, (int)d.H,
                     ln2_sums_biases ? 4 : 2, w.part_ln2, ln));
