@@ -10,10 +10,12 @@
 // 16 wavefront ballots, each of which is the column-major word pair "64 queries of one key".
 //   rowbits[(bh * S + i) * wpr + j / 32]  bit j % 32  = keep(i, j)        (forward, dQ)
 //   colbits[(bh * S + j) * wpr + i / 32]  bit i % 32  = keep(i, j)        (dK / dV)
-// What bounds it is vector arithmetic: a call's 20 products of 32 x 32 bits, each at a quarter of the rate, about 80 plain
-// operations around them, and 16 comparisons with what places their bits.  A ballot is the comparison's own mask, put into
-// its lane by v_writelane (a select per lane and half took four instructions).  64 pairs of S 1024, us: row-major alone
-// 17.0 -> 14.0, both 26.9 -> 18.3; 64 of S 2048 89.5 -> 57.5; 96 of S 777 13.6 -> 14.2, 21.6 -> 19.2.
+// What bounds it is vector arithmetic: a call's 20 products of 32 x 32 bits, each at a quarter of the rate, about 60 plain
+// operations around them, and 16 comparisons with what places their bits.  20 of the plain ones are exclusive ors of three
+// values, one instruction each instead of two.  A ballot is the comparison's own mask, put into its lane by v_writelane (a select
+// per lane and half took four instructions).  us, with selects / v_writelane / one instruction for three values: 64 pairs of
+// S 1024, row-major alone 17.0 / 14.0 / 12.5, both 26.9 / 18.1 / 17.1; 64 of S 2048, row-major 41.0 before, 36.9 now, both 89.5 /
+// 57.6 / 53.4.
 // wpr = 2 * ceil(S / 64) words per row.  Only words that a causal kernel can touch are written:
 // keys below 64 * (i / 64 + 1).
 //
@@ -34,9 +36,9 @@ GX_DEVINL Philox philox4x32_10(unsigned c0, unsigned c1, unsigned c2, unsigned c
   for (int r = 0; r < 10; r++) {
     const unsigned long long p0 = (unsigned long long)M0 * c0, p1 = (unsigned long long)M1 * c2;
     const unsigned hi0 = (unsigned)(p0 >> 32), lo0 = (unsigned)p0, hi1 = (unsigned)(p1 >> 32), lo1 = (unsigned)p1;
-    c0 = hi1 ^ c1 ^ k0;
+    c0 = __builtin_amdgcn_bitop3_b32(hi1, c1, k0, 0x96);      // hi1 ^ c1 ^ k0 in one instruction
     c1 = lo1;
-    c2 = hi0 ^ c3 ^ k1;
+    c2 = __builtin_amdgcn_bitop3_b32(hi0, c3, k1, 0x96);
     c3 = lo0;
     k0 += W0;
     k1 += W1;
