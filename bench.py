@@ -45,7 +45,7 @@ MEASURED_TRAFFIC = {
     # FETCH_SIZE x 1.9998 (copy calibration) + WRITE_SIZE x 1.0, averaged over the class's 4 launches per step:
     # dW2, dW1 (256x256 tiles) 268.7 MB, dWqkv (256x192 tiles) 235.1 MB, dWo (128x128 tiles) 117.6 MB
     ("C3", "gemm_tn_f32"): {"bytes_per_launch": 222.5e6, "algorithmic_bytes_per_launch": 109.1e6,
-                            "source_sha256": "d841ab2201fca977bd937dd2ba96648c32c96daf8a38a6b03904701d457d4c2f"},
+                            "source_sha256": "9dacd532e3deb416c39258504772d393e05ec2c3b3975a729ab9c0c6096a308b"},
 }
 
 

@@ -11,8 +11,8 @@
 //
 // Backward: two kernels so that every output has exactly one writer and sums run in a fixed order (no
 // atomics): the first owns query rows, forms D = rowsum(dO * O) and produces dQ, the second owns key/value
-// rows and produces dK, dV with that D.  Probabilities are recomputed from the saved
-// log-sum-exp.
+// rows and produces dK, dV with that D.  Small layers run both in one launch, where the second forms D itself.
+// Probabilities are recomputed from the saved log-sum-exp.
 #include "gx_kernels.h"
 #include <type_traits>
 

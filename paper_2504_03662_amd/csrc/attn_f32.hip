@@ -11,6 +11,7 @@
 // no staging and no barrier inside the loop; a tile costs a wavefront 4096 to 16384 cycles of the
 // matrix pipe against 0.5 to 1 kB per row pair of cache reads, so the matrix pipe is the bound once
 // a few wavefronts share a SIMD.
+// With few blocks dQ and dK / dV share a launch (one_launch()).
 // Head dimensions up to 128 are padded with zeros to 32, 64 or 128.  With 16 heads of 64, S 512, batch 2:
 // forward 1031 -> 25 us, dQ 2222 -> 41 us, dK / dV 2426 -> 47 us against one wavefront per row with
 // scalar multiply-adds; with 8 heads of 128 forward 1251 -> 43 us, backward 5448 -> 142 us, although dK / dV then
