@@ -158,13 +158,17 @@ GX_DEVINL void tile_of_product(const GemmArgs& g, int pid, int nwg, char* smem) 
     }
     if (kt < nk) stage(kt, std::integral_constant<int, 0>());
   } else {
-    // every stage is requested at once; stage kt's slot takes stage kt + STAGES when all wavefronts have finished with it
+    // Two stages are requested at once, of more all but the last; stage kt's slot takes stage kt + STAGES when all wavefronts
+    // have finished with it.
+    constexpr int UP = STAGES == 2 ? 2 : STAGES - 1;
 #pragma unroll
-    for (int t = 0; t < STAGES; t++) request(t, t);
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 1) * LPT) : "memory");
+    for (int t = 0; t < UP; t++) request(t, t);
     for (int kt = 0; kt < nk; kt++) {
-      if (kt > 0) {
-        // stage kt has landed (STAGES - 2 younger ones may be in flight)
+      if (UP == STAGES && kt == 0) {
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((STAGES - 1) * LPT) : "memory");
+      } else {
+        // stage kt has landed (STAGES - 2 younger ones may be in flight) and every wavefront has finished
+        // with stage kt - 1, whose slot takes the next request
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((STAGES - 2) * LPT) : "memory");
         request(kt + STAGES - 1, slot == 0 ? STAGES - 1 : slot - 1);
       }
