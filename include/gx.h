@@ -96,6 +96,14 @@ enum {
                              projection of a lone attention phase); y, p_attn and p_mlp are not written and may
                              be NULL.  For callers that recompute activations themselves, e.g. on another
                              stream ahead of the backward pass; gx_layer_bwd ignores the flag. */
+  GX_FWD_PARTS = 4096,    /* bf16, up to 256 tokens and many weights (else the flag changes nothing): the reductions of
+                             the forward products may be cut into parts, which is faster (at 128 tokens of hidden
+                             5120, degree 2, 161 -> 132 us).  Says that `workspace` has the size that
+                             gx_layer_workspace_bytes gives for this very cfg, flag included; that size does NOT grow
+                             with the tokens (31 MB at 256 tokens of the same layer, none at 257), so a buffer sized by
+                             the longest sequence, or by the same cfg without the flag, is too small.  Parts are added
+                             in another order than one launch adds: results differ in rounding from a call without
+                             the flag. */
   GX_DROPOUT = 256        /* dropout variant: cfg->drop_attn, drop_hidden and drop_seed_* are read (without
                              the flag they are ignored).  Pass the same values to the forward and the backward
                              call.  Both passes then need a workspace (gx_layer_workspace_bytes). */
@@ -108,7 +116,7 @@ typedef struct {
   int32_t seq, micro_batch;
   int32_t dtype;            /* gx_dtype */
   int32_t flags;            /* GX_PHASE_* | GX_ROW_BIAS_* | GX_ACCUM_WGRAD | GX_RECOMPUTE | GX_GELU_TANH | GX_WGRAD_BF16 |
-                               GX_DROPOUT | GX_FWD_SAVED_ONLY */
+                               GX_DROPOUT | GX_FWD_SAVED_ONLY | GX_FWD_PARTS */
   float ln_eps;             /* LayerNorm epsilon (inside the square root; biased variance) */
   /* Dropout (only with GX_DROPOUT).  Probabilities are given in 1/256ths, 0..255.  Random bytes come
    * from Philox4x32-10 keyed by the 64-bit seed (drop_seed_lo, drop_seed_hi); the 16 bytes of one
@@ -151,7 +159,8 @@ gx_status gx_layer_validate(const gx_layer_cfg* cfg);
 /* Bytes of the opaque `saved` block (activations the forward pass keeps for the backward pass)
  * and of the opaque `workspace` block (scratch; is_backward selects the pass, and with
  * GX_RECOMPUTE the backward workspace includes room for the recomputed activations).  Both depend
- * on cfg's sizes, dtype and flags; 0 is returned for an invalid cfg. */
+ * on cfg's sizes, dtype and flags; 0 is returned for an invalid cfg.  Without GX_FWD_PARTS neither
+ * shrinks when seq or micro_batch grows, so a block sized by the longest sequence serves shorter ones. */
 size_t gx_layer_saved_bytes(const gx_layer_cfg* cfg);
 size_t gx_layer_workspace_bytes(const gx_layer_cfg* cfg, int is_backward);
 
@@ -160,9 +169,8 @@ size_t gx_layer_workspace_bytes(const gx_layer_cfg* cfg, int is_backward);
  *   ATTN only   : x in, p_attn out (required); y, p_mlp ignored.
  *   MLP only    : x holds h1, p_mlp out (required); y, p_attn ignored.
  * `saved` (gx_layer_saved_bytes) receives the activations gx_layer_bwd needs; `workspace` may be
- * NULL when gx_layer_workspace_bytes(cfg, 0) is 0, and also where it is not 0 without dropout (few
- * tokens: the reductions of the products are cut into parts there; without it each product is one
- * launch, and results differ by the order of additions). */
+ * NULL when gx_layer_workspace_bytes(cfg, 0) is 0; without dropout also with GX_FWD_PARTS, which then
+ * changes nothing. */
 gx_status gx_layer_fwd(const gx_layer_cfg* cfg, const gx_params* params, const void* x, void* y, void* p_attn,
                        void* p_mlp, void* saved, void* workspace, void* hip_stream);
 

@@ -2,7 +2,9 @@
 
 Pointers are passed as integers (device addresses) or as any object with ``data_ptr()``; the
 stream is a ``hipStream_t`` handle as an integer (0 = default stream).  Every function here has
-the name and meaning of the C entry point it wraps; all compute happens in the library.
+the name and meaning of the C entry point it wraps; all compute happens in the library.  One thing is
+added: a workspace given as a tensor has a known size, so GX_FWD_PARTS is set where it has the room
+(``parts=False``: never), and ``layer_workspace_bytes`` gives the size with that room.
 """
 from __future__ import annotations
 
@@ -17,6 +19,7 @@ GX_F32, GX_BF16 = 0, 1
 GX_PHASE_ATTN, GX_PHASE_MLP = 1, 2
 GX_ROW_BIAS_ATTN, GX_ROW_BIAS_MLP = 4, 8
 GX_ACCUM_WGRAD, GX_RECOMPUTE, GX_GELU_TANH, GX_WGRAD_BF16, GX_DROPOUT, GX_FWD_SAVED_ONLY = 16, 32, 64, 128, 256, 512
+GX_FWD_PARTS = 4096
 
 PARAM_NAMES = ("ln1_g", "ln1_b", "w_qkv", "b_qkv", "w_o", "b_o",
                "ln2_g", "ln2_b", "w_fc1", "b_fc1", "w_fc2", "b_fc2")
@@ -181,12 +184,35 @@ def layer_saved_bytes(cfg):
     return int(lib().gx_layer_saved_bytes(ctypes.byref(cfg)))
 
 
-def layer_workspace_bytes(cfg, is_backward):
+def _parts(cfg):
+    c = LayerCfg.from_buffer_copy(cfg)
+    c.flags |= GX_FWD_PARTS
+    return c
+
+
+def _bytes(cfg, is_backward):
     return int(lib().gx_layer_workspace_bytes(ctypes.byref(cfg), int(bool(is_backward))))
 
 
-def layer_fwd(cfg, params, x, y, p_attn, p_mlp, saved, workspace, stream=0, check=True):
+def _parts_if_room(cfg, workspace, is_backward):
+    """cfg with GX_FWD_PARTS where `workspace` is a tensor that is large enough for that, else cfg."""
+    contiguous = getattr(workspace, "is_contiguous", None)
+    if cfg.dtype != GX_BF16 or contiguous is None or not contiguous():
+        return cfg
+    c = _parts(cfg)
+    return c if workspace.nbytes >= _bytes(c, is_backward) else cfg
+
+
+def layer_workspace_bytes(cfg, is_backward):
+    if not is_backward and not cfg.flags & GX_FWD_SAVED_ONLY:
+        cfg = _parts(cfg)
+    return _bytes(cfg, is_backward)
+
+
+def layer_fwd(cfg, params, x, y, p_attn, p_mlp, saved, workspace, stream=0, check=True, parts=True):
     p = _struct(Params, params)
+    if parts:
+        cfg = _parts_if_room(cfg, workspace, False)
     st = lib().gx_layer_fwd(ctypes.byref(cfg), ctypes.byref(p), _ptr(x), _ptr(y), _ptr(p_attn), _ptr(p_mlp),
                             _ptr(saved), _ptr(workspace), ctypes.c_void_p(stream))
     if check and st != GX_OK:

@@ -32,7 +32,7 @@ using namespace gx;
 static_assert(sizeof(gx_layer_cfg) == 15 * 4, "gx_layer_cfg is 15 packed 32-bit fields");
 
 constexpr int ALL_FLAGS = GX_PHASE_ATTN | GX_PHASE_MLP | GX_ROW_BIAS_ATTN | GX_ROW_BIAS_MLP | GX_ACCUM_WGRAD |
-                          GX_RECOMPUTE | GX_GELU_TANH | GX_WGRAD_BF16 | GX_DROPOUT | GX_FWD_SAVED_ONLY;
+                          GX_RECOMPUTE | GX_GELU_TANH | GX_WGRAD_BF16 | GX_DROPOUT | GX_FWD_SAVED_ONLY | GX_FWD_PARTS;
 
 struct Dims {
   long T, H, Hl, Fl, S, B, nl, dh;
@@ -206,11 +206,12 @@ DropBufs plan_drop(const gx_layer_cfg& c, Arena& a, bool bwd) {
 //                     hidden 5120, degree 2 256 tokens 191 / 175; 194 / 174   hidden 2048 (101 MB) 256 tokens 88 / 103; 120 / 115
 bool split_pays(const gx_layer_cfg& c) {
   const Dims d = dims_of(c);
-  if (!d.bf || (c.flags & GX_FWD_SAVED_ONLY)) return false;
+  if (!d.bf || !(c.flags & GX_FWD_PARTS) || (c.flags & GX_FWD_SAVED_ONLY)) return false;
   const long weights = (((c.flags & GX_PHASE_ATTN) ? 4 * d.H * d.Hl : 0) + ((c.flags & GX_PHASE_MLP) ? 2 * d.H * d.Fl : 0)) * 2;
   return weights >= (d.T <= 64 ? 32L << 20 : d.T <= 128 ? 90L << 20 : 256L << 20);
 }
-// The scratch that takes, for one product at a time.  A caller that gives no workspace gets one launch per product.
+// The scratch that takes, for one product at a time.  It is not monotone in the tokens, which is why the caller has to say with
+// GX_FWD_PARTS that its workspace has that size: blocks sized by the longest sequence, or by the backward pass, are smaller.
 size_t split_bytes(const gx_layer_cfg& c) {
   if (!split_pays(c)) return 0;
   const Dims d = dims_of(c);

@@ -51,3 +51,20 @@ def test_split_products_against_the_oracle(phase, hidden, ffn, seq, batch, drop)
         torch.cuda.synchronize()
         for k, v in plain.items():
             check(k, to_host(v), ref[k], TOL["bf16"])
+
+
+@pytest.mark.parametrize("drop", [0, 26])
+def test_a_workspace_sized_by_a_longer_sequence_is_not_written_past(drop):
+    shape = I.LayerShape(2048, 32, 8192, 1, 1, 0, 64, 1, "bf16", drop_attn=drop, drop_hidden=drop, drop_seed=5 if drop else 0)
+    params = I.full_params(shape, case=830, random_affine=True)
+    x, _ = I.activations(shape, case=830)
+    layer = DeviceLayer(shape, params)
+    n = max(256, gx.layer_workspace_bytes(cfg_of(shape.with_(seq=200)), False))
+    cfg = cfg_of(shape)
+    assert n < gx.layer_workspace_bytes(cfg, False)
+    block = torch.full((gx.layer_workspace_bytes(cfg, False) + 4096,), 0x5A, dtype=torch.uint8, device="cuda:0")
+    saved, y = torch.empty(gx.layer_saved_bytes(cfg), dtype=torch.uint8, device="cuda:0"), layer.empty_act()
+    gx.layer_fwd(cfg, layer.params, to_device(x, "bf16"), y, None, None, saved, block[:n], torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert bool((block[n:] == 0x5A).all())
+    check("y", to_host(y), O.layer_fwd(shape, params, x, "both", True, True)["y"], TOL["bf16"])
