@@ -103,7 +103,8 @@ enum {
                              with the tokens (31 MB at 256 tokens of the same layer, none at 257), so a buffer sized by
                              the longest sequence, or by the same cfg without the flag, is too small.  Parts are added
                              in another order than one launch adds: results differ in rounding from a call without
-                             the flag. */
+                             the flag.  GX_RECOMPUTE and GX_FWD_SAVED_ONLY give the bits of the forward pass if both
+                             calls have the flag (and a workspace) or neither has. */
   GX_DROPOUT = 256        /* dropout variant: cfg->drop_attn, drop_hidden and drop_seed_* are read (without
                              the flag they are ignored).  Pass the same values to the forward and the backward
                              call.  Both passes then need a workspace (gx_layer_workspace_bytes). */

@@ -4,7 +4,9 @@ Pointers are passed as integers (device addresses) or as any object with ``data_
 stream is a ``hipStream_t`` handle as an integer (0 = default stream).  Every function here has
 the name and meaning of the C entry point it wraps; all compute happens in the library.  One thing is
 added: a workspace given as a tensor has a known size, so GX_FWD_PARTS is set where it has the room
-(``parts=False``: never), and ``layer_workspace_bytes`` gives the size with that room.
+(``parts=False``: never; to recompute what a forward call without a workspace has computed), and
+``layer_workspace_bytes`` gives the size with that room.  A saved-only pass needs no workspace, but only
+with the one of the whole forward pass does it give that pass's bits at every size.
 """
 from __future__ import annotations
 
@@ -20,6 +22,7 @@ GX_PHASE_ATTN, GX_PHASE_MLP = 1, 2
 GX_ROW_BIAS_ATTN, GX_ROW_BIAS_MLP = 4, 8
 GX_ACCUM_WGRAD, GX_RECOMPUTE, GX_GELU_TANH, GX_WGRAD_BF16, GX_DROPOUT, GX_FWD_SAVED_ONLY = 16, 32, 64, 128, 256, 512
 GX_FWD_PARTS = 4096
+STATIC_SCRATCH_BYTES = 64 << 20        # GX_STATIC_SCRATCH_BYTES
 
 PARAM_NAMES = ("ln1_g", "ln1_b", "w_qkv", "b_qkv", "w_o", "b_o",
                "ln2_g", "ln2_b", "w_fc1", "b_fc1", "w_fc2", "b_fc2")
@@ -204,7 +207,7 @@ def _parts_if_room(cfg, workspace, is_backward):
 
 
 def layer_workspace_bytes(cfg, is_backward):
-    if not is_backward and not cfg.flags & GX_FWD_SAVED_ONLY:
+    if is_backward or not cfg.flags & GX_FWD_SAVED_ONLY:
         cfg = _parts(cfg)
     return _bytes(cfg, is_backward)
 
@@ -220,8 +223,10 @@ def layer_fwd(cfg, params, x, y, p_attn, p_mlp, saved, workspace, stream=0, chec
     return int(st)
 
 
-def layer_bwd(cfg, params, x, dy, dx, grads, saved, workspace, stream=0, check=True):
+def layer_bwd(cfg, params, x, dy, dx, grads, saved, workspace, stream=0, check=True, parts=True):
     p = _struct(Params, params)
+    if parts and cfg.flags & GX_RECOMPUTE:
+        cfg = _parts_if_room(cfg, workspace, True)
     g = _struct(Grads, grads)
     st = lib().gx_layer_bwd(ctypes.byref(cfg), ctypes.byref(p), _ptr(x), _ptr(dy), _ptr(dx), ctypes.byref(g),
                             _ptr(saved), _ptr(workspace), ctypes.c_void_p(stream))
@@ -230,8 +235,10 @@ def layer_bwd(cfg, params, x, dy, dx, grads, saved, workspace, stream=0, check=T
     return int(st)
 
 
-def layer_bwd_static(cfg, params, x, dy, dx, grads, saved, stream=0, check=True):
+def layer_bwd_static(cfg, params, x, dy, dx, grads, saved, stream=0, check=True, parts=True):
     p = _struct(Params, params)
+    if parts and cfg.flags & GX_RECOMPUTE and _bytes(_parts(cfg), True) <= STATIC_SCRATCH_BYTES:
+        cfg = _parts(cfg)
     g = _struct(Grads, grads)
     st = lib().gx_layer_bwd_static(ctypes.byref(cfg), ctypes.byref(p), _ptr(x), _ptr(dy), _ptr(dx), ctypes.byref(g),
                                    _ptr(saved), ctypes.c_void_p(stream))

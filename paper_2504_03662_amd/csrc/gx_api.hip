@@ -107,7 +107,10 @@ struct Work {
   // bias gradient (blocks of 64 rows of dz), and the plain column sums of dqkv, dp_mlp and dp_attn
   float *part_ln2, *part_ln1, *part_fc1, *part_qkv, *part_fc2, *part_o;
   void* recomputed;     // a Saved block when GX_RECOMPUTE is set
+  float* parts;         // its forward products' parts, over the buffers above, which are not in use by then
 };
+
+size_t split_bytes(const gx_layer_cfg& c);
 
 Work plan_work(const gx_layer_cfg& c, Arena& a) {
   const Dims d = dims_of(c);
@@ -139,6 +142,9 @@ Work plan_work(const gx_layer_cfg& c, Arena& a) {
   if (c.flags & GX_RECOMPUTE) {
     Arena probe(nullptr);
     plan_saved(c, probe);
+    const size_t parts = split_bytes(c);
+    if (parts) w.parts = reinterpret_cast<float*>(a.base);
+    if (parts > a.off) a.take(parts - a.off);
     w.recomputed = a.take(probe.off);
   }
   return w;
@@ -206,7 +212,7 @@ DropBufs plan_drop(const gx_layer_cfg& c, Arena& a, bool bwd) {
 //                     hidden 5120, degree 2 256 tokens 191 / 175; 194 / 174   hidden 2048 (101 MB) 256 tokens 88 / 103; 120 / 115
 bool split_pays(const gx_layer_cfg& c) {
   const Dims d = dims_of(c);
-  if (!d.bf || !(c.flags & GX_FWD_PARTS) || (c.flags & GX_FWD_SAVED_ONLY)) return false;
+  if (!d.bf || !(c.flags & GX_FWD_PARTS)) return false;
   const long weights = (((c.flags & GX_PHASE_ATTN) ? 4 * d.H * d.Hl : 0) + ((c.flags & GX_PHASE_MLP) ? 2 * d.H * d.Fl : 0)) * 2;
   return weights >= (d.T <= 64 ? 32L << 20 : d.T <= 128 ? 90L << 20 : 256L << 20);
 }
@@ -764,7 +770,7 @@ gx_status layer_bwd(const gx_layer_cfg* cfg, const gx_params* params, const void
   const Saved sv = plan_saved(*cfg, sa);
   if ((s = make_attn_mask(*cfg, db, st)) != GX_OK) return s;
   if (recompute) {
-    s = run_fwd(*cfg, *params, x, nullptr, nullptr, nullptr, sv, db, nullptr, true, st);
+    s = run_fwd(*cfg, *params, x, nullptr, nullptr, nullptr, sv, db, w.parts, true, st);
     if (s != GX_OK) return s;
   }
   return run_bwd(*cfg, *params, x, dy, dx, *grads, sv, w, db, st, allow_side);
@@ -834,7 +840,7 @@ gx_status gx_layer_fwd(const gx_layer_cfg* cfg, const gx_params* params, const v
   float* split = workspace && split_bytes(*cfg) ? static_cast<float*>(wa.take(0)) : nullptr;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   if ((s = make_attn_mask(*cfg, db, st)) != GX_OK) return s;
-  if (saved_only) return run_fwd(*cfg, *params, x, nullptr, nullptr, nullptr, sv, db, nullptr, true, st);
+  if (saved_only) return run_fwd(*cfg, *params, x, nullptr, nullptr, nullptr, sv, db, split, true, st);
   return run_fwd(*cfg, *params, x, y, p_attn, p_mlp, sv, db, split, false, st);
 }
 

@@ -88,7 +88,8 @@ class DeviceLayer:
             p_attn = out if out is not None else self.empty_act()
         else:
             p_mlp = out if out is not None else self.empty_act()
-        nws = gx.layer_workspace_bytes(cfg, False)
+        # a saved-only pass takes the whole pass's workspace, so that it takes its route and gives its bits
+        nws = gx.layer_workspace_bytes(cfg_of(self.shape, phase) if saved_only else cfg, False)
         # without dropout the workspace belongs to the saved block: passes that overlap have one of each
         ws = self._buf(workspace_key if self.shape.drop_attn or self.shape.drop_hidden else (workspace_key, saved_key),
                        nws) if nws else None

@@ -47,3 +47,10 @@ def test_the_flag_follows_the_room_of_the_tensor(drop):
     assert not c.flags & gx.GX_FWD_PARTS                                         # the caller's own stays as it is
     for unknown in (None, 4096, torch.empty((need, 2), dtype=torch.uint8)[:, 0]):
         assert not gx._parts_if_room(c, unknown, False).flags & gx.GX_FWD_PARTS
+
+
+@pytest.mark.parametrize("tokens", [1, 32, 64, 128, 256, 257])
+def test_a_recomputing_backward_pass_has_room_for_the_parts_beside_the_activations(tokens):
+    c = cfg(tokens, 0, gx.GX_RECOMPUTE | gx.GX_FWD_PARTS)
+    saved, parts = gx.layer_saved_bytes(c), c_bytes(cfg(tokens, 0, gx.GX_FWD_PARTS), 0)
+    assert c_bytes(c, 1) == max(c_bytes(cfg(tokens), 1), parts) + saved
