@@ -61,12 +61,14 @@ class DeviceLayer:
                                      dtype=torch.bfloat16 if wgrad_bf16 and n in WEIGHT_NAMES else torch.float32)
                       for n in PARAM_NAMES}
         self._bufs = {}
+        self._fwd_scratch = {}                     # forward workspaces; a DeviceStack has one set for all of its layers
 
-    def _buf(self, key, nbytes):
-        b = self._bufs.get(key)
+    def _buf(self, key, nbytes, bufs=None):
+        bufs = self._bufs if bufs is None else bufs
+        b = bufs.get(key)
         if b is None or b.numel() < nbytes:
             b = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=self.device)
-            self._bufs[key] = b
+            bufs[key] = b
         return b
 
     def empty_act(self):
@@ -90,10 +92,10 @@ class DeviceLayer:
             p_mlp = out if out is not None else self.empty_act()
         # a saved-only pass takes the whole pass's workspace, so that it takes its route and gives its bits
         nws = gx.layer_workspace_bytes(cfg_of(self.shape, phase) if saved_only else cfg, False)
-        # without dropout the workspace belongs to the saved block: passes that overlap have one of each
-        ws = self._buf(workspace_key if self.shape.drop_attn or self.shape.drop_hidden else (workspace_key, saved_key),
-                       nws) if nws else None
-        gx.layer_fwd(cfg, self.params, x, y, p_attn, p_mlp, saved, ws, torch.cuda.current_stream().cuda_stream)
+        stream = torch.cuda.current_stream().cuda_stream
+        # nothing in the workspace outlives the call: passes on one stream share it, others have their own
+        ws = self._buf((workspace_key, phase, stream), nws, self._fwd_scratch) if nws else None
+        gx.layer_fwd(cfg, self.params, x, y, p_attn, p_mlp, saved, ws, stream)
         return dict(y=y, p_attn=p_attn, p_mlp=p_mlp)
 
     def backward(self, x, dy, phase="both", row_bias_attn=True, row_bias_mlp=True, accumulate=False, recompute=False,
@@ -113,6 +115,8 @@ class DeviceStack:
     def __init__(self, shape: LayerShape, params_list, device="cuda:0", wgrad_bf16=False):
         self.shape = shape
         self.layers = [DeviceLayer(shape, p, device, wgrad_bf16) for p in params_list]
+        for layer in self.layers[1:]:
+            layer._fwd_scratch = self.layers[0]._fwd_scratch
         self.inputs = {}          # micro-batch id -> per-block input tensors
 
     def forward(self, x, mb=0, keep_saved=True):
@@ -145,8 +149,8 @@ class DeviceStack:
     def _backward_recompute_ahead(self, ins, dy, accumulate, ahead):
         main = torch.cuda.current_stream()
         if not hasattr(self, "_rc"):
-            # scratch saved-activation blocks and forward workspaces are shared by all layers of the
-            # stack (same shape): slot k % 2, recycled when block k's backward pass has finished
+            # scratch saved-activation blocks are shared by all layers of the stack (same shape):
+            # slot k % 2, recycled when block k's backward pass has finished
             self._rc = dict(filled=[torch.cuda.Event() for _ in self.layers],
                             freed=[torch.cuda.Event() for _ in range(2)], bufs={})
         rc = self._rc
@@ -155,23 +159,20 @@ class DeviceStack:
         cur = dy
         for k in reversed(range(n)):
             layer, slot = self.layers[k], k % 2
-            keys = (("rc", slot), ("rcw", slot))
+            key = ("rc", slot)
             with torch.cuda.stream(ahead):
                 if k + 2 < n:
                     ahead.wait_event(rc["freed"][slot])
-                for key in keys:
-                    if key in rc["bufs"]:
-                        layer._bufs[key] = rc["bufs"][key]
-                layer.forward(ins[k], saved_key=keys[0], saved_only=True, workspace_key=keys[1])
-                for key in keys:
-                    if key in layer._bufs:
-                        rc["bufs"][key] = layer._bufs[key]
+                if key in rc["bufs"]:
+                    layer._bufs[key] = rc["bufs"][key]
+                layer.forward(ins[k], saved_key=key, saved_only=True)
+                rc["bufs"][key] = layer._bufs[key]
                 rc["filled"][k].record()
             main.wait_event(rc["filled"][k])
             dx = layer._bufs.get(("dx", k % 2))
             if dx is None:
                 dx = layer._bufs[("dx", k % 2)] = layer.empty_act()
-            cur = layer.backward(ins[k], cur, recompute=False, accumulate=accumulate, saved_key=("rc", slot), out=dx)
+            cur = layer.backward(ins[k], cur, recompute=False, accumulate=accumulate, saved_key=key, out=dx)
             rc["freed"][slot].record()
         return cur
 
