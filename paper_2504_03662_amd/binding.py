@@ -206,8 +206,8 @@ def _parts_if_room(cfg, workspace, is_backward):
     return c if workspace.nbytes >= _bytes(c, is_backward) else cfg
 
 
-def layer_workspace_bytes(cfg, is_backward):
-    if is_backward or not cfg.flags & GX_FWD_SAVED_ONLY:
+def layer_workspace_bytes(cfg, is_backward, parts=True):
+    if parts and (is_backward or not cfg.flags & GX_FWD_SAVED_ONLY):
         cfg = _parts(cfg)
     return _bytes(cfg, is_backward)
 

@@ -75,8 +75,9 @@ class DeviceLayer:
         return torch.empty((self.shape.tokens, self.shape.hidden), dtype=self.tdtype, device=self.device)
 
     def forward(self, x, phase="both", row_bias_attn=True, row_bias_mlp=True, want_partials=False, saved_key="saved",
-                out=None, saved_only=False, workspace_key="work_fwd"):
-        """saved_only: fill only the saved activations the backward pass needs (GX_FWD_SAVED_ONLY)."""
+                out=None, saved_only=False, workspace_key="work_fwd", parts=True):
+        """saved_only: fill only the saved activations the backward pass needs (GX_FWD_SAVED_ONLY).
+        parts: products may be cut into parts (GX_FWD_PARTS); a backward pass that recomputes takes the same."""
         cfg = cfg_of(self.shape, phase, row_bias_attn, row_bias_mlp, saved_only=saved_only)
         saved = self._buf(saved_key, gx.layer_saved_bytes(cfg))
         y = p_attn = p_mlp = None
@@ -91,20 +92,20 @@ class DeviceLayer:
         else:
             p_mlp = out if out is not None else self.empty_act()
         # a saved-only pass takes the whole pass's workspace, so that it takes its route and gives its bits
-        nws = gx.layer_workspace_bytes(cfg_of(self.shape, phase) if saved_only else cfg, False)
+        nws = gx.layer_workspace_bytes(cfg_of(self.shape, phase) if saved_only else cfg, False, parts)
         stream = torch.cuda.current_stream().cuda_stream
         # nothing in the workspace outlives the call: passes on one stream share it, others have their own
-        ws = self._buf((workspace_key, phase, stream), nws, self._fwd_scratch) if nws else None
-        gx.layer_fwd(cfg, self.params, x, y, p_attn, p_mlp, saved, ws, stream)
+        ws = self._buf((workspace_key, phase, parts, stream), nws, self._fwd_scratch) if nws else None
+        gx.layer_fwd(cfg, self.params, x, y, p_attn, p_mlp, saved, ws, stream, parts=parts)
         return dict(y=y, p_attn=p_attn, p_mlp=p_mlp)
 
     def backward(self, x, dy, phase="both", row_bias_attn=True, row_bias_mlp=True, accumulate=False, recompute=False,
-                 saved_key="saved", out=None):
+                 saved_key="saved", out=None, parts=True):
         cfg = cfg_of(self.shape, phase, row_bias_attn, row_bias_mlp, accumulate, recompute, self.wgrad_bf16)
         ws = self._buf("work", gx.layer_workspace_bytes(cfg, True))
         saved = None if recompute else self._bufs[saved_key]
         dx = out if out is not None else self.empty_act()
-        gx.layer_bwd(cfg, self.params, x, dy, dx, self.grads, saved, ws, torch.cuda.current_stream().cuda_stream)
+        gx.layer_bwd(cfg, self.params, x, dy, dx, self.grads, saved, ws, torch.cuda.current_stream().cuda_stream, parts=parts)
         return dx
 
 
@@ -119,34 +120,35 @@ class DeviceStack:
             layer._fwd_scratch = self.layers[0]._fwd_scratch
         self.inputs = {}          # micro-batch id -> per-block input tensors
 
-    def forward(self, x, mb=0, keep_saved=True):
+    def forward(self, x, mb=0, keep_saved=True, parts=True):
         ins = self.inputs.get(mb)
         if ins is None:
             ins = [None] + [self.layers[0].empty_act() for _ in self.layers[1:]] + [self.layers[0].empty_act()]
             self.inputs[mb] = ins
         ins[0] = x
         for k, layer in enumerate(self.layers):
-            layer.forward(ins[k], saved_key=("saved", mb) if keep_saved else "saved_scratch", out=ins[k + 1])
+            layer.forward(ins[k], saved_key=("saved", mb) if keep_saved else "saved_scratch", out=ins[k + 1], parts=parts)
         return ins[-1]
 
-    def backward(self, dy, mb=0, recompute=False, accumulate=False, ahead=None):
+    def backward(self, dy, mb=0, recompute=False, accumulate=False, ahead=None, parts=True):
         """ahead: a stream on which the recomputation of block k-1 runs while block k's backward
         pass runs on the current stream (two scratch blocks of saved activations per stack, shared
-        by all layers).  Without it, recomputation happens inside gx_layer_bwd (GX_RECOMPUTE)."""
+        by all layers).  Without it, recomputation happens inside gx_layer_bwd (GX_RECOMPUTE).
+        parts: as in the forward pass."""
         ins = self.inputs[mb]
         cur = dy
         if recompute and ahead is not None:
-            return self._backward_recompute_ahead(ins, dy, accumulate, ahead)
+            return self._backward_recompute_ahead(ins, dy, accumulate, ahead, parts)
         for k in reversed(range(len(self.layers))):
             layer = self.layers[k]
             dx = layer._bufs.get(("dx", k % 2))
             if dx is None:
                 dx = layer._bufs[("dx", k % 2)] = layer.empty_act()
             cur = layer.backward(ins[k], cur, recompute=recompute, accumulate=accumulate, saved_key=("saved", mb),
-                                 out=dx)
+                                 out=dx, parts=parts)
         return cur
 
-    def _backward_recompute_ahead(self, ins, dy, accumulate, ahead):
+    def _backward_recompute_ahead(self, ins, dy, accumulate, ahead, parts):
         main = torch.cuda.current_stream()
         if not hasattr(self, "_rc"):
             # scratch saved-activation blocks are shared by all layers of the stack (same shape):
@@ -165,7 +167,7 @@ class DeviceStack:
                     ahead.wait_event(rc["freed"][slot])
                 if key in rc["bufs"]:
                     layer._bufs[key] = rc["bufs"][key]
-                layer.forward(ins[k], saved_key=key, saved_only=True)
+                layer.forward(ins[k], saved_key=key, saved_only=True, parts=parts)
                 rc["bufs"][key] = layer._bufs[key]
                 rc["filled"][k].record()
             main.wait_event(rc["filled"][k])
@@ -193,6 +195,14 @@ def one_f_one_b(n_micro, depth_ahead):
     return order
 
 
+# Products in parts take nearly every compute unit from a backward pass beside them, which only layers with many weights repay.
+# Stages of two blocks, four micro-batches with recomputation, us, one launch per product / parts: hidden 2048, degree 2 (50 MB)
+# 64 tokens 1764 / 1802; hidden 4096, degree 8 (50 MB) 64 tokens 1916 / 1956; hidden 2048 (101 MB) 64 tokens 2296 / 2322, 128
+# 2411 / 2507; hidden 8192, degree 8 (185 MB) 128 tokens 4228 / 4250; hidden 5120, degree 2 (315 MB) 64 tokens 4870 / 4787, 256
+# 6562 / 6393; hidden 4096 (403 MB) 128 tokens 6848 / 6727, 256 7493 / 7249.  The same without overlap, so that results are.
+PARTS_BESIDE_BACKWARD = 256 << 20
+
+
 class StageSchedule:
     """Issues one pipeline stage's passes in a given order (e.g. one_f_one_b) on two streams:
     forward passes on one, backward passes on the other, each backward pass ordered after the
@@ -206,6 +216,8 @@ class StageSchedule:
     def __init__(self, stack: DeviceStack, n_micro, overlap=True):
         self.stack = stack
         self.overlap = overlap
+        s = stack.shape
+        self.parts = 4 * s.hidden * (2 * s.hidden_local + s.ffn_local) >= PARTS_BESIDE_BACKWARD
         if overlap:
             self.fwd_stream, self.bwd_stream, self.ahead_stream = (torch.cuda.Stream() for _ in range(3))
             self.done = [torch.cuda.Event() for _ in range(n_micro)]
@@ -221,7 +233,7 @@ class StageSchedule:
         for kind, m in order:
             if kind == "F":
                 with torch.cuda.stream(self.fwd_stream if self.overlap else cur):
-                    y = self.stack.forward(xs[m], mb=m, keep_saved=not recompute)
+                    y = self.stack.forward(xs[m], mb=m, keep_saved=not recompute, parts=self.parts)
                     if self.overlap:
                         self.done[m].record()
                     if after_forward:
@@ -231,7 +243,7 @@ class StageSchedule:
                     if self.overlap:
                         torch.cuda.current_stream().wait_event(self.done[m])
                     dx = self.stack.backward(dys[m], mb=m, recompute=recompute, accumulate=seen,
-                                             ahead=self.ahead_stream if self.overlap else None)
+                                             ahead=self.ahead_stream if self.overlap else None, parts=self.parts)
                     seen = True
                     if after_backward:
                         after_backward(m, dx)

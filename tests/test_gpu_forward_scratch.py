@@ -52,3 +52,24 @@ def test_stage_with_recomputation_ahead():
         got.append(dxs + [g for layer in stack.layers for g in layer.grads.values()])
         assert len(_scratch_bytes(stack)) == (2 if overlap else 1)
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("hidden,ffn,parts", [(2048, 8192, False), (4096, 16384, True)])
+def test_a_stage_takes_parts_from_256_mib_of_weights(hidden, ffn, parts):
+    shape = I.LayerShape(hidden, hidden // 128, ffn, 1, 1, 0, 64, 1, "bf16")
+    assert gx.layer_workspace_bytes(cfg_of(shape), False) > 0                    # a pass on its own takes them
+    p = I.full_params(shape, case=861)
+    data = [I.activations(shape, case=870 + m) for m in range(2)]
+    xs, dys = ([to_device(d[k], "bf16") for d in data] for k in range(2))
+    got = []
+    for overlap in (False, True):
+        for recompute in (False, True):
+            stack = DeviceStack(shape, [p])
+            dxs = []
+            StageSchedule(stack, 2, overlap).run(one_f_one_b(2, 1), xs, dys, recompute,
+                                                 after_backward=lambda m, dx: dxs.append(dx.clone()))
+            torch.cuda.synchronize()
+            got.append(dxs + list(stack.layers[0].grads.values()))
+            assert bool(stack.layers[0]._fwd_scratch) == parts
+    for other in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], other))
