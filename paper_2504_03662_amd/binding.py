@@ -214,7 +214,7 @@ def layer_workspace_bytes(cfg, is_backward, parts=True):
 
 def layer_fwd(cfg, params, x, y, p_attn, p_mlp, saved, workspace, stream=0, check=True, parts=True):
     p = _struct(Params, params)
-    if parts:
+    if parts and workspace is not None:
         cfg = _parts_if_room(cfg, workspace, False)
     st = lib().gx_layer_fwd(ctypes.byref(cfg), ctypes.byref(p), _ptr(x), _ptr(y), _ptr(p_attn), _ptr(p_mlp),
                             _ptr(saved), _ptr(workspace), ctypes.c_void_p(stream))

@@ -50,6 +50,8 @@ extern "C" int gx_attn_key_shares(int B, int S, int nl, int dh, int backward) {
   return backward ? dh64::dq_key_shares(a) : dh64::fwd_key_shares(a);
 }
 
+extern "C" int gx_attn_bf16_one_launch(int B, int S, int nl) { return dh128::fits_one_launch(B, S, nl); }
+
 hipError_t attn_bwd_bf16(const AttnArgs& a, hipStream_t s) {
   return a.dh == 128 ? dh128::bwd(a, s) : a.dh == 64 ? dh64::bwd(a, s) : hipErrorInvalidValue;
 }

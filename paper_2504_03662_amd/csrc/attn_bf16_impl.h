@@ -1192,9 +1192,8 @@ hipError_t fwd(const AttnArgs& a, hipStream_t s) {
 // gains (hidden 1024, 1024 tokens 237 / 227) and loses (hidden 2048, 1024 tokens 454 / 467; hidden 768, degree 2, 2 x 1024 191 /
 // 197) and is not taken.
 constexpr int ONE_LAUNCH_S = 1024;
-bool one_launch(const AttnArgs& a) {
-  return a.alone && a.S <= ONE_LAUNCH_S && (long)a.B * a.nl * cdiv(a.S, KV_BJ) <= 256;
-}
+bool fits_one_launch(int B, int S, int nl) { return S <= ONE_LAUNCH_S && (long)B * nl * cdiv(S, KV_BJ) <= 256; }
+bool one_launch(const AttnArgs& a) { return a.alone && fits_one_launch(a.B, a.S, a.nl); }
 int one_launch_smem(int S) {
   const int kv = KV_SMEM + 4 * KV_BI * cdiv(S, KV_BI);
   return kv > SMEM_FEW ? kv : SMEM_FEW;

@@ -461,9 +461,9 @@ bool shape_ok(const AttnArgs& a) {
 //   512 x 8 of 64, 1024 tokens (256, 8) 403 / 390           512 x 8 of 64, 4 x 256 tokens (256, 32) 329 / 334
 //   256 x 8 of 32, 2 x 512 tokens (256, 16) 179 / 166       256 x 8 of 32, 4 x 256 tokens (256, 32) 159 / 163
 //   512 x 16 of 32, 1024 tokens (512, 16) 384 / 382         1024 x 16 of 64, 2 x 512 tokens (512, 32) 782 / 802
-bool one_launch(const AttnArgs& a) {
-  const long pairs = (long)a.B * a.nl, blocks = pairs * cdiv(a.S, 32);
-  return blocks <= 128 || (pairs <= 16 && blocks <= (a.dh <= 32 ? 512 : 256));
+bool one_launch(int B, int S, int nl, int dh) {
+  const long pairs = (long)B * nl, blocks = pairs * cdiv(S, 32);
+  return blocks <= 128 || (pairs <= 16 && blocks <= (dh <= 32 ? 512 : 256));
 }
 
 Args make_args(const AttnArgs& a, float* out) {
@@ -489,6 +489,8 @@ Args make_args(const AttnArgs& a, float* out) {
 
 }  // namespace
 
+extern "C" int gx_attn_f32_one_launch(int B, int S, int nl, int dh) { return one_launch(B, S, nl, dh); }
+
 hipError_t attn_fwd_f32(const AttnArgs& a, hipStream_t s) {
   if (!shape_ok(a)) return hipErrorInvalidValue;
   const Args f = make_args(a, (float*)a.ctx);
@@ -499,7 +501,7 @@ hipError_t attn_fwd_f32(const AttnArgs& a, hipStream_t s) {
 hipError_t attn_bwd_f32(const AttnArgs& a, hipStream_t s) {
   if (!shape_ok(a)) return hipErrorInvalidValue;
   const Args f = make_args(a, (float*)a.dqkv);
-  if (one_launch(a)) {
+  if (one_launch(a.B, a.S, a.nl, a.dh)) {
     GX_F32_ATTN(attn_bwd_f32_kernel, f, 2);
     return hipGetLastError();
   }

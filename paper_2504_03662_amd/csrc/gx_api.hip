@@ -540,8 +540,20 @@ bool pair_products(const Dims& d, bool attn, bool mlp) {
 // 512 (3.6 G) 162 / 163, 1024 192 / 195; hidden 1024 64 tokens 153 / 145, degree 4 1024 tokens (3.2 G) 168 / 157; hidden 2048 64
 // tokens (3.2 G) 227 / 225, degree 8 256 tokens (1.6 G) 156 / 147; hidden 768, halves alone: attention 1024 tokens (2.4 G) 120 /
 // 110, feed-forward 512 (2.4 G) 86 / 79.
+// Two more lines, since a weight gradient of few tiles takes time by its tokens, whatever the weights, and an attention kernel of
+// long sequences leaves compute units to it.
+//   whole blocks: up to 1792 tokens, and only where dQ and dK / dV share a launch (two streams / one: hidden 256 7 x 256 tokens
+//     142 / 137, 1536 169 / 173, 2 x 1024 156 / 161, 4 x 1024 189 / 197, 2 heads and 2048 215 / 222; hidden 512, degree 4, 1536
+//     168 / 171, 4 x 512 143 / 146)
+//   attention halves: up to 2560 tokens (hidden 256 2048 135 / 131; hidden 1024, degree 4, 2048 177 / 172; hidden 2048, degree 8,
+//     1536 175 / 167; hidden 512, degree 4, 2 x 1500 129 / 130), up to 4096 where the kernels share a launch (8 x 512: hidden 256
+//     115 / 106, hidden 512, degree 2, 115 / 112; beyond: hidden 512, degree 2, 12 x 512 129 / 143; 8192 of hidden 768, degree
+//     6, 437 / 452)
+//   feed-forward halves: up to 6144 (hidden 256 4096 91 / 87, hidden 512 6144 111 / 110)
 bool one_stream(const Dims& d, bool attn, bool mlp) {
-  return d.bf && d.T * ((attn ? 4 * d.H * d.Hl : 0) + (mlp ? 2 * d.H * d.Fl : 0)) <= 3250000000L;
+  const bool together = attn && gx_attn_bf16_one_launch((int)d.B, (int)d.S, (int)d.nl);
+  const long most = !attn ? 6144 : mlp ? (together ? 1792 : 0) : together ? 4096 : 2560;
+  return d.bf && d.T <= most && d.T * ((attn ? 4 * d.H * d.Hl : 0) + (mlp ? 2 * d.H * d.Fl : 0)) <= 3250000000L;
 }
 
 gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, const void* dy, void* dx,
@@ -796,6 +808,15 @@ void* static_scratch() {
 extern "C" {
 
 gx_status gx_layer_validate(const gx_layer_cfg* cfg) { return validate(cfg); }
+
+// What the rules above say of a backward pass, for tests: 1 pairs of products, 2 one stream, 4 attention in one launch
+int gx_bwd_route(const gx_layer_cfg* cfg) {
+  const Dims d = dims_of(*cfg);
+  const bool attn = cfg->flags & GX_PHASE_ATTN, mlp = cfg->flags & GX_PHASE_MLP, serial = one_stream(d, attn, mlp);
+  const int B = (int)d.B, S = (int)d.S, nl = (int)d.nl;
+  const bool one = attn && (d.bf ? serial && gx_attn_bf16_one_launch(B, S, nl) : gx_attn_f32_one_launch(B, S, nl, (int)d.dh));
+  return (pair_products(d, attn, mlp) ? 1 : 0) | (serial ? 2 : 0) | (one ? 4 : 0);
+}
 
 size_t gx_layer_saved_bytes(const gx_layer_cfg* cfg) {
   if (validate(cfg) != GX_OK) return 0;

@@ -96,6 +96,9 @@ hipError_t attn_bwd_bf16(const AttnArgs& a, hipStream_t s);
 // Over how many wavefronts the forward (backward: the dQ) kernel spreads the keys of a query block: 1, 2 or 4 (host code,
 // so that tests can tell which kernel their sizes reach)
 extern "C" int gx_attn_key_shares(int B, int S, int nl, int dh, int backward);
+// Whether the backward kernels of a pass share a launch (bf16: of a pass that stays on one stream; host code)
+extern "C" int gx_attn_bf16_one_launch(int B, int S, int nl);
+extern "C" int gx_attn_f32_one_launch(int B, int S, int nl, int dh);
 hipError_t attn_fwd_f32(const AttnArgs& a, hipStream_t s);
 hipError_t attn_bwd_f32(const AttnArgs& a, hipStream_t s);
 

@@ -1,0 +1,53 @@
+"""Which backward passes stay on one stream, launch products in pairs or both attention kernels together (host code)."""
+import ctypes
+import os
+
+import pytest
+
+from paper_2504_03662_amd import binding as gx
+from paper_2504_03662_amd.inputs import LayerShape
+from paper_2504_03662_amd.runtime import cfg_of
+
+PAIRS, ONE_STREAM, ATTN_ONE_LAUNCH = 1, 2, 4
+
+
+@pytest.fixture(scope="module", autouse=True)
+def lib():
+    if not os.path.exists(gx.LIB_PATH):
+        from paper_2504_03662_amd.build import build
+        build(verbose=False)
+    return gx.lib()
+
+
+def route(shape, phase="both"):
+    return int(gx.lib().gx_bwd_route(ctypes.byref(cfg_of(shape, phase))))
+
+
+def bf16(hidden, heads, ffn, seq, batch=1, tp=1):
+    return LayerShape(hidden, heads, ffn, tp, 1, 0, seq, batch, "bf16")
+
+
+@pytest.mark.parametrize("phase,shape,one", [
+    ("both", bf16(512, 8, 2048, 1024), True), ("both", bf16(512, 8, 2048, 1040), False),             # 3.2 G, and beyond one launch
+    ("both", bf16(256, 4, 1024, 256, 7), True), ("both", bf16(256, 4, 1024, 1024, 2), False),        # 1792 tokens, 2048
+    ("both", bf16(256, 4, 1024, 1536), False), ("both", bf16(768, 12, 3072, 512), False),
+    ("attn", bf16(256, 4, 8, 512, 8), True), ("attn", bf16(256, 4, 8, 512, 9), False),
+    ("attn", bf16(768, 6, 8, 8192, 1, 6), False), ("attn", bf16(512, 8, 8, 512, 12, 2), False), ("attn", bf16(256, 4, 8, 2048, 4), False),
+    ("mlp", bf16(512, 8, 512, 1024, 6), True), ("mlp", bf16(512, 8, 512, 1025, 6), False),
+])
+def test_bf16_passes_that_stay_on_one_stream(phase, shape, one):
+    want = (ONE_STREAM | (ATTN_ONE_LAUNCH if phase != "mlp" else 0)) if one else 0
+    assert route(shape, phase) == want
+
+
+def test_attention_halves_of_long_sequences_with_two_launches():
+    assert route(bf16(256, 4, 8, 2048), "attn") == route(bf16(512, 8, 8, 512, 5), "attn") == ONE_STREAM
+    assert route(bf16(256, 4, 8, 2561), "attn") == 0
+
+
+@pytest.mark.parametrize("hidden,heads,ffn,seq,batch,want", [
+    (256, 4, 1024, 128, 2, PAIRS | ATTN_ONE_LAUNCH), (512, 8, 2048, 256, 1, PAIRS | ATTN_ONE_LAUNCH), (512, 8, 2048, 257, 1, ATTN_ONE_LAUNCH),
+    (1024, 16, 4096, 512, 2, 0), (128, 4, 256, 64, 32, PAIRS),
+])
+def test_fp32_passes(hidden, heads, ffn, seq, batch, want):
+    assert route(LayerShape(hidden, heads, ffn, 1, 1, 0, seq, batch, "f32")) == want
