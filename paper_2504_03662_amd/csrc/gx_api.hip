@@ -311,11 +311,11 @@ struct Finisher {
   }
 };
 
-hipError_t colsum_p(const void* a, long rows, long cols, float* part, float* out, bool acc, Finisher& fin,
+hipError_t colsum_p(bool bf, const void* a, long rows, long cols, float* part, float* out, bool acc, Finisher& fin,
                     hipStream_t s) {
   ProfScope ps(GX_KC_COLSUM, s);
   fin.add(part, colsum_blocks((int)rows), cols, out, acc);
-  return colsum_partial(a, (int)rows, (int)cols, (int)cols, part, s);
+  return colsum_partial(bf, a, (int)rows, (int)cols, (int)cols, part, s);
 }
 
 // The backward pass has work whose inputs are ready long before anything consumes its results:
@@ -597,7 +597,7 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
   const void* dp_attn = nullptr;
   // The bias gradient that goes with weight gradient g, the column sums of its B: with fp32 the product adds them up itself.
   auto bias_sums = [&](GemmArgs& g, float* part, float* out, hipStream_t sd) -> hipError_t {
-    if (d.bf) return colsum_p(g.B, g.K, g.N, part, out, acc, fin, sd);
+    if (d.bf) return colsum_p(true, g.B, g.K, g.N, part, out, acc, fin, sd);
     g.colpart = out;
     return hipSuccess;
   };

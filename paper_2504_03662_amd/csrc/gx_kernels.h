@@ -140,8 +140,8 @@ hipError_t colsum_finish(const FinishSeg* segs, int nseg, hipStream_t s);
 hipError_t ln_bwd(bool bf16, const void* dy, const void* x, const void* g, const float* mean, const float* rstd,
                   const void* resid, void* dx, int rows, int cols, int nsum, float* part, hipStream_t s);
 int ln_bwd_blocks(bool bf16, int rows, int cols);
-// Stage 1 of the column sums of a [rows, cols] bf16 matrix: part[colsum_blocks(rows)][cols].
-hipError_t colsum_partial(const void* a, int rows, int cols, int ld, float* part, hipStream_t s);
+// Stage 1 of the column sums of a [rows, cols] matrix: part[colsum_blocks(rows)][cols].
+hipError_t colsum_partial(bool bf16, const void* a, int rows, int cols, int ld, float* part, hipStream_t s);
 int colsum_blocks(int rows);
 
 }  // namespace gx

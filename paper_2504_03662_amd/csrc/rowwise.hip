@@ -277,12 +277,12 @@ __global__ void __launch_bounds__(512) ln_bwd_kernel(const T* __restrict__ dy, c
   }
 }
 
-// stage 1 of a column sum of bf16 values (fp32 weight gradients add up theirs themselves): workgroup (bx, by)
-// adds rows [by*rpb, (by+1)*rpb) of 64 column chunks of 16 B; its 4 wavefronts take every 4th row and combine
-// through LDS in wavefront order.
-__global__ void __launch_bounds__(256) colsum_kernel(const bf16* __restrict__ a, int rows, int cols, int ld,
+// stage 1 of a column sum: workgroup (bx, by) adds rows [by*rpb, (by+1)*rpb) of 64 column chunks of
+// 16 B; its 4 wavefronts take every 4th row and combine through LDS in wavefront order.
+template <typename T>
+__global__ void __launch_bounds__(256) colsum_kernel(const T* __restrict__ a, int rows, int cols, int ld,
                                                      int rows_per_block, float* __restrict__ part) {
-  constexpr int V = 8;
+  constexpr int V = Vec<T>::N;
   __shared__ float red[3][64][V + 1];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int c = blockIdx.x * 64 + lane;
@@ -295,7 +295,7 @@ __global__ void __launch_bounds__(256) colsum_kernel(const bf16* __restrict__ a,
 #pragma unroll 8
     for (int r = r0 + w; r < r1; r += 4) {
       float v[V];
-      load_vec<bf16>(a + (size_t)r * ld + c * V, v);
+      load_vec<T>(a + (size_t)r * ld + c * V, v);
 #pragma unroll
       for (int e = 0; e < V; e++) acc[e] += v[e];
     }
@@ -456,12 +456,16 @@ hipError_t colsum_finish(const FinishSeg* segs, int nseg, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t colsum_partial(const void* a, int rows, int cols, int ld, float* part, hipStream_t s) {
-  if (rows <= 0 || cols <= 0 || cols % 8 || ld % 8) return hipErrorInvalidValue;
+hipError_t colsum_partial(bool is_bf16, const void* a, int rows, int cols, int ld, float* part, hipStream_t s) {
+  const int vec = is_bf16 ? 8 : 4;
+  if (rows <= 0 || cols <= 0 || cols % vec || ld % vec) return hipErrorInvalidValue;
   const int nblk = colsum_blocks(rows);
   const int rpb = cdiv(rows, nblk);
-  dim3 grid(cdiv(cols / 8, 64), nblk), block(256);
-  hipLaunchKernelGGL(colsum_kernel, grid, block, 0, s, (const bf16*)a, rows, cols, ld, rpb, part);
+  dim3 grid(cdiv(cols / vec, 64), nblk), block(256);
+  if (is_bf16)
+    hipLaunchKernelGGL(colsum_kernel<bf16>, grid, block, 0, s, (const bf16*)a, rows, cols, ld, rpb, part);
+  else
+    hipLaunchKernelGGL(colsum_kernel<float>, grid, block, 0, s, (const float*)a, rows, cols, ld, rpb, part);
   return hipGetLastError();
 }
 

@@ -61,14 +61,13 @@ class DeviceLayer:
                                      dtype=torch.bfloat16 if wgrad_bf16 and n in WEIGHT_NAMES else torch.float32)
                       for n in PARAM_NAMES}
         self._bufs = {}
-        self._fwd_scratch = {}                     # forward workspaces; a DeviceStack has one set for all of its layers
+        self._scratch_layer = None                 # the layer that holds the forward workspaces, if another does (DeviceStack)
 
-    def _buf(self, key, nbytes, bufs=None):
-        bufs = self._bufs if bufs is None else bufs
-        b = bufs.get(key)
+    def _buf(self, key, nbytes):
+        b = self._bufs.get(key)
         if b is None or b.numel() < nbytes:
             b = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=self.device)
-            bufs[key] = b
+            self._bufs[key] = b
         return b
 
     def empty_act(self):
@@ -95,7 +94,7 @@ class DeviceLayer:
         nws = gx.layer_workspace_bytes(cfg_of(self.shape, phase) if saved_only else cfg, False, parts)
         stream = torch.cuda.current_stream().cuda_stream
         # nothing in the workspace outlives the call: passes on one stream share it, others have their own
-        ws = self._buf((workspace_key, phase, parts, stream), nws, self._fwd_scratch) if nws else None
+        ws = (self._scratch_layer or self)._buf((workspace_key, phase, parts, stream), nws) if nws else None
         gx.layer_fwd(cfg, self.params, x, y, p_attn, p_mlp, saved, ws, stream, parts=parts)
         return dict(y=y, p_attn=p_attn, p_mlp=p_mlp)
 
@@ -117,7 +116,7 @@ class DeviceStack:
         self.shape = shape
         self.layers = [DeviceLayer(shape, p, device, wgrad_bf16) for p in params_list]
         for layer in self.layers[1:]:
-            layer._fwd_scratch = self.layers[0]._fwd_scratch
+            layer._scratch_layer = self.layers[0]
         self.inputs = {}          # micro-batch id -> per-block input tensors
 
     def forward(self, x, mb=0, keep_saved=True, parts=True):
