@@ -67,11 +67,12 @@ GX_DEVINL f32x4 frag(const char* sub, int row, int c, int g) {
 
 // One tile of one product: workgroup `pid` of the `nwg` that the product has.
 // AHEAD: the next stage's fragments are read between the products; else at the start of their own stage (see pick()).
-// Column sums of B (LAY_TN, g.colpart): the bias gradient of the product whose weight gradient this is.  B passes through the
-// registers of the first tile-row's wavefronts anyway, so they add it up there, eight stages at a time: no pass over the
-// tensor and no partial sums in memory (hidden 256, 256 tokens, forward and backward: two launches fewer, 141 -> 137 us; hidden
-// 1024, 1024 tokens, whose passes ran beside the attention kernels, 785 as before).
-template <int LAY, int EPI, int BM, int KW, int STAGES, bool AHEAD>
+// SUMS (LAY_TN, g.colpart): column sums of B, the bias gradient of the product whose weight gradient this is.  B passes through
+// the registers of the first tile-row's wavefronts anyway, so they add it up there, eight stages at a time: no pass over the
+// tensor and no partial sums in memory (hidden 256, 256 tokens, forward and backward: two launches fewer, 141 -> 137 us).  It makes
+// a product 3 to 4 % slower (2048 x 8192 x 1024 271 -> 278 us, x 2048 533 -> 553), so the others are instances without it; which
+// products have it: sums_in_product().
+template <int LAY, int EPI, int BM, int KW, int STAGES, bool AHEAD, bool SUMS = false>
 GX_DEVINL void tile_of_product(const GemmArgs& g, int pid, int nwg, char* smem) {
   constexpr bool A_K = (LAY != LAY_TN), B_K = (LAY == LAY_NT);
   constexpr int WR = BM / 32, NW = WR * WR * KW, NT = 64 * NW;
@@ -109,16 +110,16 @@ GX_DEVINL void tile_of_product(const GemmArgs& g, int pid, int nwg, char* smem) 
     fa[set][c] = frag<A_K, BM>(ta, 32 * wm + l32, c, grp);
     fb[set][c] = frag<B_K, BM>(ta + OPER, 32 * wn + l32, c, grp);
   };
-  const bool sums = LAY == LAY_TN && g.colpart && m0 == 0, my_sums = sums && wm == 0;    // wavefront-uniform
+  const bool sums = SUMS && g.colpart && m0 == 0, my_sums = sums && wm == 0;    // wavefront-uniform
   float cs = 0.f, cs_before = 0.f;                       // of column n0 + 32 wn + l32, this wavefront's share of the rows
   auto products = [&](int set, int c) __attribute__((always_inline)) {
-    if (LAY == LAY_TN && my_sums) cs += (fb[set][c][0] + fb[set][c][1]) + (fb[set][c][2] + fb[set][c][3]);
+    if (SUMS && my_sums) cs += (fb[set][c][0] + fb[set][c][1]) + (fb[set][c][2] + fb[set][c][3]);
 #pragma unroll
     for (int e = 0; e < 4; e++)
       acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[set][c][e], fb[set][c][e], acc, 0, 0, 0);
   };
   auto sums_of_stage = [&](int kt) __attribute__((always_inline)) {
-    if (LAY == LAY_TN && (kt & 7) == 7) {
+    if (SUMS && (kt & 7) == 7) {
       cs_before += cs;
       cs = 0.f;
     }
@@ -189,13 +190,13 @@ GX_DEVINL void tile_of_product(const GemmArgs& g, int pid, int nwg, char* smem) 
   for (int v = 0; v < 16; v++)
     part[(kw * BM + 32 * wm + 8 * (v >> 2) + 4 * grp + (v & 3)) * PADN + 32 * wn + l32] = acc[v];
   float* const col_sums = part + KW * BM * PADN;        // [kw][BM columns]
-  if (LAY == LAY_TN && my_sums) {
+  if (SUMS && my_sums) {
     cs += cs_before;
     cs += __shfl_xor(cs, 32, 64);
     if (grp == 0) col_sums[kw * BM + 32 * wn + l32] = cs;
   }
   __syncthreads();
-  if (LAY == LAY_TN && sums && threadIdx.x < BM && n0 + (int)threadIdx.x < g.N) {
+  if (SUMS && sums && threadIdx.x < BM && n0 + (int)threadIdx.x < g.N) {
     float t = col_sums[threadIdx.x];
 #pragma unroll
     for (int k = 1; k < KW; k++) t += col_sums[k * BM + threadIdx.x];
@@ -254,10 +255,10 @@ GX_DEVINL void tile_of_product(const GemmArgs& g, int pid, int nwg, char* smem) 
   }
 }
 
-template <int LAY, int EPI, int BM, int KW, int STAGES, bool AHEAD>
+template <int LAY, int EPI, int BM, int KW, int STAGES, bool AHEAD, bool SUMS>
 __global__ void __launch_bounds__(BM * BM * KW / 16) gemm_f32_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  tile_of_product<LAY, EPI, BM, KW, STAGES, AHEAD>(g, blockIdx.x, gridDim.x, smem);
+  tile_of_product<LAY, EPI, BM, KW, STAGES, AHEAD, SUMS>(g, blockIdx.x, gridDim.x, smem);
 }
 
 // An input gradient and a weight gradient that need nothing of each other, in one launch: workgroups 0 .. nt_tiles - 1 have a
@@ -269,20 +270,22 @@ __global__ void __launch_bounds__(256) gemm_f32_pair_kernel(GemmArgs nt, GemmArg
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int pid = blockIdx.x;
   if (pid < nt_tiles) tile_of_product<LAY_NT, EPI_NT, 32, 4, STAGES, false>(nt, pid, nt_tiles, smem);
-  else tile_of_product<LAY_TN, EPI_TN, 32, 4, STAGES, false>(tn, pid - nt_tiles, gridDim.x - nt_tiles, smem);
+  else tile_of_product<LAY_TN, EPI_TN, 32, 4, STAGES, false, true>(tn, pid - nt_tiles, gridDim.x - nt_tiles, smem);
 }
 
-template <int LAY, int EPI, int BM, int KW, int STAGES, bool AHEAD>
+template <int LAY, int EPI, int BM, int KW, int STAGES, bool AHEAD, bool SUMS = false>
 hipError_t launch_tile(const GemmArgs& g, hipStream_t s) {
+  if constexpr (LAY == LAY_TN && !SUMS)
+    if (g.colpart) return launch_tile<LAY, EPI, BM, KW, STAGES, AHEAD, true>(g, s);
   constexpr int SMEM = STAGES * 2 * KW * BM * 128;
   static bool configured = false;
   if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_kernel<LAY, EPI, BM, KW, STAGES, AHEAD>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_kernel<LAY, EPI, BM, KW, STAGES, AHEAD, SUMS>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
     if (e != hipSuccess) return e;
     configured = true;
   }
-  hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI, BM, KW, STAGES, AHEAD>), dim3(cdiv(g.M, BM) * cdiv(g.N, BM)),
+  hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI, BM, KW, STAGES, AHEAD, SUMS>), dim3(cdiv(g.M, BM) * cdiv(g.N, BM)),
                      dim3(BM * BM * KW / 16), SMEM, s, g);
   return hipGetLastError();
 }

@@ -533,6 +533,17 @@ bool pair_products(const Dims& d, bool attn, bool mlp) {
   return most <= 128 || (most <= 256 && d.T <= 256);
 }
 
+// Whether an fp32 weight gradient adds up the bias gradient that goes with it instead of a pass over the tensor: in pairs always,
+// else not where the 3 to 4 % that it takes are more than the pass, which in part runs beside other kernels.  Forward and
+// backward, us, passes / in the products: hidden 256 4 x 512 tokens 256 / 246, hidden 512 1024 392 / 386, hidden 1024 2 x 1024
+// 1583 / 1562, 4 x 1024 3080 / 3030, attention half of hidden 1024, 4 x 512 655 / 626; hidden 1280, 2 x 512 1260 / 1262; hidden
+// 1536 1664 / 1675; hidden 2048 2650 / 2673, 2 x 1024 5415 / 5465; smaller shards of wide layers gain (attention half of hidden
+// 2048, degree 4, 2 x 512 408 / 396).  A lone feed-forward half keeps the passes: its LayerNorm then starts before the weight
+// gradients have taken every compute unit (hidden 1024, degree 4, 2048 tokens 258 / 284, hidden 512 2048 259 / 284).
+bool sums_in_product(const Dims& d, bool attn, bool paired, const GemmArgs& g) {
+  return !d.bf && (paired || (attn && (g.M <= 1280 || (long)g.M * g.N * g.K <= 4000000000L)));
+}
+
 // Whether a bf16 backward pass stays on one stream: by its multiply-adds per pass over the weights, tokens times weights.  Below
 // the line handing work over (an event recorded, one waited for, twice, and the host's part in it) costs more than what runs
 // side by side saves.  Forward and backward, us, two streams / one (with dQ and dK / dV in one launch): hidden 512 64 tokens (0.2
@@ -595,9 +606,9 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
   const int lnb = ln_bwd_blocks(d.bf, (int)d.T, (int)d.H);
   const void* dp_mlp = dy;
   const void* dp_attn = nullptr;
-  // The bias gradient that goes with weight gradient g, the column sums of its B: with fp32 the product adds them up itself.
+  // The bias gradient that goes with weight gradient g, the column sums of its B.
   auto bias_sums = [&](GemmArgs& g, float* part, float* out, hipStream_t sd) -> hipError_t {
-    if (d.bf) return colsum_p(true, g.B, g.K, g.N, part, out, acc, fin, sd);
+    if (!sums_in_product(d, attn, paired, g)) return colsum_p(d.bf, g.B, g.K, g.N, part, out, acc, fin, sd);
     g.colpart = out;
     return hipSuccess;
   };
@@ -611,7 +622,7 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
       GX_TRY(wgrad(w2, sd));
     } else if (t == 1) { // dW1 (+ b_fc1; bf16: the product that makes dz leaves its column sums)
       GemmArgs w1 = gargs(sv.y2, w.dz, gr.w_fc1, d.H, d.Fl, d.T, d.H, d.Fl, d.Fl);
-      if (!d.bf) GX_TRY(bias_sums(w1, nullptr, gr.b_fc1, sd));
+      if (!d.bf) GX_TRY(bias_sums(w1, w.part_fc1, gr.b_fc1, sd));
       GX_TRY(wgrad(w1, sd));
     } else if (t == 2) { // dWo (+ b_o)
       GemmArgs wo = gargs(sv.ctx, dp_attn, gr.w_o, d.Hl, d.H, d.T, d.Hl, d.H, d.H);
@@ -809,13 +820,17 @@ extern "C" {
 
 gx_status gx_layer_validate(const gx_layer_cfg* cfg) { return validate(cfg); }
 
-// What the rules above say of a backward pass, for tests: 1 pairs of products, 2 one stream, 4 attention in one launch
+// What the rules above say of a backward pass, for tests: 1 pairs of products, 2 one stream, 4 attention in one launch; fp32: the
+// sums for b_fc1 (8) and b_qkv (16) in the product
 int gx_bwd_route(const gx_layer_cfg* cfg) {
   const Dims d = dims_of(*cfg);
   const bool attn = cfg->flags & GX_PHASE_ATTN, mlp = cfg->flags & GX_PHASE_MLP, serial = one_stream(d, attn, mlp);
   const int B = (int)d.B, S = (int)d.S, nl = (int)d.nl;
   const bool one = attn && (d.bf ? serial && gx_attn_bf16_one_launch(B, S, nl) : gx_attn_f32_one_launch(B, S, nl, (int)d.dh));
-  return (pair_products(d, attn, mlp) ? 1 : 0) | (serial ? 2 : 0) | (one ? 4 : 0);
+  const bool paired = pair_products(d, attn, mlp);
+  const bool fc1 = mlp && sums_in_product(d, attn, paired, gargs(nullptr, nullptr, nullptr, d.H, d.Fl, d.T, 0, 0, 0));
+  const bool qkv = attn && sums_in_product(d, attn, paired, gargs(nullptr, nullptr, nullptr, d.H, 3 * d.Hl, d.T, 0, 0, 0));
+  return (paired ? 1 : 0) | (serial ? 2 : 0) | (one ? 4 : 0) | (fc1 ? 8 : 0) | (qkv ? 16 : 0);
 }
 
 size_t gx_layer_saved_bytes(const gx_layer_cfg* cfg) {

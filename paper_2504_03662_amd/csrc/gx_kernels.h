@@ -41,7 +41,7 @@ struct GemmArgs {
   unsigned next_bytes;
   float* colpart;      // bf16 EPI_DGELU, optional: partial column sums of the stored C over blocks of 64
                        // rows, [ceil(M / 64)][N] fp32 (stage 1 of the bias gradient; finished by colsum_finish).
-                       // fp32 TN, optional: column sums of B, [N], stored or, with EPI_F32_ACC, added to
+                       // fp32 TN, optional: column sums of B, [N], stored or, with EPI_F32_ACC, added to (a slower instance)
   // set by the bf16 launcher only (callers leave them 0): a launch that covers the super-tiles
   // (2 x 2 kernel tiles) numbered tile_first onwards in the tile walk, four workgroups each, the
   // tile-rows that the walk takes at a time, and how many workgroups have a tile; EPI_PART: tile_first holds

@@ -8,7 +8,7 @@ from paper_2504_03662_amd import binding as gx
 from paper_2504_03662_amd.inputs import LayerShape
 from paper_2504_03662_amd.runtime import cfg_of
 
-PAIRS, ONE_STREAM, ATTN_ONE_LAUNCH = 1, 2, 4
+PAIRS, ONE_STREAM, ATTN_ONE_LAUNCH, FC1_SUMS, QKV_SUMS = 1, 2, 4, 8, 16
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -50,4 +50,13 @@ def test_attention_halves_of_long_sequences_with_two_launches():
     (1024, 16, 4096, 512, 2, 0), (128, 4, 256, 64, 32, PAIRS),
 ])
 def test_fp32_passes(hidden, heads, ffn, seq, batch, want):
-    assert route(LayerShape(hidden, heads, ffn, 1, 1, 0, seq, batch, "f32")) == want
+    assert route(LayerShape(hidden, heads, ffn, 1, 1, 0, seq, batch, "f32")) & 7 == want
+
+
+@pytest.mark.parametrize("phase,hidden,ffn,seq,want", [
+    ("both", 256, 1024, 256, FC1_SUMS | QKV_SUMS), ("both", 1280, 5120, 4096, FC1_SUMS | QKV_SUMS), ("both", 1284, 5136, 608, QKV_SUMS),
+    ("both", 2048, 8192, 1024, 0), ("mlp", 256, 1024, 256, FC1_SUMS), ("mlp", 512, 2048, 1024, 0), ("attn", 2048, 64, 256, QKV_SUMS),
+    ("attn", 2048, 64, 512, 0),
+])
+def test_fp32_bias_gradients_in_the_product(phase, hidden, ffn, seq, want):
+    assert route(LayerShape(hidden, {1284: 12}.get(hidden, hidden // 64), ffn, 1, 1, 0, seq, 1, "f32"), phase) & 24 == want
