@@ -98,13 +98,44 @@ Saved plan_saved(const gx_layer_cfg& c, Arena& a) {
   return s;
 }
 
+// Whether the backward pass puts each weight gradient into the launch of an input gradient instead of on the side stream: fp32
+// layers whose products are at most 128 tiles of 64 x 64, or at most 256 with up to 256 tokens.  Forward and backward, us, side
+// stream / pairs: hidden 256 256 tokens 140 / 99, 1024 tokens 171 / 162; hidden 384 128 tokens 140 / 118, 256 165 / 146, 512
+// 197 / 202; hidden 512 64 tokens 147 / 128, 128 151 / 134, 256 184 / 178, 384 210 / 215; hidden 768 128 tokens 199 / 211, 256
+// 240 / 275.  Pairs in tiles of 64 x 64 gain and lose by turns (hidden 768: 512 tokens 396 / 369, 1024 602 / 617; hidden 1024:
+// 512 535 / 491, 1024 785 / 771, 1200 1198 / 1222; hidden 256, 4096 tokens 430 / 617) and are not taken.
+bool pair_products(const Dims& d, bool attn, bool mlp) {
+  if (d.bf) return false;
+  auto tiles = [](long m, long n) { return (long)cdiv(m, 64) * cdiv(n, 64); };
+  long most = 0;
+  auto product = [&](long m, long n) {
+    const long t = tiles(m, n);
+    if (t > most) most = t;
+  };
+  if (mlp) product(d.T, d.Fl), product(d.T, d.H), product(d.H, d.Fl);
+  if (attn) product(d.T, d.Hl), product(d.T, d.H), product(d.Hl, d.H), product(d.H, 3 * d.Hl);
+  return most <= 128 || (most <= 256 && d.T <= 256);
+}
+
+// Whether an fp32 weight gradient adds up the bias gradient that goes with it instead of a pass over the tensor: in pairs always,
+// else not where the 3 to 4 % that it takes are more than the pass, which in part runs beside other kernels.  Forward and
+// backward, us, passes / in the products: hidden 256 4 x 512 tokens 256 / 246, hidden 512 1024 392 / 386, hidden 1024 2 x 1024
+// 1583 / 1562, 4 x 1024 3080 / 3030, attention half of hidden 1024, 4 x 512 655 / 626; hidden 1280, 2 x 512 1260 / 1262; hidden
+// 1536 1664 / 1675; hidden 2048 2650 / 2673, 2 x 1024 5415 / 5465; smaller shards of wide layers gain (attention half of hidden
+// 2048, degree 4, 2 x 512 408 / 396).  A lone feed-forward half keeps the passes: its LayerNorm then starts before the weight
+// gradients have taken every compute unit (hidden 1024, degree 4, 2048 tokens 258 / 284, hidden 512 2048 259 / 284).
+bool sums_in_product(const Dims& d, bool attn, bool paired, long M, long N) {
+  return !d.bf && (paired || (attn && (M <= 1280 || M * N * d.T <= 4000000000L)));
+}
+
 // Backward scratch.
 struct Work {
   void *dz, *dy2, *dy1, *dh1, *dctx, *dqkv;
   float* dsum;
   // stage-1 partial sums of the column reductions, one buffer per producer (all are finished by one
   // launch at the end of the pass): the two LayerNorm-backward kernels (up to 4 sums each), the FC1
-  // bias gradient (blocks of 64 rows of dz), and the plain column sums of dqkv, dp_mlp and dp_attn
+  // bias gradient (blocks of 64 rows of dz), and the plain column sums of dqkv, dp_mlp and dp_attn;
+  // none for what an fp32 layer's products add up themselves
   float *part_ln2, *part_ln1, *part_fc1, *part_qkv, *part_fc2, *part_o;
   void* recomputed;     // a Saved block when GX_RECOMPUTE is set
   float* parts;         // its forward products' parts, over the buffers above, which are not in use by then
@@ -129,15 +160,16 @@ Work plan_work(const gx_layer_cfg& c, Arena& a) {
   }
   const size_t lnb = (size_t)ln_bwd_blocks(d.bf, (int)d.T, (int)d.H), csb = (size_t)colsum_blocks((int)d.T);
   const size_t fcb = (size_t)cdiv(d.T, 64) > csb ? (size_t)cdiv(d.T, 64) : csb;
-  if (c.flags & GX_PHASE_MLP) {
+  const bool attn = c.flags & GX_PHASE_ATTN, mlp = c.flags & GX_PHASE_MLP, paired = pair_products(d, attn, mlp);
+  auto partial = [&](size_t blocks, long N) { return static_cast<float*>(a.take(blocks * N * 4)); };
+  if (mlp) {
     w.part_ln2 = static_cast<float*>(a.take(4 * lnb * d.H * 4));
-    w.part_fc1 = static_cast<float*>(a.take(fcb * d.Fl * 4));
-    w.part_fc2 = static_cast<float*>(a.take(csb * d.H * 4));
+    if (!paired) w.part_fc1 = partial(fcb, d.Fl), w.part_fc2 = partial(csb, d.H);   // a lone half has passes: as in the whole block
   }
-  if (c.flags & GX_PHASE_ATTN) {
+  if (attn) {
     w.part_ln1 = static_cast<float*>(a.take(2 * lnb * d.H * 4));
-    w.part_qkv = static_cast<float*>(a.take(csb * 3 * d.Hl * 4));
-    w.part_o = static_cast<float*>(a.take(csb * d.H * 4));
+    if (!sums_in_product(d, attn, paired, d.H, 3 * d.Hl)) w.part_qkv = partial(csb, 3 * d.Hl);
+    if (!sums_in_product(d, attn, paired, d.Hl, d.H)) w.part_o = partial(csb, d.H);
   }
   if (c.flags & GX_RECOMPUTE) {
     Arena probe(nullptr);
@@ -514,36 +546,6 @@ gx_status zero_grad(bool acc, float* out, long cols, hipStream_t st) {
   return GX_OK;
 }
 
-// Whether the backward pass puts each weight gradient into the launch of an input gradient instead of on the side stream: fp32
-// layers whose products are at most 128 tiles of 64 x 64, or at most 256 with up to 256 tokens.  Forward and backward, us, side
-// stream / pairs: hidden 256 256 tokens 140 / 99, 1024 tokens 171 / 162; hidden 384 128 tokens 140 / 118, 256 165 / 146, 512
-// 197 / 202; hidden 512 64 tokens 147 / 128, 128 151 / 134, 256 184 / 178, 384 210 / 215; hidden 768 128 tokens 199 / 211, 256
-// 240 / 275.  Pairs in tiles of 64 x 64 gain and lose by turns (hidden 768: 512 tokens 396 / 369, 1024 602 / 617; hidden 1024:
-// 512 535 / 491, 1024 785 / 771, 1200 1198 / 1222; hidden 256, 4096 tokens 430 / 617) and are not taken.
-bool pair_products(const Dims& d, bool attn, bool mlp) {
-  if (d.bf) return false;
-  auto tiles = [](long m, long n) { return (long)cdiv(m, 64) * cdiv(n, 64); };
-  long most = 0;
-  auto product = [&](long m, long n) {
-    const long t = tiles(m, n);
-    if (t > most) most = t;
-  };
-  if (mlp) product(d.T, d.Fl), product(d.T, d.H), product(d.H, d.Fl);
-  if (attn) product(d.T, d.Hl), product(d.T, d.H), product(d.Hl, d.H), product(d.H, 3 * d.Hl);
-  return most <= 128 || (most <= 256 && d.T <= 256);
-}
-
-// Whether an fp32 weight gradient adds up the bias gradient that goes with it instead of a pass over the tensor: in pairs always,
-// else not where the 3 to 4 % that it takes are more than the pass, which in part runs beside other kernels.  Forward and
-// backward, us, passes / in the products: hidden 256 4 x 512 tokens 256 / 246, hidden 512 1024 392 / 386, hidden 1024 2 x 1024
-// 1583 / 1562, 4 x 1024 3080 / 3030, attention half of hidden 1024, 4 x 512 655 / 626; hidden 1280, 2 x 512 1260 / 1262; hidden
-// 1536 1664 / 1675; hidden 2048 2650 / 2673, 2 x 1024 5415 / 5465; smaller shards of wide layers gain (attention half of hidden
-// 2048, degree 4, 2 x 512 408 / 396).  A lone feed-forward half keeps the passes: its LayerNorm then starts before the weight
-// gradients have taken every compute unit (hidden 1024, degree 4, 2048 tokens 258 / 284, hidden 512 2048 259 / 284).
-bool sums_in_product(const Dims& d, bool attn, bool paired, const GemmArgs& g) {
-  return !d.bf && (paired || (attn && (g.M <= 1280 || (long)g.M * g.N * g.K <= 4000000000L)));
-}
-
 // Whether a bf16 backward pass stays on one stream: by its multiply-adds per pass over the weights, tokens times weights.  Below
 // the line handing work over (an event recorded, one waited for, twice, and the host's part in it) costs more than what runs
 // side by side saves.  Forward and backward, us, two streams / one (with dQ and dK / dV in one launch): hidden 512 64 tokens (0.2
@@ -608,7 +610,7 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
   const void* dp_attn = nullptr;
   // The bias gradient that goes with weight gradient g, the column sums of its B.
   auto bias_sums = [&](GemmArgs& g, float* part, float* out, hipStream_t sd) -> hipError_t {
-    if (!sums_in_product(d, attn, paired, g)) return colsum_p(d.bf, g.B, g.K, g.N, part, out, acc, fin, sd);
+    if (!sums_in_product(d, attn, paired, g.M, g.N)) return colsum_p(d.bf, g.B, g.K, g.N, part, out, acc, fin, sd);
     g.colpart = out;
     return hipSuccess;
   };
@@ -828,8 +830,8 @@ int gx_bwd_route(const gx_layer_cfg* cfg) {
   const int B = (int)d.B, S = (int)d.S, nl = (int)d.nl;
   const bool one = attn && (d.bf ? serial && gx_attn_bf16_one_launch(B, S, nl) : gx_attn_f32_one_launch(B, S, nl, (int)d.dh));
   const bool paired = pair_products(d, attn, mlp);
-  const bool fc1 = mlp && sums_in_product(d, attn, paired, gargs(nullptr, nullptr, nullptr, d.H, d.Fl, d.T, 0, 0, 0));
-  const bool qkv = attn && sums_in_product(d, attn, paired, gargs(nullptr, nullptr, nullptr, d.H, 3 * d.Hl, d.T, 0, 0, 0));
+  const bool fc1 = mlp && sums_in_product(d, attn, paired, d.H, d.Fl);
+  const bool qkv = attn && sums_in_product(d, attn, paired, d.H, 3 * d.Hl);
   return (paired ? 1 : 0) | (serial ? 2 : 0) | (one ? 4 : 0) | (fc1 ? 8 : 0) | (qkv ? 16 : 0);
 }
 

@@ -60,3 +60,20 @@ def test_fp32_passes(hidden, heads, ffn, seq, batch, want):
 ])
 def test_fp32_bias_gradients_in_the_product(phase, hidden, ffn, seq, want):
     assert route(LayerShape(hidden, {1284: 12}.get(hidden, hidden // 64), ffn, 1, 1, 0, seq, 1, "f32"), phase) & 24 == want
+
+
+@pytest.mark.parametrize("hidden,ffn", [(64, 256), (256, 1024), (324, 1300), (1284, 5136), (2048, 8192)])
+def test_fp32_workspace_grows_with_tokens_and_phases(hidden, ffn):
+    def size(seq, phase):
+        c = cfg_of(LayerShape(hidden, {1284: 12, 324: 3}.get(hidden, hidden // 64), ffn, 1, 1, 0, seq, 1, "f32"), phase)
+        return gx.layer_workspace_bytes(c, True)
+
+    sizes = {p: [size(t, p) for t in range(1, 2200, 3)] for p in ("both", "attn", "mlp")}
+    assert all(s == sorted(s) for s in sizes.values())
+    assert all(b >= max(a, m) for b, a, m in zip(*(sizes[p] for p in ("both", "attn", "mlp"))))
+
+
+def test_fp32_layers_in_pairs_hold_no_partial_sums_of_bias_gradients():
+    T, H, F, blocks = 256, 256, 1024, 16
+    c = cfg_of(LayerShape(H, 4, F, 1, 1, 0, T, 1, "f32"))
+    assert gx.layer_workspace_bytes(c, True) - 4 * (T * F + 7 * T * H) < 4 * blocks * (F + 5 * H)      # less than they would take
