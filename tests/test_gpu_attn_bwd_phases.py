@@ -1,6 +1,7 @@
 """The dK / dV kernel works on three query tiles of 32 at once: lengths for which a pair of wavefronts has no tile, one,
 two, three, or an odd or even number of them, with a last tile of one row, of all but one, or whole; more than one sample,
-so that a tile beyond a sample's end may not read the next one's rows; repeated, the same bits."""
+so that a tile beyond a sample's end may not read the next one's rows; repeated, the same bits.  The short ones run in one
+launch with dQ; on their own: test_gpu_attn_two_launches.py."""
 import pytest
 import torch
 

@@ -320,8 +320,8 @@ def test_bitwise_reproducible():
     assert np.array_equal(a["y"], b["y"]) and np.array_equal(a["dx"], b["dx"])
     for n in I.PARAM_NAMES:
         assert np.array_equal(a["grads"][n], b["grads"][n]), n
-    # queuing the whole backward pass on the caller's stream instead of forking onto the side
-    # streams only changes when kernels run, never what they compute
+    # the overlap switch never changes a result (this layer is small enough to stay on one stream;
+    # passes that fork: test_gpu_overlap.py)
     from paper_2504_03662_amd import binding as gx
     gx.set_overlap(False)
     try:
@@ -335,9 +335,9 @@ def test_bitwise_reproducible():
 
 @pytest.mark.parametrize("drop", [0, 48])
 def test_step_replays_from_a_captured_graph(drop):
-    """gx_layer_fwd / gx_layer_bwd only enqueue work (kernels, event records and waits on the
-    library's side streams), so a step can be captured into a HIP graph; every replay, with eager
-    work and synchronisations in between, must reproduce the eager result bit for bit."""
+    """gx_layer_fwd / gx_layer_bwd only enqueue work, so a step can be captured into a HIP graph; every
+    replay, with eager work and synchronisations in between, must reproduce the eager result bit for
+    bit (a layer that stays on one stream; forks and joins: test_gpu_overlap.py)."""
     shape = I.LayerShape(512, 4, 1096, 1, 1, 0, 300, 2, "bf16", drop_attn=drop, drop_hidden=drop, drop_seed=9)
     params, x, dy = _case(shape, 102)
     layer = DeviceLayer(shape, params)
@@ -407,9 +407,9 @@ def test_launch_timing_record():
 
 
 def test_calls_from_two_host_threads_overlap_safely():
-    """Each host thread gets its own side stream and events: two threads that run forward +
-    backward passes at the same time, each on its own stream and buffers, get bit for bit what one
-    thread alone gets."""
+    """Two threads that run forward + backward passes at the same time, each on its own stream and
+    buffers, get bit for bit what one thread alone gets (a layer that stays on one stream; each
+    thread's own side stream: test_gpu_overlap.py)."""
     import threading
     shape = I.LayerShape(512, 4, 1096, 2, 1, 0, 300, 2, "bf16")
     params, x, dy = _case(shape, 96)
