@@ -27,14 +27,19 @@ def model_flops(sh, blocks, mbs):
     return 3.0 * fwd * blocks * mbs
 
 
-def gemm_flops_by_class(sh, accumulate, wgrad_bf16=False):
-    """Kernel class -> list of 2*M*N*K for the GEMM launches of one layer pass (fwd + bwd)."""
+def gemm_flops_by_class(sh, accumulate, wgrad_bf16=False, paired=False):
+    """Kernel class -> list of 2*M*N*K for the GEMM launches of one layer pass (fwd + bwd).  paired: the launch of an input
+    gradient holds a weight gradient too (small fp32 layers), so no launch is of the weight gradients' own class."""
     T, H, Hl, Fl = sh.tokens, sh.hidden, sh.hidden_local, sh.ffn_local
     f = lambda m, n, k: 2.0 * m * n * k
     wg = (122 if accumulate else 120) if wgrad_bf16 else (126 if accumulate else 125)
-    return {101: [f(T, 3 * Hl, H)], 102: [f(T, H, Hl), f(T, H, Fl)], 103: [f(T, Fl, H)],
-            wg: [f(Fl, H, T), f(H, Fl, T), f(Hl, H, T), f(H, 3 * Hl, T)],
-            114: [f(T, Fl, H)], 110: [f(T, H, Fl), f(T, Hl, H), f(T, H, 3 * Hl)]}
+    fwd = {101: [f(T, 3 * Hl, H)], 102: [f(T, H, Hl), f(T, H, Fl)], 103: [f(T, Fl, H)]}
+    weights = [f(Fl, H, T), f(H, Fl, T), f(Hl, H, T), f(H, 3 * Hl, T)]
+    inputs = [f(T, Fl, H), f(T, H, Fl), f(T, Hl, H), f(T, H, 3 * Hl)]
+    if paired:
+        both = [a + b for a, b in zip(inputs, weights)]
+        return {**fwd, 114: both[:1], 110: both[1:]}
+    return {**fwd, wg: weights, 114: inputs[:1], 110: inputs[1:]}
 
 
 # HBM-side traffic of the dominant kernel class, measured with two rocprofv3 --pmc runs (FETCH_SIZE,
@@ -45,7 +50,7 @@ MEASURED_TRAFFIC = {
     # FETCH_SIZE x 1.9998 (copy calibration) + WRITE_SIZE x 1.0, averaged over the class's 4 launches per step:
     # dW2, dW1 (256x256 tiles) 268.7 MB, dWqkv (256x192 tiles) 235.1 MB, dWo (128x128 tiles) 117.6 MB
     ("C3", "gemm_tn_f32"): {"bytes_per_launch": 222.5e6, "algorithmic_bytes_per_launch": 109.1e6,
-                            "source_sha256": "9dacd532e3deb416c39258504772d393e05ec2c3b3975a729ab9c0c6096a308b"},
+                            "source_sha256": "cb436fe9eca7dbf1ee070800a5f6716f2fa1d8f78f7a1a6c131e09644a96aaf3"},
 }
 
 
@@ -373,7 +378,7 @@ def main():
     kernels = {CLASS_NAMES.get(c, str(c)): {"launches_per_step": len(v) * launches_per_step // len(rec),
                                             "avg_ms": sum(v) / len(v), "share": sum(v) / total_ms}
                for c, v in sorted(by.items(), key=lambda kv: -sum(kv[1]))}
-    gemm_fl = gemm_flops_by_class(shape, pipelined, args.wgrad_bf16)
+    gemm_fl = gemm_flops_by_class(shape, pipelined, args.wgrad_bf16, paired=not any(c in by for c in (120, 122, 125, 126)))
     dom = max((c for c in by if c >= 100), key=lambda c: sum(by[c]))
     pair = {125: 126, 126: 125, 120: 122, 122: 120}                      # store / accumulate forms of one product
     fl = gemm_fl.get(dom) or gemm_fl.get(pair.get(dom))                  # first micro-batch overwrites

@@ -1096,7 +1096,8 @@ __global__ void __launch_bounds__(64 * NQ * SPLIT, NQ * SPLIT == 4 ? 2 : 1) attn
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   dq_block<NQ, SPLIT, BKV, DROP>(a, keep, blockIdx.x, NQ * SPLIT == 4, smem);
 }
-// Both in one launch (see one_launch()), first the blocks of dK / dV, which have more to do.
+// Both in one launch (see one_launch()), first the blocks of dK / dV, which have more to do.  dQ's blocks store D here too, 4 bytes
+// a row that nobody reads.
 template <bool DROP>
 __global__ void __launch_bounds__(256, 2) attn_bwd_both_kernel(BwdArgs a, KeepArgs rows, KeepArgs cols) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];

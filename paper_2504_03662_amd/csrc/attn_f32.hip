@@ -15,7 +15,11 @@
 // Head dimensions up to 128 are padded with zeros to 32, 64 or 128.  With 16 heads of 64, S 512, batch 2:
 // forward 1031 -> 25 us, dQ 2222 -> 41 us, dK / dV 2426 -> 47 us against one wavefront per row with
 // scalar multiply-adds; with 8 heads of 128 forward 1251 -> 43 us, backward 5448 -> 142 us, although dK / dV then
-// needs more than the 512 registers there are and spills 43 (176 bytes a lane).
+// needs more than the 512 registers there are and spills 43 (176 bytes a lane; 28, 116 bytes, with padding).  In the launch that
+// holds both kernels it spills 94 (380 bytes; 34, 124 bytes, with padding), which is still the faster form where it is taken: 8
+// heads of 128, S 512, 118 -> 79 us.  dQ with padding to 64 spills one register: its text in a function that two kernels share
+// takes 256 instead of 251 (16 heads of 50, S 512, batch 2: both kernels 139.7 -> 141 us), but the same function is faster at head
+// dim 64 (16 heads, S 1024, batch 2: 240 -> 224).
 #include "gx_kernels.h"
 
 namespace gx {
@@ -461,6 +465,9 @@ bool shape_ok(const AttnArgs& a) {
 //   512 x 8 of 64, 1024 tokens (256, 8) 403 / 390           512 x 8 of 64, 4 x 256 tokens (256, 32) 329 / 334
 //   256 x 8 of 32, 2 x 512 tokens (256, 16) 179 / 166       256 x 8 of 32, 4 x 256 tokens (256, 32) 159 / 163
 //   512 x 16 of 32, 1024 tokens (512, 16) 384 / 382         1024 x 16 of 64, 2 x 512 tokens (512, 32) 782 / 802
+// Up to 128 blocks also with many pairs; the attention kernels alone: 32 x 4 heads of 32, S 32 (128 pairs) 17.1 / 10.2; 16 x 8 of
+// 64, S 32 25 / 13.7; 8 x 16 of 128, S 32 49 / 31; 4 x 16 of 64, S 64 25 / 13.9; 8 x 4 of 128, S 128 (32 pairs) 51 / 36; 8 x 4 of
+// 64, S 128 26 / 15.7.
 bool one_launch(int B, int S, int nl, int dh) {
   const long pairs = (long)B * nl, blocks = pairs * cdiv(S, 32);
   return blocks <= 128 || (pairs <= 16 && blocks <= (dh <= 32 ? 512 : 256));

@@ -250,7 +250,7 @@ GX_DEVINL void finish_run(const GemmArgs& g, size_t idx, const f32x4& xv, const 
 // Workgroups beyond the tiles read the next product's weights, so that it finds them in the memory-side cache.  With few
 // tokens a product is bound by what one compute unit can have in flight (20 GB/s of weights from memory, 30 from that cache,
 // for a 64 x 64 tile with 4 stages of 32 KB), and has fewer tiles than the chip has units: 128 x 5120 x 10240 on 160 of
-// them 64 -> 44 us.  Where: read_ahead_pays(), read_ahead_workgroups(), and only in calls without a workspace; with one the
+// them 64 -> 44 us.  Where: read_ahead_pays(), read_ahead_workgroups(), and only in calls without GX_FWD_PARTS; with it the
 // reductions are cut into parts, which is faster (gemm_bf16_split; 128 tokens of hidden 5120, degree 2, 161 us against 132).
 // A workgroup reads at most what one with a tile reads, so that it does not outlast the product.
 // The values go to LDS, where nobody reads them: no registers, and nothing that could be optimised away.

@@ -683,7 +683,10 @@ gx_status run_bwd(const gx_layer_cfg& c, const gx_params& p, const void* x, cons
     // A lone feed-forward half has nothing left after this kernel but the two weight gradients, which are most of what
     // remains: they stay on the caller's stream, and it is the LayerNorm and the sums for b_fc2 that run beside them (hidden
     // 4096, degree 8, 3003 tokens, forward and backward: 405 us with the gradients on the side stream behind it, 390, and with
-    // the sums there too 377).
+    // the sums there too 377).  At other sizes, us, the older order / this one: hidden 768 4096 tokens 209 / 185; hidden 1024 2048
+    // 179 / 158; hidden 2048 512 204 / 180, 8192 1388 / 1379; hidden 4096, degree 8, 1024 194 / 173, 8192 807 / 781; hidden 5120,
+    // degree 2, 256 343 / 322, 2048 1336 / 1329; hidden 8192, degree 8, 4096 1313 / 1287, degree 1, 2048 4755 / 4728; fp32, with the
+    // sums in passes, hidden 512 1024 193 / 171, hidden 1024 1024 472 / 446, hidden 2048 2048 3210 / 3155.
     {
       const hipStream_t ln = attn ? st : fk.branch();
       if (!attn) b_fc2_stream = ln;
