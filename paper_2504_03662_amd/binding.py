@@ -4,7 +4,7 @@ Pointers are passed as integers (device addresses) or as any object with ``data_
 stream is a ``hipStream_t`` handle as an integer (0 = default stream).  Every function here has
 the name and meaning of the C entry point it wraps; all compute happens in the library.  One thing is
 added: a workspace given as a tensor has a known size, so GX_FWD_PARTS is set where it has the room
-(``parts=False``: never; to recompute what a forward call without a workspace has computed), and
+(``parts=False``: never; to recompute what a forward call without that room has computed), and
 ``layer_workspace_bytes`` gives the size with that room.  A saved-only pass needs no workspace, but only
 with the one of the whole forward pass does it give that pass's bits at every size.
 """
@@ -203,7 +203,7 @@ def _parts_if_room(cfg, workspace, is_backward):
     if cfg.dtype != GX_BF16 or contiguous is None or not contiguous():
         return cfg
     c = _parts(cfg)
-    return c if workspace.nbytes >= _bytes(c, is_backward) else cfg
+    return c if workspace.nbytes >= lib().gx_layer_workspace_bytes(ctypes.byref(c), is_backward) else cfg
 
 
 def layer_workspace_bytes(cfg, is_backward, parts=True):
