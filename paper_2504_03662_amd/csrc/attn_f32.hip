@@ -441,7 +441,7 @@ __global__ void __launch_bounds__(64 * PARTS, 1) attn_bwd_dkv_f32_kernel(Args a)
   __shared__ float lds[lds_floats<DHP>()];
   dkv_block<DHP, EXACT, false>(a, blockIdx.x, lds);
 }
-// Both in one launch, first the blocks of dK / dV, which have more to do.
+// Both in one launch, first the blocks of dK / dV, which have more to do (dQ's store D here too, which nobody reads).
 template <int DHP, bool EXACT>
 __global__ void __launch_bounds__(64 * PARTS, 1) attn_bwd_f32_kernel(Args a) {
   __shared__ float lds[lds_floats<DHP>()];
